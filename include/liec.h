@@ -114,9 +114,10 @@ liec_status liec_create_ex(liec_ctx **out, int32_t N, int64_t d, liec_comp worke
  *   grads      [N, d] device, read only   stochastic gradients g_i of this iteration
  *   x          [N, d] device, in/out      local models x^i (they differ between workers)
  *   server_err [d]    device, in/out      global error e_t on entry, e_{t+1} on return
- * The three buffers must not overlap.  Any alignment is accepted; rows that are
- * 16-byte aligned (base pointers 16-byte aligned and d % 4 == 0) take the
- * 128-bit load path, anything else a slower element-wise path.
+ * The three buffers must not overlap.  Any multiple of 4 bytes is accepted; rows
+ * that are not 16-byte aligned (base pointers off a 16-byte boundary or
+ * d % 4 != 0) use the same 128-bit accesses at 4-byte addresses, a few per cent
+ * slower.
  * Asynchronous: work is enqueued on the context's stream and the call returns
  * without synchronising, allocating or copying to the host.  Inputs must be
  * finite; otherwise results are unspecified and liec_get_info reports it.

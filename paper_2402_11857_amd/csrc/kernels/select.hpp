@@ -302,10 +302,11 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
         constexpr bool FULL = decltype(full_c)::value;
         float4 a[4];
         if (!RK) {
-            if (VEC && FULL) {
+            if (FULL) {
+                typedef typename Vec4<VEC>::type vec;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const v4f w = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(g + (size_t)t * kWaveTile + u * kChunk + lane * 4));
+                    const vec w = __builtin_nontemporal_load(reinterpret_cast<const vec*>(g + (size_t)t * kWaveTile + u * kChunk + lane * 4));
                     a[u] = make_float4(w.x, w.y, w.z, w.w);
                 }
             } else {
