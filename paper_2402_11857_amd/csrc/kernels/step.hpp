@@ -46,11 +46,11 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 //                   sums live in LDS;
 //   WC == kRandk    reads each row's kept bitmap and fetches only the groups of 4 gradients that hold a
 //                   kept column;
-//   WC == kIdentity reads the gradients.
+// (k_aggregate_chunk below also serves the identity, which reads the gradients.)
 // With `vbits` the kernel also leaves the sign bits of v (lane-major half-words like the workers' sign
 // bits) for the update kernel of a scaled-sign server.
 // ---------------------------------------------------------------------------------------------
-template <int WC, bool SRV_L1, bool VEC, bool BATCH = false>
+template <int WC, bool SRV_L1, bool VEC>
 __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                        const uint64_t* __restrict__ gbits,
                                                        int N, uint32_t d, uint32_t nwt, float inv_n,
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
                                                        float* __restrict__ v_out, double* __restrict__ srv_partial,
                                                        BlockTable bt, bool coarse, uint16_t* __restrict__ vbits) {
     __shared__ double lds_w[4];
-    __shared__ float accs[((WC == kTopk && !BATCH) || WC == kRandk) ? 16 * kBlock : 1];
+    __shared__ float accs[(WC == kTopk || WC == kRandk) ? 16 * kBlock : 1];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     double l1 = 0.0;
     for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
@@ -108,59 +108,6 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
                         acc[u].y = __fadd_rn(acc[u].y, signed_scale(m, 4 * u + 1, sc[bidx[4 * u + 1]]));
                         acc[u].z = __fadd_rn(acc[u].z, signed_scale(m, 4 * u + 2, sc[bidx[4 * u + 2]]));
                         acc[u].w = __fadd_rn(acc[u].w, signed_scale(m, 4 * u + 3, sc[bidx[4 * u + 3]]));
-                    }
-                }
-            }
-        } else if (WC == kTopk && BATCH) {
-            // Short rows: the kernel is bound by the latency of its dependent loads (group word, then gather, row
-            // after row), not by bytes.  So the group words of 8 rows are requested together, then, chunk by
-            // chunk, the flagged groups of those 8 rows, and only then are they added, in worker order.
-            const uint64_t* __restrict__ gw = gbits + (coarse ? (size_t)t : (size_t)t * 4);
-            const size_t grow = coarse ? (size_t)nwt : (size_t)nwt * 4;
-            const uint32_t four = lane >> 2;
-            for (int i0 = 0; i0 < N; i0 += 8) {
-                uint32_t mask[8], tau[8], cut[8];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const int i = i0 + r;
-                    mask[r] = 0;
-                    tau[r] = 0;
-                    cut[r] = 0;
-                    if (i < N) {                                // uniform
-                        tau[r] = desc[i].tau;
-                        cut[r] = desc[i].cutoff;
-                        if (desc[i].dense) {
-                            mask[r] = 0xfu;
-                        } else if (coarse) {
-                            mask[r] = (uint32_t)(gw[(size_t)i * grow] >> (4 * four)) & 0xfu;
-                        } else {
-                            const uint64_t* __restrict__ w = gw + (size_t)i * grow;
-                            mask[r] = (uint32_t)((w[0] >> lane) & 1) | (uint32_t)((w[1] >> lane) & 1) << 1 |
-                                      (uint32_t)((w[2] >> lane) & 1) << 2 | (uint32_t)((w[3] >> lane) & 1) << 3;
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t j = j0 + u * kChunk;
-                    float4 gq[8];
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        gq[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if ((mask[r] >> u) & 1u) gq[r] = ld4<VEC>(grads + (size_t)(i0 + r) * d, j, d);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        if ((mask[r] >> u) & 1u) {
-                            const float gv[4] = {gq[r].x, gq[r].y, gq[r].z, gq[r].w};
-                            float* av[4] = {&acc[u].x, &acc[u].y, &acc[u].z, &acc[u].w};
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const uint32_t key = key_of(gv[q]);
-                                if (j + q < d && (key > tau[r] || (key == tau[r] && j + q <= cut[r])))
-                                    *av[q] = __fadd_rn(*av[q], gv[q]);
-                            }
-                        }
                     }
                 }
             }
@@ -232,18 +179,6 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
             for (int u = 0; u < 4; ++u)
                 acc[u] = make_float4(my[(4 * u) * kBlock], my[(4 * u + 1) * kBlock], my[(4 * u + 2) * kBlock],
                                      my[(4 * u + 3) * kBlock]);
-        } else {
-            for (int i = 0; i < N; ++i) {
-                const float* __restrict__ gi = grads + (size_t)i * d;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float4 g = ld4<VEC, true>(gi, j0 + u * kChunk, d);
-                    acc[u].x = __fadd_rn(acc[u].x, g.x);
-                    acc[u].y = __fadd_rn(acc[u].y, g.y);
-                    acc[u].z = __fadd_rn(acc[u].z, g.z);
-                    acc[u].w = __fadd_rn(acc[u].w, g.w);
-                }
-            }
         }
         uint32_t vm = 0;                                        // sign bits of my 16 values of v
 #pragma unroll
@@ -268,6 +203,156 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
         }
         // a scaled-sign server's message is these bits and one scale: the update kernel reads them instead of v
         if (vbits) vbits[(size_t)t * 64 + lane] = (uint16_t)vm;
+    }
+    if (SRV_L1) {
+        const double s = block_sum_f64(l1, lds_w);
+        if (threadIdx.x == 0) srv_partial[blockIdx.x] = s;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same sums with a wave owning one chunk (256 columns, 4 per lane) and a block one wave tile at a time: four times
+// as many waves.  For rows too short to fill the chip with a wave per tile, where the kernel is bound by the latency
+// of its dependent loads (group word, then gather, row after row) and not by bytes -- the loads of 8 rows are
+// requested together and added in worker order afterwards -- and for the identity operator on rows of any length:
+// four rows of one 128-bit load per lane in flight stream 8 x 11.7M gradients at 6.2 TB/s, a wave walking the four
+// chunks of row after row at 3.9.  On long rows the work per row and chunk (a group word for 256 columns) costs more
+// instructions than the gathers do; the host's rule has both sides' times.
+// ---------------------------------------------------------------------------------------------
+template <int WC, bool SRV_L1, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
+                                                             const uint64_t* __restrict__ gbits, int N, uint32_t d,
+                                                             uint32_t nwt, float inv_n, const RowDesc* __restrict__ desc,
+                                                             const float* __restrict__ e_in, float* __restrict__ v_out,
+                                                             double* __restrict__ srv_partial, BlockTable bt, bool coarse,
+                                                             uint16_t* __restrict__ vbits) {
+    __shared__ double lds_w[4];
+    __shared__ uint32_t nibs[4][64];
+    constexpr int kRows = 8;                                    // rows requested together
+    const uint32_t u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // my chunk of the tile
+    double l1 = 0.0;
+    for (uint32_t t = blockIdx.x; t < nwt; t += gridDim.x) {   // uniform for the block
+        const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
+        const float4 e = ld4<VEC>(e_in, j, d);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (WC == kSign || WC == kBlockSign) {
+            const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
+            const size_t brow = (size_t)nwt * 64;
+            const uint32_t tb = WC == kBlockSign ? bt.tile_blk[t] : 0u, first = tb & 0x7fffffffu;
+            uint32_t blk[4] = {first, first, first, first};
+            if (WC == kBlockSign && (tb >> 31)) {               // the tile spans a block boundary
+#pragma unroll
+                for (int q = 0; q < 4; ++q) blk[q] = block_of(bt, first, j + q < d ? j + q : d - 1);
+            }
+            for (int i0 = 0; i0 < N; i0 += kRows) {
+                uint32_t m[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) m[r] = i0 + r < N ? (uint32_t)bw[(size_t)(i0 + r) * brow] >> (4 * u) : 0u;
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (i0 + r < N) {                           // uniform
+                        float s[4];
+                        if (WC == kSign) {
+                            s[0] = s[1] = s[2] = s[3] = desc[i0 + r].scale;
+                        } else if (!(tb >> 31)) {
+                            s[0] = s[1] = s[2] = s[3] = bt.scales[(size_t)(i0 + r) * bt.B + first];
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) s[q] = bt.scales[(size_t)(i0 + r) * bt.B + blk[q]];
+                        }
+                        acc.x = __fadd_rn(acc.x, signed_scale(m[r], 0, s[0]));
+                        acc.y = __fadd_rn(acc.y, signed_scale(m[r], 1, s[1]));
+                        acc.z = __fadd_rn(acc.z, signed_scale(m[r], 2, s[2]));
+                        acc.w = __fadd_rn(acc.w, signed_scale(m[r], 3, s[3]));
+                    }
+                }
+            }
+        } else if (WC == kTopk || WC == kRandk) {
+            // which of my 4 columns to fetch: top-k, the candidate bit of my group (coarse: of its 64-byte line); random-k, the kept bits
+            const uint64_t* __restrict__ gw = gbits + (coarse ? (size_t)t : (size_t)t * 4 + u);
+            const size_t grow = coarse ? (size_t)nwt : (size_t)nwt * 4;
+            const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
+            for (int i0 = 0; i0 < N; i0 += kRows) {
+                uint32_t pick[kRows], tau[kRows], cut[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    const int i = i0 + r;
+                    pick[r] = tau[r] = cut[r] = 0;
+                    if (i < N) {                                // uniform
+                        if (WC == kRandk) {
+                            pick[r] = ((uint32_t)bw[(size_t)i * nwt * 64] >> (4 * u)) & 0xfu;
+                        } else {
+                            tau[r] = desc[i].tau;
+                            cut[r] = desc[i].cutoff;
+                            const uint64_t w = gw[(size_t)i * grow];
+                            pick[r] = desc[i].dense ? 1u
+                                                    : (uint32_t)(w >> (coarse ? 4 * (lane >> 2) + u : lane)) & 1u;
+                        }
+                    }
+                }
+                float4 gq[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    gq[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (pick[r]) gq[r] = ld4<VEC>(grads + (size_t)(i0 + r) * d, j, d);
+                }
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (pick[r]) {
+                        const float gv[4] = {gq[r].x, gq[r].y, gq[r].z, gq[r].w};
+                        float* av[4] = {&acc.x, &acc.y, &acc.z, &acc.w};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t key = key_of(gv[q]);
+                            const bool keep = WC == kRandk ? ((pick[r] >> q) & 1u) != 0
+                                                           : j + q < d && (key > tau[r] || (key == tau[r] && j + q <= cut[r]));
+                            if (keep) *av[q] = __fadd_rn(*av[q], gv[q]);
+                        }
+                    }
+                }
+            }
+        } else {
+            int i = 0;
+            for (; i + 4 <= N; i += 4) {
+                float4 g[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) g[r] = ld4<VEC, true>(grads + (size_t)(i + r) * d, j, d);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    acc.x = __fadd_rn(acc.x, g[r].x);
+                    acc.y = __fadd_rn(acc.y, g[r].y);
+                    acc.z = __fadd_rn(acc.z, g[r].z);
+                    acc.w = __fadd_rn(acc.w, g[r].w);
+                }
+            }
+            for (; i < N; ++i) {
+                const float4 g = ld4<VEC, true>(grads + (size_t)i * d, j, d);
+                acc.x = __fadd_rn(acc.x, g.x);
+                acc.y = __fadd_rn(acc.y, g.y);
+                acc.z = __fadd_rn(acc.z, g.z);
+                acc.w = __fadd_rn(acc.w, g.w);
+            }
+        }
+        float4 v;
+        v.x = __fmaf_rn(acc.x, inv_n, e.x);
+        v.y = __fmaf_rn(acc.y, inv_n, e.y);
+        v.z = __fmaf_rn(acc.z, inv_n, e.z);
+        v.w = __fmaf_rn(acc.w, inv_n, e.w);
+        st4<VEC>(v_out, j, d, v);
+        if (SRV_L1) {
+            if (j < d) l1 += (double)fabsf(v.x);
+            if (j + 1 < d) l1 += (double)fabsf(v.y);
+            if (j + 2 < d) l1 += (double)fabsf(v.z);
+            if (j + 3 < d) l1 += (double)fabsf(v.w);
+        }
+        if (vbits) {                                            // uniform; the four chunks' bits of a lane form one half-word
+            nibs[u][lane] = (v.x < 0.f ? 1u : 0u) | (v.y < 0.f ? 2u : 0u) | (v.z < 0.f ? 4u : 0u) | (v.w < 0.f ? 8u : 0u);
+            __syncthreads();
+            if (u == 0)
+                vbits[(size_t)t * 64 + lane] =
+                    (uint16_t)(nibs[0][lane] | nibs[1][lane] << 4 | nibs[2][lane] << 8 | nibs[3][lane] << 12);
+            __syncthreads();
+        }
     }
     if (SRV_L1) {
         const double s = block_sum_f64(l1, lds_w);
@@ -322,7 +407,9 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
             need_v = skeep != 0;
         }
     }
-    const float4 g = ld4<VEC, true>(gi, j, d);
+    // an uncompressed message leaves no local error: g - p^i is g - g = +0 for every finite gradient, and the gradients
+    // are not read a second time (8 rows of 11.7M + 2 columns: 195 -> 139 us)
+    const float4 g = WC == kIdentity ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4<VEC, true>(gi, j, d);
 #if defined(__HIP_DEVICE_COMPILE__)
     // One stream at a time per wave: waiting for the gradients before asking for the model measured
     // 2-4 % faster than having both 128-bit loads in flight.

@@ -104,8 +104,9 @@ struct liec_ctx {
     uint32_t row_blocks = 0;                   // scaled-sign pass over grads: grid (row_blocks, N)
     uint32_t filter_row_blocks = 0, filter_srv_blocks = 0;   // top-k filter pass (fewer, longer-lived blocks)
     uint32_t filter_run = 1;                   // consecutive wave tiles a wave of the filter takes at a time
-    bool agg_batch = false;                    // top-k workers: the aggregation gathers 8 rows at a time (short rows)
-    uint32_t agg_blocks = 0;                   // aggregation kernel
+    bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
+    uint32_t agg_tile_blocks = 0, agg_chunk_blocks = 0;      // its grid in either form
+    uint32_t agg_blocks() const { return agg_chunk ? agg_chunk_blocks : agg_tile_blocks; }
     uint32_t cold_row_blocks = 0, cold_srv_blocks = 0;   // first-digit histogram (rarely needed)
     uint32_t cap = 0;                          // candidate list capacity per row
 
@@ -113,7 +114,7 @@ struct liec_ctx {
     RowDesc* desc = nullptr;                   // [N + 1]
     float* vbuf = nullptr;                     // [d]  compensated average v
     double* w_partial = nullptr;               // [N * row_blocks]
-    double* s_partial = nullptr;               // [agg_blocks]
+    double* s_partial = nullptr;               // [the larger of the two aggregation grids]
     uint16_t* bits = nullptr;                  // [(N or N + 1) * nwt * 64] sign bits (sign operators) / kept bits (random-k; row N: server)
     RkState* rk_state = nullptr;               // random-k: seed and number of the next draw (device)
     uint32_t rk_wlo = 0, rk_whi = 0, rk_slo = 0, rk_shi = 0;   // random-k: threshold bands of the worker / server draws
@@ -354,15 +355,16 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     const uint32_t d = (uint32_t)c->d;
     L.begin(S_AGGREGATE);
     auto launch = [&](auto kernel) {
-        kernel<<<c->agg_blocks, kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
+        kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
                                                        c->s_partial, block_table(c), c->gb_coarse, c->vbits);
     };
-    if (WC == kTopk && c->agg_batch) {                          // short rows: the gathers of 8 rows at a time
-        if (srv_l1) launch(k_aggregate<WC, true, VEC, WC == kTopk>);
-        else launch(k_aggregate<WC, false, VEC, WC == kTopk>);
+    if (c->agg_chunk) {
+        if (srv_l1) launch(k_aggregate_chunk<WC, true, VEC>);
+        else launch(k_aggregate_chunk<WC, false, VEC>);
     } else {
-        if (srv_l1) launch(k_aggregate<WC, true, VEC>);
-        else launch(k_aggregate<WC, false, VEC>);
+        constexpr int W = WC == kIdentity ? (int)kSign : WC;    // the identity always takes the form above
+        if (srv_l1) launch(k_aggregate<W, true, VEC>);
+        else launch(k_aggregate<W, false, VEC>);
     }
     L.end();
 }
@@ -428,7 +430,7 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     }
     if (c->server_comp == kSign) {
         L.begin(S_S_L1_FINAL);
-        k_l1_final<<<1, kBlock, 0, c->stream>>>(c->s_partial, c->agg_blocks, d, c->desc + c->N);
+        k_l1_final<<<1, kBlock, 0, c->stream>>>(c->s_partial, c->agg_blocks(), d, c->desc + c->N);
         L.end();
     } else if (c->server_comp == kBlockSign) {
         launch_block_l1<VEC>(L, c->vbuf, 0, 1u, (uint32_t)c->N, nullptr, S_S_L1);
@@ -540,10 +542,13 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // group words it writes fill whole 128-byte lines of the bitmap: measured 2 % faster than 1 on rows of 25M
     // and 138M columns, 2 and 8 in between); short rows keep 1, so that enough blocks are in flight.
     c->filter_run = c->nwt >= 8192u ? 4u : 1u;
-    // top-k workers: on rows under 2^23 columns the aggregation is bound by the latency of its dependent loads and
-    // gathers 8 rows at a time (C2: 0.032 -> 0.021 ms); on long rows that measured slower (C4 0.127 -> 0.156 ms,
-    // C5 0.39 -> 0.57 ms)
-    c->agg_batch = c->nwt < 8192u;
+    // The aggregation's form by operator and row length (tiles of 1024 columns), a chunk per wave against a tile per
+    // wave in us: top-k, k/d = 1 %, 8 x 1M columns 7 against 28, 16 x 11.7M 61 against 77, but 16 x 25.6M (0.1 %) 112
+    // against 68; random-k 8 x 1M 6 against 15, 16 x 4.2M 34 against 36, 16 x 11.7M 81 against 77; blockwise sign
+    // 4 x 65536 4 against 12, 7 x 3.3M 17 against 19, 7 x 7.3M 33 against 27; scaled sign is never faster by chunk
+    // (the four waves of a tile read the same bits); identity, 8 x 11.7M, 75 against 119.
+    c->agg_chunk = worker_comp == LIEC_COMP_IDENTITY || (worker_comp == LIEC_COMP_TOPK && c->nwt < 12288u) ||
+                   (worker_comp == LIEC_COMP_RANDK && c->nwt < 8192u) || (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 4096u);
     auto balanced_filter = [&](uint32_t max_blocks) {
         const uint32_t iters = (c->nwt + 4 * c->filter_run - 1) / (4 * c->filter_run);
         const uint32_t per = (iters + max_blocks - 1) / max_blocks;
@@ -553,7 +558,8 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     c->filter_srv_blocks = balanced_filter(8192u);
     // the aggregation reads sign bits fastest with many short blocks, and gathers fastest with fewer
     const bool gathers = worker_comp == LIEC_COMP_TOPK || worker_comp == LIEC_COMP_RANDK;
-    c->agg_blocks = balanced(gathers ? 16384u : 65536u);
+    c->agg_tile_blocks = balanced(gathers ? 16384u : 65536u);
+    c->agg_chunk_blocks = std::min(c->nwt, 65536u);
     c->cold_row_blocks = clampu(2048u / un, 1u, blk_iters);
     c->cold_srv_blocks = clampu(2048u, 1u, blk_iters);
     // Candidate list capacity per row: the warm band lists a few per cent of k entries and the first-digit
@@ -568,7 +574,7 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     hipError_t e = dev_alloc(c, &c->desc, rows);
     if (e == hipSuccess) e = dev_alloc(c, &c->vbuf, (size_t)c->nwt * kWaveTile);
     if (e == hipSuccess) e = dev_alloc(c, &c->w_partial, (size_t)N * c->row_blocks);
-    if (e == hipSuccess) e = dev_alloc(c, &c->s_partial, (size_t)c->agg_blocks);
+    if (e == hipSuccess) e = dev_alloc(c, &c->s_partial, (size_t)std::max(c->agg_tile_blocks, c->agg_chunk_blocks));
     if (e == hipSuccess && server_comp == LIEC_COMP_RANDK)
         e = dev_alloc(c, &c->bits, rows * c->nwt * 64);
     else if (e == hipSuccess && (worker_comp == LIEC_COMP_SIGN || worker_comp == LIEC_COMP_BLOCKSIGN ||
@@ -730,7 +736,7 @@ liec_status liec_set_group_bitmap(liec_ctx* c, int32_t per_line) {
 
 liec_status liec_set_gather_batching(liec_ctx* c, int32_t on) {
     if (!c || (on != 0 && on != 1) || c->worker_comp != kTopk) return LIEC_EINVAL;
-    c->agg_batch = on != 0;
+    c->agg_chunk = on != 0;
     return LIEC_OK;
 }
 
@@ -996,7 +1002,7 @@ liec_status liec_pack_topk_message(liec_ctx* c, const float* grads, int32_t work
     const RowDesc* rd = c->desc + worker;
     // random-k: the kept set of the last draw is the worker's row of the kept bitmap
     const uint16_t* kept = c->worker_comp == kRandk ? c->bits + (size_t)worker * c->nwt * 64 : nullptr;
-    const uint32_t blocks = c->agg_blocks;
+    const uint32_t blocks = c->agg_tile_blocks;
     if (vec) k_topk_count<true><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles);
     else k_topk_count<false><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles);
     k_scan_u32<<<1, 1024, 0, c->stream>>>(c->wire_tiles, c->nwt, c->wire_tiles + c->nwt);
@@ -1030,8 +1036,8 @@ liec_status liec_l2_norm(liec_ctx* c, const float* vec, int64_t n, double* norm_
     if (c->broken) return LIEC_EDEVICE;
     DeviceScope on(c);
     if (!on.ok) return LIEC_EDEVICE;
-    // s_partial holds agg_blocks doubles; one more double behind the worker partials receives the sum
-    const uint32_t blocks = (uint32_t)std::min<int64_t>((n + kBlock - 1) / kBlock, (int64_t)std::min<uint32_t>(c->agg_blocks, 4096u));
+    // s_partial holds at least agg_tile_blocks doubles; one more double behind the worker partials receives the sum
+    const uint32_t blocks = (uint32_t)std::min<int64_t>((n + kBlock - 1) / kBlock, (int64_t)std::min<uint32_t>(c->agg_tile_blocks, 4096u));
     k_sumsq<<<blocks, kBlock, 0, c->stream>>>(vec, (uint64_t)n, c->s_partial);
     k_sumsq_final<<<1, kBlock, 0, c->stream>>>(c->s_partial, blocks, c->w_partial, false);
     double sum = 0.0;
