@@ -26,7 +26,9 @@ constexpr int kStage = 1024;            // LDS staging slots of a block of the c
 constexpr int kWaveStage = 256;         // and of each of its waves once the block's are used up (a chunk lists at most 256)
 constexpr int kDirectList = 16384;      // candidate lists up to this length are selected by one block on its own
 constexpr int kShortCap = 4096;         // entries of the first list digit's bin that are handed to the list select on their own
-constexpr int kTieCap = 4096;           // ties at the threshold the fast path resolves
+constexpr int kHeldBits = 10;           // radix digit of the list select over a list it holds in registers
+constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key
+constexpr uint32_t kFewEntries = 256;   // entries left that the list select compares with one another instead of taking further digits
 constexpr uint32_t kBandStart = 1u << 17;    // swing (an eighth of the band's half width) after a step without a prediction
 constexpr uint32_t kBandFloor = 1u << 15;    // least half width, in key units, of the predicted band (about 0.27 % in value)
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel

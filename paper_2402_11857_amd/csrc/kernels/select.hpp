@@ -26,8 +26,8 @@ namespace liec {
 //      counting into a second set of counters.  For the rows of the second kind every block picks the
 //      first list digit's bin and the bin's entries are collected into a short list (list_collect).
 //   4. k_list_select, one block per row: radix digits over the listed keys, taken relative to the band's
-//      lower end (over the short list when there is one), then the ties in index order (up to 4096 of
-//      them through LDS, more by a radix select over the listed indices); writes (tau, cut-off), predicts
+//      lower end (over the short list when there is one) until few entries are left to compare, or, among
+//      more entries of one key, a radix select over their indices; writes (tau, cut-off), predicts
 //      the next band.  Rows whose band the list cannot hold (constant or near-constant rows) are put
 //      into kSlow mode.
 //   5. k_slow_select takes the kSlow rows.
@@ -73,8 +73,9 @@ __device__ __forceinline__ uint64_t filter_chunk(const uint32_t (&keys)[4], uint
 
 // List select: the keys of a band are taken relative to its lower end and need b <= 26 bits.  The first
 // digit is their top kFirstBits bits when many blocks build its histogram in global memory (256 bins: the
-// blocks' LDS histograms then merge with few global atomics, which are slow across the chip's dies), or up
-// to kListBits bits when one block builds it in LDS; the following digits take up to kListBits bits each.
+// blocks' LDS histograms then merge with few global atomics, which are slow across the chip's dies); one block
+// that builds it in LDS, and the digits after it, take kHeldBits (a list held in registers: another pass is
+// cheap) or kListBits bits each.
 constexpr int kFirstBits = 8;
 __device__ __forceinline__ int band_bits(uint32_t width) {            // width: 1 .. 2^26
     return width > 1 ? 32 - __clz((int)(width - 1)) : 1;
@@ -569,14 +570,19 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 
 // grid = rows, 1024 threads: finishes the list select of a row.  Which band the row's list was filtered
 // against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
-// follows from the row's mode and first counter set, as in the filter passes.  Two radix digits over the
-// listed keys give tau.  For a row on its predicted band the first digit's histogram is ready (k_hist0) and,
+// follows from the row's mode and first counter set, as in the filter passes.  Radix digits over the listed
+// keys narrow them down to the at most kFewEntries that share the digits found so far, and those are compared
+// with one another, which gives tau and the cut-off at once.  For a row on its predicted band the first digit's histogram is ready (k_hist0) and,
 // when the bin holding rank k was small enough, so is the short list of that bin's entries (second k_filter
 // pass): the rest of the select then reads those few entries only.  Otherwise the block walks the list
-// itself.  The cut-off is the `rank`-th smallest index among the entries whose key is tau: through an LDS
-// buffer when at most kTieCap entries share tau, else (quantised gradients: thousands of equal magnitudes)
+// itself.  When more entries than that share the whole key (quantised gradients: thousands of equal
+// magnitudes), the cut-off is the `rank`-th smallest index among them, found
 // by a three-digit radix select over those indices.  Then the row's counters and histogram are cleared, the
-// next step's band is predicted and the row is back in kWarm mode.  Rows whose list does not hold rank k
+// next step's band is predicted and the row is back in kWarm mode.
+// The kernel is a chain of latencies (one block per row): digits of 10 bits over a list held in registers, because
+// a smaller histogram is cleared and walked faster, and the comparison in place of the second digit, the tie list
+// and its quadratic ranking: 8 x 1M columns, k = 1 %, 11.0 -> 7.3 us; 5 x 3M
+// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.  Rows whose list does not hold rank k
 // (overflow, a bin larger than the list, rank outside the band) are put into kSlow mode.
 // The same for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once by
 // hold_listed, walked by every pass of the select instead of going back to memory).
@@ -604,13 +610,13 @@ __device__ __forceinline__ void for_each_held(const uint4 (&a)[8], uint32_t n, F
 __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, RowDesc* __restrict__ desc,
                                                                uint32_t* __restrict__ ghist,
                                                                const uint2* __restrict__ list, uint32_t cap,
-                                                               const uint2* __restrict__ shortl, uint32_t k,
+                                                               const uint2* __restrict__ shortl, uint32_t k, uint32_t d,
                                                                uint32_t fix_lo, uint32_t fix_hi,
                                                                uint32_t* __restrict__ slow_sync) {
-    __shared__ uint32_t h[kListBins];                          // digit histograms, then the tie indices
+    __shared__ __align__(16) uint32_t h[kListBins];            // digit histograms, then the last few entries
     __shared__ uint32_t part[256], res[3];
-    __shared__ uint32_t s_cut, s_nties;
-    static_assert(kTieCap <= kListBins, "the tie indices reuse the histogram");
+    __shared__ uint32_t s_tau, s_cut, s_rank, s_nties;
+    static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the last entries reuse the histogram, one per thread");
     __shared__ RowDesc now;                                    // the row's descriptor as the kernel found it
     const uint32_t row = row0 + blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     // one round trip for the whole descriptor instead of one per dependent field; nobody else writes it meanwhile
@@ -636,14 +642,12 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         n = now.n_cand2;
         n_sure = sure_count2(now);
         ok = p.count <= cap && n <= cap && n_sure < k && (uint64_t)k <= (uint64_t)n_sure + n;
-        shift = first_shift(hi - lo, kListBits);
     } else {                                                    // kWarm and band_ok
         lo = now.lo;
         hi = now.hi;
         n = now.n_cand;
         n_sure = sure_count(now);
         direct = n <= (uint32_t)kDirectList;
-        shift = first_shift(hi - lo, direct ? kListBits : kFirstBits);
         if (!direct) ph = block_pick(hrow, 1 << kFirstBits, k - n_sure, part, res);
     }
     if (cold || !direct)
@@ -660,6 +664,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         return;
     }
     const uint32_t n_all = n;
+    shift = first_shift(hi - lo, direct ? (n <= kHeldMax ? kHeldBits : kListBits) : kFirstBits);
     if (!direct && ph.count <= (uint32_t)kShortCap && now.n_short == ph.count) {
         in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
         n = ph.count;
@@ -681,11 +686,26 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         __syncthreads();
         ph = block_pick(h, (int)nbins, k - n_sure, part, res);
     }
-    // the following digits, over the entries that carry the digits found so far
-    uint32_t prefix = ph.bin, want = ph.rank_in, ties = ph.count;
+    // The following digits, over the entries that carry the digits found so far, until few are left or the key is known.
+    const int digit_bits_max = held ? kHeldBits : kListBits;
+    uint32_t prefix = ph.bin, want = ph.rank_in, left = ph.count;
 #pragma unroll 1
-    while (shift > 0) {
-        const int bits = shift < kListBits ? shift : kListBits, below = shift - bits;
+    while (shift > 0 && left > kFewEntries) {
+        if (held) {                                             // gradients of few mantissa bits: one key may be all there is
+            walk([&](uint2 kv, bool valid) {
+                if (valid && ((kv.x - lo) >> shift) == prefix) s_tau = kv.x;     // any of them
+            });
+            __syncthreads();
+            const uint32_t one = s_tau;
+            bool other = false;
+            walk([&](uint2 kv, bool valid) { other |= valid && ((kv.x - lo) >> shift) == prefix && kv.x != one; });
+            if (!__syncthreads_or(other)) {
+                prefix = one - lo;
+                shift = 0;
+                break;
+            }
+        }
+        const int bits = shift < digit_bits_max ? shift : digit_bits_max, below = shift - bits;
         const uint32_t nbins = max(256u, 1u << bits), mask = (1u << bits) - 1u;
         for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
         __syncthreads();
@@ -697,60 +717,71 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         const Pick p = block_pick(h, (int)nbins, want, part, res);
         prefix = (prefix << bits) | p.bin;
         want = p.rank_in;
-        ties = p.count;
+        left = p.count;
         shift = below;
     }
-    const uint32_t tau = lo + prefix;
-    if (ties <= (uint32_t)kTieCap) {
-        if (tid == 0) {
-            s_nties = 0;
-            s_cut = 0xffffffffu;
-        }
+    // Many entries of one key (quantised gradients): the want-th of them in index order.  Digits of 11 bits over the
+    // indices, counted down from the largest, which turns "want-th smallest" into the "want-th largest" block_pick
+    // finds; again until few are left.
+    const uint32_t ties = left, want_key = want;                // entries of the key, when it is known here
+    const uint32_t top = d - 1;
+    int ishift = band_bits(d);                                  // index bits below the digits found so far
+    uint32_t ifound = 0;
+#pragma unroll 1
+    while (left > kFewEntries) {                                // indices are distinct: ends before ishift would go below 0
+        const int bits = ishift < kIndexBits ? ishift : kIndexBits, below = ishift - bits;
+        const uint32_t nbins = max(256u, 1u << bits), mask = (1u << bits) - 1u;
+        for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
         __syncthreads();
         walk([&](uint2 kv, bool valid) {
-            if (valid && kv.x == tau) {
-                const uint32_t pos = atomicAdd(&s_nties, 1u);
-                if (pos < (uint32_t)kTieCap) h[pos] = kv.y;
-            }
+            const uint32_t inv = top - kv.y;
+            wave_count(h, valid && kv.x == lo + prefix && (inv >> ishift) == ifound, (inv >> below) & mask, lane);
         });
         __syncthreads();
-        for (uint32_t q = tid; q < ties; q += kSelectBlock) {
-            const uint32_t mine = h[q];
-            uint32_t below = 0;
-            for (uint32_t r = 0; r < ties; ++r) below += h[r] < mine;
-            if (below + 1 == want) s_cut = mine;                // indices are distinct: one writer
-        }
-        __syncthreads();
-    } else {
-        // Indices are below 2^31; taking 0x7fffffff - index as the key turns "want-th smallest index" into
-        // "want-th largest key", which is what block_pick finds.  Digits of 11, 10 and 10 bits.
-        uint32_t prefix = 0, rank = want;
-#pragma unroll 1
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
-            const int above = pass == 0 ? 31 : (pass == 1 ? 20 : 10);   // bits above this digit are the prefix
-            const int nbins = pass == 0 ? 2048 : 1024;
-            for (int b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
-            __syncthreads();
-            walk([&](uint2 kv, bool valid) {
-                const uint32_t inv = 0x7fffffffu - kv.y;
-                wave_count(h, valid && kv.x == tau && (inv >> above) == prefix, (inv >> shift) & (uint32_t)(nbins - 1), lane);
-            });
-            __syncthreads();
-            const Pick p = block_pick(h, nbins, rank, part, res);
-            prefix = (prefix << (pass == 0 ? 11 : 10)) | p.bin;
-            rank = p.rank_in;
-        }
-        if (tid == 0) s_cut = 0x7fffffffu - prefix;
-        __syncthreads();
+        const Pick p = block_pick(h, (int)nbins, want, part, res);
+        ifound = (ifound << bits) | p.bin;
+        want = p.rank_in;
+        left = p.count;
+        ishift = below;
     }
+    // The entries that are left, compared with one another: the one with want - 1 others ahead of it (larger key, or
+    // the same key and a lower index) is the row's k-th.
+    uint2* few = reinterpret_cast<uint2*>(h);
+    if (tid == 0) s_nties = 0;
+    __syncthreads();
+    walk([&](uint2 kv, bool valid) {
+        if (valid && ((kv.x - lo) >> shift) == prefix && ((top - kv.y) >> ishift) == ifound) {
+            const uint32_t pos = atomicAdd(&s_nties, 1u);
+            if (pos < kFewEntries) few[pos] = kv;
+        }
+    });
+    __syncthreads();
+    if (tid < left) {
+        const uint2 mine = few[tid];
+        uint32_t larger = 0, equal = 0, earlier = 0;
+#pragma unroll 8
+        for (uint32_t r = 0; r < left; ++r) {
+            const uint2 o = few[r];
+            larger += o.x > mine.x ? 1u : 0u;
+            equal += o.x == mine.x ? 1u : 0u;
+            earlier += o.x == mine.x && o.y < mine.y ? 1u : 0u;
+        }
+        if (larger + earlier + 1 == want) {                     // indices are distinct: one thread
+            const bool by_index = ties != left;                 // the entries went through the index digits
+            s_tau = mine.x;
+            s_cut = mine.y;
+            s_rank = by_index ? want_key : want - larger;
+            s_nties = by_index ? ties : equal;
+        }
+    }
+    __syncthreads();
     if (tid == 0) {
         RowDesc r = now;
         r.n_list = n_all;
         clear_counts(r);
-        r.tau = tau;
-        r.rank = want;
-        r.ties = ties;
+        r.tau = s_tau;
+        r.rank = s_rank;
+        r.ties = s_nties;
         r.cutoff = s_cut;
         r.dense = 0;
         r.nonfinite = r.nonfinite_acc;

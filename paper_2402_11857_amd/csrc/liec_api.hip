@@ -318,7 +318,7 @@ void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t ro
     uint32_t* const scnt = slow_b > 1 ? c->slow_cnt + slow_slot * kSlowMaxBlocks : nullptr;
     uint32_t* const ssync = slow_b > 1 ? c->slow_sync + slow_slot * 2 : nullptr;
     L.begin(slot0 + 3);
-    k_list_select<<<rows, kSelectBlock, 0, st>>>(row0, c->desc, c->ghist, c->list, c->cap, c->shortl, k, rk.fix_lo, rk.fix_hi,
+    k_list_select<<<rows, kSelectBlock, 0, st>>>(row0, c->desc, c->ghist, c->list, c->cap, c->shortl, k, d, rk.fix_lo, rk.fix_hi,
                                                  ssync);
     L.end();
     L.begin(slot0 + 4);
