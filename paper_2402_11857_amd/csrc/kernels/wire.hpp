@@ -8,16 +8,30 @@ namespace liec {
 // ---------------------------------------------------------------------------------------------
 // Wire form of a (blockwise) scaled-sign message: one bit per element, bit j % 8 of byte j / 8 set
 // when the element is negative.  k_pack_sign turns one row of the lane-major bitmap into that
-// form (one thread per output byte); k_unpack_sign expands wire bits and scale(s) into the dense
-// message p_j = -s or +s (one 128-bit store per 4 columns).
+// form (a thread turns the 16 bytes of 8 lanes into four 32-bit words, one per chunk; one thread per output byte
+// took 4.7 us for 1.5 MB, this 2.9); k_unpack_sign expands wire bits and scale(s) into the dense
+// message p_j = -s or +s (one 128-bit streaming store per 4 columns: 8 messages of 11.7M columns packed and unpacked
+// took 125 us with plain stores, 98 with streaming ones).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_pack_sign(const uint16_t* __restrict__ row_bits, uint32_t nbytes,
+__global__ __launch_bounds__(kBlock) void k_pack_sign(const uint16_t* __restrict__ row_bits, uint32_t nwt, uint32_t nbytes,
                                                        uint8_t* __restrict__ out) {
-    const uint32_t b = blockIdx.x * kBlock + threadIdx.x;
-    if (b >= nbytes) return;
-    const uint32_t col = b * 8, t = col / kWaveTile, o = col % kWaveTile, u = o / kChunk, lane = (o % kChunk) / 4;
-    const uint32_t m0 = row_bits[(size_t)t * 64 + lane], m1 = row_bits[(size_t)t * 64 + lane + 1];
-    out[b] = (uint8_t)(((m0 >> (4 * u)) & 0xfu) | (((m1 >> (4 * u)) & 0xfu) << 4));
+    typedef uint32_t u32_any __attribute__((aligned(1)));
+    const uint32_t q = blockIdx.x * kBlock + threadIdx.x;      // 8 lanes' half-words of one wave tile
+    if (q >= nwt * 8) return;
+    const uint4 w = reinterpret_cast<const uint4*>(row_bits)[q];
+    const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {                               // their 32 columns of chunk u
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m |= (((h[i] >> (4 * u)) & 0xfu) | ((h[i] >> (16 + 4 * u)) & 0xfu) << 4) << (8 * i);
+        const uint32_t b = (q >> 3) * (kWaveTile / 8) + u * (kChunk / 8) + (q & 7) * 4;
+        if (b + 4 <= nbytes) {
+            *reinterpret_cast<u32_any*>(out + b) = m;           // the caller's buffer may start at any byte
+        } else {
+            for (uint32_t i = 0; b + i < nbytes; ++i) out[b + i] = (uint8_t)(m >> (8 * i));
+        }
+    }
 }
 
 template <bool VEC>
@@ -42,130 +56,180 @@ __global__ __launch_bounds__(kBlock) void k_unpack_sign(const uint8_t* __restric
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = ((m >> c) & 1u) ? -s : s;
         }
-        st4<VEC>(p, j0, d, make_float4(v[0], v[1], v[2], v[3]));
+        st4<VEC, true>(p, j0, d, make_float4(v[0], v[1], v[2], v[3]));
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Wire form of a top-k message: the kept entries of one row as (index, value) pairs in increasing
-// index order.  Three kernels: kept entries per wave tile, exclusive scan of those counts, ordered
-// emission.  Inside a wave tile the order is chunk, then lane, then component.
+// Wire form of a top-k or random-k message: the kept entries of one row as (index, value) pairs in increasing index
+// order.  Two kernels over the same blocks, each owning `per` consecutive wave tiles: k_kept_count leaves the kept
+// entries of every tile and block, k_kept_emit adds up the counts before its own tiles and writes the pairs.  Inside
+// a wave tile the order is chunk, then lane, then component.  What is kept follows from what the step left behind:
+// the candidate bitmap (top-k: only the flagged groups of columns are fetched and compared with the threshold) or
+// the kept bitmap (random-k: the count reads no gradients at all).  11.7M columns, k = 1 %: count and emit 6 + 11 us,
+// where a count and an emit that read the whole row and a one-block scan of the tiles between them took 19 + 11 + 8.
 // ---------------------------------------------------------------------------------------------
-template <bool VEC>
-__device__ __forceinline__ void kept_ballots(const float* __restrict__ g, uint32_t t, uint32_t lane, uint32_t d,
-                                             uint32_t tau, uint32_t cut, const uint16_t* __restrict__ kept_row,
-                                             float4 (&a)[4], uint64_t (&kb)[4][4]) {
+constexpr uint32_t kWireBlocks = 4096;                         // at most; every block of k_kept_emit adds up that many counts
+struct KeptRow {
+    const float* g;                                             // the row's gradients
+    const RowDesc* rd;
+    const uint64_t* groups;                                     // top-k: the row's candidate bitmap, in either form (or none)
+    const uint16_t* kept;                                       // random-k: the row's kept bitmap
+    bool coarse;
+};
+// Ballots of the kept columns of tile t: kb[u][q] for component q of chunk u.  VALUES: also the gradients of the
+// groups of 4 columns that hold one (a[u], valid where a bit of kb[u] is set).  False when the tile keeps nothing.
+template <bool VEC, bool VALUES>
+__device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint32_t lane, uint32_t d, uint32_t tau,
+                                             uint32_t cut, bool dense, float4 (&a)[4], uint64_t (&kb)[4][4]) {
+    const uint32_t j0 = t * kWaveTile + lane * 4;
+    if (r.kept) {                                               // uniform
+        const uint32_t m = r.kept[(size_t)t * 64 + lane];
+        if (__ballot(m != 0) == 0) return false;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = ld4<VEC>(g, t * kWaveTile + u * kChunk + lane * 4, d);
-    if (kept_row) {                                 // random-k: the kept set is a bitmap (wave-uniform branch)
-        const uint32_t m = kept_row[(size_t)t * 64 + lane];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            if (VALUES && ((m >> (4 * u)) & 0xfu)) a[u] = ld4<VEC>(r.g, j0 + u * kChunk, d);
 #pragma unroll
             for (int q = 0; q < 4; ++q) kb[u][q] = __ballot((m >> (4 * u + q)) & 1u);
-        return;
+        }
+        return true;
+    }
+    uint32_t mask = 0xfu;                                       // bit u: my group of chunk u may hold a kept column
+    if (r.groups) {                                             // uniform
+        if (r.coarse) {
+            mask = (uint32_t)(r.groups[t] >> (4 * (lane >> 2))) & 0xfu;
+        } else {
+            const uint64_t* __restrict__ w = r.groups + (size_t)t * 4;
+            mask = (uint32_t)((w[0] >> lane) & 1) | (uint32_t)((w[1] >> lane) & 1) << 1 | (uint32_t)((w[2] >> lane) & 1) << 2 |
+                   (uint32_t)((w[3] >> lane) & 1) << 3;
+        }
+        if (dense) mask = 0xfu;
+        if (__ballot(mask != 0) == 0) return false;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
+        a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if ((mask >> u) & 1u) a[u] = ld4<VEC>(r.g, j0 + u * kChunk, d);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t j = j0 + u * kChunk;
         const float av[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint32_t key = key_of(av[q]);
-            kb[u][q] = __ballot(j + q < d && (key > tau || (key == tau && j + q <= cut)));
+            kb[u][q] = __ballot(((mask >> u) & 1u) && j + q < d && (key > tau || (key == tau && j + q <= cut)));
         }
     }
+    return true;
 }
 
-// grid = blocks over the wave tiles of the row.
 template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_topk_count(const float* __restrict__ g, uint32_t d, uint32_t nwt,
-                                                        const RowDesc* __restrict__ rd,
-                                                        const uint16_t* __restrict__ kept_row,
-                                                        uint32_t* __restrict__ tile_cnt) {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t tau = rd->tau, cut = rd->cutoff;
-    for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
+__global__ __launch_bounds__(kBlock) void k_kept_count(KeptRow r, uint32_t d, uint32_t nwt, uint32_t per,
+                                                        uint32_t* __restrict__ tile_cnt, uint32_t* __restrict__ block_cnt) {
+    __shared__ uint32_t lds_w[4];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t tau = r.rd->tau, cut = r.rd->cutoff;
+    const bool dense = r.rd->dense != 0;
+    const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, nwt);
+    uint32_t total = 0;
+    for (uint32_t t = t0 + wave; t < t1; t += 4) {
         float4 a[4];
         uint64_t kb[4][4];
-        kept_ballots<VEC>(g, t, lane, d, tau, cut, kept_row, a, kb);
         uint32_t n = 0;
+        if (kept_ballots<VEC, false>(r, t, lane, d, tau, cut, dense, a, kb)) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) n += __popcll(kb[u][q]);
+                for (int q = 0; q < 4; ++q) n += __popcll(kb[u][q]);
+        }
         if (lane == 0) tile_cnt[t] = n;
+        total += n;
     }
+    if (lane == 0) lds_w[wave] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) block_cnt[blockIdx.x] = lds_w[0] + lds_w[1] + lds_w[2] + lds_w[3];
 }
 
-// One block of 1024 threads: exclusive scan of n counts in place; *total receives the sum.  The block walks
-// the array 4096 counts at a time (4 consecutive ones per thread, so the accesses coalesce).
-__global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* __restrict__ v, uint32_t n, uint32_t* __restrict__ total) {
-    __shared__ uint32_t wsum[16];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t carry = 0;
-    for (uint32_t base = 0; base < n; base += 4096) {          // uniform trip count
-        const uint32_t i = base + tid * 4;
-        uint32_t a[4];
+template <bool VEC>
+__global__ __launch_bounds__(kBlock) void k_kept_emit(KeptRow r, uint32_t d, uint32_t nwt, uint32_t per,
+                                                       const uint32_t* __restrict__ tile_cnt,
+                                                       const uint32_t* __restrict__ block_cnt, uint32_t k,
+                                                       uint32_t* __restrict__ idx_out, float* __restrict__ val_out) {
+    __shared__ uint32_t lds_w[4], first[kBlock], carry_in;
+    const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const uint32_t tau = r.rd->tau, cut = r.rd->cutoff;
+    const bool dense = r.rd->dense != 0;
+    // kept entries in the blocks ahead of this one: all counts requested at once (one after another they cost this
+    // kernel half its time)
+    constexpr int kLoads = kWireBlocks / (4 * kBlock);
+    uint4 c[kLoads];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) a[q] = i + q < n ? v[i + q] : 0u;
-        const uint32_t s = a[0] + a[1] + a[2] + a[3];
-        uint32_t incl = s;
+    for (int q = 0; q < kLoads; ++q) {
+        const uint32_t b = (q * kBlock + tid) * 4;
+        c[q] = b < blockIdx.x ? *reinterpret_cast<const uint4*>(block_cnt + b) : make_uint4(0u, 0u, 0u, 0u);
+    }
+    const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, nwt);
+    uint32_t carry = 0;
+    for (uint32_t base = t0; base < t1; base += kBlock) {       // uniform; the counts of up to 256 tiles at a time
+        const uint32_t n = base + tid < t1 ? tile_cnt[base + tid] : 0u;
+        const uint32_t end = min(base + kBlock, t1);
+        uint32_t t = base + wave;
+        float4 a[4];
+        uint64_t kb[4][4];
+        bool any = t < end && kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);    // (its loads run beside the sums)
+        if (base == t0) {
+            uint32_t before = 0;
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                const uint32_t b = (q * kBlock + tid) * 4;
+                before += (b < blockIdx.x ? c[q].x : 0u) + (b + 1 < blockIdx.x ? c[q].y : 0u) +
+                          (b + 2 < blockIdx.x ? c[q].z : 0u) + (b + 3 < blockIdx.x ? c[q].w : 0u);
+            }
+            before = block_sum_u32(before, lds_w);              // valid on thread 0
+            if (tid == 0) carry_in = before;
+            __syncthreads();
+            carry = carry_in;
+        }
+        uint32_t incl = n;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const uint32_t up = __shfl_up(incl, o, 64);
             if ((int)lane >= o) incl += up;
         }
-        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();                                        // the round before has read lds_w and first
+        if (lane == 63) lds_w[wave] = incl;
         __syncthreads();
-        uint32_t before = carry, all = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < (int)wave) before += wsum[w];
-            all += wsum[w];
+        uint32_t ahead = carry, all = 0;
+        for (uint32_t w = 0; w < 4; ++w) {
+            if (w < wave) ahead += lds_w[w];
+            all += lds_w[w];
         }
-        uint32_t run = before + incl - s;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (i + q < n) v[i + q] = run;
-            run += a[q];
-        }
+        first[tid] = ahead + incl - n;
         carry += all;
         __syncthreads();
-    }
-    if (tid == 0) *total = carry;
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_topk_emit(const float* __restrict__ g, uint32_t d, uint32_t nwt,
-                                                       const RowDesc* __restrict__ rd,
-                                                       const uint16_t* __restrict__ kept_row,
-                                                       const uint32_t* __restrict__ tile_off, uint32_t k,
-                                                       uint32_t* __restrict__ idx_out, float* __restrict__ val_out) {
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t tau = rd->tau, cut = rd->cutoff;
-    for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
-        float4 a[4];
-        uint64_t kb[4][4];
-        kept_ballots<VEC>(g, t, lane, d, tau, cut, kept_row, a, kb);
-        uint32_t base = tile_off[t];
+        for (; t < end; t += 4) {
+            if (t >= base + 4) any = kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);
+            if (!any) continue;
+            uint32_t at = first[t - base];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
-            const float av[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
-            // entries of lower lanes come first, then this lane's lower components
-            uint32_t pos = base + lanes_below(kb[u][0]) + lanes_below(kb[u][1]) + lanes_below(kb[u][2]) +
-                           lanes_below(kb[u][3]);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
+                const float av[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
+                // entries of lower lanes come first, then this lane's lower components
+                uint32_t pos = at + lanes_below(kb[u][0]) + lanes_below(kb[u][1]) + lanes_below(kb[u][2]) + lanes_below(kb[u][3]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if ((kb[u][q] >> lane) & 1) {
-                    if (pos < k) {
-                        idx_out[pos] = j + q;
-                        val_out[pos] = av[q];
+                for (int q = 0; q < 4; ++q) {
+                    if ((kb[u][q] >> lane) & 1) {
+                        if (pos < k) {
+                            idx_out[pos] = j + q;
+                            val_out[pos] = av[q];
+                        }
+                        ++pos;
                     }
-                    ++pos;
                 }
+                at += __popcll(kb[u][0]) + __popcll(kb[u][1]) + __popcll(kb[u][2]) + __popcll(kb[u][3]);
             }
-            base += __popcll(kb[u][0]) + __popcll(kb[u][1]) + __popcll(kb[u][2]) + __popcll(kb[u][3]);
         }
     }
 }
@@ -177,8 +241,12 @@ __global__ __launch_bounds__(kBlock) void k_scatter_pairs(const uint32_t* __rest
     if (r < k && idx[r] < d) p[idx[r]] = val[r];
 }
 
-__global__ __launch_bounds__(kBlock) void k_fill_f32(float* __restrict__ p, uint32_t n, float v) {
-    for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < n; j += gridDim.x * kBlock) p[j] = v;
+// One 128-bit streaming store per thread (8 top-k messages of 11.7M columns, packed and unpacked: 268 us, with plain
+// stores 293).
+template <bool VEC>
+__global__ __launch_bounds__(kBlock) void k_clear_f32(float* __restrict__ p, uint32_t n) {
+    const uint32_t j = (blockIdx.x * kBlock + threadIdx.x) * 4;
+    if (j < n) st4<VEC, true>(p, j, n, make_float4(0.f, 0.f, 0.f, 0.f));
 }
 
 }  // namespace liec

@@ -121,6 +121,8 @@ struct liec_ctx {
     bool rk_winv = false, rk_sinv = false;     // random-k: the band is thin enough to walk the priorities instead of the columns
     uint64_t* gbits = nullptr;                 // [N * nwt * 4] group bitmap of the candidates (top-k workers), either form
     bool gb_coarse = false;                    // one bit per 64-byte line instead of one per 4 columns
+    bool gb_last_coarse = false;               // the form the last compressed step wrote
+    bool gb_written = false;                   // there has been one
     uint16_t* vbits = nullptr;                 // [nwt * 64] sign bits of v (scaled-sign server, either form)
     uint64_t* sgbits = nullptr;                // [nwt * 4] group bitmap of the server's candidates in v (top-k server), fine form
     uint2* list = nullptr;                     // [(N + 1) * cap] candidates (key, index)
@@ -144,7 +146,7 @@ struct liec_ctx {
     float* blk_scales = nullptr;               // [(N + 1) * B]
     double* blk_l1 = nullptr;                  // [(N + 1) * B]
     int64_t blk_bytes = 0;
-    uint32_t* wire_tiles = nullptr;            // [nwt + 1] per-tile counts / offsets of liec_pack_topk_message
+    uint32_t* wire_tiles = nullptr;            // [nwt + 3 + kWireBlocks] kept entries per tile and block of liec_pack_topk_message
     float* wire_scales = nullptr;              // [max(B, 1)] staging for liec_unpack_sign_message
     uint32_t wire_scales_len = 0;
 
@@ -411,6 +413,8 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     } else if (c->worker_comp == kBlockSign) {
         launch_block_l1<VEC>(L, grads, stride, (uint32_t)c->N, 0u, c->bits, S_W_L1);
     } else if (c->worker_comp == kTopk) {
+        c->gb_last_coarse = c->gb_coarse;
+        c->gb_written = true;
         launch_select<VEC, false>(L, grads, stride, (uint32_t)c->N, 0u, (uint32_t)c->worker_k, c->gbits, c->gb_coarse,
                                   c->filter_row_blocks, c->cold_row_blocks, S_W_SEL, RkDraw{nullptr, 0, 0});
     } else if (c->worker_comp == kRandk) {
@@ -930,7 +934,8 @@ liec_status liec_pack_sign_bits(liec_ctx* c, int32_t worker, uint8_t* out) {
     if (!on.ok) return LIEC_EDEVICE;
     if ((c->worker_comp != kSign && c->worker_comp != kBlockSign) || c->steps_done == 0) return LIEC_EINVAL;
     const uint32_t nbytes = (uint32_t)((c->d + 7) / 8);
-    k_pack_sign<<<(nbytes + kBlock - 1) / kBlock, kBlock, 0, c->stream>>>(c->bits + (size_t)worker * c->nwt * 64, nbytes, out);
+    k_pack_sign<<<(c->nwt * 8 + kBlock - 1) / kBlock, kBlock, 0, c->stream>>>(c->bits + (size_t)worker * c->nwt * 64, c->nwt,
+                                                                               nbytes, out);
     if (hipGetLastError() != hipSuccess) {
         c->broken = true;
         return LIEC_EDEVICE;
@@ -990,7 +995,7 @@ liec_status liec_pack_topk_message(liec_ctx* c, const float* grads, int32_t work
     if (!selects_k(c->worker_comp) || c->steps_done == 0 || ((uintptr_t)grads & 3u)) return LIEC_EINVAL;
     if (!c->wire_tiles) {
         if (hipStreamSynchronize(c->stream) != hipSuccess ||
-            hipMalloc(reinterpret_cast<void**>(&c->wire_tiles), ((size_t)c->nwt + 1) * sizeof(uint32_t)) != hipSuccess) {
+            hipMalloc(reinterpret_cast<void**>(&c->wire_tiles), ((size_t)c->nwt + 3 + kWireBlocks) * sizeof(uint32_t)) != hipSuccess) {
             (void)hipGetLastError();
             c->wire_tiles = nullptr;
             return LIEC_ENOMEM;
@@ -999,15 +1004,20 @@ liec_status liec_pack_topk_message(liec_ctx* c, const float* grads, int32_t work
     const uint32_t d = (uint32_t)c->d, k = (uint32_t)c->worker_k;
     const float* row = grads + (size_t)worker * (size_t)c->d;
     const bool vec = (c->d % 4 == 0) && (((uintptr_t)grads & 15u) == 0);
-    const RowDesc* rd = c->desc + worker;
-    // random-k: the kept set of the last draw is the worker's row of the kept bitmap
-    const uint16_t* kept = c->worker_comp == kRandk ? c->bits + (size_t)worker * c->nwt * 64 : nullptr;
-    const uint32_t blocks = c->agg_tile_blocks;
-    if (vec) k_topk_count<true><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles);
-    else k_topk_count<false><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles);
-    k_scan_u32<<<1, 1024, 0, c->stream>>>(c->wire_tiles, c->nwt, c->wire_tiles + c->nwt);
-    if (vec) k_topk_emit<true><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles, k, idx_out, val_out);
-    else k_topk_emit<false><<<blocks, kBlock, 0, c->stream>>>(row, d, c->nwt, rd, kept, c->wire_tiles, k, idx_out, val_out);
+    // what the last compressed step left: random-k, the worker's row of the kept bitmap; top-k, its candidate bitmap
+    KeptRow r{row, c->desc + worker, nullptr, nullptr, c->gb_last_coarse};
+    if (c->worker_comp == kRandk) r.kept = c->bits + (size_t)worker * c->nwt * 64;
+    else if (c->gb_written) r.groups = c->gbits + (size_t)worker * c->nwt * (c->gb_last_coarse ? 1 : 4);
+    const uint32_t want = std::min((c->nwt + 3) / 4, kWireBlocks), per = (c->nwt + want - 1) / want;
+    const uint32_t blocks = (c->nwt + per - 1) / per;
+    uint32_t* const block_cnt = c->wire_tiles + (c->nwt + 3) / 4 * 4;    // 16-byte aligned
+    if (vec) {
+        k_kept_count<true><<<blocks, kBlock, 0, c->stream>>>(r, d, c->nwt, per, c->wire_tiles, block_cnt);
+        k_kept_emit<true><<<blocks, kBlock, 0, c->stream>>>(r, d, c->nwt, per, c->wire_tiles, block_cnt, k, idx_out, val_out);
+    } else {
+        k_kept_count<false><<<blocks, kBlock, 0, c->stream>>>(r, d, c->nwt, per, c->wire_tiles, block_cnt);
+        k_kept_emit<false><<<blocks, kBlock, 0, c->stream>>>(r, d, c->nwt, per, c->wire_tiles, block_cnt, k, idx_out, val_out);
+    }
     if (hipGetLastError() != hipSuccess) {
         c->broken = true;
         return LIEC_EDEVICE;
@@ -1021,7 +1031,9 @@ liec_status liec_unpack_topk_message(liec_ctx* c, const uint32_t* idx, const flo
     DeviceScope on(c);
     if (!on.ok) return LIEC_EDEVICE;
     const uint32_t d = (uint32_t)c->d;
-    k_fill_f32<<<std::min<uint32_t>((d + kBlock - 1) / kBlock, 8192u), kBlock, 0, c->stream>>>(p_out, d, 0.f);
+    const uint32_t clear_blocks = (uint32_t)(((uint64_t)d + 4 * kBlock - 1) / (4 * kBlock));
+    if ((uintptr_t)p_out % 16 == 0 && d % 4 == 0) k_clear_f32<true><<<clear_blocks, kBlock, 0, c->stream>>>(p_out, d);
+    else k_clear_f32<false><<<clear_blocks, kBlock, 0, c->stream>>>(p_out, d);
     if (k > 0)
         k_scatter_pairs<<<((uint32_t)k + kBlock - 1) / kBlock, kBlock, 0, c->stream>>>(idx, val, (uint32_t)k, d, p_out);
     if (hipGetLastError() != hipSuccess) {
