@@ -47,31 +47,53 @@ __global__ __launch_bounds__(kBlock) void k_l1_bits(const float* __restrict__ sr
     if (threadIdx.x == 0) partial[(size_t)row * gridDim.x + blockIdx.x] = s;
 }
 
+// A finished L1 norm and what follows from it, in the row's descriptor.
+__device__ __forceinline__ void set_scale(RowDesc& r, double s, uint32_t d) {
+    r.l1 = s;
+    r.scale = (float)(s / (double)d);
+    r.nonfinite = (s - s == 0.0) ? 0u : 1u;                     // s - s is NaN for NaN and Inf
+}
+
 // Finishes the L1 norm of each row from its block partials (fixed order) and sets the scale.
-// grid = rows, desc points at the first row's descriptor.
-__global__ __launch_bounds__(kBlock) void k_l1_final(const double* __restrict__ partial, uint32_t nparts,
-                                                      uint32_t d, RowDesc* __restrict__ desc) {
-    __shared__ double lds_w[4];
-    const uint32_t row = blockIdx.x;
+// grid = rows, desc points at the first row's descriptor.  256 threads, or 1024 for long rows: the kernel is a round
+// trip or two to memory, and fewer rounds of loads shorten it (16 rows of 33779 partials 15 -> 8 us, event-timed).
+__global__ __launch_bounds__(1024) void k_l1_final(const double* __restrict__ partial, uint32_t nparts,
+                                                   uint32_t d, RowDesc* __restrict__ desc) {
+    __shared__ double lds_w[16];
+    const uint32_t row = blockIdx.x, step = blockDim.x;
     const double* __restrict__ p = partial + (size_t)row * nparts;
     // four independent running sums per thread (fixed assignment, fixed combination order) keep
     // four loads in flight
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    uint32_t q = threadIdx.x;
-    for (; q + 3 * kBlock < nparts; q += 4 * kBlock) {
-        a0 += p[q];
-        a1 += p[q + kBlock];
-        a2 += p[q + 2 * kBlock];
-        a3 += p[q + 3 * kBlock];
+    for (uint32_t q = threadIdx.x; q < nparts; q += 4 * step) {
+        const double b0 = p[q];
+        const double b1 = q + step < nparts ? p[q + step] : 0.0;
+        const double b2 = q + 2 * step < nparts ? p[q + 2 * step] : 0.0;
+        const double b3 = q + 3 * step < nparts ? p[q + 3 * step] : 0.0;
+        a0 += b0;
+        a1 += b1;
+        a2 += b2;
+        a3 += b3;
     }
-    for (; q < nparts; q += kBlock) a0 += p[q];
     const double acc = (a0 + a1) + (a2 + a3);
     const double s = block_sum_f64(acc, lds_w);
-    if (threadIdx.x == 0) {
-        desc[row].l1 = s;
-        desc[row].scale = (float)(s / (double)d);
-        desc[row].nonfinite = (s - s == 0.0) ? 0u : 1u;   // s - s is NaN for NaN and Inf
+    if (threadIdx.x == 0) set_scale(desc[row], s, d);
+}
+
+// The same by one wave, for the kernels that finish a few short sums themselves instead of waiting for a kernel that
+// does.  The sum is valid on lane 0, and the same in every wave that forms it.
+__device__ __forceinline__ double wave_l1(const double* __restrict__ p, uint32_t nparts, uint32_t lane) {
+    double s = 0.0;
+    for (uint32_t q = lane; q < nparts; q += 256) {
+        const double b0 = p[q];
+        const double b1 = q + 64 < nparts ? p[q + 64] : 0.0;
+        const double b2 = q + 128 < nparts ? p[q + 128] : 0.0;
+        const double b3 = q + 192 < nparts ? p[q + 192] : 0.0;
+        s += (b0 + b1) + (b2 + b3);
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    return s;
 }
 
 // ---------------------------------------------------------------------------------------------

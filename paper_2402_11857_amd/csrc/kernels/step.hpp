@@ -49,17 +49,31 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 // (k_aggregate_chunk below also serves the identity, which reads the gradients.)
 // With `vbits` the kernel also leaves the sign bits of v (lane-major half-words like the workers' sign
 // bits) for the update kernel of a scaled-sign server.
+// FOLD (scaled sign, few workers on short rows): the block forms the workers' scales from the partial sums itself.
 // ---------------------------------------------------------------------------------------------
-template <int WC, bool SRV_L1, bool VEC>
+constexpr int kFoldRows = 64;                                   // workers whose scales a block forms at most
+template <int WC, bool SRV_L1, bool VEC, bool FOLD = false>
 __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                        const uint64_t* __restrict__ gbits,
                                                        int N, uint32_t d, uint32_t nwt, float inv_n,
-                                                       const RowDesc* __restrict__ desc, const float* __restrict__ e_in,
+                                                       RowDesc* __restrict__ desc, const float* __restrict__ e_in,
                                                        float* __restrict__ v_out, double* __restrict__ srv_partial,
-                                                       BlockTable bt, bool coarse, uint16_t* __restrict__ vbits) {
+                                                       BlockTable bt, bool coarse, uint16_t* __restrict__ vbits,
+                                                       const double* __restrict__ w_partial, uint32_t w_parts) {
     __shared__ double lds_w[4];
+    __shared__ float folded[FOLD ? kFoldRows : 1];
     __shared__ float accs[(WC == kTopk || WC == kRandk) ? 16 * kBlock : 1];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (FOLD) {
+        for (uint32_t i = wave; i < (uint32_t)N; i += 4) {
+            const double s = wave_l1(w_partial + (size_t)i * w_parts, w_parts, lane);
+            if (lane == 0) {
+                folded[i] = (float)(s / (double)d);
+                if (blockIdx.x == 0) set_scale(desc[i], s, d);  // for the update and the caller's queries
+            }
+        }
+        __syncthreads();
+    }
     double l1 = 0.0;
     for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
         const uint32_t j0 = t * kWaveTile + lane * 4;
@@ -69,15 +83,23 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
         if (WC == kSign) {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
+            auto scale_of = [&](int i) { return FOLD ? folded[i] : desc[i].scale; };
             int i = 0;
             for (; i + 8 <= N; i += 8) {                       // 8 rows of bits in flight
                 uint32_t m[8];
 #pragma unroll
                 for (int r = 0; r < 8; ++r) m[r] = bw[(size_t)(i + r) * brow];
 #pragma unroll
-                for (int r = 0; r < 8; ++r) add_signed(acc, m[r], desc[i + r].scale);
+                for (int r = 0; r < 8; ++r) add_signed(acc, m[r], scale_of(i + r));
             }
-            for (; i < N; ++i) add_signed(acc, bw[(size_t)i * brow], desc[i].scale);
+            if (i < N) {                                        // and the rest of them
+                uint32_t m[7];
+#pragma unroll
+                for (int r = 0; r < 7; ++r) m[r] = bw[(size_t)min(i + r, N - 1) * brow];
+#pragma unroll
+                for (int r = 0; r < 7; ++r)
+                    if (i + r < N) add_signed(acc, m[r], scale_of(i + r));      // uniform
+            }
         } else if (WC == kBlockSign) {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
@@ -91,7 +113,14 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
 #pragma unroll
                     for (int r = 0; r < 8; ++r) add_signed(acc, m[r], bt.scales[(size_t)(i + r) * bt.B + first]);
                 }
-                for (; i < N; ++i) add_signed(acc, bw[(size_t)i * brow], bt.scales[(size_t)i * bt.B + first]);
+                if (i < N) {
+                    uint32_t m[7];
+#pragma unroll
+                    for (int r = 0; r < 7; ++r) m[r] = bw[(size_t)min(i + r, N - 1) * brow];
+#pragma unroll
+                    for (int r = 0; r < 7; ++r)
+                        if (i + r < N) add_signed(acc, m[r], bt.scales[(size_t)(i + r) * bt.B + first]);
+                }
             } else {
                 uint32_t bidx[16];
 #pragma unroll
@@ -222,10 +251,11 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
 template <int WC, bool SRV_L1, bool VEC>
 __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                              const uint64_t* __restrict__ gbits, int N, uint32_t d,
-                                                             uint32_t nwt, float inv_n, const RowDesc* __restrict__ desc,
+                                                             uint32_t nwt, float inv_n, RowDesc* __restrict__ desc,
                                                              const float* __restrict__ e_in, float* __restrict__ v_out,
                                                              double* __restrict__ srv_partial, BlockTable bt, bool coarse,
-                                                             uint16_t* __restrict__ vbits) {
+                                                             uint16_t* __restrict__ vbits, const double* /* w_partial */,
+                                                             uint32_t /* w_parts */) {
     __shared__ double lds_w[4];
     __shared__ uint32_t nibs[4][64];
     constexpr int kRows = 8;                                    // rows requested together
@@ -235,12 +265,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
         const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
         const float4 e = ld4<VEC>(e_in, j, d);
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (WC == kSign || WC == kBlockSign) {
+        if (WC == kBlockSign) {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
-            const uint32_t tb = WC == kBlockSign ? bt.tile_blk[t] : 0u, first = tb & 0x7fffffffu;
+            const uint32_t tb = bt.tile_blk[t], first = tb & 0x7fffffffu;
             uint32_t blk[4] = {first, first, first, first};
-            if (WC == kBlockSign && (tb >> 31)) {               // the tile spans a block boundary
+            if (tb >> 31) {               // the tile spans a block boundary
 #pragma unroll
                 for (int q = 0; q < 4; ++q) blk[q] = block_of(bt, first, j + q < d ? j + q : d - 1);
             }
@@ -252,9 +282,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
                 for (int r = 0; r < kRows; ++r) {
                     if (i0 + r < N) {                           // uniform
                         float s[4];
-                        if (WC == kSign) {
-                            s[0] = s[1] = s[2] = s[3] = desc[i0 + r].scale;
-                        } else if (!(tb >> 31)) {
+                        if (!(tb >> 31)) {
                             s[0] = s[1] = s[2] = s[3] = bt.scales[(size_t)(i0 + r) * bt.B + first];
                         } else {
 #pragma unroll
@@ -367,14 +395,27 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
 // consecutive column tiles), inside a panel row by row, so every row is walked in long contiguous
 // runs while the panel's slice of v stays in cache for the N rows that reuse it; the row-0 block of
 // a tile also writes e.  grid = number of panels * panel * N.
+// FOLD (scaled-sign server, few blocks): the block forms the server's scale from the partial sums itself.
 // ---------------------------------------------------------------------------------------------
-template <int WC, int SC, bool VEC>
+template <int WC, int SC, bool VEC, bool FOLD = false>
 __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ grads, float* __restrict__ x,
                                                     const float* __restrict__ v_in, float* __restrict__ e_out, int N,
                                                     uint32_t panel, uint32_t ncol_tiles, uint32_t d, float neg_lr,
-                                                    const RowDesc* __restrict__ desc, BlockTable bt,
+                                                    RowDesc* __restrict__ desc, BlockTable bt,
                                                     const uint16_t* __restrict__ kbits, const uint16_t* __restrict__ vbits,
-                                                    const uint64_t* __restrict__ sgbits) {
+                                                    const uint64_t* __restrict__ sgbits,
+                                                    const double* __restrict__ s_partial, uint32_t s_parts) {
+    __shared__ float folded;
+    if (FOLD) {                                                 // before any thread leaves
+        if (threadIdx.x < 64) {
+            const double s = wave_l1(s_partial, s_parts, threadIdx.x);
+            if (threadIdx.x == 0) {
+                folded = (float)(s / (double)d);
+                if (blockIdx.x == 0) set_scale(desc[N], s, d);
+            }
+        }
+        __syncthreads();
+    }
     const uint32_t per_panel = panel * (uint32_t)N;
     const uint32_t pn = blockIdx.x / per_panel, r = blockIdx.x % per_panel;
     const uint32_t i = r / panel, tile = pn * panel + r % panel;
@@ -426,13 +467,13 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
         for (int c = 0; c < 4; ++c) {
             const uint32_t b = (tb >> 31) ? block_of(bt, first, j + c < d ? j + c : d - 1) : first;
             sw[c] = WC == kBlockSign ? bt.scales[(size_t)i * bt.B + b] : desc[i].scale;
-            ss[c] = SC == kBlockSign ? bt.scales[(size_t)N * bt.B + b] : sd->scale;
+            ss[c] = SC == kBlockSign ? bt.scales[(size_t)N * bt.B + b] : FOLD ? folded : sd->scale;
         }
     } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             sw[c] = desc[i].scale;
-            ss[c] = sd->scale;
+            ss[c] = FOLD ? folded : sd->scale;
         }
     }
     float4 p;

@@ -107,6 +107,9 @@ struct liec_ctx {
     bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
     uint32_t agg_tile_blocks = 0, agg_chunk_blocks = 0;      // its grid in either form
     uint32_t agg_blocks() const { return agg_chunk ? agg_chunk_blocks : agg_tile_blocks; }
+    // scaled sign on short rows: the aggregation forms the workers' scales from their partial sums, the update the server's
+    bool fold_workers = false;
+    bool fold_server() const { return agg_blocks() <= 256u && (uint64_t)ncol_tiles * (uint64_t)N <= 2048u; }
     uint32_t cold_row_blocks = 0, cold_srv_blocks = 0;   // first-digit histogram (rarely needed)
     uint32_t cap = 0;                          // candidate list capacity per row
 
@@ -358,15 +361,25 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     L.begin(S_AGGREGATE);
     auto launch = [&](auto kernel) {
         kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
-                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits);
+                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->w_partial, c->row_blocks);
     };
-    if (c->agg_chunk) {
-        if (srv_l1) launch(k_aggregate_chunk<WC, true, VEC>);
-        else launch(k_aggregate_chunk<WC, false, VEC>);
-    } else {
-        constexpr int W = WC == kIdentity ? (int)kSign : WC;    // the identity always takes the form above
-        if (srv_l1) launch(k_aggregate<W, true, VEC>);
-        else launch(k_aggregate<W, false, VEC>);
+    bool done = false;
+    if constexpr (WC != kSign) {                                // (scaled sign has the form by tile only)
+        if (WC == kIdentity || c->agg_chunk) {                  // (the identity the form by chunk only)
+            if (srv_l1) launch(k_aggregate_chunk<WC, true, VEC>);
+            else launch(k_aggregate_chunk<WC, false, VEC>);
+            done = true;
+        }
+    } else if (c->fold_workers) {
+        if (srv_l1) launch(k_aggregate<WC, true, VEC, true>);
+        else launch(k_aggregate<WC, false, VEC, true>);
+        done = true;
+    }
+    if constexpr (WC != kIdentity) {
+        if (!done) {
+            if (srv_l1) launch(k_aggregate<WC, true, VEC>);
+            else launch(k_aggregate<WC, false, VEC>);
+        }
     }
     L.end();
 }
@@ -378,9 +391,13 @@ void launch_update(Launcher& L, const float* grads, float* x, float* e) {
     const uint32_t npanels = (c->ncol_tiles + panel - 1) / panel;
     const uint64_t blocks = (uint64_t)npanels * panel * (uint64_t)c->N;
     L.begin(S_UPDATE);
-    k_update<WC, SC, VEC><<<(uint32_t)blocks, kBlock, 0, c->stream>>>(grads, x, c->vbuf, e, c->N, panel, c->ncol_tiles,
-                                                                       (uint32_t)c->d, -c->lr, c->desc, block_table(c),
-                                                                       c->bits, c->vbits, c->sgbits);
+    auto launch = [&](auto kernel) {
+        kernel<<<(uint32_t)blocks, kBlock, 0, c->stream>>>(grads, x, c->vbuf, e, c->N, panel, c->ncol_tiles, (uint32_t)c->d,
+                                                           -c->lr, c->desc, block_table(c), c->bits, c->vbits, c->sgbits,
+                                                           c->s_partial, c->agg_blocks());
+    };
+    if (SC == kSign && c->fold_server()) launch(k_update<WC, SC, VEC, SC == kSign>);
+    else launch(k_update<WC, SC, VEC>);
     L.end();
 }
 
@@ -407,9 +424,11 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
         k_l1_bits<VEC><<<dim3(c->row_blocks, c->N), kBlock, 0, c->stream>>>(grads, stride, d, c->nwt, c->w_partial,
                                                                              c->bits);
         L.end();
-        L.begin(S_W_L1_FINAL);
-        k_l1_final<<<c->N, kBlock, 0, c->stream>>>(c->w_partial, c->row_blocks, d, c->desc);
-        L.end();
+        if (!c->fold_workers) {
+            L.begin(S_W_L1_FINAL);
+            k_l1_final<<<c->N, c->row_blocks > 1024 ? 1024 : kBlock, 0, c->stream>>>(c->w_partial, c->row_blocks, d, c->desc);
+            L.end();
+        }
     } else if (c->worker_comp == kBlockSign) {
         launch_block_l1<VEC>(L, grads, stride, (uint32_t)c->N, 0u, c->bits, S_W_L1);
     } else if (c->worker_comp == kTopk) {
@@ -433,9 +452,11 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     default: launch_aggregate<kTopk, VEC>(L, grads, e, srv_l1); break;
     }
     if (c->server_comp == kSign) {
-        L.begin(S_S_L1_FINAL);
-        k_l1_final<<<1, kBlock, 0, c->stream>>>(c->s_partial, c->agg_blocks(), d, c->desc + c->N);
-        L.end();
+        if (!c->fold_server()) {
+            L.begin(S_S_L1_FINAL);
+            k_l1_final<<<1, c->agg_blocks() > 1024 ? 1024 : kBlock, 0, c->stream>>>(c->s_partial, c->agg_blocks(), d, c->desc + c->N);
+            L.end();
+        }
     } else if (c->server_comp == kBlockSign) {
         launch_block_l1<VEC>(L, c->vbuf, 0, 1u, (uint32_t)c->N, nullptr, S_S_L1);
     } else if (c->server_comp == kTopk) {
@@ -549,10 +570,15 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // The aggregation's form by operator and row length (tiles of 1024 columns), a chunk per wave against a tile per
     // wave in us: top-k, k/d = 1 %, 8 x 1M columns 7 against 28, 16 x 11.7M 61 against 77, but 16 x 25.6M (0.1 %) 112
     // against 68; random-k 8 x 1M 6 against 15, 16 x 4.2M 34 against 36, 16 x 11.7M 81 against 77; blockwise sign
-    // 4 x 65536 4 against 12, 7 x 3.3M 17 against 19, 7 x 7.3M 33 against 27; scaled sign is never faster by chunk
+    // 4 x 65536 4 against 8, 8 x 1M 7 against 11, 16 x 2.1M 18 against 16, 7 x 3.3M 18 against 12; scaled sign is never faster by chunk
     // (the four waves of a tile read the same bits); identity, 8 x 11.7M, 75 against 119.
     c->agg_chunk = worker_comp == LIEC_COMP_IDENTITY || (worker_comp == LIEC_COMP_TOPK && c->nwt < 12288u) ||
-                   (worker_comp == LIEC_COMP_RANDK && c->nwt < 8192u) || (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 4096u);
+                   (worker_comp == LIEC_COMP_RANDK && c->nwt < 8192u) || (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
+    // A kernel that only finishes a few short sums costs its launch and two round trips to memory (3.5 us); the kernels
+    // that use the scales form them as fast while the sums are few.  us per step with and without: 4 x 65536 columns
+    // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 19.4 against 20.8; at 16 x 262144
+    // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.
+    c->fold_workers = worker_comp == LIEC_COMP_SIGN && N <= kFoldRows && (uint64_t)N * c->row_blocks <= 512u;
     auto balanced_filter = [&](uint32_t max_blocks) {
         const uint32_t iters = (c->nwt + 4 * c->filter_run - 1) / (4 * c->filter_run);
         const uint32_t per = (iters + max_blocks - 1) / max_blocks;

@@ -74,8 +74,8 @@ def _chain_blocks_topk(N, d, off):
 
 # first lengths (and one more tile) that take a wave per tile
 @pytest.mark.parametrize("wc,sc,N,d", [("topk", "sign", 2, 12288 * 1024 + 5), ("topk", "sign", 2, 12287 * 1024),
-                                       ("randk", "sign", 2, 8192 * 1024 + 1028), ("blocksign", "sign", 3, 4096 * 1024 + 7),
-                                       ("blocksign", "sign", 3, 4095 * 1024)])
+                                       ("randk", "sign", 2, 8192 * 1024 + 1028), ("blocksign", "sign", 3, 2048 * 1024 + 7),
+                                       ("blocksign", "sign", 3, 2047 * 1024)])
 def test_aggregate_either_side_of_the_rule(wc, sc, N, d):
     say(f"case aggregate rule N={N} d={d} {wc}/{sc}")
     off = [0, 5, d // 3 + 2, d // 3 + 3, d - 1, d] if wc == "blocksign" else None
