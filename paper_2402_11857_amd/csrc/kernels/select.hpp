@@ -238,6 +238,21 @@ __device__ __forceinline__ void put_candidate(uint2* stage, uint2* wst, const St
     else wst[sp.wbase + (p - sp.first_spill)] = entry;
 }
 
+// Appends a chunk's candidates: those of component q are the lanes of bc[q], at column j + q.
+__device__ __forceinline__ void stage_candidates(const FilterBand& fb, const uint32_t (&keys)[4], uint32_t j,
+                                                 const uint64_t (&bc)[4], uint2* stage, uint2* wst, uint32_t& wcnt,
+                                                 uint32_t* staged, uint32_t lane) {
+    if ((bc[0] | bc[1] | bc[2] | bc[3]) == 0) return;           // wave-uniform
+    const uint32_t m = __popcll(bc[0]) + __popcll(bc[1]) + __popcll(bc[2]) + __popcll(bc[3]);
+    const StagePos sp = reserve_stage(fb, m, staged, wst, wcnt, lane);
+    uint32_t off = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if ((bc[q] >> lane) & 1) put_candidate(stage, wst, sp, off + lanes_below(bc[q]), make_uint2(keys[q], j + q));
+        off += __popcll(bc[q]);
+    }
+}
+
 // End of a filter block.  n_hi: keys above the band, per lane; wst / wcnt: the wave's own stage.  Every thread of
 // the block calls it.
 __device__ __forceinline__ void finish_filter_block(const FilterBand& fb, const uint2* stage, const uint2* wst, uint32_t wcnt,
@@ -338,17 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
                 if (!coarse) pend = lane == 4 * ti + (uint32_t)u ? any_lo : pend;
             }
             sure16 |= hi4 << (4 * u);
-            const uint64_t any_cand = bc[0] | bc[1] | bc[2] | bc[3];
-            if (any_cand) {                                     // wave-uniform
-                const uint32_t m = __popcll(bc[0]) + __popcll(bc[1]) + __popcll(bc[2]) + __popcll(bc[3]);
-                const StagePos sp = reserve_stage(fb, m, staged, wst, wcnt, lane);
-                uint32_t off = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if ((bc[q] >> lane) & 1) put_candidate(stage, wst, sp, off + lanes_below(bc[q]), make_uint2(keys[q], j + q));
-                    off += __popcll(bc[q]);
-                }
-            }
+            stage_candidates(fb, keys, j, bc, stage, wst, wcnt, staged, lane);
         }
         if (RK) kbits[((size_t)row * nwt + t) * 64 + lane] = (uint16_t)sure16;
         else if (coarse) pend = lane == ti ? line_word : pend;

@@ -1,6 +1,7 @@
 // Server compensation, server compression, error update and the workers' update (Algorithm 1).
 #pragma once
 #include "common.hpp"
+#include "select.hpp"
 #include "sign.hpp"
 
 namespace liec {
@@ -239,6 +240,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
     }
 }
 
+struct ServerFilter {          // the first filter pass of the server's row, ridden by the aggregation
+    uint2* list;
+    uint32_t cap, k;
+    uint64_t* sgbits;
+};
+
 // ---------------------------------------------------------------------------------------------
 // The same sums with a wave owning one chunk (256 columns, 4 per lane) and a block one wave tile at a time: four times
 // as many waves.  For rows too short to fill the chip with a wave per tile, where the kernel is bound by the latency
@@ -248,17 +255,28 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
 // chunks of row after row at 3.9.  On long rows the work per row and chunk (a group word for 256 columns) costs more
 // instructions than the gathers do; the host's rule has both sides' times.
 // ---------------------------------------------------------------------------------------------
-template <int WC, bool SRV_L1, bool VEC>
+// SRV_FILTER (top-k server): the values of v are filtered against the server's predicted band while they are in
+// registers, as k_filter's first pass would after reading them back.
+template <int WC, bool SRV_L1, bool VEC, bool SRV_FILTER>
 __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                              const uint64_t* __restrict__ gbits, int N, uint32_t d,
                                                              uint32_t nwt, float inv_n, RowDesc* __restrict__ desc,
                                                              const float* __restrict__ e_in, float* __restrict__ v_out,
                                                              double* __restrict__ srv_partial, BlockTable bt, bool coarse,
-                                                             uint16_t* __restrict__ vbits, const double* /* w_partial */,
-                                                             uint32_t /* w_parts */) {
+                                                             uint16_t* __restrict__ vbits, ServerFilter sf) {
     __shared__ double lds_w[4];
     __shared__ uint32_t nibs[4][64];
+    __shared__ uint2 stage[SRV_FILTER ? kStage : 1], wstage[4][SRV_FILTER ? kWaveStage : 1];
+    __shared__ uint32_t wsure[5], staged[2];
     constexpr int kRows = 8;                                    // rows requested together
+    FilterBand fb{};
+    bool filter = false;                                        // uniform: the server's row has a predicted band
+    uint32_t n_hi = 0, kmax = 0, wcnt = 0;
+    if (SRV_FILTER) {
+        filter = filter_band(desc, (uint32_t)N, false, nullptr, sf.list, sf.cap, sf.k, nullptr, nullptr, fb);
+        if (threadIdx.x < 2) staged[threadIdx.x] = 0;
+        __syncthreads();
+    }
     const uint32_t u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // my chunk of the tile
     double l1 = 0.0;
     for (uint32_t t = blockIdx.x; t < nwt; t += gridDim.x) {   // uniform for the block
@@ -367,6 +385,14 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
         v.z = __fmaf_rn(acc.z, inv_n, e.z);
         v.w = __fmaf_rn(acc.w, inv_n, e.w);
         st4<VEC>(v_out, j, d, v);
+        if (SRV_FILTER && filter) {
+            const uint32_t keys[4] = {key_of(v.x), key_of(v.y), key_of(v.z), key_of(v.w)};
+            uint64_t bc[4];
+            uint32_t hi4;
+            const uint64_t any_lo = filter_chunk<false, false>(keys, j, d, fb.lo, fb.hi, bc, n_hi, kmax, hi4);
+            if (lane == 0) sf.sgbits[(size_t)t * 4 + u] = any_lo;
+            stage_candidates(fb, keys, j, bc, stage, wstage[u], wcnt, staged, lane);
+        }
         if (SRV_L1) {
             if (j < d) l1 += (double)fabsf(v.x);
             if (j + 1 < d) l1 += (double)fabsf(v.y);
@@ -385,6 +411,10 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     if (SRV_L1) {
         const double s = block_sum_f64(l1, lds_w);
         if (threadIdx.x == 0) srv_partial[blockIdx.x] = s;
+    }
+    if (SRV_FILTER && filter) {
+        if (__ballot(kmax >= 0x7f800000u) && lane == 0) atomicOr(&desc[N].nonfinite_acc, 1u);     // Inf / NaN
+        finish_filter_block(fb, stage, wstage[u], wcnt, n_hi, staged, wsure);
     }
 }
 

@@ -88,6 +88,12 @@ hipError_t static_scratch(double** out) {
 
 }  // namespace
 
+// Top-k server on rows of at most so many tiles, aggregation by chunk: v is filtered against the server's predicted
+// band where it is formed, which saves reading it back and a launch.  us per step with and without: 8 x 262144 columns
+// 42.4 against 46.6, 8 x 1M 63.6 against 67.2, 8 x 4.2M 164 against 168; even at 8 x 8M and 8 x 11.7M, where every
+// tile's block adds to the row's one counter word.
+constexpr uint32_t kAggFilterTiles = 4096;
+
 struct liec_ctx {
     int32_t N = 0;
     int64_t d = 0;
@@ -107,6 +113,8 @@ struct liec_ctx {
     bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
     uint32_t agg_tile_blocks = 0, agg_chunk_blocks = 0;      // its grid in either form
     uint32_t agg_blocks() const { return agg_chunk ? agg_chunk_blocks : agg_tile_blocks; }
+    // top-k server on short rows: the aggregation makes the first filter pass over v
+    bool agg_filters() const { return server_comp == kTopk && agg_chunk && nwt <= kAggFilterTiles; }
     // scaled sign on short rows: the aggregation forms the workers' scales from their partial sums, the update the server's
     bool fold_workers = false;
     bool fold_server() const { return agg_blocks() <= 256u && (uint64_t)ncol_tiles * (uint64_t)N <= 2048u; }
@@ -285,7 +293,7 @@ struct Launcher {
 template <bool VEC, bool RK>
 void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t rows, uint32_t row0, uint32_t k,
                    uint64_t* gbits, bool coarse, uint32_t blocks, uint32_t cold_blocks, int slot0, RkDraw rk,
-                   bool rk_inverse = false) {
+                   bool rk_inverse = false, bool filtered = false) {
     liec_ctx* c = L.c;
     const uint32_t d = (uint32_t)c->d;
     hipStream_t st = c->stream;
@@ -297,6 +305,7 @@ void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t ro
     const dim3 zero_grid(std::min<uint32_t>((c->nwt * 32 + kBlock - 1) / kBlock, 4096u), rows);
     for (int pass = 0; pass < 2; ++pass) {
         const bool cold_pass = pass == 1;
+        if (!cold_pass && filtered) continue;                   // whoever wrote `src` has made the first pass
         if (cold_pass) {
             L.begin(slot0 + 1);
             k_hist0<VEC, RK><<<cold_grid, kBlock, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, c->ghist, c->list, c->cap, k, rk);
@@ -359,15 +368,22 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     const float inv_n = 1.0f / (float)c->N;
     const uint32_t d = (uint32_t)c->d;
     L.begin(S_AGGREGATE);
+    auto launch_chunk = [&](auto kernel) {
+        const ServerFilter sf{c->list, c->cap, (uint32_t)c->server_k, c->sgbits};
+        kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
+                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, sf);
+    };
     auto launch = [&](auto kernel) {
         kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
-                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->w_partial, c->row_blocks);
+                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->w_partial,
+                                                       c->row_blocks);
     };
     bool done = false;
     if constexpr (WC != kSign) {                                // (scaled sign has the form by tile only)
         if (WC == kIdentity || c->agg_chunk) {                  // (the identity the form by chunk only)
-            if (srv_l1) launch(k_aggregate_chunk<WC, true, VEC>);
-            else launch(k_aggregate_chunk<WC, false, VEC>);
+            if (srv_l1) launch_chunk(k_aggregate_chunk<WC, true, VEC, false>);
+            else if (c->agg_filters()) launch_chunk(k_aggregate_chunk<WC, false, VEC, true>);
+            else launch_chunk(k_aggregate_chunk<WC, false, VEC, false>);
             done = true;
         }
     } else if (c->fold_workers) {
@@ -463,7 +479,8 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
         // v is always 16-byte aligned scratch, but d % 4 decides whether 128-bit loads stay in bounds
         // the server's candidates get the fine group bitmap: the update kernel reads v only where a bit is set
         launch_select<VEC, false>(L, c->vbuf, 0, 1u, (uint32_t)c->N, (uint32_t)c->server_k, c->sgbits, false,
-                                  c->filter_srv_blocks, c->cold_srv_blocks, S_S_SEL, RkDraw{nullptr, 0, 0});
+                                  c->filter_srv_blocks, c->cold_srv_blocks, S_S_SEL, RkDraw{nullptr, 0, 0}, false,
+                                  c->agg_filters());
     } else if (c->server_comp == kRandk) {
         launch_select<VEC, true>(L, c->vbuf, 0, 1u, (uint32_t)c->N, (uint32_t)c->server_k, nullptr, false,
                                  c->filter_srv_blocks, c->cold_srv_blocks, S_S_SEL,

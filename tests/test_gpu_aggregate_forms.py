@@ -41,20 +41,21 @@ def _chain(N, d, wc, sc, k, steps, off=None, batching=None):
 
 
 @pytest.mark.parametrize("wc,sc", [("topk", "sign"), ("topk", "blocksign"), ("randk", "sign"), ("identity", "sign"),
-                                   ("identity", "topk"), ("blocksign", "blocksign"), ("sign", "sign")])
+                                   ("identity", "topk"), ("blocksign", "blocksign"), ("sign", "sign"),
+                                   ("topk", "topk"), ("randk", "topk"), ("blocksign", "topk")])
 @pytest.mark.parametrize("N,d", [(1, 1024), (7, 1025), (8, 255), (9, 257), (16, 1280), (17, 3079)])
 def test_aggregate_small(N, d, wc, sc):
     say(f"case aggregate N={N} d={d} {wc}/{sc}")
     off = None
     if "blocksign" in (wc, sc):
         off = [0, 3, 254, d] if d > 254 else [0, 3, d]          # boundaries inside a group of 4 columns and near a chunk's end
-    if off is not None and wc == "topk":
-        _chain_blocks_topk(N, d, off)
+    if off is not None and "topk" in (wc, sc):
+        _chain_blocks_topk(N, d, off, wc, sc)
     else:
         _chain(N, d, wc, sc, max(1, d // 10), 3, off, 0 if wc == "topk" else None)
 
 
-def _chain_blocks_topk(N, d, off):
+def _chain_blocks_topk(N, d, off, wc, sc):
     import oracle
     from paper_2402_11857_amd import LiecContext
 
@@ -62,21 +63,24 @@ def _chain_blocks_topk(N, d, off):
     k = max(1, d // 10)
     x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
     xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
-    with LiecContext(N, d, "topk", "blocksign", k, 0, 0.05) as ctx:
+    with LiecContext(N, d, wc, sc, k, k, 0.05) as ctx:
         ctx.set_blocks(off)
         for t in range(3):
             g = rng.standard_normal((N, d), dtype=np.float32)
             ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
             torch.cuda.synchronize()
-            oracle.step_blocks(g, x, e, "topk", "blocksign", 0.05, off, k, 0)
+            oracle.step_blocks(g, x, e, wc, sc, 0.05, off, k, k)
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
 
 
 # first lengths (and one more tile) that take a wave per tile
 @pytest.mark.parametrize("wc,sc,N,d", [("topk", "sign", 2, 12288 * 1024 + 5), ("topk", "sign", 2, 12287 * 1024),
                                        ("randk", "sign", 2, 8192 * 1024 + 1028), ("blocksign", "sign", 3, 2048 * 1024 + 7),
-                                       ("blocksign", "sign", 3, 2047 * 1024)])
+                                       ("blocksign", "sign", 3, 2047 * 1024),
+                                       # the aggregation makes a top-k server's first filter pass, and does not any more
+                                       ("topk", "topk", 2, 4096 * 1024), ("topk", "topk", 2, 4096 * 1024 + 3),
+                                       ("identity", "topk", 2, 4095 * 1024 + 6), ("identity", "topk", 2, 4096 * 1024 + 4)])
 def test_aggregate_either_side_of_the_rule(wc, sc, N, d):
     say(f"case aggregate rule N={N} d={d} {wc}/{sc}")
     off = [0, 5, d // 3 + 2, d // 3 + 3, d - 1, d] if wc == "blocksign" else None
-    _chain(N, d, wc, sc, d // 500, 2, off)
+    _chain(N, d, wc, sc, d // 500, 3 if sc == "topk" else 2, off)
