@@ -62,11 +62,11 @@ liec_status liec_set_group_bitmap(liec_ctx *ctx, int32_t per_line);
 
 /*
  * Testing and tuning aid for top-k workers: how the aggregation (Algorithm 1,
- * v = e + mean p^i) fetches the rows' candidates -- 0: a wave per 1024 columns, row
- * after row, 1: a wave per 256 columns, the candidates of 8 rows requested
- * together, then added in worker order.  liec_create* picks the second for rows
- * under 12288 * 1024 columns, where the kernel is bound by the latency of its
- * dependent loads; results do not depend on it.  Takes effect with the next
+ * v = e + mean p^i) fetches the rows' candidates -- 0: a wave per 1024 columns, the
+ * candidates of 16 rows through a list, 1: a wave per 256 columns, the candidates
+ * of 8 rows requested together.  Either way they are added in worker order.
+ * liec_create* picks the second for rows under 2^23 columns; results do not
+ * depend on it.  Takes effect with the next
  * step.  LIEC_EINVAL for another value or when the workers' operator is not
  * top-k.
  */

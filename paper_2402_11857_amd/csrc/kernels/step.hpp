@@ -42,12 +42,7 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 // |v| (fp64) for the server's scaled-sign operator.  grid = blocks; waves stride over wave tiles.
 //   WC == kSign / kBlockSign  read the packed sign bits instead of the gradients (blockwise: the scale
 //                   comes from the column's block);
-//   WC == kTopk     reads each row's group bitmap (one bit per 4 columns, or `coarse`: per 64-byte line) and
-//                   fetches only the flagged groups, testing their gradients against (tau, cut-off); per-lane
-//                   sums live in LDS;
-//   WC == kRandk    reads each row's kept bitmap and fetches only the groups of 4 gradients that hold a
-//                   kept column;
-// (k_aggregate_chunk below also serves the identity, which reads the gradients.)
+// (k_aggregate_sparse and k_aggregate_chunk below serve the other operators.)
 // With `vbits` the kernel also leaves the sign bits of v (lane-major half-words like the workers' sign
 // bits) for the update kernel of a scaled-sign server.
 // FOLD (scaled sign, few workers on short rows): the block forms the workers' scales from the partial sums itself.
@@ -63,7 +58,6 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
                                                        const double* __restrict__ w_partial, uint32_t w_parts) {
     __shared__ double lds_w[4];
     __shared__ float folded[FOLD ? kFoldRows : 1];
-    __shared__ float accs[(WC == kTopk || WC == kRandk) ? 16 * kBlock : 1];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (FOLD) {
         for (uint32_t i = wave; i < (uint32_t)N; i += 4) {
@@ -141,74 +135,6 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
                     }
                 }
             }
-        } else if (WC == kTopk) {
-            float* my = accs + threadIdx.x;                    // slot b of this lane: my[b * kBlock]
-#pragma unroll
-            for (int b = 0; b < 16; ++b) my[b * kBlock] = 0.f;
-            // the tile's group word(s) of row 0: one (coarse: bit 4m + u for 64-byte line m of chunk u) or four (a bit per lane)
-            const uint64_t* __restrict__ gw = gbits + (coarse ? (size_t)t : (size_t)t * 4);
-            const size_t grow = coarse ? (size_t)nwt : (size_t)nwt * 4;
-            const uint32_t four = lane >> 2;                   // my 64-byte line inside a chunk
-            for (int i = 0; i < N; ++i) {
-                const float* __restrict__ gi = grads + (size_t)i * d;
-                const uint32_t tau = desc[i].tau, cut = desc[i].cutoff;
-                uint32_t mask = 0xfu;                          // bit u: my line of chunk u holds a candidate
-                if (!desc[i].dense && coarse) {
-                    mask = (uint32_t)(gw[(size_t)i * grow] >> (4 * four)) & 0xfu;   // bit 4 * line + chunk
-                } else if (!desc[i].dense) {
-                    const uint64_t* __restrict__ w = gw + (size_t)i * grow;
-                    mask = (uint32_t)((w[0] >> lane) & 1) | (uint32_t)((w[1] >> lane) & 1) << 1 |
-                           (uint32_t)((w[2] >> lane) & 1) << 2 | (uint32_t)((w[3] >> lane) & 1) << 3;
-                }
-                while (mask) {
-                    const int u = __builtin_ctz(mask);
-                    mask &= mask - 1;
-                    const uint32_t j = j0 + u * kChunk;
-                    const float4 g = ld4<VEC>(gi, j, d);
-                    const float gv[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t key = key_of(gv[q]);
-                        if (j + q < d && (key > tau || (key == tau && j + q <= cut))) {
-                            float* slot = my + (4 * u + q) * kBlock;
-                            *slot = __fadd_rn(*slot, gv[q]);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                acc[u] = make_float4(my[(4 * u) * kBlock], my[(4 * u + 1) * kBlock], my[(4 * u + 2) * kBlock],
-                                     my[(4 * u + 3) * kBlock]);
-        } else if (WC == kRandk) {
-            // the kept bitmap of each row (one half-word per lane and wave tile) names the columns to fetch
-            float* my = accs + threadIdx.x;
-#pragma unroll
-            for (int b = 0; b < 16; ++b) my[b * kBlock] = 0.f;
-            const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
-            const size_t brow = (size_t)nwt * 64;
-            for (int i = 0; i < N; ++i) {
-                const float* __restrict__ gi = grads + (size_t)i * d;
-                uint32_t m = bw[(size_t)i * brow];
-                while (m) {
-                    const int u = __builtin_ctz(m) >> 2;
-                    const uint32_t nib = (m >> (4 * u)) & 0xfu;
-                    m &= ~(0xfu << (4 * u));
-                    const float4 g = ld4<VEC>(gi, j0 + u * kChunk, d);
-                    const float gv[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if ((nib >> q) & 1) {
-                            float* slot = my + (4 * u + q) * kBlock;
-                            *slot = __fadd_rn(*slot, gv[q]);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                acc[u] = make_float4(my[(4 * u) * kBlock], my[(4 * u + 1) * kBlock], my[(4 * u + 2) * kBlock],
-                                     my[(4 * u + 3) * kBlock]);
         }
         uint32_t vm = 0;                                        // sign bits of my 16 values of v
 #pragma unroll
@@ -221,9 +147,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
             v.z = __fmaf_rn(acc[u].z, inv_n, e.z);
             v.w = __fmaf_rn(acc[u].w, inv_n, e.w);
             vm |= ((v.x < 0.f ? 1u : 0u) | (v.y < 0.f ? 2u : 0u) | (v.z < 0.f ? 4u : 0u) | (v.w < 0.f ? 8u : 0u)) << (4 * u);
-            // with the gathering operators a streaming store of v measured 10 % faster, with the others slower
-            if (WC == kTopk || WC == kRandk) st4<VEC, true>(v_out, j, d, v);
-            else st4<VEC>(v_out, j, d, v);
+            st4<VEC>(v_out, j, d, v);
             if (SRV_L1) {
                 if (j < d) l1 += (double)fabsf(v.x);
                 if (j + 1 < d) l1 += (double)fabsf(v.y);
@@ -233,6 +157,226 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
         }
         // a scaled-sign server's message is these bits and one scale: the update kernel reads them instead of v
         if (vbits) vbits[(size_t)t * 64 + lane] = (uint16_t)vm;
+    }
+    if (SRV_L1) {
+        const double s = block_sum_f64(l1, lds_w);
+        if (threadIdx.x == 0) srv_partial[blockIdx.x] = s;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Top-k and random-k on long rows: the same sums, a wave per wave tile, from each row's bitmap -- top-k, the candidate
+// bitmap (one bit per 4 columns, or `coarse`: per 64-byte line), whose groups are fetched and tested against (tau,
+// cut-off); random-k, the kept bitmap.  A tile holds a few flagged groups per row, so going row after row spends a
+// dependent gather, and instructions for 64 lanes, on a handful of lanes each time.  Instead the lanes share 16 rows'
+// flags (4 lanes a row), write the flagged groups to a list in LDS in row order, and take it 64 entries at a time:
+// one gather for 64 groups of all rows.  Sums live in LDS, one float4 per group.  Entries of one batch that fall on
+// the same group are added in row order: every lane offers its row to the group's slot (atomic minimum), the lowest
+// one adds, the others offer again.  Tiles with more flagged groups than the list holds (layers of large gradients,
+// rows without a valid bitmap) go row by row, two rows' groups requested together.  Row after row with one dependent
+// gather each, against this: random-k 32 x 25.6M columns 154 -> 75 us, top-k of the same size 109 -> 71 (90 with a list
+// of 256), both 0.1 %; top-k 16 x 16M, 1 %, 83 -> 60; top-k 16 x 138M, 0.5 % (1.1 GB of e and v and 0.8 GB of gradients
+// in layers where every line holds a candidate), 391 -> 380.
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kSparseList = 512;                           // flagged groups (coarse: lines) of 16 rows the list holds
+__device__ __forceinline__ void wave_sync() {                   // LDS traffic between the lanes of one wave
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ uint32_t nonzero_nibbles(uint32_t x) {
+    x |= x >> 1;
+    x |= x >> 2;
+    return x & 0x11111111u;
+}
+// Which of the 4 columns j .. j + 3 are kept, by the threshold.
+__device__ __forceinline__ uint32_t kept_of_4(float4 g, uint32_t j, uint32_t d, uint32_t tau, uint32_t cut) {
+    const float gv[4] = {g.x, g.y, g.z, g.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t key = key_of(gv[q]);
+        m |= (j + q < d && (key > tau || (key == tau && j + q <= cut)) ? 1u : 0u) << q;
+    }
+    return m;
+}
+__device__ __forceinline__ void add_kept(float4& acc, float4 g, uint32_t keep) {
+    if (keep & 1u) acc.x = __fadd_rn(acc.x, g.x);
+    if (keep & 2u) acc.y = __fadd_rn(acc.y, g.y);
+    if (keep & 4u) acc.z = __fadd_rn(acc.z, g.z);
+    if (keep & 8u) acc.w = __fadd_rn(acc.w, g.w);
+}
+template <int WC, bool SRV_L1, bool VEC>
+__global__ __launch_bounds__(kBlock) void k_aggregate_sparse(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
+                                                              const uint64_t* __restrict__ gbits, int N, uint32_t d,
+                                                              uint32_t nwt, float inv_n, const RowDesc* __restrict__ desc,
+                                                              const float* __restrict__ e_in, float* __restrict__ v_out,
+                                                              double* __restrict__ srv_partial, bool coarse,
+                                                              uint16_t* __restrict__ vbits) {
+    __shared__ double lds_w[4];
+    __shared__ float4 accs[4][256];
+    __shared__ uint32_t slots[4][256], lists[4][kSparseList];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    float4* const acc = accs[wave];                             // group 64u + l: the 4 columns of lane l in chunk u
+    uint32_t* const slot = slots[wave];
+    uint32_t* const list = lists[wave];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) slot[u * 64 + lane] = 0xffffffffu;
+    double l1 = 0.0;
+    for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
+        const uint32_t j0 = t * kWaveTile + lane * 4;
+        float4 e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            e[u] = ld4<VEC>(e_in, j0 + u * kChunk, d);
+            acc[u * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        wave_sync();
+        for (int i0 = 0; i0 < N; i0 += 16) {
+            const uint32_t row = (uint32_t)i0 + (lane >> 2), part = lane & 3;
+            uint64_t w = 0;                                     // top-k: my share of my row's flags
+            uint32_t x[8] = {0, 0, 0, 0, 0, 0, 0, 0};           // random-k: my 16 half-words of them
+            uint32_t cnt = 0;
+            if (row < (uint32_t)N) {
+                if (WC == kTopk) {
+                    if (coarse) w = (gbits[(size_t)row * nwt + t] >> (16 * part)) & 0xffffu;
+                    else w = gbits[((size_t)row * nwt + t) * 4 + part];
+                    if (desc[row].dense) w = coarse ? 0xffffull : ~0ull;
+                    cnt = (uint32_t)__popcll(w);
+                } else {
+                    const uint4* __restrict__ b = reinterpret_cast<const uint4*>(bits + ((size_t)row * nwt + t) * 64) + part * 2;
+                    const uint4 b0 = b[0], b1 = b[1];
+                    x[0] = b0.x; x[1] = b0.y; x[2] = b0.z; x[3] = b0.w;
+                    x[4] = b1.x; x[5] = b1.y; x[6] = b1.z; x[7] = b1.w;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) cnt += (uint32_t)__popc(nonzero_nibbles(x[q]));
+                }
+            }
+            uint32_t incl = cnt;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t up = __shfl_up(incl, o, 64);
+                if ((int)lane >= o) incl += up;
+            }
+            const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+            if (total == 0) continue;
+            if (total <= kSparseList) {                         // wave-uniform
+                uint32_t pos = incl - cnt;
+                if (WC == kTopk) {
+                    while (w) {
+                        const uint32_t b = (uint32_t)__builtin_ctzll(w), line = 16 * part + b;
+                        w &= w - 1;
+                        list[pos++] = row << 16 | (coarse ? (line & 3) * 64 + (line >> 2) * 4 : part * 64 + b) << 4;
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        uint32_t m = nonzero_nibbles(x[q]);
+                        while (m) {
+                            const uint32_t b = (uint32_t)__builtin_ctz(m);
+                            m &= m - 1;
+                            list[pos++] = row << 16 | ((b >> 2 & 3) * 64 + part * 16 + q * 2 + (b >> 4)) << 4 | (x[q] >> b & 0xfu);
+                        }
+                    }
+                }
+                wave_sync();
+                const uint32_t sub = WC == kTopk && coarse ? 2 : 0, n = total << sub;      // a line is 4 groups
+                for (uint32_t base = 0; base < n; base += 64) {
+                    const uint32_t at = base + lane;
+                    const bool live = at < n;
+                    const uint32_t ent = live ? list[at >> sub] : 0u;
+                    const uint32_t r = ent >> 16, gi = (ent >> 4 & 0xffu) + (sub ? at & 3u : 0u);
+                    const uint32_t j = t * kWaveTile + (gi >> 6) * kChunk + (gi & 63) * 4;
+                    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+                    uint32_t keep = 0;
+                    if (live) {
+                        g = ld4<VEC>(grads + (size_t)r * d, j, d);
+                        keep = WC == kRandk ? ent & 0xfu : kept_of_4(g, j, d, desc[r].tau, desc[r].cutoff);
+                    }
+                    while (__ballot(keep != 0)) {
+                        if (keep) atomicMin(&slot[gi], r);
+                        wave_sync();
+                        const bool mine = keep && slot[gi] == r;
+                        wave_sync();
+                        if (mine) {
+                            float4 a = acc[gi];
+                            add_kept(a, g, keep);
+                            acc[gi] = a;
+                            slot[gi] = 0xffffffffu;
+                            keep = 0;
+                        }
+                        wave_sync();
+                    }
+                }
+            } else {
+                const int end = min(i0 + 16, N);
+                for (int i = i0; i < end; i += 2) {
+                    float4 g[2][4];
+                    uint32_t flag[2];                           // top-k: bit u, my group of chunk u; random-k: my kept bits
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const size_t ir = (size_t)min(i + r, N - 1);
+                        if (WC == kRandk) {
+                            flag[r] = bits[(ir * nwt + t) * 64 + lane];
+                        } else if (coarse) {
+                            flag[r] = (uint32_t)(gbits[ir * nwt + t] >> (4 * (lane >> 2))) & 0xfu;
+                        } else {
+                            const uint64_t* __restrict__ f = gbits + (ir * nwt + t) * 4;
+                            flag[r] = (uint32_t)((f[0] >> lane) & 1) | (uint32_t)((f[1] >> lane) & 1) << 1 |
+                                      (uint32_t)((f[2] >> lane) & 1) << 2 | (uint32_t)((f[3] >> lane) & 1) << 3;
+                        }
+                        if (WC == kTopk && desc[ir].dense) flag[r] = 0xfu;
+                        if (i + r >= N) flag[r] = 0;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const float* __restrict__ gr = grads + (size_t)min(i + r, N - 1) * d;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const bool want = WC == kRandk ? ((flag[r] >> (4 * u)) & 0xfu) != 0 : ((flag[r] >> u) & 1u) != 0;
+                            g[r][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                            if (want) g[r][u] = ld4<VEC>(gr, j0 + u * kChunk, d);
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const int ir = min(i + r, N - 1);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            uint32_t keep = (flag[r] >> (4 * u)) & 0xfu;
+                            if (WC == kTopk)
+                                keep = ((flag[r] >> u) & 1u) ? kept_of_4(g[r][u], j0 + u * kChunk, d, desc[ir].tau, desc[ir].cutoff) : 0u;
+                            if (keep) {                         // my own groups: no other lane adds to them here
+                                float4 a = acc[u * 64 + lane];
+                                add_kept(a, g[r][u], keep);
+                                acc[u * 64 + lane] = a;
+                            }
+                        }
+                    }
+                }
+            }
+            wave_sync();
+        }
+        uint32_t vm = 0;                                        // sign bits of my 16 values of v
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t j = j0 + u * kChunk;
+            const float4 a = acc[u * 64 + lane];
+            float4 v;
+            v.x = __fmaf_rn(a.x, inv_n, e[u].x);
+            v.y = __fmaf_rn(a.y, inv_n, e[u].y);
+            v.z = __fmaf_rn(a.z, inv_n, e[u].z);
+            v.w = __fmaf_rn(a.w, inv_n, e[u].w);
+            vm |= ((v.x < 0.f ? 1u : 0u) | (v.y < 0.f ? 2u : 0u) | (v.z < 0.f ? 4u : 0u) | (v.w < 0.f ? 8u : 0u)) << (4 * u);
+            st4<VEC, true>(v_out, j, d, v);
+            if (SRV_L1) {
+                if (j < d) l1 += (double)fabsf(v.x);
+                if (j + 1 < d) l1 += (double)fabsf(v.y);
+                if (j + 2 < d) l1 += (double)fabsf(v.z);
+                if (j + 3 < d) l1 += (double)fabsf(v.w);
+            }
+        }
+        if (vbits) vbits[(size_t)t * 64 + lane] = (uint16_t)vm;
+        wave_sync();                                            // the sums are read before the next tile clears them
     }
     if (SRV_L1) {
         const double s = block_sum_f64(l1, lds_w);

@@ -391,7 +391,16 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
         else launch(k_aggregate<WC, false, VEC, true>);
         done = true;
     }
-    if constexpr (WC != kIdentity) {
+    if constexpr (WC == kTopk || WC == kRandk) {
+        if (!done) {
+            auto launch_sparse = [&](auto kernel) {
+                kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e,
+                                                               c->vbuf, c->s_partial, c->gb_coarse, c->vbits);
+            };
+            if (srv_l1) launch_sparse(k_aggregate_sparse<WC, true, VEC>);
+            else launch_sparse(k_aggregate_sparse<WC, false, VEC>);
+        }
+    } else if constexpr (WC != kIdentity) {
         if (!done) {
             if (srv_l1) launch(k_aggregate<WC, true, VEC>);
             else launch(k_aggregate<WC, false, VEC>);
@@ -584,13 +593,16 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // group words it writes fill whole 128-byte lines of the bitmap: measured 2 % faster than 1 on rows of 25M
     // and 138M columns, 2 and 8 in between); short rows keep 1, so that enough blocks are in flight.
     c->filter_run = c->nwt >= 8192u ? 4u : 1u;
-    // The aggregation's form by operator and row length (tiles of 1024 columns), a chunk per wave against a tile per
-    // wave in us: top-k, k/d = 1 %, 8 x 1M columns 7 against 28, 16 x 11.7M 61 against 77, but 16 x 25.6M (0.1 %) 112
-    // against 68; random-k 8 x 1M 6 against 15, 16 x 4.2M 34 against 36, 16 x 11.7M 81 against 77; blockwise sign
-    // 4 x 65536 4 against 8, 8 x 1M 7 against 11, 16 x 2.1M 18 against 16, 7 x 3.3M 18 against 12; scaled sign is never faster by chunk
-    // (the four waves of a tile read the same bits); identity, 8 x 11.7M, 75 against 119.
-    c->agg_chunk = worker_comp == LIEC_COMP_IDENTITY || (worker_comp == LIEC_COMP_TOPK && c->nwt < 12288u) ||
-                   (worker_comp == LIEC_COMP_RANDK && c->nwt < 8192u) || (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
+    // The aggregation's form by operator and size (tiles of 1024 columns): a chunk per wave against a tile per wave, in
+    // us.  Top-k, k/d = 1 %: 8 x 262144 columns 8 against 15, 8 x 1M 10 against 18, 64 x 1M 45 against 141, 8 x 8M even,
+    // 16 x 11.7M 61 against 50, 32 x 25.6M (0.1 %) 112 against 68.  Random-k gains by the tile with every row more (its
+    // flags are exact): 8 x 1M 6 against 7, 64 x 1M (0.1 %) 26 against 11, 16 x 4.2M 34 against 22, 16 x 8M 57 against
+    // 39.  Blockwise sign 4 x 65536 4 against 8, 8 x 1M 7 against 11, 16 x 2.1M 18 against 16, 7 x 3.3M 18 against 12;
+    // scaled sign is never faster by chunk (the four waves of a tile read the same bits); identity, 8 x 11.7M, 75
+    // against 119.
+    c->agg_chunk = worker_comp == LIEC_COMP_IDENTITY || (worker_comp == LIEC_COMP_TOPK && c->nwt < 8192u) ||
+                   (worker_comp == LIEC_COMP_RANDK && (uint64_t)c->nwt * un < 16384u) ||
+                   (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
     // A kernel that only finishes a few short sums costs its launch and two round trips to memory (3.5 us); the kernels
     // that use the scales form them as fast while the sums are few.  us per step with and without: 4 x 65536 columns
     // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 19.4 against 20.8; at 16 x 262144

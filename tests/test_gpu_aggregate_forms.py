@@ -74,8 +74,8 @@ def _chain_blocks_topk(N, d, off, wc, sc):
 
 
 # first lengths (and one more tile) that take a wave per tile
-@pytest.mark.parametrize("wc,sc,N,d", [("topk", "sign", 2, 12288 * 1024 + 5), ("topk", "sign", 2, 12287 * 1024),
-                                       ("randk", "sign", 2, 8192 * 1024 + 1028), ("blocksign", "sign", 3, 2048 * 1024 + 7),
+@pytest.mark.parametrize("wc,sc,N,d", [("topk", "sign", 2, 8192 * 1024 + 5), ("topk", "sign", 2, 8191 * 1024),
+                                       ("randk", "sign", 2, 8192 * 1024 + 1028), ("randk", "sign", 64, 255 * 1024), ("blocksign", "sign", 3, 2048 * 1024 + 7),
                                        ("blocksign", "sign", 3, 2047 * 1024),
                                        # the aggregation makes a top-k server's first filter pass, and does not any more
                                        ("topk", "topk", 2, 4096 * 1024), ("topk", "topk", 2, 4096 * 1024 + 3),
@@ -84,3 +84,36 @@ def test_aggregate_either_side_of_the_rule(wc, sc, N, d):
     say(f"case aggregate rule N={N} d={d} {wc}/{sc}")
     off = [0, 5, d // 3 + 2, d // 3 + 3, d - 1, d] if wc == "blocksign" else None
     _chain(N, d, wc, sc, d // 500, 3 if sc == "topk" else 2, off)
+
+
+# a wave per tile: batches of 16 rows, lists from a few entries to more than they hold, columns that several or all
+# workers keep, both forms of the candidate bitmap, and rows that have none
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 33])
+@pytest.mark.parametrize("d,k", [(1024, 1), (1024, 1000), (1025, 60), (5000, 40), (5003, 1500), (30_001, 300)])
+@pytest.mark.parametrize("same", [0.0, 0.5, 1.0])
+def test_aggregate_by_tile(N, d, k, same):
+    say(f"case aggregate by tile N={N} d={d} k={k} same={same}")
+    from paper_2402_11857_amd import LiecContext
+
+    rng = np.random.default_rng(N * 7 + d + k)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, "topk", "sign", k, 0, 0.05) as ctx:
+        ctx.set_gather_batching(0)
+        for t in range(4):
+            g = rng.standard_normal((N, d), dtype=np.float32)
+            common = rng.random(d) < same                       # columns whose gradient all workers share, up to the scale
+            g[:, common] = (g[0, common] * (1.0 + 0.001 * np.arange(N)[:, None])).astype(np.float32)
+            ctx.set_group_bitmap(t % 2)
+            if t == 3:
+                ctx.force_search_mode(4)                        # no valid bitmap: every column is a candidate
+            ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+            torch.cuda.synchronize()
+            H.oracle_step_rows(g, x, e, "topk", "sign", 0.05, k, 0)
+            assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
+
+
+@pytest.mark.parametrize("N,d,k", [(64, 256 * 1024, 300), (64, 256 * 1024 + 3, 200_000), (70, 240 * 1024, 20_000)])
+def test_aggregate_by_tile_randk(N, d, k):
+    say(f"case aggregate by tile randk N={N} d={d} k={k}")
+    _chain(N, d, "randk", "sign", k, 2)
