@@ -155,6 +155,46 @@ __global__ __launch_bounds__(kBlock) void k_l1_items(const float* __restrict__ s
     if (threadIdx.x == 0) partial[(size_t)(row0 + blockIdx.y) * gridDim.x + blockIdx.x] = s;
 }
 
+// The same sums by tile, for the aggregation, which has all of a 4096-column tile of v at hand.
+struct TileItems {
+    const uint2* tile;          // [tiles] x: the tile's item when it has one (y == 1), else where its y items start in `of`
+    const uint32_t* of;         // [items]
+    const L1Item* items;        // [items]
+};
+// The partial sums of |a| of one 4096-column tile, which a block of 4 waves holds as wave tiles of 16 columns a lane
+// (a[u]: columns j0 + 256u .. + 3 of this lane, 0 beyond the row's end).  Every thread of the block calls it, with the
+// tile's entry of it.tile (read ahead of the columns, or its latency comes on top of theirs); lds_w: 4 words.  out: the
+// row's partials.
+__device__ __forceinline__ void l1_of_tile(const TileItems& it, uint2 entry, uint32_t j0, const float4 (&a)[4], double* lds_w,
+                                           double* __restrict__ out) {
+    for (uint32_t q = 0; q < entry.y; ++q) {                    // uniform
+        const uint32_t item = entry.y == 1 ? entry.x : it.of[entry.x + q];
+        double acc = 0.0;
+        if (entry.y == 1) {                                     // the whole tile lies in one block
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                acc += (double)fabsf(a[u].x);
+                acc += (double)fabsf(a[u].y);
+                acc += (double)fabsf(a[u].z);
+                acc += (double)fabsf(a[u].w);
+            }
+        } else {
+            const uint2 r = make_uint2(it.items[item].lo, it.items[item].hi);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = j0 + u * kChunk;
+                if (j >= r.x && j < r.y) acc += (double)fabsf(a[u].x);
+                if (j + 1 >= r.x && j + 1 < r.y) acc += (double)fabsf(a[u].y);
+                if (j + 2 >= r.x && j + 2 < r.y) acc += (double)fabsf(a[u].z);
+                if (j + 3 >= r.x && j + 3 < r.y) acc += (double)fabsf(a[u].w);
+            }
+        }
+        const double s = block_sum_f64(acc, lds_w);
+        if (threadIdx.x == 0) out[item] = s;
+        __syncthreads();                                        // lds_w is free for the next item
+    }
+}
+
 // grid = (B, rows).  Adds up the item partials of block b in a fixed order and sets its scale.
 __global__ __launch_bounds__(kBlock) void k_l1_items_final(const double* __restrict__ partial, uint32_t nitems,
                                                             const uint32_t* __restrict__ item_start,

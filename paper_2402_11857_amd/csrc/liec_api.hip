@@ -113,6 +113,10 @@ struct liec_ctx {
     bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
     uint32_t agg_tile_blocks = 0, agg_chunk_blocks = 0;      // its grid in either form
     uint32_t agg_blocks() const { return agg_chunk ? agg_chunk_blocks : agg_tile_blocks; }
+    // blockwise server: the aggregation by tile leaves the partial sums of v's items
+    bool agg_sums_items() const {
+        return server_comp == kBlockSign && (worker_comp == kSign || (worker_comp == kBlockSign && !agg_chunk));
+    }
     // top-k server on short rows: the aggregation makes the first filter pass over v
     bool agg_filters() const { return server_comp == kTopk && agg_chunk && nwt <= kAggFilterTiles; }
     // scaled sign on short rows: the aggregation forms the workers' scales from their partial sums, the update the server's
@@ -149,9 +153,12 @@ struct liec_ctx {
 
     // blockwise scaled sign (Definition 5): block table and its scratch, set by liec_set_blocks
     uint32_t B = 0, nitems = 0;
+    uint32_t* blk_tables = nullptr;            // one allocation for the five tables below
     uint32_t* blk_off = nullptr;               // [B + 1]
     uint32_t* tile_blk = nullptr;              // [ncol_tiles]
     uint32_t* item_start = nullptr;            // [B + 1]
+    uint2* tile_entry = nullptr;               // [4096-column tiles]
+    uint32_t* tile_items = nullptr;            // [nitems]
     L1Item* items = nullptr;                   // [nitems]
     double* blk_partial = nullptr;             // [(N + 1) * nitems]
     float* blk_scales = nullptr;               // [(N + 1) * B]
@@ -201,14 +208,13 @@ hipError_t dev_alloc(liec_ctx* c, T** p, size_t count) {
 }
 
 void free_blocks(liec_ctx* c) {
-    (void)hipFree(c->blk_off);
-    (void)hipFree(c->tile_blk);
-    (void)hipFree(c->item_start);
+    (void)hipFree(c->blk_tables);
     (void)hipFree(c->items);
     (void)hipFree(c->blk_partial);
     (void)hipFree(c->blk_scales);
     (void)hipFree(c->blk_l1);
-    c->blk_off = c->tile_blk = c->item_start = nullptr;
+    c->blk_tables = c->blk_off = c->tile_blk = c->item_start = c->tile_items = nullptr;
+    c->tile_entry = nullptr;
     c->items = nullptr;
     c->blk_partial = c->blk_l1 = nullptr;
     c->blk_scales = nullptr;
@@ -217,6 +223,7 @@ void free_blocks(liec_ctx* c) {
     c->B = c->nitems = 0;
 }
 
+TileItems tile_items(const liec_ctx* c) { return TileItems{c->tile_entry, c->tile_items, c->items}; }
 BlockTable block_table(const liec_ctx* c) { return BlockTable{c->tile_blk, c->blk_off, c->blk_scales, c->B}; }
 
 void free_scratch(liec_ctx* c) {
@@ -350,12 +357,14 @@ void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t ro
 // workers also the sign bits.  slot0 and slot0 + 1 time the two kernels.
 template <bool VEC>
 void launch_block_l1(Launcher& L, const float* src, size_t row_stride, uint32_t rows, uint32_t row0, uint16_t* bits,
-                     int slot0) {
+                     int slot0, bool summed = false) {
     liec_ctx* c = L.c;
-    L.begin(slot0);
-    k_l1_items<VEC><<<dim3(c->nitems, rows), kBlock, 0, c->stream>>>(src, row_stride, (uint32_t)c->d, c->nwt, row0, c->items,
-                                                                      c->blk_partial, bits);
-    L.end();
+    if (!summed) {                                              // (by whoever wrote `src`)
+        L.begin(slot0);
+        k_l1_items<VEC><<<dim3(c->nitems, rows), kBlock, 0, c->stream>>>(src, row_stride, (uint32_t)c->d, c->nwt, row0, c->items,
+                                                                          c->blk_partial, bits);
+        L.end();
+    }
     L.begin(slot0 + 1);
     k_l1_items_final<<<dim3(c->B, rows), kBlock, 0, c->stream>>>(c->blk_partial, c->nitems, c->item_start, c->blk_off,
                                                                   c->B, row0, c->blk_scales, c->blk_l1);
@@ -376,8 +385,10 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     auto launch = [&](auto kernel) {
         kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
                                                        c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->w_partial,
-                                                       c->row_blocks);
+                                                       c->row_blocks, tile_items(c),
+                                                       c->blk_partial ? c->blk_partial + (size_t)c->N * c->nitems : nullptr);
     };
+    const bool items = c->agg_sums_items();
     bool done = false;
     if constexpr (WC != kSign) {                                // (scaled sign has the form by tile only)
         if (WC == kIdentity || c->agg_chunk) {                  // (the identity the form by chunk only)
@@ -387,8 +398,9 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
             done = true;
         }
     } else if (c->fold_workers) {
-        if (srv_l1) launch(k_aggregate<WC, true, VEC, true>);
-        else launch(k_aggregate<WC, false, VEC, true>);
+        if (srv_l1) launch(k_aggregate<WC, true, VEC, true, false>);
+        else if (items) launch(k_aggregate<WC, false, VEC, true, true>);
+        else launch(k_aggregate<WC, false, VEC, true, false>);
         done = true;
     }
     if constexpr (WC == kTopk || WC == kRandk) {
@@ -402,8 +414,9 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
         }
     } else if constexpr (WC != kIdentity) {
         if (!done) {
-            if (srv_l1) launch(k_aggregate<WC, true, VEC>);
-            else launch(k_aggregate<WC, false, VEC>);
+            if (srv_l1) launch(k_aggregate<WC, true, VEC, false, false>);
+            else if (items) launch(k_aggregate<WC, false, VEC, false, true>);
+            else launch(k_aggregate<WC, false, VEC, false, false>);
         }
     }
     L.end();
@@ -483,7 +496,7 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
             L.end();
         }
     } else if (c->server_comp == kBlockSign) {
-        launch_block_l1<VEC>(L, c->vbuf, 0, 1u, (uint32_t)c->N, nullptr, S_S_L1);
+        launch_block_l1<VEC>(L, c->vbuf, 0, 1u, (uint32_t)c->N, nullptr, S_S_L1, c->agg_sums_items());
     } else if (c->server_comp == kTopk) {
         // v is always 16-byte aligned scratch, but d % 4 decides whether 128-bit loads stay in bounds
         // the server's candidates get the fine group bitmap: the update kernel reads v only where a bit is set
@@ -885,8 +898,9 @@ liec_status liec_set_blocks(liec_ctx* c, const int64_t* offsets, int32_t nblocks
         tile_blk[t] = b | (last >= off[b + 1] ? 0x80000000u : 0u);
     }
     std::vector<L1Item> items;
-    const uint32_t big = 4u * (uint32_t)kWaveTile;                 // columns per block of k_l1_items
-    std::vector<uint32_t> owner((d + big - 1) / big, 0xffffffffu); // the first item of a tile writes its bits
+    const uint32_t big = 4u * (uint32_t)kWaveTile, ntiles = (d + big - 1) / big;   // columns per block of k_l1_items
+    std::vector<uint32_t> tile_first(ntiles + 1, 0u);              // items of the tiles before
+    std::vector<uint32_t> owner(ntiles, 0xffffffffu); // the first item of a tile writes its bits
     for (uint32_t b = 0; b < B; ++b) {
         item_start[b] = (uint32_t)items.size();
         for (uint32_t t = off[b] / big; t <= (off[b + 1] - 1) / big; ++t) {
@@ -897,24 +911,49 @@ liec_status liec_set_blocks(liec_ctx* c, const int64_t* offsets, int32_t nblocks
             it.write_bits = owner[t] == 0xffffffffu ? 1u : 0u;
             owner[t] = b;
             items.push_back(it);
+            ++tile_first[t + 1];
         }
+    }
+    for (uint32_t t = 0; t < ntiles; ++t) tile_first[t + 1] += tile_first[t];
+    std::vector<uint32_t> tile_items(items.size()), next(tile_first.begin(), tile_first.end() - 1);
+    for (uint32_t q = 0; q < (uint32_t)items.size(); ++q) tile_items[next[items[q].tile]++] = q;
+    std::vector<uint2> entry(ntiles);
+    for (uint32_t t = 0; t < ntiles; ++t) {
+        const uint32_t begin = tile_first[t], n = tile_first[t + 1] - begin;
+        entry[t] = make_uint2(n == 1 ? tile_items[begin] : begin, n);
     }
     item_start[B] = (uint32_t)items.size();
     c->B = B;
     c->nitems = (uint32_t)items.size();
     const size_t rows = (size_t)c->N + 1;
     const int64_t before = c->scratch_bytes;
-    hipError_t e = dev_alloc(c, &c->blk_off, (size_t)B + 1);
-    if (e == hipSuccess) e = dev_alloc(c, &c->tile_blk, (size_t)c->ncol_tiles);
-    if (e == hipSuccess) e = dev_alloc(c, &c->item_start, (size_t)B + 1);
+    // the tables in one buffer, one copy: entries first (8-byte aligned)
+    std::vector<uint32_t> tables;
+    tables.reserve(2 * (size_t)ntiles + tile_items.size() + off.size() + tile_blk.size() + item_start.size());
+    for (const uint2& q : entry) {
+        tables.push_back(q.x);
+        tables.push_back(q.y);
+    }
+    size_t at[4];
+    const std::vector<uint32_t>* const parts[4] = {&tile_items, &off, &tile_blk, &item_start};
+    for (int q = 0; q < 4; ++q) {
+        at[q] = tables.size();
+        tables.insert(tables.end(), parts[q]->begin(), parts[q]->end());
+    }
+    hipError_t e = dev_alloc(c, &c->blk_tables, tables.size());
+    if (e == hipSuccess) {
+        c->tile_entry = reinterpret_cast<uint2*>(c->blk_tables);
+        c->tile_items = c->blk_tables + at[0];
+        c->blk_off = c->blk_tables + at[1];
+        c->tile_blk = c->blk_tables + at[2];
+        c->item_start = c->blk_tables + at[3];
+    }
     if (e == hipSuccess) e = dev_alloc(c, &c->items, items.size());
     if (e == hipSuccess) e = dev_alloc(c, &c->blk_partial, rows * items.size());
     if (e == hipSuccess) e = dev_alloc(c, &c->blk_scales, rows * B);
     if (e == hipSuccess) e = dev_alloc(c, &c->blk_l1, rows * B);
     c->blk_bytes = c->scratch_bytes - before;
-    if (e == hipSuccess) e = hipMemcpy(c->blk_off, off.data(), off.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->tile_blk, tile_blk.data(), tile_blk.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->item_start, item_start.data(), item_start.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(c->blk_tables, tables.data(), tables.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->items, items.data(), items.size() * sizeof(L1Item), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->blk_scales, 0, rows * B * sizeof(float));
     if (e == hipSuccess) e = hipMemset(c->blk_l1, 0, rows * B * sizeof(double));

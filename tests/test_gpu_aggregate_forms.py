@@ -117,3 +117,16 @@ def test_aggregate_by_tile(N, d, k, same):
 def test_aggregate_by_tile_randk(N, d, k):
     say(f"case aggregate by tile randk N={N} d={d} k={k}")
     _chain(N, d, "randk", "sign", k, 2)
+
+
+# a blockwise server's partial sums left by the aggregation: rounds with waves beyond the last tile, tables with many
+# boundaries in one 4096-column tile, blocks that end with a tile
+@pytest.mark.parametrize("wc", ["sign", "blocksign"])
+@pytest.mark.parametrize("N,d", [(2, 1), (3, 1025), (9, 4096), (2, 4097), (5, 12_289), (2, 70_001), (2, 2048 * 1024 + 1030)])
+@pytest.mark.parametrize("table", ["one", "tiles", "crowded"])
+def test_blockwise_sums_by_tile(wc, N, d, table):
+    say(f"case blockwise sums N={N} d={d} {wc} {table}")
+    off = {"one": [0, d], "tiles": list(range(0, d, 4096)) + [d],
+           "crowded": sorted({0, 1, 2, 5, 1023, 1024, 1500, 4095, d // 2, d // 2 + 1, d - 1, d} - {o for o in range(d + 1, 4097)})}[table]
+    off = [o for o in sorted(set(off)) if 0 <= o <= d]
+    _chain(N, d, wc, "blocksign", 1, 2, off)
