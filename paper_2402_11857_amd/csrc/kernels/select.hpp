@@ -387,14 +387,18 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
 // The work is O(k * 2^32 / d) per row instead of O(d).  Same outputs as k_filter<., true>: the count of
 // keys above the band, the candidate list, and the bits of the columns above the band -- set with
 // atomic ORs into a bitmap that k_rk_zero cleared.  grid = (blocks, rows).
+// Bound by its integer arithmetic and the atomics of the columns above the band (8e5 to as many lines for 32 rows of
+// 25.6M columns, k/d = 0.1 %).  Two multiplications and every step for each of the 1.5e8 words took 128 us there, one
+// multiplication and a look at the index's upper half 99.
+constexpr int kInverseWords = 4;                                // words per lane and iteration (8: 5 us slower)
 __global__ __launch_bounds__(kBlock) void k_rk_zero(uint32_t nwt, uint32_t row0, const RowDesc* __restrict__ desc,
                                                      bool cold_pass, uint32_t cap, uint32_t k,
                                                      uint16_t* __restrict__ kbits) {
     const uint32_t row = row0 + blockIdx.y;
     if (cold_pass ? !wants_cold(desc[row], cap, k) : desc[row].mode != kWarm) return;
-    uint32_t* __restrict__ words = reinterpret_cast<uint32_t*>(kbits + (size_t)row * nwt * 64);
-    const uint32_t n = nwt * 32;
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += gridDim.x * kBlock) words[q] = 0u;
+    uint4* __restrict__ words = reinterpret_cast<uint4*>(kbits + (size_t)row * nwt * 64);
+    const uint32_t n = nwt * 8;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += gridDim.x * kBlock) words[q] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32_t nwt, uint32_t row0,
@@ -420,27 +424,47 @@ __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint64_t stream = rk_stream(rk.state->seed, rk.state->draw, row);
     const uint32_t k0 = (uint32_t)stream, k1 = (uint32_t)(stream >> 32);
-    const uint64_t y_begin = 2ull * lo, y_end = 1ull << 32;    // words whose priority is at least lo
+    // The words y whose priority is at least lo, y in [2 lo, 2^32), are walked as w = y ^ (y >> 16), the inverse's first
+    // step (its own inverse, and a permutation of each block of 2^16 words): w runs over whole such blocks, from the one
+    // that holds 2 lo.  The multiplication that follows is linear in w, so a step to the next words is one addition.
+    // Almost every word lands beyond d, which the upper half of the index shows before the last step.
+    const uint32_t y_first = 2u * lo, top = (d - 1) | 0xffffu;
+    const uint64_t w_end = 1ull << 32;
     uint32_t n_hi = 0;
     uint2* wst = wstage[wave];
     uint32_t wcnt = 0;
-    for (uint64_t base = y_begin + ((uint64_t)blockIdx.x * 4 + wave) * 64; base < y_end; base += (uint64_t)gridDim.x * kBlock) {
-        const uint64_t y64 = base + lane;
-        const uint32_t y = (uint32_t)y64, key = y >> 1;
-        const uint32_t j = rk_index_of(k0, k1, y);
-        const bool ok = y64 < y_end && j < d;
-        const bool ge_hi = ok && key >= hi;
-        if (ge_hi) {
-            const uint32_t t = j / kWaveTile, o = j % kWaveTile;
-            const uint32_t half = t * 64 + (o % kChunk) / 4;              // half-word of the row holding the column
-            atomicOr(&words[half >> 1], 1u << ((half & 1) * 16 + 4 * (o / kChunk) + o % 4));
-            ++n_hi;
+    const uint32_t stride = gridDim.x * 4 * 64 * kInverseWords;
+    uint64_t base = (y_first & 0xffff0000u) + ((uint64_t)blockIdx.x * 4 + wave) * 64 * kInverseWords;
+    uint32_t p = ((uint32_t)base + lane) * 0x7ED1B41Du - k1;
+    for (; base < w_end; base += stride, p += stride * 0x7ED1B41Du) {
+        uint32_t h[kInverseWords];
+        uint32_t hit = 0;
+#pragma unroll
+        for (int i = 0; i < kInverseWords; ++i) {
+            const uint32_t f = p + (uint32_t)i * (64u * 0x7ED1B41Du);
+            h[i] = (f ^ (f >> 13) ^ (f >> 26)) * 0xA5CB9243u;
+            hit |= ((h[i] ^ k0) <= top ? 1u : 0u) << i;         // the last step only changes the lower half
         }
-        const uint64_t bc = __ballot(ok && !ge_hi);             // candidates: lo <= key < hi
-        if (bc) {                                               // wave-uniform
-            const uint32_t m = __popcll(bc);
-            const StagePos sp = reserve_stage(fb, m, staged, wst, wcnt, lane);
-            if ((bc >> lane) & 1) put_candidate(stage, wst, sp, lanes_below(bc), make_uint2(key, j));
+        if (__ballot(hit != 0) == 0) continue;                  // wave-uniform
+#pragma unroll
+        for (int i = 0; i < kInverseWords; ++i) {
+            const uint32_t w = (uint32_t)base + (uint32_t)i * 64u + lane, y = w ^ (w >> 16), key = y >> 1;
+            const uint32_t j = h[i] ^ (h[i] >> 16) ^ k0;
+            const bool ok = j < d && y >= y_first;
+            if (__ballot(ok) == 0) continue;                    // wave-uniform
+            const bool ge_hi = ok && key >= hi;
+            if (ge_hi) {
+                const uint32_t t = j / kWaveTile, o = j % kWaveTile;
+                const uint32_t half = t * 64 + (o % kChunk) / 4;              // half-word of the row holding the column
+                atomicOr(&words[half >> 1], 1u << ((half & 1) * 16 + 4 * (o / kChunk) + o % 4));
+                ++n_hi;
+            }
+            const uint64_t bc = __ballot(ok && !ge_hi);         // candidates: lo <= key < hi
+            if (bc) {                                           // wave-uniform
+                const uint32_t m = __popcll(bc);
+                const StagePos sp = reserve_stage(fb, m, staged, wst, wcnt, lane);
+                if ((bc >> lane) & 1) put_candidate(stage, wst, sp, lanes_below(bc), make_uint2(key, j));
+            }
         }
     }
     finish_filter_block(fb, stage, wst, wcnt, n_hi, staged, wsure);
