@@ -23,8 +23,8 @@ DEFAULT_WORKLOAD = "c5_vgg16_mixed"   # the largest configuration; fits one GPU 
 ALSO = ["c3_resnet18_sign", "c3_resnet18_blocksign", "c4_resnet50_topk", "c4_resnet50_randk", "c5_vgg16_sign",
         "c1_tiny_sign", "c2_topk_mid"]
 # small configurations whose tensors fit the caches and whose step is a chain of short dependent kernels
-CACHE_RESIDENT = {"c1_tiny_sign": "1 MiB of gradients: cache-resident, bound by the gaps between 5 dependent kernels",
-                  "c2_topk_mid": "32 MiB of gradients: cache-resident, bound by the gaps between 20 dependent kernels"}
+CACHE_RESIDENT = {"c1_tiny_sign": "1 MiB of gradients: cache-resident, bound by the latencies of 3 dependent kernels",
+                  "c2_topk_mid": "32 MiB of gradients: cache-resident, bound by the latencies of 11 dependent kernels"}
 N_GRAD_BUFFERS = 4          # distinct gradient batches rotated through the timed steps
 REPEATS = 5                 # timed regions per workload; the median one is reported
 # kernels that make up a steady-state step (the rest of a profile summary -- cold and general search,
