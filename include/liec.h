@@ -120,7 +120,9 @@ liec_status liec_create_ex(liec_ctx **out, int32_t N, int64_t d, liec_comp worke
  * slower.
  * Asynchronous: work is enqueued on the context's stream and the call returns
  * without synchronising, allocating or copying to the host.  Inputs must be
- * finite; otherwise results are unspecified and liec_get_info reports it.
+ * finite; otherwise results are unspecified, and liec_get_info reports it where
+ * an L1 sum or a top-k key met the value: the identity and random-k compare and
+ * add up nothing, so a step with only these two on both sides reports nothing.
  */
 liec_status liec_step(liec_ctx *ctx, const float *grads, float *x, float *server_err);
 

@@ -106,6 +106,10 @@ __host__ __device__ constexpr int digit_shift(int pass) { return pass == 0 ? 19 
 __host__ __device__ constexpr int digit_bits(int pass) { return pass == 0 ? 12 : (pass == 1 ? 10 : 9); }
 
 __device__ __forceinline__ uint32_t key_of(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+constexpr uint32_t kInfKey = 0x7f800000u;                       // keys of Inf and NaN start here
+__device__ __forceinline__ bool any_nonfinite(float a, float b, float c, float d) {
+    return max(max(key_of(a), key_of(b)), max(key_of(c), key_of(d))) >= kInfKey;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Random-k (Definition 3): the k-subset is drawn by giving index j the priority

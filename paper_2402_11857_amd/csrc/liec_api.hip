@@ -139,6 +139,7 @@ struct liec_ctx {
     bool gb_last_coarse = false;               // the form the last compressed step wrote
     bool gb_written = false;                   // there has been one
     uint16_t* vbits = nullptr;                 // [nwt * 64] sign bits of v (scaled-sign server, either form)
+    uint64_t* vodd = nullptr;                  // [nwt * 4] groups of 4 columns in which v is not finite (identity workers, random-k server)
     uint64_t* sgbits = nullptr;                // [nwt * 4] group bitmap of the server's candidates in v (top-k server), fine form
     uint2* list = nullptr;                     // [(N + 1) * cap] candidates (key, index)
     uint32_t* ghist = nullptr;                 // [(N + 1) * kHistBins] first digit of a row (12 bits) or of its list (8 bits)
@@ -238,6 +239,7 @@ void free_scratch(liec_ctx* c) {
     (void)hipFree(c->rk_state);
     (void)hipFree(c->gbits);
     (void)hipFree(c->vbits);
+    (void)hipFree(c->vodd);
     (void)hipFree(c->sgbits);
     (void)hipFree(c->list);
     (void)hipFree(c->ghist);
@@ -382,7 +384,7 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     auto launch_chunk = [&](auto kernel) {
         const ServerFilter sf{c->list, c->cap, (uint32_t)c->server_k, c->sgbits};
         kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
-                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, sf);
+                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->vodd, sf);
     };
     auto launch = [&](auto kernel) {
         kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
@@ -433,7 +435,7 @@ void launch_update(Launcher& L, const float* grads, float* x, float* e) {
     L.begin(S_UPDATE);
     auto launch = [&](auto kernel) {
         kernel<<<(uint32_t)blocks, kBlock, 0, c->stream>>>(grads, x, c->vbuf, e, c->N, panel, c->ncol_tiles, (uint32_t)c->d,
-                                                           -c->lr, c->desc, block_table(c), c->bits, c->vbits, c->sgbits,
+                                                           -c->lr, c->desc, block_table(c), c->bits, c->vbits, c->sgbits, c->vodd,
                                                            c->s_partial, c->agg_blocks());
     };
     if (SC == kSign && c->fold_server()) launch(k_update<WC, SC, VEC, SC == kSign>);
@@ -665,6 +667,8 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         e = dev_alloc(c, &c->gbits, (size_t)N * c->nwt * 4);      // room for either form
     if (e == hipSuccess && (server_comp == LIEC_COMP_SIGN || server_comp == LIEC_COMP_BLOCKSIGN))
         e = dev_alloc(c, &c->vbits, (size_t)c->nwt * 64);
+    if (e == hipSuccess && worker_comp == LIEC_COMP_IDENTITY && server_comp == LIEC_COMP_RANDK)
+        e = dev_alloc(c, &c->vodd, (size_t)c->nwt * 4);
     if (e == hipSuccess && server_comp == LIEC_COMP_TOPK) e = dev_alloc(c, &c->sgbits, (size_t)c->nwt * 4);
     if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->list, rows * c->cap);
     if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->ghist, rows * kHistBins);
