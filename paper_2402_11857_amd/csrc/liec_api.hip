@@ -94,6 +94,16 @@ hipError_t static_scratch(double** out) {
 // tile's block adds to the row's one counter word.
 constexpr uint32_t kAggFilterTiles = 4096;
 
+// Blockwise server: items in a 4096-column tile up to which the aggregation leaves their partial sums.  One block sums
+// all items of its tile, 0.9 us each, one after another; without it a pass over v has a block for every item, for a
+// launch (2 us) and the reading.  us per step with sign workers, in the aggregation against in the pass, n items in
+// every tile (in one tile, 1 in the others): 4 x 65536 columns n = 3 16.9 against 17.3 (16.1, 16.9), n = 4 16.9, 16.5
+// (16.3, 16.2), n = 5 18.7, 17.5 (18.0, 16.9); 8 x 1M n = 5 52.4, 54.7 (42.6, 43.4), n = 7 57.5, 59.7 (44.3, 43.9);
+// 2 x 4.2M n = 8 66.4, 80.4 (50.1, 51.3), n = 9 72.4, 85.4 (51.2, 51.0).  A tile of 4096 one-column blocks, 8 x 1M:
+// 3710 against 435.
+constexpr uint32_t kAggTileItems = 8;
+uint32_t agg_tile_items(uint32_t nwt) { return std::min(3u + nwt / 512u, kAggTileItems); }
+
 struct liec_ctx {
     int32_t N = 0;
     int64_t d = 0;
@@ -113,9 +123,10 @@ struct liec_ctx {
     bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
     uint32_t agg_tile_blocks = 0, agg_chunk_blocks = 0;      // its grid in either form
     uint32_t agg_blocks() const { return agg_chunk ? agg_chunk_blocks : agg_tile_blocks; }
-    // blockwise server: the aggregation by tile leaves the partial sums of v's items
+    // blockwise server: the aggregation by tile leaves the partial sums of v's items, unless some tile has too many
     bool agg_sums_items() const {
-        return server_comp == kBlockSign && (worker_comp == kSign || (worker_comp == kBlockSign && !agg_chunk));
+        return server_comp == kBlockSign && (worker_comp == kSign || (worker_comp == kBlockSign && !agg_chunk)) &&
+               tile_items_max <= agg_tile_items(nwt);
     }
     // top-k server on short rows: the aggregation makes the first filter pass over v
     bool agg_filters() const { return server_comp == kTopk && agg_chunk && nwt <= kAggFilterTiles; }
@@ -153,7 +164,7 @@ struct liec_ctx {
     int64_t scratch_bytes = 0;
 
     // blockwise scaled sign (Definition 5): block table and its scratch, set by liec_set_blocks
-    uint32_t B = 0, nitems = 0;
+    uint32_t B = 0, nitems = 0, tile_items_max = 0;
     uint32_t* blk_tables = nullptr;            // one allocation for the five tables below
     uint32_t* blk_off = nullptr;               // [B + 1]
     uint32_t* tile_blk = nullptr;              // [ncol_tiles]
@@ -924,9 +935,11 @@ liec_status liec_set_blocks(liec_ctx* c, const int64_t* offsets, int32_t nblocks
     std::vector<uint32_t> tile_items(items.size()), next(tile_first.begin(), tile_first.end() - 1);
     for (uint32_t q = 0; q < (uint32_t)items.size(); ++q) tile_items[next[items[q].tile]++] = q;
     std::vector<uint2> entry(ntiles);
+    c->tile_items_max = 0;
     for (uint32_t t = 0; t < ntiles; ++t) {
         const uint32_t begin = tile_first[t], n = tile_first[t + 1] - begin;
         entry[t] = make_uint2(n == 1 ? tile_items[begin] : begin, n);
+        c->tile_items_max = std::max(c->tile_items_max, n);
     }
     item_start[B] = (uint32_t)items.size();
     c->B = B;

@@ -130,3 +130,25 @@ def test_blockwise_sums_by_tile(wc, N, d, table):
            "crowded": sorted({0, 1, 2, 5, 1023, 1024, 1500, 4095, d // 2, d // 2 + 1, d - 1, d} - {o for o in range(d + 1, 4097)})}[table]
     off = [o for o in sorted(set(off)) if 0 <= o <= d]
     _chain(N, d, wc, "blocksign", 1, 2, off)
+
+
+# as many items in a tile as the aggregation sums itself (3 on the shortest rows, 5 at a million columns, never more
+# than 8), one more, and as many as a tile has columns: the pass over v sums those
+@pytest.mark.parametrize("wc", ["sign", "blocksign"])
+@pytest.mark.parametrize("N,d,items,by_pass", [(2, 9_000, 3, False), (2, 9_000, 4, True), (2, 1024 * 1024 + 2, 5, False),
+                                               (2, 1024 * 1024 + 2, 6, True), (1, 4096 * 1024 + 1, 8, False),
+                                               (1, 4096 * 1024 + 1, 9, True), (3, 8195, 4096, True)])
+def test_blockwise_sums_of_a_crowded_tile(wc, N, d, items, by_pass):
+    say(f"case blockwise sums of a crowded tile N={N} d={d} {wc} items={items}")
+    from paper_2402_11857_amd import LiecContext
+
+    off = list(range(4096, 4096 + items)) + [8192, d]           # the second tile: one-column blocks and the rest of it
+    off = [0] + off
+    _chain(N, d, wc, "blocksign", 1, 2, off)
+    g, x, e = (torch.ones(s, device=DEV) for s in ((N, d), (N, d), d))
+    with LiecContext(N, d, wc, "blocksign", 0, 0, 0.05) as ctx:
+        ctx.set_blocks(off)
+        ctx.profile_begin(1)
+        ctx.step(g, x, e)
+        short = wc == "blocksign" and d < 2048 * 1024           # (a wave per chunk leaves no sums)
+        assert ("server_l1" in ctx.profile_end()) == (by_pass or short)
