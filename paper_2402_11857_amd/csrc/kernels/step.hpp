@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
 #pragma unroll
                 for (int b = 0; b < 16; ++b) {
                     const uint32_t j = j0 + (b >> 2) * kChunk + (b & 3);
-                    bidx[b] = block_of(bt, first, j < d ? j : d - 1);
+                    bidx[b] = block_of(bt, b ? bidx[b - 1] : first, j < d ? j : d - 1);     // columns ascend with b
                 }
                 for (int i = 0; i < N; ++i) {
                     const uint32_t m = bw[(size_t)i * brow];
