@@ -182,13 +182,19 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ 
 // flags (4 lanes a row), write the flagged groups to a list in LDS in row order, and take it 64 entries at a time:
 // one gather for 64 groups of all rows.  Sums live in LDS, one float4 per group.  Entries of one batch that fall on
 // the same group are added in row order: every lane offers its row to the group's slot (atomic minimum), the lowest
-// one adds, the others offer again.  Tiles with more flagged groups than the list holds (layers of large gradients,
-// rows without a valid bitmap) go row by row, two rows' groups requested together.  Row after row with one dependent
-// gather each, against this: random-k 32 x 25.6M columns 154 -> 75 us, top-k of the same size 109 -> 71 (90 with a list
-// of 256), both 0.1 %; top-k 16 x 16M, 1 %, 83 -> 60; top-k 16 x 138M, 0.5 % (1.1 GB of e and v and 0.8 GB of gradients
-// in layers where every line holds a candidate), 391 -> 380.
+// one adds, the others offer again.  Tiles with more flagged groups than pay (layers of large gradients, few rows, rows
+// without a valid bitmap) go row by row, two rows' groups requested together: a row then costs its share of four gathers,
+// an entry of the list 1/64 of a gather and its turns at the slots.  Row after row with one dependent
+// gather each, against this: random-k 32 x 25.6M columns 159 -> 72 us, top-k of the same size 108 -> 64 (90 with a list
+// of 128), both 0.1 %; top-k 16 x 16M, 1 %, 85 -> 59, 5 % 101 -> 71, 40 % 191 -> 170; 8 x 50M, 3 %, 147 -> 143; 16 x 138M,
+// 0.5 % (1.1 GB of e and v and 0.8 GB of gradients in layers where every line holds a candidate), 383 -> 365.  The line
+// between the two ways: with every tile of up to 512 entries listed, 1 x 16M, 40 %, took 51 us, row by row 34 (2 rows 64
+// and 41; 8 x 50M in the coarse form, whose entries are four groups, 409 and 283); with 16 or 24 groups per row as the
+// limit 32 x 25.6M, 0.1 %, took 80 us, with 48 64; 32, 48 and 64 differ by no more than runs do but at 16 x 138M (375,
+// 365, 366).
 // ---------------------------------------------------------------------------------------------
-constexpr uint32_t kSparseList = 512;                           // flagged groups (coarse: lines) of 16 rows the list holds
+constexpr uint32_t kSparseList = 512;                           // flagged groups (coarse: lines) of 16 rows the list holds,
+constexpr uint32_t kSparseGroups = 48;                          // and groups per row up to which it is used
 __device__ __forceinline__ void wave_sync() {                   // LDS traffic between the lanes of one wave
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -269,7 +275,8 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_sparse(const float* __rest
             }
             const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
             if (total == 0) continue;
-            if (total <= kSparseList) {                         // wave-uniform
+            const uint32_t per_row = WC == kTopk && coarse ? kSparseGroups / 4 : kSparseGroups;
+            if (total <= min(kSparseList, (uint32_t)min(16, N - i0) * per_row)) {     // wave-uniform
                 uint32_t pos = incl - cnt;
                 if (WC == kTopk) {
                     while (w) {

@@ -152,3 +152,35 @@ def test_blockwise_sums_of_a_crowded_tile(wc, N, d, items, by_pass):
         ctx.step(g, x, e)
         short = wc == "blocksign" and d < 2048 * 1024           # (a wave per chunk leaves no sums)
         assert ("server_l1" in ctx.profile_end()) == (by_pass or short)
+
+
+# a wave per tile: as many flagged groups of 4 columns as are listed (48 a row in the fine bitmap, 12 lines in the coarse
+# one, 512 in all), one fewer and one more, on rows that keep one column of each of their first groups and little else
+@pytest.mark.parametrize("N,groups", [(1, 48), (2, 96), (10, 480), (11, 512), (16, 512), (17, 512)])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("coarse", [0, 1])
+def test_aggregate_at_the_limit_of_the_list(N, groups, extra, coarse):
+    say(f"case aggregate list limit N={N} flagged={groups + extra} coarse={coarse}")
+    from paper_2402_11857_amd import LiecContext
+
+    rows = min(N, 16)
+    flagged = (min(12 * rows, groups) if coarse else groups) + extra     # of the first 16 rows
+    width = 16 if coarse else 4
+    d, k = 2048, -(-flagged // rows)                            # every row keeps k columns
+    rng = np.random.default_rng(N + groups + extra)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, "topk", "sign", k, 0, 0.05) as ctx:
+        ctx.set_gather_batching(0)
+        ctx.set_group_bitmap(coarse)
+        for t in range(3):
+            g = np.float32(1e-6) * rng.standard_normal((N, d), dtype=np.float32)
+            for i in range(N):
+                mine = flagged // rows + (1 if i % 16 < flagged % rows else 0)
+                at = np.arange(k) * width + rng.integers(0, width, k)
+                at[mine:] = (at[0] // 4 * 4 + np.arange(4))[at[0] // 4 * 4 + np.arange(4) != at[0]][:k - mine]   # (in a flagged group)
+                g[i, at] = rng.uniform(1.0, 1.001, k)
+            ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+            torch.cuda.synchronize()
+            H.oracle_step_rows(g, x, e, "topk", "sign", 0.05, k, 0)
+            assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
