@@ -50,7 +50,7 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 // tile's items as k_l1_items would after reading v back (7 x 7.3M columns: 19 -> 23 us, and 11 us less for the
 // pass over v).
 // ---------------------------------------------------------------------------------------------
-constexpr int kFoldRows = 64;                                   // workers whose scales a block forms at most
+constexpr int kFoldRows = 16;                                   // workers whose scales a block forms at most, 4 to a wave
 template <int WC, bool SRV_L1, bool VEC, bool FOLD, bool ITEMS>
 __global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                        const uint64_t* __restrict__ gbits,

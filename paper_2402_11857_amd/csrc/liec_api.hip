@@ -633,8 +633,10 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
                    (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
     // A kernel that only finishes a few short sums costs its launch and two round trips to memory (3.5 us); the kernels
     // that use the scales form them as fast while the sums are few.  us per step with and without: 4 x 65536 columns
-    // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 19.4 against 20.8; at 16 x 262144
-    // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.
+    // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 18.6 against 20.6; at 16 x 262144
+    // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.  A wave forms its workers' scales
+    // one after another, 0.5 us each however short the rows: sign / identity, 16 x 16384 13.3 against 13.4, 24 x 16384
+    // 16.1 against 14.8, 64 x 16384 30.2 against 21.6.
     c->fold_workers = worker_comp == LIEC_COMP_SIGN && N <= kFoldRows && (uint64_t)N * c->row_blocks <= 512u;
     auto balanced_filter = [&](uint32_t max_blocks) {
         const uint32_t iters = (c->nwt + 4 * c->filter_run - 1) / (4 * c->filter_run);

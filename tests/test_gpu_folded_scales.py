@@ -14,7 +14,7 @@ from _gpu import DEV, GPU_MARKS, say  # noqa: E402
 pytestmark = GPU_MARKS
 
 
-# workers' scales: rows times partials of 512 and above, 64 rows and above; the server's: 2048 blocks of the update and above
+# few and many workers' partial sums (the rule's edges: below); the server's: 2048 blocks of the update and above
 @pytest.mark.parametrize("wc", ["sign", "identity", "topk", "randk", "blocksign"])
 @pytest.mark.parametrize("N,d", [(1, 1), (3, 4097), (64, 32_768), (64, 32_769), (65, 4_100), (32, 65_536), (33, 65_536), (1, 262_144),
                                  (1, 262_145), (1, 1_048_577), (2, 1_048_580)])
@@ -51,3 +51,23 @@ def test_scales_formed_by_their_users(N, d, wc):
         ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
         if wc != "randk":                                       # a draw does not look at the gradients and may leave it out
             assert ctx.info_status()[0].nonfinite == 1
+
+
+# the aggregation forms the scales of up to 16 workers and 512 partial sums; a kernel of its own does beyond that
+@pytest.mark.parametrize("N,d,own_kernel", [(16, 4_097, False), (17, 4_097, True), (64, 1_000, True), (16, 131_072, False),
+                                            (16, 131_073, True), (1, 2_097_152, False), (1, 2_097_153, True)])
+def test_which_kernel_forms_the_workers_scales(N, d, own_kernel):
+    say(f"case who forms the scales N={N} d={d}")
+    from paper_2402_11857_amd import LiecContext
+
+    rng = np.random.default_rng(N + d)
+    g = rng.standard_normal((N, d), dtype=np.float32)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, "sign", "identity", 0, 0, 0.05) as ctx:
+        ctx.profile_begin(1)
+        ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+        assert ("worker_l1_final" in ctx.profile_end()) == own_kernel
+        wdesc = H.oracle_step_rows(g, x, e, "sign", "identity", 0.05)[0]
+        assert ctx.worker_desc()["scale"] == [float(np.float32(w.scale)) for w in wdesc]
+    assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e)
