@@ -66,10 +66,16 @@ __global__ __launch_bounds__(kBlock) void k_unpack_sign(const uint8_t* __restric
 // entries of every tile and block, k_kept_emit adds up the counts before its own tiles and writes the pairs.  Inside
 // a wave tile the order is chunk, then lane, then component.  What is kept follows from what the step left behind:
 // the candidate bitmap (top-k: only the flagged groups of columns are fetched and compared with the threshold) or
-// the kept bitmap (random-k: the count reads no gradients at all).  11.7M columns, k = 1 %: count and emit 6 + 11 us,
-// where a count and an emit that read the whole row and a one-block scan of the tiles between them took 19 + 11 + 8.
+// the kept bitmap (random-k: the count reads no gradients at all).  Count and emit, against a count and an emit that read
+// the whole row and a one-block scan of the tiles between them (us): 11.7M columns, k = 1 %, 5 + 9, 10 + 11 + 8; 60M
+// columns, 1 %, 13 + 24, 35 + 37 + 35, and all columns kept, 69 + 215, 64 + 186 + 36; 8.4M columns of one magnitude, which
+// have no bitmap, 1.25 %, 7 + 7, 6 + 7 + 6.
 // ---------------------------------------------------------------------------------------------
-constexpr uint32_t kWireBlocks = 4096;                         // at most; every block of k_kept_emit adds up that many counts
+// At most so many blocks; every block of k_kept_emit adds up the counts of those ahead of it.  No row (d < 2^31) has more
+// than kBlock tiles to a block, one per thread of k_kept_emit.  With 4096: 60M columns 16 + 29 and 72 + 230 us; with 2048
+// 11.7M columns 7 + 13.
+constexpr uint32_t kWireBlocks = 8192;
+static_assert((uint64_t)kWireBlocks * kBlock * kWaveTile >= (1ull << 31), "a block's tiles have a thread each");
 struct KeptRow {
     const float* g;                                             // the row's gradients
     const RowDesc* rd;
@@ -95,7 +101,7 @@ __device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint3
         return true;
     }
     uint32_t mask = 0xfu;                                       // bit u: my group of chunk u may hold a kept column
-    if (r.groups) {                                             // uniform
+    if (r.groups && !dense) {                                   // uniform
         if (r.coarse) {
             mask = (uint32_t)(r.groups[t] >> (4 * (lane >> 2))) & 0xfu;
         } else {
@@ -103,7 +109,6 @@ __device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint3
             mask = (uint32_t)((w[0] >> lane) & 1) | (uint32_t)((w[1] >> lane) & 1) << 1 | (uint32_t)((w[2] >> lane) & 1) << 2 |
                    (uint32_t)((w[3] >> lane) & 1) << 3;
         }
-        if (dense) mask = 0xfu;
         if (__ballot(mask != 0) == 0) return false;
     }
 #pragma unroll
@@ -156,80 +161,75 @@ __global__ __launch_bounds__(kBlock) void k_kept_emit(KeptRow r, uint32_t d, uin
                                                        const uint32_t* __restrict__ tile_cnt,
                                                        const uint32_t* __restrict__ block_cnt, uint32_t k,
                                                        uint32_t* __restrict__ idx_out, float* __restrict__ val_out) {
-    __shared__ uint32_t lds_w[4], first[kBlock], carry_in;
+    __shared__ uint32_t wave_before[4], wave_n[4], first[kBlock];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const uint32_t tau = r.rd->tau, cut = r.rd->cutoff;
     const bool dense = r.rd->dense != 0;
-    // kept entries in the blocks ahead of this one: all counts requested at once (one after another they cost this
-    // kernel half its time)
-    constexpr int kLoads = kWireBlocks / (4 * kBlock);
+    // kept entries in the blocks ahead of this one: the first 4096 counts requested at once (one after another they cost
+    // this kernel half its time)
+    constexpr int kLoads = 4;
     uint4 c[kLoads];
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) {
         const uint32_t b = (q * kBlock + tid) * 4;
         c[q] = b < blockIdx.x ? *reinterpret_cast<const uint4*>(block_cnt + b) : make_uint4(0u, 0u, 0u, 0u);
     }
-    const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, nwt);
-    uint32_t carry = 0;
-    for (uint32_t base = t0; base < t1; base += kBlock) {       // uniform; the counts of up to 256 tiles at a time
-        const uint32_t n = base + tid < t1 ? tile_cnt[base + tid] : 0u;
-        const uint32_t end = min(base + kBlock, t1);
-        uint32_t t = base + wave;
-        float4 a[4];
-        uint64_t kb[4][4];
-        bool any = t < end && kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);    // (its loads run beside the sums)
-        if (base == t0) {
-            uint32_t before = 0;
+    const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, nwt);     // at most kBlock tiles
+    const uint32_t n = t0 + tid < t1 ? tile_cnt[t0 + tid] : 0u;
+    float4 a[4];
+    uint64_t kb[4][4];
+    // a row without a valid bitmap is not read where it keeps nothing
+    auto look = [&](uint32_t t) {
+        return (!dense || tile_cnt[t] != 0) && kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);
+    };
+    uint32_t t = t0 + wave;
+    bool any = t < t1 && look(t);                               // (its loads run beside the sums)
+    auto count4 = [&](uint4 v, uint32_t b) {
+        return (b < blockIdx.x ? v.x : 0u) + (b + 1 < blockIdx.x ? v.y : 0u) + (b + 2 < blockIdx.x ? v.z : 0u) +
+               (b + 3 < blockIdx.x ? v.w : 0u);
+    };
+    uint32_t before = 0;
 #pragma unroll
-            for (int q = 0; q < kLoads; ++q) {
-                const uint32_t b = (q * kBlock + tid) * 4;
-                before += (b < blockIdx.x ? c[q].x : 0u) + (b + 1 < blockIdx.x ? c[q].y : 0u) +
-                          (b + 2 < blockIdx.x ? c[q].z : 0u) + (b + 3 < blockIdx.x ? c[q].w : 0u);
-            }
-            before = block_sum_u32(before, lds_w);              // valid on thread 0
-            if (tid == 0) carry_in = before;
-            __syncthreads();
-            carry = carry_in;
-        }
-        uint32_t incl = n;
+    for (int q = 0; q < kLoads; ++q) before += count4(c[q], (q * kBlock + tid) * 4);
+    for (uint32_t b = (kLoads * kBlock + tid) * 4; b < blockIdx.x; b += kBlock * 4)     // rows of more than 16.8M columns
+        before += count4(*reinterpret_cast<const uint4*>(block_cnt + b), b);
+    uint32_t incl = n;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_up(incl, o, 64);
-            if ((int)lane >= o) incl += up;
-        }
-        __syncthreads();                                        // the round before has read lds_w and first
-        if (lane == 63) lds_w[wave] = incl;
-        __syncthreads();
-        uint32_t ahead = carry, all = 0;
-        for (uint32_t w = 0; w < 4; ++w) {
-            if (w < wave) ahead += lds_w[w];
-            all += lds_w[w];
-        }
-        first[tid] = ahead + incl - n;
-        carry += all;
-        __syncthreads();
-        for (; t < end; t += 4) {
-            if (t >= base + 4) any = kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);
-            if (!any) continue;
-            uint32_t at = first[t - base];
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(incl, o, 64);
+        if ((int)lane >= o) incl += up;
+        before += __shfl_xor(before, o, 64);
+    }
+    if (lane == 63) {
+        wave_before[wave] = before;
+        wave_n[wave] = incl;
+    }
+    __syncthreads();
+    uint32_t ahead = wave_before[0] + wave_before[1] + wave_before[2] + wave_before[3];
+    for (uint32_t w = 0; w < wave; ++w) ahead += wave_n[w];
+    first[tid] = ahead + incl - n;
+    __syncthreads();
+    for (; t < t1; t += 4) {
+        if (t >= t0 + 4) any = look(t);
+        if (!any) continue;
+        uint32_t at = first[t - t0];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
-                const float av[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
-                // entries of lower lanes come first, then this lane's lower components
-                uint32_t pos = at + lanes_below(kb[u][0]) + lanes_below(kb[u][1]) + lanes_below(kb[u][2]) + lanes_below(kb[u][3]);
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
+            const float av[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
+            // entries of lower lanes come first, then this lane's lower components
+            uint32_t pos = at + lanes_below(kb[u][0]) + lanes_below(kb[u][1]) + lanes_below(kb[u][2]) + lanes_below(kb[u][3]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if ((kb[u][q] >> lane) & 1) {
-                        if (pos < k) {
-                            idx_out[pos] = j + q;
-                            val_out[pos] = av[q];
-                        }
-                        ++pos;
+            for (int q = 0; q < 4; ++q) {
+                if ((kb[u][q] >> lane) & 1) {
+                    if (pos < k) {
+                        idx_out[pos] = j + q;
+                        val_out[pos] = av[q];
                     }
+                    ++pos;
                 }
-                at += __popcll(kb[u][0]) + __popcll(kb[u][1]) + __popcll(kb[u][2]) + __popcll(kb[u][3]);
             }
+            at += __popcll(kb[u][0]) + __popcll(kb[u][1]) + __popcll(kb[u][2]) + __popcll(kb[u][3]);
         }
     }
 }

@@ -66,10 +66,11 @@ def _check(ctx, comp, g, k, i, rng, gd):
     assert H.bit_equal(p.cpu().numpy(), ref), f"worker {i}: decompressed"
 
 
-# one tile, one block of 4 tiles and the next one, blocks beyond 1024 counts, and rows whose blocks own more than 4 tiles
+# one tile, one block of 4 tiles and the next one, blocks beyond 1024 and beyond 4096 counts, and rows whose blocks own more
+# than 4 tiles
 @pytest.mark.parametrize("comp", ["topk", "randk"])
 @pytest.mark.parametrize("N,d,k", [(2, 1, 1), (2, 1000, 1000), (3, 4096, 40), (2, 4097, 4000), (2, 70_003, 3500),
-                                   (2, 4_300_001, 20_000), (1, 16_780_300, 10_000)])
+                                   (2, 4_300_001, 20_000), (1, 16_780_300, 10_000), (1, 33_600_001, 50_000)])
 def test_kept_entries(comp, N, d, k):
     say(f"case kept entries {comp} N={N} d={d} k={k}")
     from paper_2402_11857_amd import LiecContext
@@ -106,3 +107,20 @@ def test_kept_entries_of_rows_without_a_bitmap(comp):
         assert ctx.info().slow_rows == N
         for i in range(N):
             _check(ctx, comp, g, k, i, (8, 0), gd)
+
+
+def test_kept_entries_of_a_constant_row():
+    """No bitmap, the kept entries all at the row's start: the blocks of the rest look at their tiles' counts only."""
+    say("case kept entries constant row")
+    from paper_2402_11857_amd import LiecContext
+
+    N, d, k = 1, 4_200_003, 30_000
+    g = np.full((N, d), 0.5, np.float32)
+    g[0, 1_500_000] = 2.0                                       # and one more, far from them
+    gd = torch.from_numpy(g).to(DEV)
+    x, e = torch.zeros((N, d), device=DEV), torch.zeros(d, device=DEV)
+    with LiecContext(N, d, "topk", "sign", k, 0, 0.1) as ctx:
+        for t in range(2):
+            ctx.step(gd, x, e)
+            assert ctx.info().slow_rows == N
+            _check(ctx, "topk", g, k, 0, None, gd)
