@@ -424,6 +424,8 @@ __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint64_t stream = rk_stream(rk.state->seed, rk.state->draw, row);
     const uint32_t k0 = (uint32_t)stream, k1 = (uint32_t)(stream >> 32);
+    // The index whose 32-bit word (priority with its dropped bit put back) is y: every step of rk_priority undone in reverse
+    // order (the multipliers' inverses modulo 2^32; x ^= x >> 13 is undone by two shifts, x ^= x >> 16 by itself).
     // The words y whose priority is at least lo, y in [2 lo, 2^32), are walked as w = y ^ (y >> 16), the inverse's first
     // step (its own inverse, and a permutation of each block of 2^16 words): w runs over whole such blocks, from the one
     // that holds 2 lo.  The multiplication that follows is linear in w, so a step to the next words is one addition.
@@ -435,14 +437,14 @@ __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32
     uint32_t wcnt = 0;
     const uint32_t stride = gridDim.x * 4 * 64 * kInverseWords;
     uint64_t base = (y_first & 0xffff0000u) + ((uint64_t)blockIdx.x * 4 + wave) * 64 * kInverseWords;
-    uint32_t p = ((uint32_t)base + lane) * 0x7ED1B41Du - k1;
+    uint32_t p = ((uint32_t)base + lane) * 0x7ED1B41Du - k1;    // 0xC2B2AE35^-1
     for (; base < w_end; base += stride, p += stride * 0x7ED1B41Du) {
         uint32_t h[kInverseWords];
         uint32_t hit = 0;
 #pragma unroll
         for (int i = 0; i < kInverseWords; ++i) {
             const uint32_t f = p + (uint32_t)i * (64u * 0x7ED1B41Du);
-            h[i] = (f ^ (f >> 13) ^ (f >> 26)) * 0xA5CB9243u;
+            h[i] = (f ^ (f >> 13) ^ (f >> 26)) * 0xA5CB9243u;   // 0x85EBCA6B^-1
             hit |= ((h[i] ^ k0) <= top ? 1u : 0u) << i;         // the last step only changes the lower half
         }
         if (__ballot(hit != 0) == 0) continue;                  // wave-uniform

@@ -52,12 +52,10 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 // ---------------------------------------------------------------------------------------------
 constexpr int kFoldRows = 16;                                   // workers whose scales a block forms at most, 4 to a wave
 template <int WC, bool SRV_L1, bool VEC, bool FOLD, bool ITEMS>
-__global__ __launch_bounds__(kBlock) void k_aggregate(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
-                                                       const uint64_t* __restrict__ gbits,
-                                                       int N, uint32_t d, uint32_t nwt, float inv_n,
+__global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict__ bits, int N, uint32_t d, uint32_t nwt, float inv_n,
                                                        RowDesc* __restrict__ desc, const float* __restrict__ e_in,
                                                        float* __restrict__ v_out, double* __restrict__ srv_partial,
-                                                       BlockTable bt, bool coarse, uint16_t* __restrict__ vbits,
+                                                       BlockTable bt, uint16_t* __restrict__ vbits,
                                                        const double* __restrict__ w_partial, uint32_t w_parts, TileItems items,
                                                        double* __restrict__ item_partial) {
     __shared__ double lds_w[4];
@@ -430,7 +428,9 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
                                                              ServerFilter sf) {
     __shared__ double lds_w[4];
     __shared__ uint32_t nibs[4][64];
-    __shared__ uint2 stage[SRV_FILTER ? kStage : 1], wstage[4][SRV_FILTER ? kWaveStage : 1];
+    // a block has one tile, so its stage never overflows into stages of the waves' own
+    static_assert(!SRV_FILTER || kStage >= kWaveTile, "a tile's candidates fit the block's stage");
+    __shared__ uint2 stage[SRV_FILTER ? kStage : 1];
     __shared__ uint32_t wsure[5], staged[2];
     constexpr int kRows = 8;                                    // rows requested together
     FilterBand fb{};
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
             uint32_t hi4;
             const uint64_t any_lo = filter_chunk<false, false>(keys, j, d, fb.lo, fb.hi, bc, n_hi, kmax, hi4);
             if (lane == 0) sf.sgbits[(size_t)t * 4 + u] = any_lo;
-            stage_candidates(fb, keys, j, bc, stage, wstage[u], wcnt, staged, lane);
+            stage_candidates(fb, keys, j, bc, stage, nullptr, wcnt, staged, lane);
         }
         if (SRV_L1) {
             if (j < d) l1 += (double)fabsf(v.x);
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     }
     if (SRV_FILTER && filter) {
         if (__ballot(kmax >= 0x7f800000u) && lane == 0) atomicOr(&desc[N].nonfinite_acc, 1u);     // Inf / NaN
-        finish_filter_block(fb, stage, wstage[u], wcnt, n_hi, staged, wsure);
+        finish_filter_block(fb, stage, nullptr, wcnt, n_hi, staged, wsure);
     }
 }
 

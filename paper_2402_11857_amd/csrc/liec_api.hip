@@ -93,6 +93,8 @@ hipError_t static_scratch(double** out) {
 // 42.4 against 46.6, 8 x 1M 63.6 against 67.2, 8 x 4.2M 164 against 168; even at 8 x 8M and 8 x 11.7M, where every
 // tile's block adds to the row's one counter word.
 constexpr uint32_t kAggFilterTiles = 4096;
+constexpr uint32_t kAggChunkBlocks = 65536;                     // most blocks of the aggregation by chunk
+static_assert(kAggFilterTiles <= kAggChunkBlocks, "a block that filters v has one tile");
 
 // Blockwise server: items in a 4096-column tile up to which the aggregation leaves their partial sums.  One block sums
 // all items of its tile, 0.9 us each, one after another; without it a pass over v has a block for every item, for a
@@ -398,9 +400,8 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
                                                        c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->vodd, sf);
     };
     auto launch = [&](auto kernel) {
-        kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(grads, c->bits, c->gbits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf,
-                                                       c->s_partial, block_table(c), c->gb_coarse, c->vbits, c->w_partial,
-                                                       c->row_blocks, tile_items(c),
+        kernel<<<c->agg_blocks(), kBlock, 0, c->stream>>>(c->bits, c->N, d, c->nwt, inv_n, c->desc, e, c->vbuf, c->s_partial,
+                                                       block_table(c), c->vbits, c->w_partial, c->row_blocks, tile_items(c),
                                                        c->blk_partial ? c->blk_partial + (size_t)c->N * c->nitems : nullptr);
     };
     const bool items = c->agg_sums_items();
@@ -648,7 +649,7 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // the aggregation reads sign bits fastest with many short blocks, and gathers fastest with fewer
     const bool gathers = worker_comp == LIEC_COMP_TOPK || worker_comp == LIEC_COMP_RANDK;
     c->agg_tile_blocks = balanced(gathers ? 16384u : 65536u);
-    c->agg_chunk_blocks = std::min(c->nwt, 65536u);
+    c->agg_chunk_blocks = std::min(c->nwt, kAggChunkBlocks);
     c->cold_row_blocks = clampu(2048u / un, 1u, blk_iters);
     c->cold_srv_blocks = clampu(2048u, 1u, blk_iters);
     // Candidate list capacity per row: the warm band lists a few per cent of k entries and the first-digit
