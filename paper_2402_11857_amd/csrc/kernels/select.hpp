@@ -599,24 +599,8 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
     }
 }
 
-// grid = rows, 1024 threads: finishes the list select of a row.  Which band the row's list was filtered
-// against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
-// follows from the row's mode and first counter set, as in the filter passes.  Radix digits over the listed
-// keys narrow them down to the at most kFewEntries that share the digits found so far, and those are compared
-// with one another, which gives tau and the cut-off at once.  For a row on its predicted band the first digit's histogram is ready (k_hist0) and,
-// when the bin holding rank k was small enough, so is the short list of that bin's entries (second k_filter
-// pass): the rest of the select then reads those few entries only.  Otherwise the block walks the list
-// itself.  When more entries than that share the whole key (quantised gradients: thousands of equal
-// magnitudes), the cut-off is the `rank`-th smallest index among them, found
-// by a three-digit radix select over those indices.  Then the row's counters and histogram are cleared, the
-// next step's band is predicted and the row is back in kWarm mode.
-// The kernel is a chain of latencies (one block per row): digits of 10 bits over a list held in registers, because
-// a smaller histogram is cleared and walked faster, and the comparison in place of the second digit, the tie list
-// and its quadratic ranking: 8 x 1M columns, k = 1 %, 11.0 -> 7.3 us; 5 x 3M
-// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.  Rows whose list does not hold rank k
-// (overflow, a bin larger than the list, rank outside the band) are put into kSlow mode.
-// The same for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once by
-// hold_listed, walked by every pass of the select instead of going back to memory).
+// for_each_listed for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once
+// by hold_listed, walked by every pass of the select instead of going back to memory).
 constexpr uint32_t kHeldMax = 16u * kSelectBlock;
 __device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, uint4 (&a)[8]) {
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
@@ -638,6 +622,22 @@ __device__ __forceinline__ void for_each_held(const uint4 (&a)[8], uint32_t n, F
     }
 }
 
+// grid = rows, 1024 threads: finishes the list select of a row.  Which band the row's list was filtered
+// against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
+// follows from the row's mode and first counter set, as in the filter passes.  Radix digits over the listed
+// keys narrow them down to the at most kFewEntries that share the digits found so far, and those are compared
+// with one another, which gives tau and the cut-off at once.  For a row on its predicted band the first digit's histogram is ready (k_hist0) and,
+// when the bin holding rank k was small enough, so is the short list of that bin's entries (second k_filter
+// pass): the rest of the select then reads those few entries only.  Otherwise the block walks the list
+// itself.  When more entries than that share the whole key (quantised gradients: thousands of equal
+// magnitudes), the cut-off is the `rank`-th smallest index among them, found by radix digits of those indices
+// until at most kFewEntries are left, which are compared as before.  Then the row's counters and histogram are
+// cleared, the next step's band is predicted and the row is back in kWarm mode.
+// The kernel is a chain of latencies (one block per row): digits of 10 bits over a list held in registers, because
+// a smaller histogram is cleared and walked faster, and the comparison in place of the second digit, the tie list
+// and its quadratic ranking: 8 x 1M columns, k = 1 %, 11.0 -> 7.3 us; 5 x 3M
+// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.  Rows whose list does not hold rank k
+// (overflow, a bin larger than the list, rank outside the band) are put into kSlow mode.
 __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, RowDesc* __restrict__ desc,
                                                                uint32_t* __restrict__ ghist,
                                                                const uint2* __restrict__ list, uint32_t cap,

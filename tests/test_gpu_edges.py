@@ -163,7 +163,8 @@ def test_random_chains_on_degenerate_gradients(case):
 @pytest.mark.parametrize("wc,sc", [("topk", "topk"), ("topk", "sign")])
 def test_quantised_gradients_with_thousands_of_ties_at_the_threshold(wc, sc):
     """Gradients that carry 5 mantissa bits (as after a low-precision backward pass): about 10^4 entries of a
-    row share the threshold magnitude, more than the tie buffer holds.  The result must still be the oracle's,
+    row share the threshold magnitude, far more than the 256 entries the list select compares with one another: the
+    cut-off is found through digits of their indices.  The result must still be the oracle's,
     and the rows must not fall to the general single-block search (slow_rows stays 0)."""
     import oracle
     from paper_2402_11857_amd import LiecContext
@@ -183,7 +184,7 @@ def test_quantised_gradients_with_thousands_of_ties_at_the_threshold(wc, sc):
             keys = gh.view(np.uint32) & np.uint32(0x7FFFFFFF)
             for i in range(N):
                 tau = np.partition(keys[i], d - k)[d - k]
-                assert int((keys[i] == tau).sum()) > 4096, "the case must exceed the tie buffer"
+                assert int((keys[i] == tau).sum()) > 4096, "the case must leave thousands of ties"
             ctx.step(g, x, e)
             oracle.step(gh, xo, eo, wc, sc, 0.1, k, k if sc == "topk" else 0)
             say(f"  step {t} done")
