@@ -55,10 +55,9 @@ liec_status liec_set_search_wait(liec_ctx *ctx, int32_t polls);
  * the threshold search leaves for the aggregation -- 0: one bit per 4 columns,
  * 1: one bit per 64-byte line (16 columns).  liec_create* picks it from d (the
  * second form from 4e7 columns up, where it measured faster); results do not
- * depend on it.  Takes effect with the next step.  A step captured into a HIP graph
- * keeps the form of its capture, and liec_pack_topk_message reads the bitmap in the
- * form of the last step that was called: replay a capture and pack in one form.
- * LIEC_EINVAL for another value or when the workers' operator is not top-k.
+ * depend on it.  Takes effect with the next step (one captured into a HIP graph keeps
+ * the form of its capture).  LIEC_EINVAL for another value or when the workers'
+ * operator is not top-k.
  */
 liec_status liec_set_group_bitmap(liec_ctx *ctx, int32_t per_line);
 

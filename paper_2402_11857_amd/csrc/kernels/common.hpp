@@ -58,6 +58,7 @@ struct alignas(128) RowDesc {
     uint32_t mode;         // SelMode
     uint32_t n_list;       // candidates that were listed when the search finished (random-k marks the kept ones)
     uint32_t dense;        // the row's candidate bitmap is not valid: test every column
+    uint32_t form;         // top-k worker: form of that bitmap, 1 a bit per 4 columns, 2 per 64-byte line, 0 not valid or none yet
     uint32_t prev_tau;     // tau of the step before (valid when have_prev)
     uint32_t have_prev;
     uint32_t misses;       // steps in which the predicted band was not usable (since the context was created)

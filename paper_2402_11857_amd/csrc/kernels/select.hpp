@@ -642,7 +642,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
                                                                uint32_t* __restrict__ ghist,
                                                                const uint2* __restrict__ list, uint32_t cap,
                                                                const uint2* __restrict__ shortl, uint32_t k, uint32_t d,
-                                                               uint32_t fix_lo, uint32_t fix_hi,
+                                                               uint32_t fix_lo, uint32_t fix_hi, uint32_t form,
                                                                uint32_t* __restrict__ slow_sync) {
     __shared__ __align__(16) uint32_t h[kListBins];            // digit histograms, then the last few entries
     __shared__ uint32_t part[256], res[3];
@@ -815,6 +815,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         r.ties = s_nties;
         r.cutoff = s_cut;
         r.dense = 0;
+        r.form = form;
         r.nonfinite = r.nonfinite_acc;
         r.nonfinite_acc = 0;
         r.was_cold = cold ? 1u : 0u;
@@ -874,6 +875,7 @@ __device__ __forceinline__ void slow_write_result(RowDesc* __restrict__ desc, ui
     r.ties = ties;
     r.cutoff = cut;
     r.dense = 1;
+    r.form = 0;
     r.nonfinite = bad | r.nonfinite_acc;
     r.nonfinite_acc = 0;
     clear_counts(r);

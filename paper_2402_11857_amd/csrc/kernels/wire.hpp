@@ -79,15 +79,15 @@ static_assert((uint64_t)kWireBlocks * kBlock * kWaveTile >= (1ull << 31), "a blo
 struct KeptRow {
     const float* g;                                             // the row's gradients
     const RowDesc* rd;
-    const uint64_t* groups;                                     // top-k: the row's candidate bitmap, in either form (or none)
+    const uint64_t* groups;                                     // top-k: the workers' candidate bitmaps
+    uint32_t worker;                                            // and the row's number
     const uint16_t* kept;                                       // random-k: the row's kept bitmap
-    bool coarse;
 };
 // Ballots of the kept columns of tile t: kb[u][q] for component q of chunk u.  VALUES: also the gradients of the
 // groups of 4 columns that hold one (a[u], valid where a bit of kb[u] is set).  False when the tile keeps nothing.
 template <bool VEC, bool VALUES>
-__device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint32_t lane, uint32_t d, uint32_t tau,
-                                             uint32_t cut, bool dense, float4 (&a)[4], uint64_t (&kb)[4][4]) {
+__device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint32_t lane, uint32_t d, uint32_t nwt, uint32_t tau,
+                                             uint32_t cut, uint32_t form, float4 (&a)[4], uint64_t (&kb)[4][4]) {
     const uint32_t j0 = t * kWaveTile + lane * 4;
     if (r.kept) {                                               // uniform
         const uint32_t m = r.kept[(size_t)t * 64 + lane];
@@ -101,11 +101,12 @@ __device__ __forceinline__ bool kept_ballots(const KeptRow& r, uint32_t t, uint3
         return true;
     }
     uint32_t mask = 0xfu;                                       // bit u: my group of chunk u may hold a kept column
-    if (r.groups && !dense) {                                   // uniform
-        if (r.coarse) {
-            mask = (uint32_t)(r.groups[t] >> (4 * (lane >> 2))) & 0xfu;
+    if (form) {                                                 // uniform
+        const size_t at = (size_t)r.worker * nwt + t;
+        if (form == 2) {
+            mask = (uint32_t)(r.groups[at] >> (4 * (lane >> 2))) & 0xfu;
         } else {
-            const uint64_t* __restrict__ w = r.groups + (size_t)t * 4;
+            const uint64_t* __restrict__ w = r.groups + at * 4;
             mask = (uint32_t)((w[0] >> lane) & 1) | (uint32_t)((w[1] >> lane) & 1) << 1 | (uint32_t)((w[2] >> lane) & 1) << 2 |
                    (uint32_t)((w[3] >> lane) & 1) << 3;
         }
@@ -135,14 +136,14 @@ __global__ __launch_bounds__(kBlock) void k_kept_count(KeptRow r, uint32_t d, ui
     __shared__ uint32_t lds_w[4];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const uint32_t tau = r.rd->tau, cut = r.rd->cutoff;
-    const bool dense = r.rd->dense != 0;
+    const uint32_t form = r.rd->form;                           // of the bitmap, 0: look at every column
     const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, nwt);
     uint32_t total = 0;
     for (uint32_t t = t0 + wave; t < t1; t += 4) {
         float4 a[4];
         uint64_t kb[4][4];
         uint32_t n = 0;
-        if (kept_ballots<VEC, false>(r, t, lane, d, tau, cut, dense, a, kb)) {
+        if (kept_ballots<VEC, false>(r, t, lane, d, nwt, tau, cut, form, a, kb)) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -164,7 +165,8 @@ __global__ __launch_bounds__(kBlock) void k_kept_emit(KeptRow r, uint32_t d, uin
     __shared__ uint32_t wave_before[4], wave_n[4], first[kBlock];
     const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const uint32_t tau = r.rd->tau, cut = r.rd->cutoff;
-    const bool dense = r.rd->dense != 0;
+    const uint32_t form = r.rd->form;
+    const bool all = !r.kept && form == 0;                      // uniform: neither bitmap
     // kept entries in the blocks ahead of this one: the first 4096 counts requested at once (one after another they cost
     // this kernel half its time)
     constexpr int kLoads = 4;
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_kept_emit(KeptRow r, uint32_t d, uin
     uint64_t kb[4][4];
     // a row without a valid bitmap is not read where it keeps nothing
     auto look = [&](uint32_t t) {
-        return (!dense || tile_cnt[t] != 0) && kept_ballots<VEC, true>(r, t, lane, d, tau, cut, dense, a, kb);
+        return (!all || tile_cnt[t] != 0) && kept_ballots<VEC, true>(r, t, lane, d, nwt, tau, cut, form, a, kb);
     };
     uint32_t t = t0 + wave;
     bool any = t < t1 && look(t);                               // (its loads run beside the sums)

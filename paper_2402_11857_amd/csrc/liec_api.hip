@@ -149,8 +149,6 @@ struct liec_ctx {
     bool rk_winv = false, rk_sinv = false;     // random-k: the band is thin enough to walk the priorities instead of the columns
     uint64_t* gbits = nullptr;                 // [N * nwt * 4] group bitmap of the candidates (top-k workers), either form
     bool gb_coarse = false;                    // one bit per 64-byte line instead of one per 4 columns
-    bool gb_last_coarse = false;               // the form the last compressed step wrote
-    bool gb_written = false;                   // there has been one
     uint16_t* vbits = nullptr;                 // [nwt * 64] sign bits of v (scaled-sign server, either form)
     uint64_t* vodd = nullptr;                  // [nwt * 4] groups of 4 columns in which v is not finite (identity workers, random-k server)
     uint64_t* sgbits = nullptr;                // [nwt * 4] group bitmap of the server's candidates in v (top-k server), fine form
@@ -357,7 +355,7 @@ void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t ro
     uint32_t* const ssync = slow_b > 1 ? c->slow_sync + slow_slot * 2 : nullptr;
     L.begin(slot0 + 3);
     k_list_select<<<rows, kSelectBlock, 0, st>>>(row0, c->desc, c->ghist, c->list, c->cap, c->shortl, k, d, rk.fix_lo, rk.fix_hi,
-                                                 ssync);
+                                                 RK ? 0u : coarse ? 2u : 1u, ssync);
     L.end();
     L.begin(slot0 + 4);
     k_slow_select<VEC, RK><<<dim3(slow_b, rows), 1024, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, k, rk, shist, scnt,
@@ -486,8 +484,6 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     } else if (c->worker_comp == kBlockSign) {
         launch_block_l1<VEC>(L, grads, stride, (uint32_t)c->N, 0u, c->bits, S_W_L1);
     } else if (c->worker_comp == kTopk) {
-        c->gb_last_coarse = c->gb_coarse;
-        c->gb_written = true;
         launch_select<VEC, false>(L, grads, stride, (uint32_t)c->N, 0u, (uint32_t)c->worker_k, c->gbits, c->gb_coarse,
                                   c->filter_row_blocks, c->cold_row_blocks, S_W_SEL, RkDraw{nullptr, 0, 0});
     } else if (c->worker_comp == kRandk) {
@@ -1121,9 +1117,9 @@ liec_status liec_pack_topk_message(liec_ctx* c, const float* grads, int32_t work
     const float* row = grads + (size_t)worker * (size_t)c->d;
     const bool vec = (c->d % 4 == 0) && (((uintptr_t)grads & 15u) == 0);
     // what the last compressed step left: random-k, the worker's row of the kept bitmap; top-k, its candidate bitmap
-    KeptRow r{row, c->desc + worker, nullptr, nullptr, c->gb_last_coarse};
-    if (c->worker_comp == kRandk) r.kept = c->bits + (size_t)worker * c->nwt * 64;
-    else if (c->gb_written) r.groups = c->gbits + (size_t)worker * c->nwt * (c->gb_last_coarse ? 1 : 4);
+    // (in the form its descriptor names)
+    const KeptRow r{row, c->desc + worker, c->gbits, (uint32_t)worker,
+                    c->worker_comp == kRandk ? c->bits + (size_t)worker * c->nwt * 64 : nullptr};
     const uint32_t want = std::min((c->nwt + 3) / 4, kWireBlocks), per = (c->nwt + want - 1) / want;
     const uint32_t blocks = (c->nwt + per - 1) / per;
     uint32_t* const block_cnt = c->wire_tiles + (c->nwt + 3) / 4 * 4;    // 16-byte aligned

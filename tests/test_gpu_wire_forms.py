@@ -124,3 +124,40 @@ def test_kept_entries_of_a_constant_row():
             ctx.step(gd, x, e)
             assert ctx.info().slow_rows == N
             _check(ctx, "topk", g, k, 0, None, gd)
+
+
+@pytest.mark.parametrize("captured", [0, 1])
+def test_kept_entries_after_a_replayed_step(captured):
+    """The bitmap a message is packed from is in the form of the step that ran last, also when that was the replay of a
+    captured one and a step in the other form was called in between."""
+    say(f"case kept entries after a replay, captured form {captured}")
+    from paper_2402_11857_amd import LiecContext
+
+    N, d, k = 3, 70_003, 700
+    rng = np.random.default_rng(captured)
+    gs = [rng.standard_normal((N, d), dtype=np.float32) for _ in range(4)]
+    g, x, e = torch.zeros((N, d), device=DEV), torch.zeros((N, d), device=DEV), torch.zeros(d, device=DEV)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with LiecContext(N, d, "topk", "sign", k, 0, 0.1, stream=s) as ctx, torch.cuda.stream(s):
+        def step(data, form):
+            g.copy_(torch.from_numpy(data))
+            ctx.set_group_bitmap(form)
+            ctx.step(g, x, e)
+            for i in range(N):
+                _check(ctx, "topk", data, k, i, None, g)
+
+        step(gs[0], captured)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        graph.capture_begin()
+        ctx.step(g, x, e)
+        graph.capture_end()
+        for t in range(1, 4):
+            step(gs[0], 1 - captured)
+            g.copy_(torch.from_numpy(gs[t]))
+            graph.replay()
+            for i in range(N):
+                _check(ctx, "topk", gs[t], k, i, None, g)
+        s.synchronize()
+        del graph
