@@ -628,8 +628,8 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     c->agg_chunk = worker_comp == LIEC_COMP_IDENTITY || (worker_comp == LIEC_COMP_TOPK && c->nwt < 8192u) ||
                    (worker_comp == LIEC_COMP_RANDK && (uint64_t)c->nwt * un < 16384u) ||
                    (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
-    // A kernel that only finishes a few short sums costs its launch and two round trips to memory (3.5 us); the kernels
-    // that use the scales form them as fast while the sums are few.  us per step with and without: 4 x 65536 columns
+    // A kernel that only finishes a few short sums costs its launch and two round trips to memory (2 us); the kernels
+    // that use the scales form them as fast while the sums are few (both sides here, the server's in the update).  us per step with and without: 4 x 65536 columns
     // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 18.6 against 20.6; at 16 x 262144
     // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.  A wave forms its workers' scales
     // one after another, 0.5 us each however short the rows: sign / identity, 16 x 16384 13.3 against 13.4, 24 x 16384
