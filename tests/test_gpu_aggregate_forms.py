@@ -1,4 +1,4 @@
-"""The aggregation's two forms (a wave per chunk of 256 columns, a wave per tile of 1024) around the sizes where they
+"""The aggregation's forms (a wave per chunk of 256 columns, a wave per tile of 1024) around the sizes where they
 split the work: batches of 8 rows, ends of chunks and tiles, and rows on the far side of the rule that picks a form.
 """
 import os
@@ -119,8 +119,8 @@ def test_aggregate_by_tile_randk(N, d, k):
     _chain(N, d, "randk", "sign", k, 2)
 
 
-# a blockwise server's partial sums left by the aggregation: rounds with waves beyond the last tile, tables with many
-# boundaries in one 4096-column tile, blocks that end with a tile
+# a blockwise server's partial sums, left by the aggregation or, on tables with many boundaries in one 4096-column tile,
+# by the pass over v: rounds with waves beyond the last tile, blocks that end with a tile
 @pytest.mark.parametrize("wc", ["sign", "blocksign"])
 @pytest.mark.parametrize("N,d", [(2, 1), (3, 1025), (9, 4096), (2, 4097), (5, 12_289), (2, 70_001), (2, 2048 * 1024 + 1030)])
 @pytest.mark.parametrize("table", ["one", "tiles", "crowded"])
@@ -184,3 +184,21 @@ def test_aggregate_at_the_limit_of_the_list(N, groups, extra, coarse):
             torch.cuda.synchronize()
             H.oracle_step_rows(g, x, e, "topk", "sign", 0.05, k, 0)
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
+
+
+# the aggregation sums three items in every tile: boundaries inside a group of 4 columns, at a wave's end, next to a tile's end
+@pytest.mark.parametrize("wc,N,d", [("sign", 3, 12_289), ("sign", 17, 70_001), ("blocksign", 2, 2048 * 1024 + 1030)])
+def test_blockwise_sums_at_block_boundaries(wc, N, d):
+    say(f"case blockwise sums at boundaries N={N} d={d} {wc}")
+    from paper_2402_11857_amd import LiecContext
+
+    off = [0]
+    for t in range(0, d, 4096):
+        off += [o for o in (t + (1024 if t // 4096 % 2 else 1501), t + (4094 if t // 4096 % 3 else 4095)) if o < d]
+    off.append(d)
+    _chain(N, d, wc, "blocksign", 1, 2, off)
+    with LiecContext(N, d, wc, "blocksign", 0, 0, 0.05) as ctx:
+        ctx.set_blocks(off)
+        ctx.profile_begin(1)
+        ctx.step(*(torch.ones(s, device=DEV) for s in ((N, d), (N, d), d)))
+        assert "server_l1" not in ctx.profile_end()
