@@ -65,6 +65,7 @@ struct alignas(128) RowDesc {
     uint32_t centre;       // where the last prediction expected tau
     uint32_t swing;        // decaying maximum of the distances between tau and that centre
     uint32_t was_cold;     // the last band came from the first-digit histogram, not from a prediction
+    uint32_t general;      // the last step took the general search because no list could hold the row's candidates
     // second line: what the blocks of the passes add to with atomics (kept off the line every block reads when
     // it starts).  Counters of the pass over the predicted band, one 64-bit word that a block of the filter adds
     // to with a single atomic.  Low half: candidates appended (may exceed the capacity: overflow); high half:
@@ -82,12 +83,13 @@ static_assert(sizeof(RowDesc) == 256, "two lines per row");
 
 __host__ __device__ __forceinline__ uint32_t sure_count(const RowDesc& r) { return r.n_sure; }
 __host__ __device__ __forceinline__ uint32_t sure_count2(const RowDesc& r) { return r.n_sure2; }
-// Both passes' counters back to zero (whoever finishes a row's search calls it).
+// The second line back to zero (the update kernel does it for every row, once nobody looks at the counters any more).
 __host__ __device__ __forceinline__ void clear_counts(RowDesc& r) {
     r.n_cand = 0;
     r.n_cand2 = 0;
     r.n_short = 0;
     r.n_sure = r.n_sure2 = 0;
+    r.nonfinite_acc = 0;
 }
 
 // After a filter pass: the band is usable when its list did not overflow and rank k falls inside it.
@@ -124,8 +126,11 @@ struct RkState {               // in device memory, so that a captured step draw
     uint64_t seed, draw;       // draw: number of the draw the next step makes
 };
 struct RkDraw {
-    const RkState* state;
-    uint32_t fix_lo, fix_hi;   // band that holds rank k of uniform priorities (set by the host); fix_hi == 0: not random-k
+    const RkState* state = nullptr;
+    uint32_t fix_lo = 0, fix_hi = 0;   // band that holds rank k of uniform priorities (set by the host); fix_hi == 0: not random-k
+    // random-k on both sides: the server's draw, which no gradient enters, is one more row of the workers' launches, with
+    // a k and a band of its own
+    uint32_t srv_row = 0xffffffffu, srv_k = 0, srv_lo = 0, srv_hi = 0;
 };
 
 __host__ __device__ __forceinline__ uint64_t rk_mix64(uint64_t z) {

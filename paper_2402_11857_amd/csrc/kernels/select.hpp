@@ -7,7 +7,8 @@ namespace liec {
 
 // ---------------------------------------------------------------------------------------------
 // Top-k (Definition 2).  The k-th largest magnitude key tau of a row and the index cut-off
-// among its ties are found without sorting, by five kernels the host enqueues every step:
+// among its ties are found without sorting, on long rows by five kernels the host enqueues every step (on short rows, and
+// for random-k, one kernel, k_select, does what 2 to 5 do):
 //   1. k_filter (pass over the predicted band) streams the row once against a band [lo, hi) of keys
 //      expected to hold tau, predicted from the previous steps' tau (rows in kWarm mode): keys >= hi are
 //      only counted, keys inside the band are appended to a candidate list (key, index), and a group
@@ -33,7 +34,7 @@ namespace liec {
 //   5. k_slow_select takes the kSlow rows.
 // All decisions are taken on the device per row, each kernel re-deriving from the row's mode and
 // counters whether it has work; in the steady state kernels 2 and 3 only touch the lists and 5 returns at once.  A row's mode
-// and its result are written only by k_list_select and k_slow_select.
+// and its result are written only by k_list_select, k_slow_select and k_select, its counters cleared by the update.
 // `row0` is added to blockIdx.y to address per-row state (the server's vector uses row N).
 // ---------------------------------------------------------------------------------------------
 // Coarse group bitmap: bit 4m of the result is set when some lane of 4m .. 4m + 3 has its bit set in the
@@ -191,9 +192,22 @@ struct StagePos {
     uint32_t wbase;                              // slot of that entry in the wave's own stage
     bool drop;                                   // the list is full: nothing is kept any more
 };
+// Words that blocks of one launch hand to one another (they may run on dies with an L2 of their own): stored past the L2,
+// loaded past it.  Complete once the wave that stored them has waited for its stores.
+template <typename T>
+__device__ __forceinline__ void st_shared(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T ld_shared(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// An entry of a list; SHARED: for another block of this launch.
+template <bool SHARED>
+__device__ __forceinline__ void put_entry(uint2* at, uint2 e) {
+    if (SHARED) st_shared(reinterpret_cast<unsigned long long*>(at), (unsigned long long)e.y << 32 | e.x);
+    else *at = e;
+}
 // Empties the wave's own stage into the list.  staged[1] is set once a reservation of this block has gone past
 // the list's capacity: the row's count then stays above the capacity, which is all that anyone reads from an
 // overflowed list, and the block stops listing and counting candidates.
+template <bool SHARED>
 __device__ __forceinline__ void flush_wave_stage(const FilterBand& fb, const uint2* wst, uint32_t cnt, uint32_t* staged,
                                                  uint32_t lane) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -204,11 +218,12 @@ __device__ __forceinline__ void flush_wave_stage(const FilterBand& fb, const uin
     }
     base = __builtin_amdgcn_readfirstlane(base);
     for (uint32_t s = lane; s < cnt; s += 64)
-        if (base + s < fb.cap) fb.out[base + s] = wst[s];
+        if (base + s < fb.cap) put_entry<SHARED>(&fb.out[base + s], wst[s]);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 // The wave has m <= kWaveStage entries to append (wave-uniform, every lane calls).  staged[0]: the block's LDS
 // counter of stage positions handed out; wst / wcnt: the wave's own stage and how many entries it holds.
+template <bool SHARED = false>
 __device__ __forceinline__ StagePos reserve_stage(const FilterBand& fb, uint32_t m, uint32_t* staged, const uint2* wst,
                                                   uint32_t& wcnt, uint32_t lane) {
     StagePos sp;
@@ -222,7 +237,7 @@ __device__ __forceinline__ StagePos reserve_stage(const FilterBand& fb, uint32_t
     if (sp.pos + m > (uint32_t)kStage) {                        // uniform
         const uint32_t nsp = sp.pos + m - sp.first_spill;
         if (wcnt + nsp > (uint32_t)kWaveStage) {
-            flush_wave_stage(fb, wst, wcnt, staged, lane);
+            flush_wave_stage<SHARED>(fb, wst, wcnt, staged, lane);
             wcnt = 0;
         }
         sp.wbase = wcnt;
@@ -239,12 +254,13 @@ __device__ __forceinline__ void put_candidate(uint2* stage, uint2* wst, const St
 }
 
 // Appends a chunk's candidates: those of component q are the lanes of bc[q], at column j + q.
+template <bool SHARED = false>
 __device__ __forceinline__ void stage_candidates(const FilterBand& fb, const uint32_t (&keys)[4], uint32_t j,
                                                  const uint64_t (&bc)[4], uint2* stage, uint2* wst, uint32_t& wcnt,
                                                  uint32_t* staged, uint32_t lane) {
     if ((bc[0] | bc[1] | bc[2] | bc[3]) == 0) return;           // wave-uniform
     const uint32_t m = __popcll(bc[0]) + __popcll(bc[1]) + __popcll(bc[2]) + __popcll(bc[3]);
-    const StagePos sp = reserve_stage(fb, m, staged, wst, wcnt, lane);
+    const StagePos sp = reserve_stage<SHARED>(fb, m, staged, wst, wcnt, lane);
     uint32_t off = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -253,27 +269,28 @@ __device__ __forceinline__ void stage_candidates(const FilterBand& fb, const uin
     }
 }
 
-// End of a filter block.  n_hi: keys above the band, per lane; wst / wcnt: the wave's own stage.  Every thread of
-// the block calls it.
+// End of a filter block of WAVES waves.  n_hi: keys above the band, per lane; wst / wcnt: the wave's own stage.  Every
+// thread of the block calls it.
+template <int WAVES = kBlock / 64, bool SHARED = false>
 __device__ __forceinline__ void finish_filter_block(const FilterBand& fb, const uint2* stage, const uint2* wst, uint32_t wcnt,
-                                                    uint32_t n_hi, uint32_t* staged, uint32_t* wsure /* 5 words */) {
+                                                    uint32_t n_hi, uint32_t* staged, uint32_t* wsure /* WAVES + 1 words */) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n_hi += __shfl_down(n_hi, o, 64);
     if (lane == 0) wsure[wave] = n_hi;
-    if (wcnt) flush_wave_stage(fb, wst, wcnt, staged, lane);    // wave-uniform
+    if (wcnt) flush_wave_stage<SHARED>(fb, wst, wcnt, staged, lane);    // wave-uniform
     __syncthreads();
     const uint32_t n_staged = min(staged[0], (uint32_t)kStage);
     if (threadIdx.x == 0) {
-        const uint32_t sure = wsure[0] + wsure[1] + wsure[2] + wsure[3];
-        uint32_t base = 0;
+        uint32_t sure = 0, base = 0;
+        for (int w = 0; w < WAVES; ++w) sure += wsure[w];
         if (sure | n_staged) base = (uint32_t)atomicAdd(fb.counts, ((unsigned long long)sure << 32) | n_staged);
-        wsure[4] = base;
+        wsure[WAVES] = base;
     }
     __syncthreads();
-    const uint32_t base = wsure[4];
-    for (uint32_t s = threadIdx.x; s < n_staged; s += kBlock)
-        if (base + s < fb.cap) fb.out[base + s] = stage[s];
+    const uint32_t base = wsure[WAVES];
+    for (uint32_t s = threadIdx.x; s < n_staged; s += WAVES * 64)
+        if (base + s < fb.cap) put_entry<SHARED>(&fb.out[base + s], stage[s]);
 }
 
 // RK: the keys are the priorities of a random-k draw (nothing is read from src), and instead of the
@@ -290,13 +307,13 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
     __shared__ uint32_t wsure[5], staged[2];
     __shared__ uint32_t part[256], res[3];
     const uint32_t row = row0 + blockIdx.y;
-    if (cold_pass && desc[row].mode == kWarm && !wants_cold(desc[row], cap, k)) {   // uniform for the block
+    if (!RK && cold_pass && desc[row].mode == kWarm && !wants_cold(desc[row], cap, k)) {   // uniform for the block
         list_collect(desc, row, list + (size_t)row * cap, ghist + (size_t)row * kHistBins,
                      shortl + (size_t)row * kShortCap, k, part, res);
         return;
     }
     FilterBand fb;
-    if (!filter_band(desc, row, cold_pass, ghist, list, cap, k, part, res, fb)) return;   // uniform for the block
+    if (!filter_band(desc, row, !RK && cold_pass, ghist, list, cap, k, part, res, fb)) return;   // uniform for the block
     if (threadIdx.x < 2) staged[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t lo = fb.lo, hi = fb.hi;
@@ -392,31 +409,22 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
 // multiplication and a look at the index's upper half 99.
 constexpr int kInverseWords = 4;                                // words per lane and iteration (8: 5 us slower)
 __global__ __launch_bounds__(kBlock) void k_rk_zero(uint32_t nwt, uint32_t row0, const RowDesc* __restrict__ desc,
-                                                     bool cold_pass, uint32_t cap, uint32_t k,
                                                      uint16_t* __restrict__ kbits) {
     const uint32_t row = row0 + blockIdx.y;
-    if (cold_pass ? !wants_cold(desc[row], cap, k) : desc[row].mode != kWarm) return;
+    if (desc[row].mode != kWarm) return;
     uint4* __restrict__ words = reinterpret_cast<uint4*>(kbits + (size_t)row * nwt * 64);
     const uint32_t n = nwt * 8;
     for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < n; q += gridDim.x * kBlock) words[q] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32_t nwt, uint32_t row0,
-                                                               RowDesc* __restrict__ desc, bool cold_pass,
-                                                               const uint32_t* __restrict__ ghist, uint32_t k,
-                                                               uint16_t* __restrict__ kbits, uint2* __restrict__ list,
-                                                               uint32_t cap, uint2* __restrict__ shortl, RkDraw rk) {
+                                                               RowDesc* __restrict__ desc, uint16_t* __restrict__ kbits,
+                                                               uint2* __restrict__ list, uint32_t cap, RkDraw rk) {
     __shared__ uint2 stage[kStage], wstage[4][kWaveStage];
     __shared__ uint32_t wsure[5], staged[2];
-    __shared__ uint32_t part[256], res[3];
     const uint32_t row = row0 + blockIdx.y;
-    if (cold_pass && desc[row].mode == kWarm && !wants_cold(desc[row], cap, k)) {   // uniform for the block
-        list_collect(desc, row, list + (size_t)row * cap, ghist + (size_t)row * kHistBins,
-                     shortl + (size_t)row * kShortCap, k, part, res);
-        return;
-    }
     FilterBand fb;
-    if (!filter_band(desc, row, cold_pass, ghist, list, cap, k, part, res, fb)) return;   // uniform for the block
+    if (!filter_band(desc, row, false, nullptr, list, cap, 0u, nullptr, nullptr, fb)) return;   // uniform for the block
     if (threadIdx.x < 2) staged[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t lo = fb.lo, hi = fb.hi;
@@ -475,11 +483,11 @@ __global__ __launch_bounds__(kBlock) void k_rk_filter_inverse(uint32_t d, uint32
 // First radix digit (12 bits) of every key of the rows that have no usable band; for the rows whose
 // predicted band holds rank k, the first digit of the listed keys instead (list_first_digit).  Either
 // histogram goes to the row's kHistBins words of `hist`.  grid = (blocks, rows).
-template <bool VEC, bool RK>
+template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src, size_t row_stride, uint32_t d,
                                                    uint32_t nwt, uint32_t row0, const RowDesc* __restrict__ desc,
                                                    uint32_t* __restrict__ hist, const uint2* __restrict__ list, uint32_t cap,
-                                                   uint32_t k, RkDraw rk) {
+                                                   uint32_t k) {
     __shared__ uint32_t h[kHistBins];
     const uint32_t row = row0 + blockIdx.y;
     if (!wants_cold(desc[row], cap, k)) {                       // uniform for the block
@@ -490,31 +498,14 @@ __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src,
     for (int b = threadIdx.x; b < kHistBins; b += kBlock) h[b] = 0;
     __syncthreads();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    uint32_t k0 = 0, k1 = 0;
-    if (RK) {
-        const uint64_t stream = rk_stream(rk.state->seed, rk.state->draw, row);
-        k0 = (uint32_t)stream;
-        k1 = (uint32_t)(stream >> 32);
-    }
     for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
         float4 a[4];
-        if (!RK) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
-        }
+        for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
-            uint32_t keys[4];
-            if (RK) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) keys[q] = rk_priority(k0, k1, j + q);
-            } else {
-                keys[0] = key_of(a[u].x);
-                keys[1] = key_of(a[u].y);
-                keys[2] = key_of(a[u].z);
-                keys[3] = key_of(a[u].w);
-            }
+            const uint32_t keys[4] = {key_of(a[u].x), key_of(a[u].y), key_of(a[u].z), key_of(a[u].w)};
 #pragma unroll
             for (int q = 0; q < 4; ++q) wave_count(h, j + q < d, keys[q] >> 19, lane);
         }
@@ -622,84 +613,28 @@ __device__ __forceinline__ void for_each_held(const uint4 (&a)[8], uint32_t n, F
     }
 }
 
-// grid = rows, 1024 threads: finishes the list select of a row.  Which band the row's list was filtered
-// against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
-// follows from the row's mode and first counter set, as in the filter passes.  Radix digits over the listed
-// keys narrow them down to the at most kFewEntries that share the digits found so far, and those are compared
-// with one another, which gives tau and the cut-off at once.  For a row on its predicted band the first digit's histogram is ready (k_hist0) and,
-// when the bin holding rank k was small enough, so is the short list of that bin's entries (second k_filter
-// pass): the rest of the select then reads those few entries only.  Otherwise the block walks the list
-// itself.  When more entries than that share the whole key (quantised gradients: thousands of equal
+// What is left of a row's search once its candidates are listed: radix digits over the listed keys narrow them down to
+// the at most kFewEntries that share the digits found so far, and those are compared with one another, which gives tau
+// and the cut-off at once.  When more entries than that share the whole key (quantised gradients: thousands of equal
 // magnitudes), the cut-off is the `rank`-th smallest index among them, found by radix digits of those indices
-// until at most kFewEntries are left, which are compared as before.  Then the row's counters and histogram are
-// cleared, the next step's band is predicted and the row is back in kWarm mode.
-// The kernel is a chain of latencies (one block per row): digits of 10 bits over a list held in registers, because
+// until at most kFewEntries are left, which are compared as before.
+// One block of kSelectBlock threads, a chain of latencies: digits of 10 bits over a list held in registers, because
 // a smaller histogram is cleared and walked faster, and the comparison in place of the second digit, the tie list
 // and its quadratic ranking: 8 x 1M columns, k = 1 %, 11.0 -> 7.3 us; 5 x 3M
-// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.  Rows whose list does not hold rank k
-// (overflow, a bin larger than the list, rank outside the band) are put into kSlow mode.
-__global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, RowDesc* __restrict__ desc,
-                                                               uint32_t* __restrict__ ghist,
-                                                               const uint2* __restrict__ list, uint32_t cap,
-                                                               const uint2* __restrict__ shortl, uint32_t k, uint32_t d,
-                                                               uint32_t fix_lo, uint32_t fix_hi, uint32_t form,
-                                                               uint32_t* __restrict__ slow_sync) {
-    __shared__ __align__(16) uint32_t h[kListBins];            // digit histograms, then the last few entries
-    __shared__ uint32_t part[256], res[3];
-    __shared__ uint32_t s_tau, s_cut, s_rank, s_nties;
-    static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the last entries reuse the histogram, one per thread");
-    __shared__ RowDesc now;                                    // the row's descriptor as the kernel found it
-    const uint32_t row = row0 + blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    // one round trip for the whole descriptor instead of one per dependent field; nobody else writes it meanwhile
-    static_assert(sizeof(RowDesc) == 64 * sizeof(uint32_t), "64 lanes copy the descriptor");
-    if (tid < 64) reinterpret_cast<uint32_t*>(&now)[tid] = reinterpret_cast<const uint32_t*>(&desc[row])[tid];
-    // the meeting counter and give-up flag of the general search that may follow start every step at zero
-    if (slow_sync && tid < 2) slow_sync[(size_t)blockIdx.x * 2 + tid] = 0;
-    __syncthreads();
-    if (now.mode == kSlow) return;
-    const bool cold = wants_cold(now, cap, k);                  // uniform for the block
-    const uint32_t missed = (cold && now.mode == kWarm) ? 1u : 0u;    // there was a prediction and it failed
-    uint32_t* __restrict__ hrow = ghist + (size_t)row * kHistBins;
-    const uint2* __restrict__ in = list + (size_t)row * cap;
-    uint32_t lo, hi, n, n_sure;
-    bool ok = true;
-    Pick ph;                                                    // first digit: bin holding rank k, rank inside it
-    int shift;                                                  // key bits below the digits found so far
-    bool direct = cold;                                         // this block builds the first digit's histogram itself
-    if (cold) {
-        const Pick p = block_pick(hrow, kHistBins, k, part, res);
-        lo = p.bin << 19;
-        hi = (p.bin + 1) << 19;
-        n = now.n_cand2;
-        n_sure = sure_count2(now);
-        ok = p.count <= cap && n <= cap && n_sure < k && (uint64_t)k <= (uint64_t)n_sure + n;
-    } else {                                                    // kWarm and band_ok
-        lo = now.lo;
-        hi = now.hi;
-        n = now.n_cand;
-        n_sure = sure_count(now);
-        direct = n <= (uint32_t)kDirectList;
-        if (!direct) ph = block_pick(hrow, 1 << kFirstBits, k - n_sure, part, res);
-    }
-    if (cold || !direct)
-        for (int b = tid; b < kHistBins; b += kSelectBlock) hrow[b] = 0;    // the row's histogram is ready for the next step
-    if (!ok) {
-        if (tid == 0) {
-            RowDesc r = now;
-            clear_counts(r);
-            r.n_list = 0;
-            r.misses += missed;
-            r.mode = kSlow;
-            desc[row] = r;
-        }
-        return;
-    }
-    const uint32_t n_all = n;
-    shift = first_shift(hi - lo, direct ? (n <= kHeldMax ? kHeldBits : kListBits) : kFirstBits);
-    if (!direct && ph.count <= (uint32_t)kShortCap && now.n_short == ph.count) {
-        in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
-        n = ph.count;
-    }
+// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.
+struct ListLds {
+    __align__(16) uint32_t h[kListBins];       // digit histograms, then the last few entries
+    uint32_t part[256], res[3];
+    uint32_t tau, cut, rank, nties;            // the result
+};
+static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the last entries reuse the histogram, one per thread");
+// in: n entries with keys in [lo, lo + width), `rank`: how many from the top the searched one is.  first: the first digit
+// is not known yet (it has first_shift(width, .) bits below it); otherwise ph and shift say what is.  Every thread of the
+// block calls it; the result is in s (all threads see it).
+__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
+                                              uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    uint32_t* const h = s.h;
     // a list of up to kHeldMax entries is read once and kept in registers for all the passes below
     const bool held = n <= kHeldMax;                            // uniform for the block
     uint4 own[8];
@@ -708,14 +643,15 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         if (held) for_each_held(own, n, fn);
         else for_each_listed(in, n, fn);
     };
-    if (direct) {
+    if (first) {
         // first digit of every listed key, in LDS
-        const uint32_t nbins = max(256u, 1u << (band_bits(hi - lo) - shift));
+        shift = first_shift(width, held ? kHeldBits : kListBits);
+        const uint32_t nbins = max(256u, 1u << (band_bits(width) - shift));
         for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
         __syncthreads();
         walk([&](uint2 kv, bool valid) { wave_count(h, valid, (kv.x - lo) >> shift, lane); });
         __syncthreads();
-        ph = block_pick(h, (int)nbins, k - n_sure, part, res);
+        ph = block_pick(h, (int)nbins, rank, s.part, s.res);
     }
     // The following digits, over the entries that carry the digits found so far, until few are left or the key is known.
     const int digit_bits_max = held ? kHeldBits : kListBits;
@@ -724,10 +660,10 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
     while (shift > 0 && left > kFewEntries) {
         if (held) {                                             // gradients of few mantissa bits: one key may be all there is
             walk([&](uint2 kv, bool valid) {
-                if (valid && ((kv.x - lo) >> shift) == prefix) s_tau = kv.x;     // any of them
+                if (valid && ((kv.x - lo) >> shift) == prefix) s.tau = kv.x;     // any of them
             });
             __syncthreads();
-            const uint32_t one = s_tau;
+            const uint32_t one = s.tau;
             bool other = false;
             walk([&](uint2 kv, bool valid) { other |= valid && ((kv.x - lo) >> shift) == prefix && kv.x != one; });
             if (!__syncthreads_or(other)) {
@@ -745,7 +681,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
             wave_count(h, valid && (rel >> shift) == prefix, (rel >> below) & mask, lane);
         });
         __syncthreads();
-        const Pick p = block_pick(h, (int)nbins, want, part, res);
+        const Pick p = block_pick(h, (int)nbins, want, s.part, s.res);
         prefix = (prefix << bits) | p.bin;
         want = p.rank_in;
         left = p.count;
@@ -769,7 +705,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
             wave_count(h, valid && kv.x == lo + prefix && (inv >> ishift) == ifound, (inv >> below) & mask, lane);
         });
         __syncthreads();
-        const Pick p = block_pick(h, (int)nbins, want, part, res);
+        const Pick p = block_pick(h, (int)nbins, want, s.part, s.res);
         ifound = (ifound << bits) | p.bin;
         want = p.rank_in;
         left = p.count;
@@ -778,11 +714,11 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
     // The entries that are left, compared with one another: the one with want - 1 others ahead of it (larger key, or
     // the same key and a lower index) is the row's k-th.
     uint2* few = reinterpret_cast<uint2*>(h);
-    if (tid == 0) s_nties = 0;
+    if (tid == 0) s.nties = 0;
     __syncthreads();
     walk([&](uint2 kv, bool valid) {
         if (valid && ((kv.x - lo) >> shift) == prefix && ((top - kv.y) >> ishift) == ifound) {
-            const uint32_t pos = atomicAdd(&s_nties, 1u);
+            const uint32_t pos = atomicAdd(&s.nties, 1u);
             if (pos < kFewEntries) few[pos] = kv;
         }
     });
@@ -799,39 +735,118 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         }
         if (larger + earlier + 1 == want) {                     // indices are distinct: one thread
             const bool by_index = ties != left;                 // the entries went through the index digits
-            s_tau = mine.x;
-            s_cut = mine.y;
-            s_rank = by_index ? want_key : want - larger;
-            s_nties = by_index ? ties : equal;
+            s.tau = mine.x;
+            s.cut = mine.y;
+            s.rank = by_index ? want_key : want - larger;
+            s.nties = by_index ? ties : equal;
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        RowDesc r = now;
-        r.n_list = n_all;
-        clear_counts(r);
-        r.tau = s_tau;
-        r.rank = s_rank;
-        r.ties = s_nties;
-        r.cutoff = s_cut;
-        r.dense = 0;
-        r.form = form;
-        r.nonfinite = r.nonfinite_acc;
-        r.nonfinite_acc = 0;
-        r.was_cold = cold ? 1u : 0u;
-        r.misses += missed;
-        predict_band(r, fix_lo, fix_hi);
-        r.mode = kWarm;
-        desc[row] = r;
+}
+
+// The row's descriptor in LDS, in one round trip instead of one per dependent field.  64 threads or more; the caller
+// synchronises.
+static_assert(sizeof(RowDesc) == 64 * sizeof(uint32_t), "64 lanes copy the descriptor");
+__device__ __forceinline__ void fetch_desc(RowDesc& now, const RowDesc* __restrict__ desc) {
+    if (threadIdx.x < 64) reinterpret_cast<uint32_t*>(&now)[threadIdx.x] = reinterpret_cast<const uint32_t*>(desc)[threadIdx.x];
+}
+// And back, its first line: the counters of the second stay as the passes left them (every block of a kernel that finishes
+// searches can still tell from them what the row needed) until the update kernel clears them.  Every thread calls it, after
+// thread 0 has changed `now`.
+constexpr uint32_t kFirstLineWords = 32;
+__device__ __forceinline__ void put_result(RowDesc* __restrict__ desc, const RowDesc& now) {
+    __syncthreads();
+    if (threadIdx.x < kFirstLineWords)
+        reinterpret_cast<uint32_t*>(desc)[threadIdx.x] = reinterpret_cast<const uint32_t*>(&now)[threadIdx.x];
+}
+// The end of a search over a list of n_all candidates whose result is in s (thread 0).
+__device__ __forceinline__ void finish_listed(RowDesc& r, const ListLds& s, uint32_t n_all, uint32_t form, bool cold, uint32_t missed,
+                                              uint32_t fix_lo, uint32_t fix_hi) {
+    r.n_list = n_all;
+    r.tau = s.tau;
+    r.rank = s.rank;
+    r.ties = s.nties;
+    r.cutoff = s.cut;
+    r.dense = r.general = 0;
+    r.form = form;
+    r.nonfinite = r.nonfinite_acc;
+    r.was_cold = cold ? 1u : 0u;
+    r.misses += missed;
+    predict_band(r, fix_lo, fix_hi);
+    r.mode = kWarm;
+}
+
+// grid = rows, kSelectBlock threads: finishes the list select of a row.  Which band the row's list was filtered
+// against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
+// follows from the row's mode and first counter set, as in the filter passes.  For a row on its predicted band the first
+// digit's histogram is ready (k_hist0) and,
+// when the bin holding rank k was small enough, so is the short list of that bin's entries (second k_filter
+// pass): the rest of the select then reads those few entries only.  Otherwise the block walks the list
+// itself.  Then the row's histogram is
+// cleared, the next step's band is predicted and the row is back in kWarm mode.
+// Rows whose list does not hold rank k
+// (overflow, a bin larger than the list, rank outside the band) are put into kSlow mode.
+__global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, RowDesc* __restrict__ desc,
+                                                               uint32_t* __restrict__ ghist,
+                                                               const uint2* __restrict__ list, uint32_t cap,
+                                                               const uint2* __restrict__ shortl, uint32_t k, uint32_t d,
+                                                               uint32_t form) {
+    __shared__ ListLds s;
+    __shared__ RowDesc now;                                    // the row's descriptor as the kernel found it
+    const uint32_t row = row0 + blockIdx.x, tid = threadIdx.x;
+    fetch_desc(now, desc + row);
+    __syncthreads();
+    if (now.mode == kSlow) return;
+    const bool cold = wants_cold(now, cap, k);                  // uniform for the block
+    const uint32_t missed = (cold && now.mode == kWarm) ? 1u : 0u;    // there was a prediction and it failed
+    uint32_t* __restrict__ hrow = ghist + (size_t)row * kHistBins;
+    const uint2* __restrict__ in = list + (size_t)row * cap;
+    uint32_t lo, hi, n, n_sure;
+    bool ok = true;
+    Pick ph{0, 0, 0};                                           // first digit: bin holding rank k, rank inside it
+    bool direct = cold;                                         // this block builds the first digit's histogram itself
+    if (cold) {
+        const Pick p = block_pick(hrow, kHistBins, k, s.part, s.res);
+        lo = p.bin << 19;
+        hi = (p.bin + 1) << 19;
+        n = now.n_cand2;
+        n_sure = sure_count2(now);
+        ok = p.count <= cap && n <= cap && n_sure < k && (uint64_t)k <= (uint64_t)n_sure + n;
+    } else {                                                    // kWarm and band_ok
+        lo = now.lo;
+        hi = now.hi;
+        n = now.n_cand;
+        n_sure = sure_count(now);
+        direct = n <= (uint32_t)kDirectList;
+        if (!direct) ph = block_pick(hrow, 1 << kFirstBits, k - n_sure, s.part, s.res);
     }
+    if (cold || !direct)
+        for (int b = tid; b < kHistBins; b += kSelectBlock) hrow[b] = 0;    // the row's histogram is ready for the next step
+    if (!ok) {
+        if (tid == 0) {
+            now.n_list = 0;
+            now.misses += missed;
+            now.mode = kSlow;
+        }
+        put_result(desc + row, now);
+        return;
+    }
+    const uint32_t n_all = n;
+    if (!direct && ph.count <= (uint32_t)kShortCap && now.n_short == ph.count) {
+        in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
+        n = ph.count;
+    }
+    select_listed(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
+    if (tid == 0) finish_listed(now, s, n_all, form, cold, missed, 0u, 0u);
+    put_result(desc + row, now);
 }
 
 // ---------------------------------------------------------------------------------------------
-// General search for rows in kSlow mode: three radix digits over the whole row, then the ties in
-// index order.  Only degenerate rows come here (constant or mostly-zero rows, values on a handful of
+// General search: three radix digits over the whole row, then the ties in
+// index order.  On long rows only degenerate ones come here (constant or mostly-zero rows, values on a handful of
 // levels: a threshold shared by more entries than the candidate list holds).
 //   grid = (B, rows), 1024 threads.  With B > 1 the B blocks of a row split it into contiguous ranges
-// and meet between the phases at a counter in the row's descriptor (every block adds one and polls
+// and meet between the phases at a counter (every block adds one and polls
 // until all B have arrived); the histograms of the three digits and the blocks' tie counts live in
 // global memory.  The poll is bounded: when a wait runs out (blocks that could not all be resident
 // at once, a GPU shared with other work) the row is flagged, every block leaves, and block 0
@@ -842,12 +857,14 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
 // ---------------------------------------------------------------------------------------------
 constexpr int kSlowMaxBlocks = 64;
 constexpr uint32_t kSlowHistWords = 4096 + 1024 + 512;        // the three digit histograms of a row
+constexpr uint32_t kSyncWords = 4;                            // of a row: arrivals; some block has given up; the histograms are not zero
 
 struct SlowLds {
     uint32_t h[kHistBins];
     uint32_t part[256], res[3];
     uint32_t wtot[16];
-    uint32_t cut, bad, ok;
+    uint32_t cut, bad, ok, dirty;
+    RowDesc now;
 };
 
 // the 4 keys of columns j .. j + 3 (columns at or beyond d give unspecified keys; callers test j + q < d)
@@ -866,37 +883,41 @@ __device__ __forceinline__ void slow_keys_at(const float* __restrict__ g, uint32
     }
 }
 
-// What either path leaves in the row's descriptor (one thread calls it).
-__device__ __forceinline__ void slow_write_result(RowDesc* __restrict__ desc, uint32_t row, uint32_t tau, uint32_t rank,
-                                                  uint32_t ties, uint32_t cut, uint32_t bad, bool is_rk, RkDraw rk) {
-    RowDesc r = desc[row];
-    r.tau = tau;
-    r.rank = rank;
-    r.ties = ties;
-    r.cutoff = cut;
-    r.dense = 1;
-    r.form = 0;
-    r.nonfinite = bad | r.nonfinite_acc;
-    r.nonfinite_acc = 0;
-    clear_counts(r);
-    r.n_list = 0;
-    r.have_prev = 0;
-    r.was_cold = 0;
-    r.mode = kCold;
-    if (is_rk) {                               // the band of a random-k draw is known without a prediction
-        r.lo = rk.fix_lo;
-        r.hi = rk.fix_hi;
-        r.mode = kWarm;
+// What a general search found.
+struct SlowFound {
+    uint32_t tau, rank, ties, cut, bad;
+    uint32_t first;                            // entries that share tau's first digit
+};
+// And what it leaves in the row's descriptor (thread 0).  degenerate: no candidate list could hold the row, so there is
+// no use in a prediction; form: of the row's candidate bitmap, 0 none.
+__device__ __forceinline__ void finish_general(RowDesc& r, const SlowFound& f, bool degenerate, uint32_t form, uint32_t fix_lo,
+                                               uint32_t fix_hi) {
+    r.tau = f.tau;
+    r.rank = f.rank;
+    r.ties = f.ties;
+    r.cutoff = f.cut;
+    r.dense = form ? 0u : 1u;
+    r.form = form;
+    r.general = degenerate ? 1u : 0u;
+    r.nonfinite = r.nonfinite_acc;
+    r.n_list = degenerate ? 0u : f.first;
+    if (degenerate && !fix_hi) {
+        r.have_prev = 0;
+        r.was_cold = 0;
+        r.mode = kCold;
+        return;
     }
-    desc[row] = r;
+    if (degenerate) r.have_prev = 0;           // the band of a random-k draw is known without a prediction
+    r.was_cold = 1;
+    predict_band(r, fix_lo, fix_hi);
+    r.mode = kWarm;
 }
 
 // One block on its own, histograms in LDS.
 template <bool VEC, bool RK>
-__device__ void slow_single(SlowLds& s, const float* __restrict__ g, uint32_t d, uint32_t row, RowDesc* __restrict__ desc,
-                            uint32_t k, RkDraw rk, uint32_t k0, uint32_t k1) {
+__device__ __forceinline__ SlowFound slow_single(SlowLds& s, const float* __restrict__ g, uint32_t d, uint32_t k, uint32_t k0, uint32_t k1) {
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t prefix = 0, rank = k, ties = 0;
+    uint32_t prefix = 0, rank = k, ties = 0, first = 0;
     if (tid == 0) s.bad = 0;
     for (int pass = 0; pass < 3; ++pass) {
         const int shift = digit_shift(pass), nbins = 1 << digit_bits(pass);
@@ -920,6 +941,7 @@ __device__ void slow_single(SlowLds& s, const float* __restrict__ g, uint32_t d,
         prefix |= p.bin << shift;
         rank = p.rank_in;
         ties = p.count;
+        if (pass == 0) first = p.count;
     }
     // the rank-th entry with key == prefix, in index order
     if (tid == 0) s.cut = 0xffffffffu;
@@ -958,60 +980,77 @@ __device__ void slow_single(SlowLds& s, const float* __restrict__ g, uint32_t d,
         if (seen >= rank) break;
     }
     __syncthreads();
-    if (tid == 0) slow_write_result(desc, row, prefix, rank, ties, s.cut, s.bad, RK, rk);
+    return SlowFound{prefix, rank, ties, s.cut, s.bad, first};
 }
 
-// Meeting point of the B blocks of a row: true when all have arrived `target / B` times, false when the
+// Meeting point of blocks that share a row: true when `target` arrivals have been counted, false when the
 // wait ran out or another block has given up (the row is then flagged).  Every thread calls it.
-__device__ __forceinline__ bool slow_meet(SlowLds& s, uint32_t* __restrict__ sync, uint32_t target, uint32_t spin_limit) {
-    __threadfence();                           // my stores and atomics are out before my block arrives
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicAdd(&sync[0], 1u);                // sync[0]: arrivals, sync[1]: some block has given up
-        uint32_t ok = 0;
-        for (uint32_t spin = 0; spin < spin_limit; ++spin) {
-            if (__hip_atomic_load(&sync[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (__hip_atomic_load(&sync[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) {
-                ok = 1;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(16);
-        }
-        if (!ok) atomicExch(&sync[1], 1u);
-        s.ok = ok;
-    }
-    __syncthreads();
-    __threadfence();                           // what the other blocks wrote before arriving is visible from here on
-    return s.ok != 0;
-}
-
-// Arrival without a wait: my stores are out, then the counter says so.  Every thread calls it.
+// No fence: what the blocks hand to one another goes past their L2s (st_shared, ld_shared, atomics), and every wave waits
+// for its own stores.  With a device-wide fence (an L2 written back and its stale lines dropped) in every one
+// of the blocks' 16 waves a meeting took 0.1 ms: a general search of 8 x 262144 columns, 5 meetings, 580 us; with one fence a
+// block 55.
 __device__ __forceinline__ void slow_arrive(uint32_t* __restrict__ sync) {
-    __threadfence();
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(&sync[0], 1u);
 }
+__device__ __forceinline__ bool slow_meet(uint32_t& ok_lds, uint32_t* __restrict__ sync, uint32_t target, uint32_t spin_limit) {
+    slow_arrive(sync);
+    if (threadIdx.x == 0) {
+        uint32_t ok = 0;
+        for (uint32_t spin = 0; spin < spin_limit; ++spin) {
+            if (ld_shared(&sync[1])) break;
+            if (ld_shared(&sync[0]) >= target) {
+                ok = 1;
+                break;
+            }
+            if (spin < 64) __builtin_amdgcn_s_sleep(1);
+            else __builtin_amdgcn_s_sleep(16);
+        }
+        if (!ok) atomicExch(&sync[1], 1u);
+        ok_lds = ok;
+    }
+    __syncthreads();
+    return ok_lds != 0;
+}
 
-// The B blocks of a row together.  Only block 0 ever writes the row's descriptor, and only its return
-// value matters: false when one of its waits ran out (the descriptor is untouched then, and the caller
-// repeats the search on block 0 alone), true when it has written the result.  A block other than 0 whose
+// The B blocks of a row together.  Only block 0's return value matters: kGaveUp when one of its waits ran out (the
+// caller then repeats the search on block 0 alone), kFound when `found` is the result.  A block other than 0 whose
 // wait runs out just leaves (block 0 then fails its next wait, because the give-up flag is set or the
-// arrivals never add up).
+// arrivals never add up).  groups: the row's candidate bitmap (top-k, in the form that k_filter writes), for which the
+// blocks flag the groups that hold a key of at least tau while they count the ties; valid when block 0 returns kFound.
+// kListed (to every block): at most list_cap entries share the first digit found.tau that holds rank k, as number
+// found.rank of its found.first, and the caller goes on with a list of those.
+// The histograms are zero before and after; when waits have run out, sync[2] says that they may not be, and the next
+// search starts by clearing them.
+__device__ __forceinline__ void clear_slow_hist(uint32_t* __restrict__ ghist, uint32_t* __restrict__ sync) {    // block 0, the others are done
+    for (uint32_t q = threadIdx.x; q < kSlowHistWords; q += 1024) ghist[q] = 0;
+    if (threadIdx.x == 0) sync[2] = 0;
+}
+enum SlowEnd : int { kGaveUp = 0, kFound = 1, kListed = 2 };
 template <bool VEC, bool RK>
-__device__ bool slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, uint32_t nwt, uint32_t row,
-                           RowDesc* __restrict__ desc, uint32_t k, RkDraw rk, uint32_t k0, uint32_t k1,
-                           uint32_t* __restrict__ ghist, uint32_t* __restrict__ gcnt, uint32_t* __restrict__ sync,
-                           uint32_t spin_limit) {
+__device__ __forceinline__ SlowEnd slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, uint32_t nwt, uint32_t k, uint32_t k0, uint32_t k1,
+                              uint32_t* __restrict__ ghist, uint32_t* __restrict__ gcnt, uint32_t* __restrict__ sync,
+                              uint32_t spin_limit, uint64_t* __restrict__ groups, bool coarse, uint32_t list_cap, uint32_t& meetings,
+                              SlowFound& found) {
     const uint32_t B = gridDim.x, b = blockIdx.x;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t tpb = (nwt + B - 1) / B;                     // wave tiles per block: a contiguous range of the row
     const uint32_t t0 = min(b * tpb, nwt), t1 = min(t0 + tpb, nwt);
-    uint32_t meetings = 0;
+    meetings = 0;
+    if (tid == 0) {
+        s.bad = 0;
+        s.dirty = ld_shared(&sync[2]);
+    }
+    __syncthreads();
     // whatever an earlier, abandoned search left in the global histograms goes first
-    for (uint32_t q = b * 1024 + tid; q < kSlowHistWords; q += B * 1024) ghist[q] = 0;
-    if (tid == 0) s.bad = 0;
-    if (!slow_meet(s, sync, B * ++meetings, spin_limit)) return false;
-    uint32_t prefix = 0, rank = k, ties = 0, off = 0;
+    if (s.dirty) {                                              // uniform for the block
+        for (uint32_t q = b * 1024 + tid; q < kSlowHistWords; q += B * 1024) st_shared(&ghist[q], 0u);
+        if (!slow_meet(s.ok, sync, B * ++meetings, spin_limit)) return kGaveUp;
+    }
+    uint32_t prefix = 0, rank = k, ties = 0, off = 0, first = 0;
 #pragma unroll 1
     for (int pass = 0; pass < 3; ++pass) {
         const int shift = digit_shift(pass), nbins = 1 << digit_bits(pass);
@@ -1019,15 +1058,16 @@ __device__ bool slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, 
         for (int q = tid; q < nbins; q += 1024) s.h[q] = 0;
         __syncthreads();
         for (uint32_t t = t0 + wave; t < t1; t += 16) {
+            uint32_t key[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) slow_keys_at<VEC, RK>(g, d, k0, k1, t * kWaveTile + u * kChunk + lane * 4, key[u]);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
-                uint32_t key[4];
-                slow_keys_at<VEC, RK>(g, d, k0, k1, j, key);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const bool valid = j + q < d && ((key[q] ^ prefix) >> hi_shift) == 0;
-                    const uint32_t bin = (key[q] >> shift) & (uint32_t)(nbins - 1);
+                    const bool valid = j + q < d && ((key[u][q] ^ prefix) >> hi_shift) == 0;
+                    const uint32_t bin = (key[u][q] >> shift) & (uint32_t)(nbins - 1);
                     wave_count(s.h, valid, bin, lane);
                 }
             }
@@ -1037,30 +1077,54 @@ __device__ bool slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, 
             const uint32_t c = s.h[q];
             if (c) atomicAdd(&ghist[off + q], c);
         }
-        if (!slow_meet(s, sync, B * ++meetings, spin_limit)) return false;
+        if (!slow_meet(s.ok, sync, B * ++meetings, spin_limit)) return kGaveUp;
+        for (int q = tid; q < nbins; q += 1024) s.h[q] = ld_shared(&ghist[off + q]);
+        __syncthreads();
         if (pass == 0 && !RK) {                       // keys >= 0x7f800000 (Inf/NaN) sit in the bins from 0xff0 up
-            if (tid < 16 && ghist[0xff0 + tid] != 0) s.bad = 1;
+            if (tid < 16 && s.h[0xff0 + tid] != 0) s.bad = 1;
         }
-        const Pick p = block_pick(ghist + off, nbins, rank, s.part, s.res);
+        const Pick p = block_pick(s.h, nbins, rank, s.part, s.res);
         prefix |= p.bin << shift;
         rank = p.rank_in;
         ties = p.count;
+        if (pass == 0) {
+            first = p.count;
+            if (first <= list_cap) {                            // uniform for the row
+                found = SlowFound{p.bin, rank, 0u, 0u, s.bad, first};
+                return kListed;
+            }
+        }
         off += nbins;
     }
     // ties inside my range; block 0 then walks the range that holds the rank-th tie in index order
     uint32_t mine = 0;
     for (uint32_t t = t0 + wave; t < t1; t += 16) {
+        uint64_t line_word = 0, fine = 0;                       // lane u holds fine word u
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
             uint32_t key[4];
             slow_keys_at<VEC, RK>(g, d, k0, k1, j, key);
+            bool any = false;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) mine += (j + q < d && key[q] == prefix) ? 1u : 0u;
+            for (int q = 0; q < 4; ++q) {
+                mine += (j + q < d && key[q] == prefix) ? 1u : 0u;
+                any |= j + q < d && key[q] >= prefix;
+            }
+            const uint64_t flags = __ballot(any);
+            line_word |= any_of_four_lanes(flags) << u;
+            fine = lane == (uint32_t)u ? flags : fine;
+        }
+        if (!RK && groups) {
+            if (coarse) {
+                if (lane == 0) groups[t] = line_word;
+            } else if (lane < 4) {
+                groups[(size_t)t * 4 + lane] = fine;
+            }
         }
     }
     const uint32_t total = block_sum_u32(mine, s.wtot);         // valid on thread 0
-    if (tid == 0) gcnt[b] = total;
+    if (tid == 0) st_shared(&gcnt[b], total);
     // Last meeting.  From here on block 0 alone speaks for the row: the other blocks publish their count,
     // arrive and leave without waiting, so no block can pass this meeting while the one that would have
     // written the result gives up.  Block 0 either sees every count and walks the range that holds the
@@ -1068,19 +1132,22 @@ __device__ bool slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, 
     ++meetings;
     if (b != 0) {
         slow_arrive(sync);
-        return true;
+        return kFound;
     }
-    if (!slow_meet(s, sync, B * meetings, spin_limit)) return false;
+    if (!slow_meet(s.ok, sync, B * meetings, spin_limit)) return kGaveUp;
+    clear_slow_hist(ghist, sync);
+    if (tid < (uint32_t)kSlowMaxBlocks) s.part[tid] = tid < B ? ld_shared(&gcnt[tid]) : 0u;
+    __syncthreads();
     uint32_t before = 0, owner = B;
     for (uint32_t q = 0; q < B; ++q) {                          // uniform for the block
-        const uint32_t here = gcnt[q];
+        const uint32_t here = s.part[q];
         if (before < rank && rank <= before + here) {
             owner = q;
             break;
         }
         before += here;
     }
-    if (owner == B) return false;                               // counts that do not add up to the histogram: search alone
+    if (owner == B) return kGaveUp;                             // counts that do not add up to the histogram: search alone
     const uint32_t need = rank - before;
     const uint32_t w0 = min(owner * tpb, nwt), w1 = min(w0 + tpb, nwt);   // the owner's range of wave tiles
     if (tid == 0) s.cut = 0xffffffffu;
@@ -1138,66 +1205,75 @@ __device__ bool slow_multi(SlowLds& s, const float* __restrict__ g, uint32_t d, 
         if (seen >= need) break;
     }
     __syncthreads();
-    if (tid == 0) slow_write_result(desc, row, prefix, rank, ties, s.cut, s.bad, RK, rk);
-    return true;
+    found = SlowFound{prefix, rank, ties, s.cut, s.bad, first};
+    return kFound;
 }
 
-template <bool VEC, bool RK>
+// Scratch of the kernels whose blocks share rows: slot y for the y-th row of a launch with B > 1 blocks a row.
+struct SharedRows {
+    uint32_t* hist;                            // [rows * kSlowHistWords] digit histograms of a general search
+    uint32_t* cnt;                             // [rows * kSlowMaxBlocks] ties per block
+    uint32_t* list_hist;                       // [rows * B * 256] first list digit per block
+    uint32_t* sync;                            // [rows * kSyncWords]; arrivals and give-up flag zero when a step starts (see the update)
+    uint32_t spin_limit;                       // bound, in polls, of the waits
+};
+
+// The top-k rows in kSlow mode (long rows; k_select does it for short ones).
+template <bool VEC>
 __global__ __launch_bounds__(1024) void k_slow_select(const float* __restrict__ src, size_t row_stride, uint32_t d,
                                                        uint32_t nwt, uint32_t row0, RowDesc* __restrict__ desc, uint32_t k,
-                                                       RkDraw rk, uint32_t* __restrict__ slow_hist,
-                                                       uint32_t* __restrict__ slow_cnt, uint32_t* __restrict__ slow_sync,
-                                                       uint32_t spin_limit) {
+                                                       uint64_t* __restrict__ gbits, bool coarse, SharedRows sh) {
     __shared__ SlowLds s;
     const uint32_t row = row0 + blockIdx.y;
     if (desc[row].mode != kSlow) return;
     const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
-    uint32_t k0 = 0, k1 = 0;
-    if (RK) {
-        const uint64_t stream = rk_stream(rk.state->seed, rk.state->draw, row);
-        k0 = (uint32_t)stream;
-        k1 = (uint32_t)(stream >> 32);
+    SlowFound f;
+    SlowEnd end = kGaveUp;
+    if (gridDim.x > 1) {
+        uint32_t* const sync = sh.sync + (size_t)blockIdx.y * kSyncWords;
+        uint32_t meetings;
+        end = slow_multi<VEC, false>(s, g, d, nwt, k, 0u, 0u, sh.hist + (size_t)blockIdx.y * kSlowHistWords,
+                                     sh.cnt + (size_t)blockIdx.y * kSlowMaxBlocks, sync, sh.spin_limit,
+                                     gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4), coarse, 0u, meetings, f);
+        if (blockIdx.x != 0) return;
+        if (end == kGaveUp && threadIdx.x == 0) sync[2] = 1;
     }
-    if (gridDim.x == 1) {
-        slow_single<VEC, RK>(s, g, d, row, desc, k, rk, k0, k1);
-        return;
+    const bool bitmap = end == kFound;
+    if (!bitmap) f = slow_single<VEC, false>(s, g, d, k, 0u, 0u);
+    if (threadIdx.x == 0) {
+        s.now = desc[row];
+        s.now.nonfinite_acc |= f.bad;
+        finish_general(s.now, f, true, bitmap ? (coarse ? 2u : 1u) : 0u, 0u, 0u);
     }
-    const bool done = slow_multi<VEC, RK>(s, g, d, nwt, row, desc, k, rk, k0, k1,
-                                          slow_hist + (size_t)blockIdx.y * kSlowHistWords,
-                                          slow_cnt + (size_t)blockIdx.y * kSlowMaxBlocks,
-                                          slow_sync + (size_t)blockIdx.y * 2, spin_limit);
-    if (!done && blockIdx.x == 0) slow_single<VEC, RK>(s, g, d, row, desc, k, rk, k0, k1);
+    put_result(desc + row, s.now);
 }
 
-// Random-k: completes the kept bitmap of each row once (tau, cut-off) are known.  k_filter has set the
+// Random-k: completes the kept bitmap of a row once (tau, cut-off) are known.  k_filter has set the
 // bits of the columns whose key is above the band; here the listed candidates that are kept get
-// theirs (atomic OR on the 32-bit word holding the lane's half-word).  Rows that went through the
-// slow search have no valid list: every block recomputes the priorities of its tiles and writes
-// whole half-words.  grid = (blocks, rows).
-__global__ __launch_bounds__(kBlock) void k_rk_mark(uint32_t d, uint32_t nwt, uint32_t row0, const RowDesc* __restrict__ desc,
-                                                     const uint2* __restrict__ list, uint32_t cap,
-                                                     uint16_t* __restrict__ kbits, RkDraw rk) {
-    const uint32_t row = row0 + blockIdx.y;
-    const uint32_t tau = desc[row].tau, cut = desc[row].cutoff;
-    if (!desc[row].dense) {
-        const uint32_t n = desc[row].n_list;
-        const uint2* __restrict__ in = list + (size_t)row * cap;
-        uint32_t* __restrict__ words = reinterpret_cast<uint32_t*>(kbits + (size_t)row * nwt * 64);
-        for (uint32_t e = blockIdx.x * kBlock + threadIdx.x; e < n; e += gridDim.x * kBlock) {
-            const uint2 kv = in[e];
-            if (kv.x > tau || (kv.x == tau && kv.y <= cut)) {
-                const uint32_t t = kv.y / kWaveTile, o = kv.y % kWaveTile;
+// theirs (atomic OR on the 32-bit word holding the lane's half-word).
+__device__ __forceinline__ void mark_listed(const uint2* __restrict__ in, uint32_t n, uint32_t tau, uint32_t cut,
+                                            uint32_t* __restrict__ words) {
+    for (uint32_t base = threadIdx.x; base < n; base += 4 * kSelectBlock) {
+        uint2 kv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) kv[i] = base + i * kSelectBlock < n ? in[base + i * kSelectBlock] : make_uint2(0u, 0u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (base + i * kSelectBlock < n && (kv[i].x > tau || (kv[i].x == tau && kv[i].y <= cut))) {
+                const uint32_t t = kv[i].y / kWaveTile, o = kv[i].y % kWaveTile;
                 const uint32_t u = o / kChunk, l = (o % kChunk) / 4, q = o % 4;
                 const uint32_t half = t * 64 + l;                     // half-word of the row holding the column
                 atomicOr(&words[half >> 1], 1u << ((half & 1) * 16 + 4 * u + q));
             }
         }
-        return;
     }
-    const uint64_t stream = rk_stream(rk.state->seed, rk.state->draw, row);
-    const uint32_t k0 = (uint32_t)stream, k1 = (uint32_t)(stream >> 32);
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
+}
+// A row that went through the general search has no valid list: its priorities are
+// computed again and whole half-words written.
+__device__ __forceinline__ void mark_row(uint64_t stream, uint32_t d, uint32_t nwt, uint32_t tau, uint32_t cut,
+                                         uint16_t* __restrict__ row_bits) {
+    const uint32_t k0 = (uint32_t)stream, k1 = (uint32_t)(stream >> 32), lane = threadIdx.x & 63;
+    for (uint32_t t = threadIdx.x >> 6; t < nwt; t += kSelectBlock / 64) {
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -1207,11 +1283,208 @@ __global__ __launch_bounds__(kBlock) void k_rk_mark(uint32_t d, uint32_t nwt, ui
                 const uint32_t key = rk_priority(k0, k1, j);
                 m |= ((j < d && (key > tau || (key == tau && j <= cut))) ? 1u : 0u) << (4 * u + q);
             }
-        kbits[((size_t)row * nwt + t) * 64 + lane] = (uint16_t)m;
+        row_bits[(size_t)t * 64 + lane] = (uint16_t)m;
     }
 }
 
-// One thread, after the last kernel of a step that used the draw.
-__global__ void k_rk_advance(RkState* __restrict__ state) { state->draw += 1; }
+// ---------------------------------------------------------------------------------------------
+// Everything that follows the pass over the predicted band, in one launch, for rows on which what a launch costs (2 us)
+// counts: five launches of a steady-state step become one.  grid = (B, rows), kSelectBlock threads.
+// Block 0 finishes a row whose list holds rank k and is short; up to B blocks share a longer list's first digit (each
+// leaves a histogram of its share, all add them up, and the entries of the digit's bin go to the row's short list); all B
+// share the search of a row without a usable list: the first digit of the whole row, then a list of the entries of
+// the bin that holds rank k, or, when those are too many, the rest of the general search.  Which of the three it is every
+// block decides by itself from the mode and the counters of the
+// first pass, which this kernel leaves as they are: block 0 may have finished the row before another block starts.
+// ---------------------------------------------------------------------------------------------
+struct CollectLds {                            // the second pass of a row without a usable prediction
+    uint2 stage[kStage], wstage[kSelectBlock / 64][kWaveStage];
+    uint32_t wsure[kSelectBlock / 64 + 1], staged[2];
+};
+// Lists the entries of keys [lo, lo + 2^19) of this block's share of the row, for block 0, and leaves their group bitmap
+// or, random-k, the bits of the keys above the band.
+template <bool VEC, bool RK>
+__device__ __forceinline__ void collect_bin(CollectLds& s, const float* __restrict__ g, uint32_t d, uint32_t nwt, uint32_t lo,
+                                            uint2* out, uint32_t cap, unsigned long long* counts, uint64_t* __restrict__ groups,
+                                            bool coarse, uint16_t* row_bits, uint64_t stream) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, B = gridDim.x;
+    const uint32_t tpb = (nwt + B - 1) / B, t0 = min(blockIdx.x * tpb, nwt), t1 = min(t0 + tpb, nwt);
+    FilterBand fb;
+    fb.lo = lo;
+    fb.hi = lo + (1u << 19);                                    // 0x80000000 for the top bin: no key reaches it
+    fb.out = out;
+    fb.cap = cap;
+    fb.counts = counts;
+    __syncthreads();                                            // what shared this memory is done
+    if (tid < 2) s.staged[tid] = 0;
+    __syncthreads();
+    uint32_t n_hi = 0, kmax = 0, wcnt = 0;
+    for (uint32_t t = t0 + wave; t < t1; t += kSelectBlock / 64) {
+        uint32_t key[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            slow_keys_at<VEC, RK>(g, d, (uint32_t)stream, (uint32_t)(stream >> 32), t * kWaveTile + u * kChunk + lane * 4, key[u]);
+        uint64_t line_word = 0, fine = 0;
+        uint32_t sure16 = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
+            uint64_t bc[4];
+            uint32_t hi4;
+            const uint64_t flags = filter_chunk<false, RK>(key[u], j, d, fb.lo, fb.hi, bc, n_hi, kmax, hi4);
+            sure16 |= hi4 << (4 * u);
+            line_word |= any_of_four_lanes(flags) << u;
+            fine = lane == (uint32_t)u ? flags : fine;
+            stage_candidates<true>(fb, key[u], j, bc, s.stage, s.wstage[wave], wcnt, s.staged, lane);
+        }
+        if (RK) {
+            st_shared(&row_bits[(size_t)t * 64 + lane], (uint16_t)sure16);      // block 0 adds the kept ones with atomics
+        } else if (coarse) {
+            if (lane == 0) groups[t] = line_word;
+        } else if (lane < 4) {
+            groups[(size_t)t * 4 + lane] = fine;
+        }
+    }
+    finish_filter_block<kSelectBlock / 64, true>(fb, s.stage, s.wstage[wave], wcnt, 0u, s.staged, s.wsure);
+}
+
+template <bool VEC, bool RK>
+__global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict__ src, size_t row_stride, uint32_t d, uint32_t nwt,
+                                                          uint32_t row0, RowDesc* __restrict__ desc, uint2* __restrict__ list,
+                                                          uint32_t cap, uint2* __restrict__ shortl, uint32_t k, RkDraw rk,
+                                                          uint64_t* __restrict__ gbits, uint16_t* __restrict__ kbits, bool coarse,
+                                                          SharedRows sh) {
+    __shared__ union {
+        ListLds list;
+        SlowLds slow;
+        CollectLds collect;
+    } s;
+    __shared__ RowDesc now;
+    __shared__ uint32_t met;
+    const uint32_t row = row0 + blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const bool srv = RK && row == rk.srv_row;
+    if (srv) k = rk.srv_k;
+    const uint32_t fix_lo = srv ? rk.srv_lo : rk.fix_lo, fix_hi = srv ? rk.srv_hi : rk.fix_hi;
+    fetch_desc(now, desc + row);
+    __syncthreads();
+    const uint32_t form = RK ? 0u : coarse ? 2u : 1u;
+    uint16_t* const row_bits = RK ? kbits + (size_t)row * nwt * 64 : nullptr;
+    uint32_t* const words = reinterpret_cast<uint32_t*>(row_bits);
+    uint2* const row_list = list + (size_t)row * cap;
+    uint32_t* const sync = sh.sync + (size_t)blockIdx.y * kSyncWords;
+    const bool cold = now.mode != kWarm || !band_ok(now, cap, k);       // uniform for the row
+    // a row on its predicted band: its list
+    uint32_t lo = now.lo, width = now.hi - lo, n = now.n_cand, rank = k - sure_count(now);
+    if (cold) {
+        const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
+        uint64_t* const groups = gbits ? gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4) : nullptr;
+        const uint64_t stream = RK ? rk_stream(rk.state->seed, rk.state->draw, row) : 0ull;
+        SlowFound f{0, 0, 0, 0, 0, 0};
+        SlowEnd end = kGaveUp;
+        if (gridDim.x > 1) {
+            uint32_t* const hist = sh.hist + (size_t)blockIdx.y * kSlowHistWords;
+            uint32_t meetings;
+            // (a caller can send a row through the whole of the general search)
+            end = slow_multi<VEC, RK>(s.slow, g, d, nwt, k, (uint32_t)stream, (uint32_t)(stream >> 32), hist,
+                                      sh.cnt + (size_t)blockIdx.y * kSlowMaxBlocks, sync, sh.spin_limit, groups, coarse,
+                                      now.mode == kSlow ? 0u : cap, meetings, f);
+            if (end == kListed) {                               // every block of the row
+                collect_bin<VEC, RK>(s.collect, g, d, nwt, f.tau << 19, row_list, cap,
+                                     reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, row_bits, stream);
+                if (blockIdx.x != 0) {
+                    slow_arrive(sync);
+                    return;
+                }
+                if (slow_meet(met, sync, gridDim.x * (meetings + 1), sh.spin_limit)) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // the list is read with plain loads
+                    clear_slow_hist(hist, sync);
+                } else {
+                    end = kGaveUp;
+                }
+            }
+            if (blockIdx.x != 0) return;
+            if (end == kGaveUp && tid == 0) sync[2] = 1;
+        }
+        if (end == kGaveUp) f = slow_single<VEC, RK>(s.slow, g, d, k, (uint32_t)stream, (uint32_t)(stream >> 32));
+        if (tid == 0) {
+            now.misses += now.mode == kWarm ? 1u : 0u;          // there was a prediction and it failed
+            now.nonfinite_acc |= f.bad;
+        }
+        if (end != kListed) {
+            const bool bitmap = end == kFound && groups;
+            if (tid == 0) finish_general(now, f, now.mode == kSlow || f.first > cap, bitmap ? form : 0u, fix_lo, fix_hi);
+            put_result(desc + row, now);
+            if (RK) mark_row(stream, d, nwt, f.tau, f.cut, row_bits);
+            return;
+        }
+        lo = f.tau << 19;
+        width = 1u << 19;
+        n = f.first;
+        rank = f.rank;
+    }
+    const uint2* in = row_list;
+    uint32_t n_in = n;
+    const uint32_t nb = !cold && n > (uint32_t)kDirectList ? list_blocks_for(n, gridDim.x) : 1u;
+    if (blockIdx.x >= nb) return;
+    bool first = true;
+    Pick ph{0, 0, 0};
+    const int shift = first_shift(width, kFirstBits);
+    if (nb > 1) {
+        uint32_t* const h = s.list.h;
+        uint32_t* const hists = sh.list_hist + (size_t)blockIdx.y * gridDim.x * 256;
+        if (tid < 256) h[tid] = 0;
+        __syncthreads();
+        for (uint32_t base = blockIdx.x * kSelectBlock; base < n; base += nb * kSelectBlock) {    // uniform for the block
+            const uint32_t e = base + tid;
+            wave_count(h, e < n, ((e < n ? row_list[e].x : lo) - lo) >> shift, lane);
+        }
+        __syncthreads();
+        if (tid < 256) st_shared(&hists[blockIdx.x * 256 + tid], h[tid]);
+        const bool ok = slow_meet(met, sync, nb, sh.spin_limit);
+        if (!ok && blockIdx.x != 0) return;
+        if (ok) {
+            uint32_t sum = 0;
+            for (uint32_t b = tid >> 8; b < nb; b += kSelectBlock / 256) sum += ld_shared(&hists[b * 256 + (tid & 255)]);
+            if (tid < 256) h[tid] = 0;
+            __syncthreads();
+            if (sum) atomicAdd(&h[tid & 255], sum);
+            __syncthreads();
+            ph = block_pick(h, 256, rank, s.list.part, s.list.res);
+            if (ph.count > (uint32_t)kShortCap) {               // too many for the short list: block 0 walks the list
+                if (blockIdx.x != 0) return;
+                first = false;
+            } else {
+                uint2* const out = shortl + (size_t)row * kShortCap;
+                for (uint32_t base = blockIdx.x * kSelectBlock; base < n; base += nb * kSelectBlock) {
+                    const uint32_t e = base + tid;
+                    const uint2 kv = e < n ? row_list[e] : make_uint2(0u, 0u);
+                    const bool hit = e < n && ((kv.x - lo) >> shift) == ph.bin;
+                    const uint64_t m = __ballot(hit);
+                    if (m) {                                    // wave-uniform
+                        uint32_t at = 0;
+                        if (lane == 0) at = atomicAdd(&desc[row].n_short, (uint32_t)__popcll(m));
+                        at = __builtin_amdgcn_readfirstlane(at);
+                        if (hit) put_entry<true>(&out[at + lanes_below(m)], kv);      // the bin's count bounds the total: at most kShortCap
+                    }
+                }
+                if (blockIdx.x != 0) {
+                    slow_arrive(sync);
+                    return;
+                }
+                if (slow_meet(met, sync, 2 * nb, sh.spin_limit)) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    first = false;
+                    in = out;
+                    n_in = ph.count;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    select_listed(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
+    if (tid == 0) finish_listed(now, s.list, n, form, cold, 0u, fix_lo, fix_hi);
+    put_result(desc + row, now);
+    if (RK) mark_listed(row_list, n, s.list.tau, s.list.cut, words);
+}
 
 }  // namespace liec

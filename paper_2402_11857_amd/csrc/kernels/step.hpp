@@ -586,6 +586,27 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     }
 }
 
+// What the last kernel of a step with a threshold search leaves behind it: the rows' counters and the meeting points of
+// the blocks that share rows are zero, and the next compressed iteration makes the next draw.  None of its other blocks
+// looks at any of these.  (The grid has at least one thread a row.)
+struct StepTail {
+    uint32_t* counters;         // second line of the first row's descriptor
+    uint32_t* sync;             // [nsync]
+    uint64_t* draw;             // random-k on a side, else null
+    uint32_t rows, nsync;
+};
+__device__ __forceinline__ void end_searches(const StepTail& t) {
+    const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
+    if (blockIdx.x * kBlock >= max(t.rows, t.nsync)) return;    // uniform for the block
+    if (q < t.rows) {
+        uint2* const c = reinterpret_cast<uint2*>(t.counters + (size_t)q * (sizeof(RowDesc) / 4));
+        c[0] = c[1] = c[2] = make_uint2(0u, 0u);
+    }
+    if (q < t.nsync && (q & (kSyncWords - 1)) < 2) t.sync[q] = 0;      // (the third word is the searches' own)
+    if (q == 0 && t.draw) *t.draw += 1;
+}
+static_assert(offsetof(RowDesc, n_cand) == 128 && offsetof(RowDesc, nonfinite_acc) == 148, "the six counters of the second line");
+
 // ---------------------------------------------------------------------------------------------
 // Server compression + error update + broadcast + local immediate compensation (Algorithm 1):
 //   p_j = C_s(v)_j ; e_j <- v_j - p_j ; x_ij <- x_ij - lr * (p_j + (g_ij - p^i_j)).
@@ -602,8 +623,9 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
                                                     RowDesc* __restrict__ desc, BlockTable bt,
                                                     const uint16_t* __restrict__ kbits, const uint16_t* __restrict__ vbits,
                                                     const uint64_t* __restrict__ sgbits, const uint64_t* __restrict__ vodd,
-                                                    const double* __restrict__ s_partial, uint32_t s_parts) {
+                                                    const double* __restrict__ s_partial, uint32_t s_parts, StepTail tail) {
     __shared__ float folded;
+    if (WC == kTopk || WC == kRandk || SC == kTopk || SC == kRandk) end_searches(tail);
     if (FOLD) {                                                 // before any thread leaves
         if (threadIdx.x < 64) {
             const double s = wave_l1(s_partial, s_parts, threadIdx.x);

@@ -20,7 +20,7 @@ using namespace liec;
 namespace {
 
 // Kernel slots for per-kernel timing: worker side, aggregation, server side, update.
-constexpr int kSelSlots = 6;
+constexpr int kSelSlots = 5;
 enum Slot : int {
     S_W_L1 = 0, S_W_L1_FINAL,
     S_W_SEL,                       // kSelSlots slots of the worker-side top-k / random-k search
@@ -32,10 +32,10 @@ enum Slot : int {
     S_COUNT
 };
 
-const char* const kWorkerSel[kSelSlots] = {"worker_filter_warm", "worker_hist0", "worker_filter_cold", "worker_list_select",
-                                           "worker_slow_select", "worker_randk_mark"};
-const char* const kServerSel[kSelSlots] = {"server_filter_warm", "server_hist0", "server_filter_cold", "server_list_select",
-                                           "server_slow_select", "server_randk_mark"};
+const char* const kWorkerSel[kSelSlots] = {"worker_filter_warm", "worker_hist0", "worker_filter_cold", "worker_select",
+                                           "worker_slow_select"};
+const char* const kServerSel[kSelSlots] = {"server_filter_warm", "server_hist0", "server_filter_cold", "server_select",
+                                           "server_slow_select"};
 
 const char* slot_name(int s) {
     if (s == S_W_L1) return "worker_l1_bits";
@@ -160,7 +160,14 @@ struct liec_ctx {
     uint32_t slow_spin = 1u << 16;             // bound, in polls, of the waits between those blocks
     uint32_t* slow_hist = nullptr;             // [rows that share * kSlowHistWords] digit histograms
     uint32_t* slow_cnt = nullptr;              // [rows that share * kSlowMaxBlocks] ties per block
-    uint32_t* slow_sync = nullptr;             // [rows that share * 2] arrivals, give-up flag
+    uint32_t* slow_sync = nullptr;             // [rows that share * kSyncWords] arrivals, give-up flag, histograms not zero
+    uint32_t* list_hist = nullptr;             // [blocks that share * 256] first digit of a block's share of a list
+    uint32_t slow_slots = 0;                   // rows that share
+    bool w_one = false, s_one = false;         // the search behind the first pass is one launch (short rows), by side
+    // random-k on both sides, same form of the draw: one set of launches makes the workers' draws and the server's
+    bool joint_draw() const {
+        return worker_comp == kRandk && server_comp == kRandk && rk_winv == rk_sinv && N < 65535;
+    }
     int64_t scratch_bytes = 0;
 
     // blockwise scaled sign (Definition 5): block table and its scratch, set by liec_set_blocks
@@ -258,6 +265,7 @@ void free_scratch(liec_ctx* c) {
     (void)hipFree(c->slow_hist);
     (void)hipFree(c->slow_cnt);
     (void)hipFree(c->slow_sync);
+    (void)hipFree(c->list_hist);
 }
 
 bool valid_comp(int c) {
@@ -303,69 +311,88 @@ struct Launcher {
     }
 };
 
+// Scratch of the blocks that share rows: the worker rows' slots come first, then the server's.
+SharedRows shared_rows(const liec_ctx* c, bool server_side) {
+    if ((server_side ? c->slow_bs : c->slow_bw) == 1) return SharedRows{nullptr, nullptr, nullptr, nullptr, c->slow_spin};
+    const size_t slot = server_side && c->slow_bw > 1 ? (size_t)c->N : 0;
+    return SharedRows{c->slow_hist + slot * kSlowHistWords, c->slow_cnt + slot * kSlowMaxBlocks, c->list_hist + slot * c->slow_bw * 256,
+                      c->slow_sync + slot * kSyncWords, c->slow_spin};
+}
+
+// The rest of the search in one launch, on short rows and for random-k.
+template <bool VEC, bool RK>
+void launch_one(Launcher& L, const float* src, size_t row_stride, uint32_t rows, uint32_t row0, uint32_t k, uint64_t* gbits,
+                bool coarse, int slot0, const RkDraw& rk) {
+    liec_ctx* c = L.c;
+    L.begin(slot0 + 3);
+    k_select<VEC, RK><<<dim3(row0 ? c->slow_bs : c->slow_bw, rows), kSelectBlock, 0, c->stream>>>(
+        src, row_stride, (uint32_t)c->d, c->nwt, row0, c->desc, c->list, c->cap, c->shortl, k, rk, gbits, c->bits, coarse,
+        shared_rows(c, row0 != 0));
+    L.end();
+}
+
 // Top-k threshold search (Definition 2) of `rows` rows of `src`; per-row state lives at row0 + r.
-// The host enqueues the same five kernels every step; each one acts only on the rows whose state
-// asks for it, so the steady state costs one pass over the data, two short passes over the candidate
+// One pass over the data against the predicted band, then, on short rows (`one`), a single launch that does whatever each
+// row still needs.  On long rows the host enqueues four more kernels, each of which acts only on the rows whose state
+// asks for it: the steady state costs one pass over the data, two short passes over the candidate
 // lists (in the launches that otherwise serve rows without a prediction) and one block per row of list
 // select; the general search returns at once.
-// RK: the same search over the priorities of a random-k draw (Definition 3), which read nothing from
-// `src`, followed by the kernel that completes the kept bitmap.
-template <bool VEC, bool RK>
-void launch_select(Launcher& L, const float* src, size_t row_stride, uint32_t rows, uint32_t row0, uint32_t k,
-                   uint64_t* gbits, bool coarse, uint32_t blocks, uint32_t cold_blocks, int slot0, RkDraw rk,
-                   bool rk_inverse = false, bool filtered = false) {
+// filtered: whoever wrote `src` has made the first pass.
+template <bool VEC>
+void launch_topk(Launcher& L, const float* src, size_t row_stride, uint32_t rows, uint32_t row0, uint32_t k,
+                 uint64_t* gbits, bool coarse, uint32_t blocks, uint32_t cold_blocks, int slot0, bool one, bool filtered = false) {
     liec_ctx* c = L.c;
     const uint32_t d = (uint32_t)c->d;
     hipStream_t st = c->stream;
-    const dim3 grid(blocks, rows), cold_grid(cold_blocks, rows);
-    // random-k with a thin band: clear the kept bitmap, then walk the priorities above the band
-    // few, long-lived blocks (every block ends with an atomic on the row's counters): one per 32768 words to invert, and
-    // up to four times as many when there are few rows (1 row of 25.6M columns 20 -> 16 us; 32 rows 111 -> 123)
-    const uint64_t inv_words = 2ull * (0x80000000ull - rk.fix_lo);
-    const uint64_t inv_blocks = std::max<uint64_t>(inv_words / 32768, std::min<uint64_t>(inv_words / 8192, 1024 / rows));
-    const dim3 inv_grid((uint32_t)std::min<uint64_t>(std::max<uint64_t>(inv_blocks, 128), 1024), rows);
-    const dim3 zero_grid(std::min<uint32_t>((c->nwt * 8 + kBlock - 1) / kBlock, 4096u), rows);
-    for (int pass = 0; pass < 2; ++pass) {
-        const bool cold_pass = pass == 1;
-        if (!cold_pass && filtered) continue;                   // whoever wrote `src` has made the first pass
-        if (cold_pass) {
-            L.begin(slot0 + 1);
-            k_hist0<VEC, RK><<<cold_grid, kBlock, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, c->ghist, c->list, c->cap, k, rk);
-            L.end();
-        }
-        L.begin(slot0 + (cold_pass ? 2 : 0));
-        if (RK && rk_inverse) {
-            // (the second pass is rare: a small grid, so that its blocks' returning at once costs little)
-            const dim3 zg(cold_pass ? std::min(zero_grid.x, 256u) : zero_grid.x, rows);
-            k_rk_zero<<<zg, kBlock, 0, st>>>(c->nwt, row0, c->desc, cold_pass, c->cap, k, c->bits);
-            k_rk_filter_inverse<<<inv_grid, kBlock, 0, st>>>(d, c->nwt, row0, c->desc, cold_pass, c->ghist, k, c->bits,
-                                                             c->list, c->cap, c->shortl, rk);
-        } else {
-            k_filter<VEC, RK><<<grid, kBlock, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, cold_pass, c->ghist, k,
-                                                        gbits, c->bits, c->list, c->cap, c->shortl, rk, coarse, c->filter_run);
-        }
+    auto filter = [&](int slot, bool cold_pass) {
+        L.begin(slot);
+        k_filter<VEC, false><<<dim3(blocks, rows), kBlock, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, cold_pass, c->ghist, k,
+                                                                     gbits, nullptr, c->list, c->cap, c->shortl, RkDraw{}, coarse,
+                                                                     c->filter_run);
         L.end();
+    };
+    if (!filtered) filter(slot0, false);
+    if (one) {
+        launch_one<VEC, false>(L, src, row_stride, rows, row0, k, gbits, coarse, slot0, RkDraw{});
+        return;
     }
-    // scratch of the general search: the worker rows' slots come first, then the server's
-    const bool server_side = row0 != 0;
-    const uint32_t slow_b = server_side ? c->slow_bs : c->slow_bw;
-    const size_t slow_slot = server_side && c->slow_bw > 1 ? (size_t)c->N : 0;
-    uint32_t* const shist = slow_b > 1 ? c->slow_hist + slow_slot * kSlowHistWords : nullptr;
-    uint32_t* const scnt = slow_b > 1 ? c->slow_cnt + slow_slot * kSlowMaxBlocks : nullptr;
-    uint32_t* const ssync = slow_b > 1 ? c->slow_sync + slow_slot * 2 : nullptr;
+    L.begin(slot0 + 1);
+    k_hist0<VEC><<<dim3(cold_blocks, rows), kBlock, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, c->ghist, c->list, c->cap, k);
+    L.end();
+    filter(slot0 + 2, true);
     L.begin(slot0 + 3);
-    k_list_select<<<rows, kSelectBlock, 0, st>>>(row0, c->desc, c->ghist, c->list, c->cap, c->shortl, k, d, rk.fix_lo, rk.fix_hi,
-                                                 RK ? 0u : coarse ? 2u : 1u, ssync);
+    k_list_select<<<rows, kSelectBlock, 0, st>>>(row0, c->desc, c->ghist, c->list, c->cap, c->shortl, k, d, coarse ? 2u : 1u);
     L.end();
     L.begin(slot0 + 4);
-    k_slow_select<VEC, RK><<<dim3(slow_b, rows), 1024, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, k, rk, shist, scnt,
-                                                                 ssync, c->slow_spin);
+    k_slow_select<VEC><<<dim3(row0 ? c->slow_bs : c->slow_bw, rows), 1024, 0, st>>>(src, row_stride, d, c->nwt, row0, c->desc, k, gbits,
+                                                                                     coarse, shared_rows(c, row0 != 0));
     L.end();
-    if (RK) {
-        L.begin(slot0 + 5);
-        k_rk_mark<<<dim3(cold_blocks, rows), kBlock, 0, st>>>(d, c->nwt, row0, c->desc, c->list, c->cap, c->bits, rk);
-        L.end();
+}
+
+// Random-k (Definition 3): the same search over the priorities of a draw, which read nothing from the gradients, with the
+// kept bitmap as its result.  The band misses the threshold in two draws of 10^6 for k = 1 and far fewer for larger k,
+// so what a row without a usable list costs does not count.
+void launch_randk(Launcher& L, uint32_t rows, uint32_t row0, uint32_t k, uint32_t blocks, int slot0, const RkDraw& rk, bool inverse) {
+    liec_ctx* c = L.c;
+    const uint32_t d = (uint32_t)c->d;
+    hipStream_t st = c->stream;
+    L.begin(slot0);
+    if (inverse) {
+        // a thin band: clear the kept bitmap, then walk the priorities above the band
+        // few, long-lived blocks (every block ends with an atomic on the row's counters): one per 32768 words to invert, and
+        // up to four times as many when there are few rows (1 row of 25.6M columns 20 -> 16 us; 32 rows 111 -> 123)
+        const uint64_t inv_words = 2ull * (0x80000000ull - rk.fix_lo);
+        const uint64_t inv_blocks = std::max<uint64_t>(inv_words / 32768, std::min<uint64_t>(inv_words / 8192, 1024 / rows));
+        const dim3 inv_grid((uint32_t)std::min<uint64_t>(std::max<uint64_t>(inv_blocks, 128), 1024), rows);
+        k_rk_zero<<<dim3(std::min<uint32_t>((c->nwt * 8 + kBlock - 1) / kBlock, 4096u), rows), kBlock, 0, st>>>(c->nwt, row0, c->desc,
+                                                                                                             c->bits);
+        k_rk_filter_inverse<<<inv_grid, kBlock, 0, st>>>(d, c->nwt, row0, c->desc, c->bits, c->list, c->cap, rk);
+    } else {
+        k_filter<true, true><<<dim3(blocks, rows), kBlock, 0, st>>>(nullptr, 0, d, c->nwt, row0, c->desc, false, nullptr, k, nullptr,
+                                                                     c->bits, c->list, c->cap, nullptr, rk, false, c->filter_run);
     }
+    L.end();
+    launch_one<true, true>(L, nullptr, 0, rows, row0, k, nullptr, false, slot0, rk);
 }
 
 // Blockwise scaled sign (Definition 5): per-block L1 norms of `rows` rows of `src` -> scales; for the
@@ -442,11 +469,14 @@ void launch_update(Launcher& L, const float* grads, float* x, float* e) {
     const uint32_t panel = c->ncol_tiles < kUpdatePanel ? c->ncol_tiles : kUpdatePanel;
     const uint32_t npanels = (c->ncol_tiles + panel - 1) / panel;
     const uint64_t blocks = (uint64_t)npanels * panel * (uint64_t)c->N;
+    const bool draws = c->worker_comp == kRandk || c->server_comp == kRandk;
+    const StepTail tail{reinterpret_cast<uint32_t*>(c->desc) + offsetof(RowDesc, n_cand) / 4, c->slow_sync, draws ? &c->rk_state->draw : nullptr,
+                        (uint32_t)c->N + 1, c->slow_slots * kSyncWords};
     L.begin(S_UPDATE);
     auto launch = [&](auto kernel) {
         kernel<<<(uint32_t)blocks, kBlock, 0, c->stream>>>(grads, x, c->vbuf, e, c->N, panel, c->ncol_tiles, (uint32_t)c->d,
                                                            -c->lr, c->desc, block_table(c), c->bits, c->vbits, c->sgbits, c->vodd,
-                                                           c->s_partial, c->agg_blocks());
+                                                           c->s_partial, c->agg_blocks(), tail);
     };
     if (SC == kSign && c->fold_server()) launch(k_update<WC, SC, VEC, SC == kSign>);
     else launch(k_update<WC, SC, VEC>);
@@ -484,12 +514,18 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     } else if (c->worker_comp == kBlockSign) {
         launch_block_l1<VEC>(L, grads, stride, (uint32_t)c->N, 0u, c->bits, S_W_L1);
     } else if (c->worker_comp == kTopk) {
-        launch_select<VEC, false>(L, grads, stride, (uint32_t)c->N, 0u, (uint32_t)c->worker_k, c->gbits, c->gb_coarse,
-                                  c->filter_row_blocks, c->cold_row_blocks, S_W_SEL, RkDraw{nullptr, 0, 0});
+        launch_topk<VEC>(L, grads, stride, (uint32_t)c->N, 0u, (uint32_t)c->worker_k, c->gbits, c->gb_coarse,
+                         c->filter_row_blocks, c->cold_row_blocks, S_W_SEL, c->w_one);
     } else if (c->worker_comp == kRandk) {
-        launch_select<VEC, true>(L, grads, stride, (uint32_t)c->N, 0u, (uint32_t)c->worker_k, nullptr, false,
-                                 c->filter_row_blocks, c->cold_row_blocks, S_W_SEL,
-                                 RkDraw{c->rk_state, c->rk_wlo, c->rk_whi}, c->rk_winv);
+        RkDraw rk{c->rk_state, c->rk_wlo, c->rk_whi};
+        const bool joint = c->joint_draw();
+        if (joint) {
+            rk.srv_row = (uint32_t)c->N;
+            rk.srv_k = (uint32_t)c->server_k;
+            rk.srv_lo = c->rk_slo;
+            rk.srv_hi = c->rk_shi;
+        }
+        launch_randk(L, (uint32_t)c->N + (joint ? 1u : 0u), 0u, (uint32_t)c->worker_k, c->filter_row_blocks, S_W_SEL, rk, c->rk_winv);
     }
 
     // ---- server: v = e + mean_i p^i, then the descriptor of C_s(v) ---------------------------------
@@ -512,13 +548,11 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     } else if (c->server_comp == kTopk) {
         // v is always 16-byte aligned scratch, but d % 4 decides whether 128-bit loads stay in bounds
         // the server's candidates get the fine group bitmap: the update kernel reads v only where a bit is set
-        launch_select<VEC, false>(L, c->vbuf, 0, 1u, (uint32_t)c->N, (uint32_t)c->server_k, c->sgbits, false,
-                                  c->filter_srv_blocks, c->cold_srv_blocks, S_S_SEL, RkDraw{nullptr, 0, 0}, false,
-                                  c->agg_filters());
-    } else if (c->server_comp == kRandk) {
-        launch_select<VEC, true>(L, c->vbuf, 0, 1u, (uint32_t)c->N, (uint32_t)c->server_k, nullptr, false,
-                                 c->filter_srv_blocks, c->cold_srv_blocks, S_S_SEL,
-                                 RkDraw{c->rk_state, c->rk_slo, c->rk_shi}, c->rk_sinv);
+        launch_topk<VEC>(L, c->vbuf, 0, 1u, (uint32_t)c->N, (uint32_t)c->server_k, c->sgbits, false, c->filter_srv_blocks,
+                         c->cold_srv_blocks, S_S_SEL, c->s_one, c->agg_filters());
+    } else if (c->server_comp == kRandk && !c->joint_draw()) {
+        launch_randk(L, 1u, (uint32_t)c->N, (uint32_t)c->server_k, c->filter_srv_blocks, S_S_SEL,
+                     RkDraw{c->rk_state, c->rk_slo, c->rk_shi}, c->rk_sinv);
     }
 
     // ---- p = C_s(v), e <- v - p, x^i <- x^i - lr (p + (g_i - p^i)) ---------------------------------
@@ -528,11 +562,6 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     case kBlockSign: launch_update_sc<kBlockSign, VEC>(L, c->server_comp, grads, x, e); break;
     case kRandk: launch_update_sc<kRandk, VEC>(L, c->server_comp, grads, x, e); break;
     default: launch_update_sc<kTopk, VEC>(L, c->server_comp, grads, x, e); break;
-    }
-    // the next compressed iteration makes the next draw
-    if (c->worker_comp == kRandk || c->server_comp == kRandk) {
-        k_rk_advance<<<1, 1, 0, c->stream>>>(c->rk_state);
-        if (hipGetLastError() != hipSuccess) L.ok = false;
     }
 }
 
@@ -688,14 +717,28 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         // at most one per compute unit
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) cus = 1;
-        c->slow_bw = clampu((uint32_t)cus / un, 1u, (uint32_t)kSlowMaxBlocks);
-        c->slow_bs = clampu((uint32_t)cus, 1u, (uint32_t)kSlowMaxBlocks);
+        // and a wave tile for each of their waves
+        const uint32_t useful = (c->nwt + 15) / 16;
+        c->slow_bw = clampu(std::min((uint32_t)cus / (un + (c->joint_draw() ? 1u : 0u)), useful), 1u, (uint32_t)kSlowMaxBlocks);
+        c->slow_bs = clampu(std::min((uint32_t)cus, useful), 1u, (uint32_t)kSlowMaxBlocks);
         const size_t slots = (c->slow_bw > 1 ? (size_t)N : 0) + (c->slow_bs > 1 ? 1 : 0);
+        // The search behind the first pass in one launch instead of four: us per step in one launch against four,
+        // in the steady state and (in brackets) without predictions, top-k on both sides, 1 %: 32 x 16384 38 against 46
+        // (59, 65), 8 x 1M 54 against 63 (96, 106), 5 x 3M 87 against 97 (144, 157), 32 x 1M 133 against 144 (204, 202),
+        // 8 x 4.2M 142 against 154 (219, 228).  Beyond, the launches are under 3 % of a step and the passes of a row without a prediction
+        // have too few blocks: 2 x 16.8M 199 against 204 (362, 312).  Random-k rows always know their band: 8 x 1M 44
+        // against 72, 32 x 4.2M 406 against 452, 32 x 25.6M, 0.1 %, 1810 against 1850 (with the server's draw in the workers'
+        // launches).
+        c->w_one = worker_comp == LIEC_COMP_RANDK || (c->nwt <= 8192u && (uint64_t)c->nwt * un <= 32768u);
+        c->s_one = server_comp == LIEC_COMP_RANDK || c->nwt <= 4096u;
+        c->slow_slots = (uint32_t)slots;
         if (slots) {
             e = dev_alloc(c, &c->slow_hist, slots * kSlowHistWords);
             if (e == hipSuccess) e = dev_alloc(c, &c->slow_cnt, slots * kSlowMaxBlocks);
-            if (e == hipSuccess) e = dev_alloc(c, &c->slow_sync, slots * 2);
-            if (e == hipSuccess) e = hipMemsetAsync(c->slow_sync, 0, slots * 2 * sizeof(uint32_t), c->stream);
+            if (e == hipSuccess) e = dev_alloc(c, &c->slow_sync, slots * kSyncWords);
+            if (e == hipSuccess) e = dev_alloc(c, &c->list_hist, ((size_t)un * c->slow_bw + c->slow_bs) * 256);
+            if (e == hipSuccess) e = hipMemsetAsync(c->slow_sync, 0, slots * kSyncWords * sizeof(uint32_t), c->stream);
+            if (e == hipSuccess) e = hipMemsetAsync(c->slow_hist, 0, slots * kSlowHistWords * sizeof(uint32_t), c->stream);
         }
     }
     if (e == hipSuccess) {
@@ -811,7 +854,7 @@ liec_status liec_get_search_state(liec_ctx* c, int32_t row, uint32_t* out) {
     out[3] = r.n_list;
     out[4] = r.misses;
     out[5] = r.swing;
-    out[6] = r.dense;
+    out[6] = r.general;
     out[7] = 0;
     return LIEC_OK;
 }
@@ -1227,7 +1270,7 @@ liec_status liec_get_info(liec_ctx* c, liec_info* info) {
     }
     for (size_t r = 0; r < h.size(); ++r) {
         if (!selects_k(r < (size_t)c->N ? c->worker_comp : c->server_comp)) continue;
-        if (h[r].dense) ++info->slow_rows;
+        if (h[r].general) ++info->slow_rows;
         info->band_misses += (int64_t)h[r].misses;
     }
     bool bad = (c->server_comp == kSign || c->server_comp == kTopk) && s.nonfinite;

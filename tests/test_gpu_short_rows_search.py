@@ -1,0 +1,52 @@
+"""The search of short rows in one launch behind the first pass: rows on their prediction, rows without one, the whole
+general search, each with the blocks of a row waiting for one another and with waits that run out, in any order."""
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(__file__))
+import _harness as H  # noqa: E402
+from _gpu import DEV, GPU_MARKS, say  # noqa: E402
+
+pytestmark = GPU_MARKS
+
+WAIT = 1 << 16                                                  # the default bound
+# (mode of the search, bound of its waits): after a wait that ran out the next search finds its histograms not zero
+STEPS = [(None, WAIT), (0, WAIT), (1, 0), (1, WAIT), (4, 3), (0, WAIT), (4, WAIT), (1, 2), (0, 0), (0, WAIT), (4, 0), (1, WAIT)]
+
+
+# rows of one block (16 tiles), of two, of many; too many rows for more than one block each; a list longer than one block
+# takes (uniform magnitudes crowd the band); the two random-k draws in one set of launches, with k and bands of their own
+@pytest.mark.parametrize("wc,sc,N,d,wk,sk,uniform", [
+    ("topk", "topk", 2, 16_384, 300, 700, False), ("topk", "topk", 2, 16_385, 300, 700, False),
+    ("topk", "topk", 3, 70_001, 4000, 1000, False), ("topk", "topk", 1, 1_000_003, 60_000, 40_000, True),
+    ("topk", "identity", 140, 20_001, 200, 0, False), ("topk", "topk", 33, 40_000, 999, 999, False),
+    ("randk", "randk", 3, 70_001, 4000, 70, False), ("randk", "randk", 140, 20_001, 200, 90, False),
+    ("randk", "randk", 2, 1_000_003, 500, 600, False), ("randk", "topk", 5, 33_333, 333, 33, False),
+    ("identity", "randk", 2, 50_000, 0, 512, False)])
+def test_search_modes_and_waits_in_any_order(wc, sc, N, d, wk, sk, uniform):
+    say(f"case short rows {wc}/{sc} N={N} d={d} k={wk}/{sk}")
+    import oracle
+    from paper_2402_11857_amd import LiecContext
+
+    rng = np.random.default_rng(d + N)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, wc, sc, wk, sk, 0.05) as ctx:
+        ctx.set_random(7, 0)
+        for t, (mode, wait) in enumerate(STEPS):
+            g = rng.standard_normal((N, d), dtype=np.float32)
+            if uniform:
+                g = (0.5 + rng.random((N, d), dtype=np.float32) * np.float32(0.4 if t % 2 else 0.5)).astype(np.float32)
+            if mode is not None:
+                ctx.force_search_mode(mode)
+            ctx.set_search_wait(wait)
+            ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+            torch.cuda.synchronize()
+            oracle.step(g, x, e, wc, sc, 0.05, wk, sk, rng=(7, t))
+            assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}: mode {mode}, wait {wait}"
+            if mode == 4:
+                assert ctx.info().slow_rows == (N if wk else 0) + (1 if sk else 0), f"step {t}"
