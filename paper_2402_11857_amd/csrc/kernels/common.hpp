@@ -219,10 +219,41 @@ __device__ __forceinline__ void wave_count(uint32_t* h, bool valid, uint32_t bin
     }
 }
 
-// Sum over the block in a fixed order (lanes by halving, then waves in order).  Valid on thread 0.
+// Sums over the wave in a fixed order; all 64 lanes call them.  The lanes' values move through the vector
+// unit's own data path (inside rows of 16 lanes, then from row to row), a few cycles a step where a shuffle through LDS
+// takes a hundred (scaled sign, four such sums in a row: 8 x 262144 columns 16.1 -> 15.3 us a step).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint64_t lo = dpp_or_zero<CTRL, ROWS>((uint32_t)b), hi = dpp_or_zero<CTRL, ROWS>((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(hi << 32 | lo));
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ double last_lane(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)((uint64_t)last_lane((uint32_t)(b >> 32)) << 32 | last_lane((uint32_t)b)));
+}
+// Sum of the lanes up to and including this one.
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v) {
+    v += dpp_or_zero<0x111, 0xf>(v);           // row_shr:1, 2, 4, 8: lane 15 of a row has the row's sum
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);           // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xc>(v);           // row_bcast:31 into rows 2 and 3
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) { return last_lane(wave_scan(v)); }
+
+// Sum over the block in a fixed order (wave_sum, then waves in order).  Valid on thread 0.
 __device__ __forceinline__ double block_sum_f64(double v, double* lds_waves) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    v = wave_sum(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     if (lane == 0) lds_waves[wave] = v;
     __syncthreads();
@@ -233,8 +264,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double* lds_waves) {
 }
 
 __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* lds_waves) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    v = wave_sum(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     if (lane == 0) lds_waves[wave] = v;
     __syncthreads();
@@ -264,12 +294,7 @@ __device__ __forceinline__ Pick block_pick(const uint32_t* __restrict__ h, int n
         for (int q = 0; q < per; ++q) sum += h[tid * per + ((q + tid) & (per - 1))];
     }
     // count in the bins above this thread's range: suffix sum over the 256 threads (lanes, then waves)
-    uint32_t incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t up = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += up;
-    }
+    const uint32_t upto = wave_scan(sum), incl = last_lane(upto) - upto + sum;
     if (tid < 256 && lane == 0) part[wave] = incl;             // total of wave `wave`
     if (tid == 0) {
         part[8] = 0xffffffffu;                                  // the thread whose bins hold the rank: none yet
@@ -291,12 +316,7 @@ __device__ __forceinline__ Pick block_pick(const uint32_t* __restrict__ h, int n
     if (owner != 0xffffffffu && tid < 64) {                     // wave 0 walks the owner's bins from the top
         const uint32_t above = part[9];
         const uint32_t c = (int)lane < per ? h[owner * per + lane] : 0u;
-        uint32_t suf = c;                                       // sum over the lanes at and above mine
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_down(suf, o, 64);
-            if (lane + o < 64) suf += up;
-        }
+        const uint32_t upto_me = wave_scan(c), suf = last_lane(upto_me) - upto_me + c;      // sum over the lanes at and above mine
         const uint64_t reach = __ballot((int)lane < per && above + suf >= rank);    // lane 0 always does
         const uint32_t top = 63u - (uint32_t)__clzll((long long)reach);
         if (lane == top) {

@@ -275,8 +275,7 @@ template <int WAVES = kBlock / 64, bool SHARED = false>
 __device__ __forceinline__ void finish_filter_block(const FilterBand& fb, const uint2* stage, const uint2* wst, uint32_t wcnt,
                                                     uint32_t n_hi, uint32_t* staged, uint32_t* wsure /* WAVES + 1 words */) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n_hi += __shfl_down(n_hi, o, 64);
+    n_hi = wave_sum(n_hi);
     if (lane == 0) wsure[wave] = n_hi;
     if (wcnt) flush_wave_stage<SHARED>(fb, wst, wcnt, staged, lane);    // wave-uniform
     __syncthreads();
@@ -888,6 +887,9 @@ struct SlowFound {
     uint32_t tau, rank, ties, cut, bad;
     uint32_t first;                            // entries that share tau's first digit
 };
+// A candidate bitmap is worth having while most of the row is not in it (a constant row is read faster without one: 40M
+// columns packed in 63 us against 90).
+__device__ __forceinline__ bool bitmap_pays(const SlowFound& f, uint32_t k, uint32_t d) { return (uint64_t)(k - f.rank + f.ties) * 8 <= d; }
 // And what it leaves in the row's descriptor (thread 0).  degenerate: no candidate list could hold the row, so there is
 // no use in a prediction; form: of the row's candidate bitmap, 0 none.
 __device__ __forceinline__ void finish_general(RowDesc& r, const SlowFound& f, bool degenerate, uint32_t form, uint32_t fix_lo,
@@ -954,12 +956,7 @@ __device__ __forceinline__ SlowFound slow_single(SlowLds& s, const float* __rest
         const bool m0 = j < d && key[0] == prefix, m1 = j + 1 < d && key[1] == prefix;
         const bool m2 = j + 2 < d && key[2] == prefix, m3 = j + 3 < d && key[3] == prefix;
         const uint32_t mine = m0 + m1 + m2 + m3;
-        uint32_t incl = mine;                                   // inclusive scan inside the wave
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_up(incl, o, 64);
-            if ((int)lane >= o) incl += up;
-        }
+        const uint32_t incl = wave_scan(mine);
         if (lane == 63) s.wtot[wave] = incl;
         __syncthreads();
         uint32_t before = seen, total = 0;
@@ -1238,11 +1235,11 @@ __global__ __launch_bounds__(1024) void k_slow_select(const float* __restrict__ 
         if (blockIdx.x != 0) return;
         if (end == kGaveUp && threadIdx.x == 0) sync[2] = 1;
     }
-    const bool bitmap = end == kFound;
-    if (!bitmap) f = slow_single<VEC, false>(s, g, d, k, 0u, 0u);
+    if (end != kFound) f = slow_single<VEC, false>(s, g, d, k, 0u, 0u);
     if (threadIdx.x == 0) {
         s.now = desc[row];
         s.now.nonfinite_acc |= f.bad;
+        const bool bitmap = end == kFound && bitmap_pays(f, k, d);
         finish_general(s.now, f, true, bitmap ? (coarse ? 2u : 1u) : 0u, 0u, 0u);
     }
     put_result(desc + row, s.now);
@@ -1411,7 +1408,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
             now.nonfinite_acc |= f.bad;
         }
         if (end != kListed) {
-            const bool bitmap = end == kFound && groups;
+            const bool bitmap = end == kFound && groups && bitmap_pays(f, k, d);
             if (tid == 0) finish_general(now, f, now.mode == kSlow || f.first > cap, bitmap ? form : 0u, fix_lo, fix_hi);
             put_result(desc + row, now);
             if (RK) mark_row(stream, d, nwt, f.tau, f.cut, row_bits);

@@ -9,18 +9,18 @@ namespace liec {
 // of the row.  Bit layout ("lane-major"): wave tile t of row i owns 64 half-words
 // bits[(i*nwt + t)*64 + l]; bit 4u + q of half-word l is (g[1024t + 256u + 4l + q] < 0), i.e. every
 // lane keeps the 16 bits of the 16 columns it owns, and a wave reads or writes 128 contiguous bytes.
-// grid = (blocks per row, rows); waves stride over the row's wave tiles.
+// grid = (blocks per row, rows), blocks of 4 or 16 waves; waves stride over the row's wave tiles.
 // ---------------------------------------------------------------------------------------------
 template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_l1_bits(const float* __restrict__ src, size_t row_stride, uint32_t d,
+__global__ __launch_bounds__(1024) void k_l1_bits(const float* __restrict__ src, size_t row_stride, uint32_t d,
                                                      uint32_t nwt, double* __restrict__ partial,
                                                      uint16_t* __restrict__ bits) {
-    __shared__ double lds_w[4];
+    __shared__ double lds_w[16];
     const uint32_t row = blockIdx.y;
     const float* __restrict__ g = src + (size_t)row * row_stride;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     double acc = 0.0;
-    for (uint32_t t = blockIdx.x * 4 + wave; t < nwt; t += gridDim.x * 4) {
+    for (uint32_t t = blockIdx.x * waves + wave; t < nwt; t += gridDim.x * waves) {
         float4 a[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
@@ -80,20 +80,26 @@ __global__ __launch_bounds__(1024) void k_l1_final(const double* __restrict__ pa
     if (threadIdx.x == 0) set_scale(desc[row], s, d);
 }
 
-// The same by one wave, for the kernels that finish a few short sums themselves instead of waiting for a kernel that
-// does.  The sum is valid on lane 0, and the same in every wave that forms it.
-__device__ __forceinline__ double wave_l1(const double* __restrict__ p, uint32_t nparts, uint32_t lane) {
-    double s = 0.0;
-    for (uint32_t q = lane; q < nparts; q += 256) {
-        const double b0 = p[q];
-        const double b1 = q + 64 < nparts ? p[q + 64] : 0.0;
-        const double b2 = q + 128 < nparts ? p[q + 128] : 0.0;
-        const double b3 = q + 192 < nparts ? p[q + 192] : 0.0;
-        s += (b0 + b1) + (b2 + b3);
+// The same by one wave for ROWS rows at once (row r's partials at p + r * stride, those from row n on left out), for the
+// kernels that finish a few short sums themselves instead of waiting for a kernel that does.  Every lane has the sums, and
+// they are the same in every wave that forms them.
+template <int ROWS>
+__device__ __forceinline__ void wave_l1(const double* __restrict__ p, size_t stride, int n, uint32_t nparts, uint32_t lane,
+                                        double (&s)[ROWS]) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) s[r] = 0.0;
+    for (uint32_t q = lane; q < nparts; q += 128) {
+        double b[ROWS][2];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) b[r][i] = r < n && q + 64 * i < nparts ? p[r * stride + q + 64 * i] : 0.0;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) s[r] += b[r][0] + b[r][1];
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    return s;
+    for (int r = 0; r < ROWS; ++r)
+        if (r < n) s[r] = wave_sum(s[r]);                       // uniform
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -61,12 +61,27 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
     __shared__ double lds_w[4];
     __shared__ float folded[FOLD ? kFoldRows : 1];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // FOLD: what the first tile needs is requested ahead of the sums, or its latency comes on top of theirs (here and in the
+    // update, with sums in the vector unit: 8 x 262144 columns 17.5 -> 15.3 us a step, 16 x 65536 17.2 -> 14.6)
+    uint32_t m0[8];
+    float4 e0[4];
     if (FOLD) {
-        for (uint32_t i = wave; i < (uint32_t)N; i += 4) {
-            const double s = wave_l1(w_partial + (size_t)i * w_parts, w_parts, lane);
-            if (lane == 0) {
-                folded[i] = (float)(s / (double)d);
-                if (blockIdx.x == 0) set_scale(desc[i], s, d);  // for the update and the caller's queries
+        const uint32_t t = min(blockIdx.x * 4 + wave, nwt - 1);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) m0[r] = bits[((size_t)min(r, N - 1) * nwt + t) * 64 + lane];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e0[u] = ld4<VEC>(e_in, t * kWaveTile + lane * 4 + u * kChunk, d);
+        // a wave's share of the workers: wave, wave + 4, ..
+        double s[kFoldRows / 4];
+        wave_l1(w_partial + (size_t)wave * w_parts, (size_t)4 * w_parts, (N - (int)wave + 3) / 4, w_parts, lane, s);
+        if (lane == 0) {
+#pragma unroll
+            for (int q = 0; q < kFoldRows / 4; ++q) {
+                const uint32_t i = wave + 4 * q;
+                if (i < (uint32_t)N) {
+                    folded[i] = (float)(s[q] / (double)d);
+                    if (blockIdx.x == 0) set_scale(desc[i], s[q], d);   // for the update and the caller's queries
+                }
             }
         }
         __syncthreads();
@@ -86,6 +101,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
             const size_t brow = (size_t)nwt * 64;
             auto scale_of = [&](int i) { return FOLD ? folded[i] : desc[i].scale; };
             int i = 0;
+            if (FOLD && tb == blockIdx.x * 4) {                 // the ones requested ahead
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (r < N) add_signed(acc, m0[r], scale_of(r));     // uniform
+                i = 8;
+            }
             for (; i + 8 <= N; i += 8) {                       // 8 rows of bits in flight
                 uint32_t m[8];
 #pragma unroll
@@ -146,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = j0 + u * kChunk;
-            const float4 e = ld4<VEC>(e_in, j, d);
+            const float4 e = FOLD && tb == blockIdx.x * 4 ? e0[u] : ld4<VEC>(e_in, j, d);
             float4 v;
             v.x = __fmaf_rn(acc[u].x, inv_n, e.x);
             v.y = __fmaf_rn(acc[u].y, inv_n, e.y);
@@ -265,13 +286,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_sparse(const float* __rest
                     for (int q = 0; q < 8; ++q) cnt += (uint32_t)__popc(nonzero_nibbles(x[q]));
                 }
             }
-            uint32_t incl = cnt;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = __shfl_up(incl, o, 64);
-                if ((int)lane >= o) incl += up;
-            }
-            const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+            const uint32_t incl = wave_scan(cnt), total = last_lane(incl);
             if (total == 0) continue;
             const uint32_t per_row = WC == kTopk && coarse ? kSparseGroups / 4 : kSparseGroups;
             if (total <= min(kSparseList, (uint32_t)min(16, N - i0) * per_row)) {     // wave-uniform
@@ -614,7 +629,7 @@ static_assert(offsetof(RowDesc, n_cand) == 128 && offsetof(RowDesc, nonfinite_ac
 // consecutive column tiles), inside a panel row by row, so every row is walked in long contiguous
 // runs while the panel's slice of v stays in cache for the N rows that reuse it; the row-0 block of
 // a tile also writes e.  grid = number of panels * panel * N.
-// FOLD (scaled-sign server, few blocks): the block forms the server's scale from the partial sums itself.
+// FOLD (scaled-sign server, few blocks): every wave forms the server's scale from the partial sums itself.
 // ---------------------------------------------------------------------------------------------
 template <int WC, int SC, bool VEC, bool FOLD = false>
 __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ grads, float* __restrict__ x,
@@ -624,26 +639,25 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
                                                     const uint16_t* __restrict__ kbits, const uint16_t* __restrict__ vbits,
                                                     const uint64_t* __restrict__ sgbits, const uint64_t* __restrict__ vodd,
                                                     const double* __restrict__ s_partial, uint32_t s_parts, StepTail tail) {
-    __shared__ float folded;
     if (WC == kTopk || WC == kRandk || SC == kTopk || SC == kRandk) end_searches(tail);
-    if (FOLD) {                                                 // before any thread leaves
-        if (threadIdx.x < 64) {
-            const double s = wave_l1(s_partial, s_parts, threadIdx.x);
-            if (threadIdx.x == 0) {
-                folded = (float)(s / (double)d);
-                if (blockIdx.x == 0) set_scale(desc[N], s, d);
-            }
-        }
-        __syncthreads();
-    }
     const uint32_t per_panel = panel * (uint32_t)N;
     const uint32_t pn = blockIdx.x / per_panel, r = blockIdx.x % per_panel;
     const uint32_t i = r / panel, tile = pn * panel + r % panel;
     if (tile >= ncol_tiles) return;
     const uint32_t j = tile * kColTile + threadIdx.x * 4;
-    if (j >= d) return;
     const float* __restrict__ gi = grads + (size_t)i * d;
     float* __restrict__ xi = x + (size_t)i * d;
+    float4 g0 = make_float4(0.f, 0.f, 0.f, 0.f), x0 = g0;
+    float folded = 0.f;
+    if (FOLD) {                                                 // the streams are requested ahead of the sum, which every wave forms
+        if (WC != kIdentity) g0 = ld4<VEC, true>(gi, j, d);
+        x0 = ld4<VEC, true>(xi, j, d);
+        double s[1];
+        wave_l1(s_partial, 0, 1, s_parts, threadIdx.x & 63, s);
+        folded = (float)(s[0] / (double)d);
+        if (blockIdx.x == 0 && threadIdx.x == 0) set_scale(desc[N], s[0], d);
+    }
+    if (j >= d) return;
     const uint32_t lane = threadIdx.x & 63, chunk = threadIdx.x >> 6;   // this thread is lane `lane` of chunk `chunk` of wave tile `tile`
     uint32_t tb = 0;
     if (WC == kBlockSign || SC == kBlockSign) tb = bt.tile_blk[tile];   // issued ahead of the streams
@@ -672,13 +686,13 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
     }
     // an uncompressed message leaves no local error: g - p^i is g - g = +0 for every finite gradient (the others: see the
     // end), and the gradients are not read a second time (8 rows of 11.7M + 2 columns: 195 -> 139 us)
-    const float4 g = WC == kIdentity ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4<VEC, true>(gi, j, d);
+    const float4 g = FOLD ? g0 : WC == kIdentity ? make_float4(0.f, 0.f, 0.f, 0.f) : ld4<VEC, true>(gi, j, d);
 #if defined(__HIP_DEVICE_COMPILE__)
     // One stream at a time per wave: waiting for the gradients before asking for the model measured
     // 2-4 % faster than having both 128-bit loads in flight.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (!FOLD) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
-    const float4 xv = ld4<VEC, true>(xi, j, d);
+    const float4 xv = FOLD ? x0 : ld4<VEC, true>(xi, j, d);
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (need_v) v = ld4<VEC>(v_in, j, d);
     const uint32_t stau = sd->tau, scut = sd->cutoff;

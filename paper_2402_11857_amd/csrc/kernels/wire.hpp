@@ -195,13 +195,8 @@ __global__ __launch_bounds__(kBlock) void k_kept_emit(KeptRow r, uint32_t d, uin
     for (int q = 0; q < kLoads; ++q) before += count4(c[q], (q * kBlock + tid) * 4);
     for (uint32_t b = (kLoads * kBlock + tid) * 4; b < blockIdx.x; b += kBlock * 4)     // rows of more than 16.8M columns
         before += count4(*reinterpret_cast<const uint4*>(block_cnt + b), b);
-    uint32_t incl = n;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t up = __shfl_up(incl, o, 64);
-        if ((int)lane >= o) incl += up;
-        before += __shfl_xor(before, o, 64);
-    }
+    const uint32_t incl = wave_scan(n);
+    before = wave_sum(before);
     if (lane == 63) {
         wave_before[wave] = before;
         wave_n[wave] = incl;

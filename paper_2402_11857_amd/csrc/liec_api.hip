@@ -119,7 +119,7 @@ struct liec_ctx {
 
     uint32_t nwt = 0;                          // wave tiles of 1024 columns per row
     uint32_t ncol_tiles = 0;                   // column tiles of the update kernel
-    uint32_t row_blocks = 0;                   // scaled-sign pass over grads: grid (row_blocks, N)
+    uint32_t row_blocks = 0, row_threads = kBlock;   // scaled-sign pass over grads: grid (row_blocks, N)
     uint32_t filter_row_blocks = 0, filter_srv_blocks = 0;   // top-k filter pass (fewer, longer-lived blocks)
     uint32_t filter_run = 1;                   // consecutive wave tiles a wave of the filter takes at a time
     bool agg_chunk = false;                    // the aggregation takes a chunk per wave instead of a tile (short rows, identity)
@@ -134,7 +134,7 @@ struct liec_ctx {
     bool agg_filters() const { return server_comp == kTopk && agg_chunk && nwt <= kAggFilterTiles; }
     // scaled sign on short rows: the aggregation forms the workers' scales from their partial sums, the update the server's
     bool fold_workers = false;
-    bool fold_server() const { return agg_blocks() <= 256u && (uint64_t)ncol_tiles * (uint64_t)N <= 2048u; }
+    bool fold_server() const { return agg_blocks() <= 256u && (uint64_t)ncol_tiles * (uint64_t)N <= 4096u; }
     uint32_t cold_row_blocks = 0, cold_srv_blocks = 0;   // first-digit histogram (rarely needed)
     uint32_t cap = 0;                          // candidate list capacity per row
 
@@ -503,7 +503,7 @@ void run_step(Launcher& L, const float* grads, float* x, float* e) {
     // ---- workers: p^i = C_w(g_i), reduced to a per-row descriptor (+ packed bits) ------------------
     if (c->worker_comp == kSign) {
         L.begin(S_W_L1);
-        k_l1_bits<VEC><<<dim3(c->row_blocks, c->N), kBlock, 0, c->stream>>>(grads, stride, d, c->nwt, c->w_partial,
+        k_l1_bits<VEC><<<dim3(c->row_blocks, c->N), c->row_threads, 0, c->stream>>>(grads, stride, d, c->nwt, c->w_partial,
                                                                              c->bits);
         L.end();
         if (!c->fold_workers) {
@@ -641,6 +641,14 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     };
     // the scaled-sign pass streams best as one 4096-column iteration per block
     c->row_blocks = balanced(1u << 20);
+    // Scaled sign on both sides, rows of middling length: blocks of 16 waves leave a quarter of the partial sums, few enough
+    // for the kernels that use the scales to finish them (both sides: two launches less).  us per step with and without:
+    // 8 x 524288 columns 23.0 against 26.0, 4 x 1M 25.6 against 28.2, 2 x 2.1M 30.1 against 31.1, 16 x 262144 23.8 against 26.5,
+    // 16 x 524288 36.6 against 37.3, 8 x 1M 36.9 against 38.6; beyond, the sums are too many again.
+    if (worker_comp == LIEC_COMP_SIGN && server_comp == LIEC_COMP_SIGN && N <= kFoldRows && c->nwt * un > 2048u && c->nwt * un <= 8192u) {
+        c->row_threads = 1024;
+        c->row_blocks = (c->nwt + 15) / 16;
+    }
     // the filter pays one atomic on the row's counters per block: about 1024 long-lived blocks per row
     // (more when there are too few rows to fill the chip)
     // A wave of the filter takes 4 consecutive wave tiles at a time on long rows (a block then covers 16, and the
@@ -658,7 +666,8 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
                    (worker_comp == LIEC_COMP_RANDK && (uint64_t)c->nwt * un < 16384u) ||
                    (worker_comp == LIEC_COMP_BLOCKSIGN && c->nwt < 2048u);
     // A kernel that only finishes a few short sums costs its launch and two round trips to memory (2 us); the kernels
-    // that use the scales form them as fast while the sums are few (both sides here, the server's in the update).  us per step with and without: 4 x 65536 columns
+    // that use the scales form them as fast while the sums are few (both sides here, the server's in the update), with what
+    // they need besides requested ahead of the sums.  us per step with and without: 4 x 65536 columns
     // 11.4 against 15.4, 8 x 65537 15.4 against 19.1, 16 x 131072 (512 partials) 18.6 against 20.6; at 16 x 262144
     // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.  A wave forms its workers' scales
     // one after another, 0.5 us each however short the rows: sign / identity, 16 x 16384 13.3 against 13.4, 24 x 16384
