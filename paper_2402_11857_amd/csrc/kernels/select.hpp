@@ -335,12 +335,7 @@ __global__ __launch_bounds__(kBlock) void k_filter(const float* __restrict__ src
         float4 a[4];
         if (!RK) {
             if (FULL) {
-                typedef typename Vec4<VEC>::type vec;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const vec w = __builtin_nontemporal_load(reinterpret_cast<const vec*>(g + (size_t)t * kWaveTile + u * kChunk + lane * 4));
-                    a[u] = make_float4(w.x, w.y, w.z, w.w);
-                }
+                ld_tile<VEC>(g, t, lane, a);
             } else {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);

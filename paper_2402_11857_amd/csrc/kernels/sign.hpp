@@ -22,8 +22,12 @@ __global__ __launch_bounds__(1024) void k_l1_bits(const float* __restrict__ src,
     double acc = 0.0;
     for (uint32_t t = blockIdx.x * waves + wave; t < nwt; t += gridDim.x * waves) {
         float4 a[4];
+        if ((t + 1) * (uint32_t)kWaveTile <= d) {               // wave-uniform
+            ld_tile<VEC>(g, t, lane, a);
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
+            for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
+        }
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -140,8 +144,12 @@ __global__ __launch_bounds__(kBlock) void k_l1_items(const float* __restrict__ s
     double acc = 0.0;
     if (t < nwt) {
         float4 a[4];
+        if ((t + 1) * (uint32_t)kWaveTile <= d) {               // wave-uniform
+            ld_tile<VEC>(g, t, lane, a);
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
+            for (int u = 0; u < 4; ++u) a[u] = ld4<VEC, true>(g, t * kWaveTile + u * kChunk + lane * 4, d);
+        }
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
