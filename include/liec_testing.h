@@ -32,8 +32,8 @@ liec_status liec_force_search_mode(liec_ctx *ctx, int32_t mode);
  * HOST array `out` of 8 words: out[0] mode the next step starts in (0, 1 or 4 as
  * above), out[1] / out[2] lower / upper end of the band of keys predicted for the
  * next step, out[3] candidates the last step listed, out[4] steps so far whose
- * predicted band failed, out[5] the predictor's current swing (an eighth of the
- * band's half width unless a floor or the last change of the threshold decides),
+ * predicted band failed, out[5] the predictor's current swing (a sixth of the
+ * band's half width unless a floor or an earlier change of the threshold decides),
  * out[6] 1 if the last step took the general search, out[7] reserved (0).
  * Synchronises the stream.  LIEC_EINVAL for a row out of range or one whose
  * operator has no threshold search.

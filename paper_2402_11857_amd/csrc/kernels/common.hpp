@@ -29,7 +29,7 @@ constexpr int kShortCap = 4096;         // entries of the first list digit's bin
 constexpr int kHeldBits = 10;           // radix digit of the list select over a list it holds in registers
 constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key
 constexpr uint32_t kFewEntries = 256;   // entries left that the list select compares with one another instead of taking further digits
-constexpr uint32_t kBandStart = 1u << 17;    // swing (an eighth of the band's half width) after a step without a prediction
+constexpr uint32_t kBandStart = 1u << 17;    // swing after a step without a prediction (an eighth of the band's half width then)
 constexpr uint32_t kBandFloor = 1u << 15;    // least half width, in key units, of the predicted band (about 0.27 % in value)
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel
 
@@ -62,8 +62,10 @@ struct alignas(128) RowDesc {
     uint32_t prev_tau;     // tau of the step before (valid when have_prev)
     uint32_t have_prev;
     uint32_t misses;       // steps in which the predicted band was not usable (since the context was created)
-    uint32_t centre;       // where the last prediction expected tau
-    uint32_t swing;        // decaying maximum of the distances between tau and that centre
+    uint32_t centre;       // where the last change of tau, continued, leads
+    uint32_t swing;        // decaying maximum of the distances between tau and that
+    uint32_t swing_still;  // and of those between tau and prev_tau
+    uint32_t far;          // a slowly decaying maximum of the smaller of the two distances
     uint32_t was_cold;     // the last band came from the first-digit histogram, not from a prediction
     uint32_t general;      // the last step took the general search because no list could hold the row's candidates
     // second line: what the blocks of the passes add to with atomics (kept off the line every block reads when

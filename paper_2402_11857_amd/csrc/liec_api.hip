@@ -862,7 +862,7 @@ liec_status liec_get_search_state(liec_ctx* c, int32_t row, uint32_t* out) {
     out[2] = r.hi;
     out[3] = r.n_list;
     out[4] = r.misses;
-    out[5] = r.swing;
+    out[5] = std::min(r.swing, r.swing_still);
     out[6] = r.general;
     out[7] = 0;
     return LIEC_OK;
