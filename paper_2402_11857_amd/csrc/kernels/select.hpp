@@ -1366,7 +1366,7 @@ __device__ __forceinline__ void collect_bin(CollectLds& s, const float* __restri
 template <bool VEC, bool RK>
 __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict__ src, size_t row_stride, uint32_t d, uint32_t nwt,
                                                           uint32_t row0, RowDesc* __restrict__ desc, uint2* __restrict__ list,
-                                                          uint32_t cap, uint2* __restrict__ shortl, uint32_t k, RkDraw rk,
+                                                          uint32_t cap, uint2* __restrict__ shortl, uint32_t short_cap, uint32_t k, RkDraw rk,
                                                           uint64_t* __restrict__ gbits, uint16_t* __restrict__ kbits, bool coarse,
                                                           SharedRows sh) {
     __shared__ union {
@@ -1465,11 +1465,19 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
             if (sum) atomicAdd(&h[tid & 255], sum);
             __syncthreads();
             ph = block_pick(h, 256, rank, s.list.part, s.list.res);
-            if (ph.count > (uint32_t)kShortCap) {               // too many for the short list: block 0 walks the list
+            if (ph.count > short_cap) {                         // too many for the short list: block 0 walks the list
                 if (blockIdx.x != 0) return;
                 first = false;
             } else {
-                uint2* const out = shortl + (size_t)row * kShortCap;
+                // where my entries go follows from the histograms (with an atomic on the row's counter for every wave that has
+                // some, 8 ns each, one after another, the collecting took longer than the rest)
+                static_assert(kSlowMaxBlocks <= 64, "a lane for every block");
+                if (tid < 64) {
+                    const uint32_t ahead = wave_sum(lane < blockIdx.x ? ld_shared(&hists[lane * 256 + ph.bin]) : 0u);
+                    if (tid == 0) s.list.nties = ahead;
+                }
+                __syncthreads();
+                uint2* const out = shortl + (size_t)row * short_cap;
                 for (uint32_t base = blockIdx.x * kSelectBlock; base < n; base += nb * kSelectBlock) {
                     const uint32_t e = base + tid;
                     const uint2 kv = e < n ? row_list[e] : make_uint2(0u, 0u);
@@ -1477,9 +1485,9 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                     const uint64_t m = __ballot(hit);
                     if (m) {                                    // wave-uniform
                         uint32_t at = 0;
-                        if (lane == 0) at = atomicAdd(&desc[row].n_short, (uint32_t)__popcll(m));
+                        if (lane == 0) at = atomicAdd(&s.list.nties, (uint32_t)__popcll(m));       // LDS
                         at = __builtin_amdgcn_readfirstlane(at);
-                        if (hit) put_entry<true>(&out[at + lanes_below(m)], kv);      // the bin's count bounds the total: at most kShortCap
+                        if (hit) put_entry<true>(&out[at + lanes_below(m)], kv);      // the bin's count bounds the total: at most short_cap
                     }
                 }
                 if (blockIdx.x != 0) {

@@ -154,7 +154,8 @@ struct liec_ctx {
     uint64_t* sgbits = nullptr;                // [nwt * 4] group bitmap of the server's candidates in v (top-k server), fine form
     uint2* list = nullptr;                     // [(N + 1) * cap] candidates (key, index)
     uint32_t* ghist = nullptr;                 // [(N + 1) * kHistBins] first digit of a row (12 bits) or of its list (8 bits)
-    uint2* shortl = nullptr;                   // [(N + 1) * kShortCap] listed entries of the first list digit's bin
+    uint2* shortl = nullptr;                   // [(N + 1) * short_cap] listed entries of the first list digit's bin
+    uint32_t short_cap = kShortCap;
     // general (degenerate-row) search: B thread blocks share a row when B * rows fit the chip
     uint32_t slow_bw = 1, slow_bs = 1;         // blocks per worker row / for the server's vector
     uint32_t slow_spin = 1u << 16;             // bound, in polls, of the waits between those blocks
@@ -326,7 +327,7 @@ void launch_one(Launcher& L, const float* src, size_t row_stride, uint32_t rows,
     liec_ctx* c = L.c;
     L.begin(slot0 + 3);
     k_select<VEC, RK><<<dim3(row0 ? c->slow_bs : c->slow_bw, rows), kSelectBlock, 0, c->stream>>>(
-        src, row_stride, (uint32_t)c->d, c->nwt, row0, c->desc, c->list, c->cap, c->shortl, k, rk, gbits, c->bits, coarse,
+        src, row_stride, (uint32_t)c->d, c->nwt, row0, c->desc, c->list, c->cap, c->shortl, c->short_cap, k, rk, gbits, c->bits, coarse,
         shared_rows(c, row0 != 0));
     L.end();
 }
@@ -720,7 +721,9 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     if (e == hipSuccess && server_comp == LIEC_COMP_TOPK) e = dev_alloc(c, &c->sgbits, (size_t)c->nwt * 4);
     if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->list, rows * c->cap);
     if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->ghist, rows * kHistBins);
-    if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->shortl, rows * kShortCap);
+    // (a row that one block searches on its own has no use for it; up to 129 rows: 16 MiB)
+    c->short_cap = N <= 128 ? kShortCapOne : (uint32_t)kShortCap;
+    if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->shortl, rows * c->short_cap);
     if (e == hipSuccess && any_topk) {
         // blocks that share a row meet inside the kernel, so all of them must be resident at once:
         // at most one per compute unit
