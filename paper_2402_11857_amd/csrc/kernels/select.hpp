@@ -1470,7 +1470,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                 first = false;
             } else {
                 // where my entries go follows from the histograms (with an atomic on the row's counter for every wave that has
-                // some, 8 ns each, one after another, the collecting took longer than the rest)
+                // some, one after another, and bins of at most 4096: 2 x 4.2M columns, 5 %, a step 90 -> 82 us)
                 static_assert(kSlowMaxBlocks <= 64, "a lane for every block");
                 if (tid < 64) {
                     const uint32_t ahead = wave_sum(lane < blockIdx.x ? ld_shared(&hists[lane * 256 + ph.bin]) : 0u);
