@@ -12,7 +12,7 @@ SOURCES = [os.path.join(_HERE, "csrc", "liec_api.hip")]
 HEADERS = [os.path.join(_HERE, "csrc", "liec_kernels.hpp"), os.path.join(_ROOT, "include", "liec.h"),
            os.path.join(_ROOT, "include", "liec_testing.h")] + \
           [os.path.join(_HERE, "csrc", "kernels", n)
-           for n in ("common.hpp", "select.hpp", "sign.hpp", "step.hpp", "sync.hpp", "telemetry.hpp", "wire.hpp")]
+           for n in ("common.hpp", "rows.hpp", "select.hpp", "sign.hpp", "step.hpp", "sync.hpp", "telemetry.hpp", "wire.hpp")]
 
 
 def hipcc() -> str:

@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+#include "rows.hpp"
 
 namespace liec {
 
@@ -20,7 +21,6 @@ constexpr int kChunk = 256;             // columns per wave and load instruction
 constexpr int kWaveTile = 1024;         // columns per wave iteration
 constexpr int kColTile = 1024;          // columns per block of the update kernel
 constexpr int kHistBins = 4096;         // first radix digit of a whole row (12 bits)
-constexpr int kListBits = 13;           // widest radix digit of the list select (two digits cover a band of 2^26 keys)
 constexpr int kListBins = 1 << kListBits;
 constexpr int kStage = 1024;            // LDS staging slots of a block of the candidate filter
 constexpr int kWaveStage = 256;         // and of each of its waves once the block's are used up (a chunk lists at most 256)
@@ -30,82 +30,9 @@ constexpr uint32_t kShortCapOne = 16384;     // the same where one launch does t
 constexpr int kHeldBits = 10;           // radix digit of the list select over a list it holds in registers
 constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key
 constexpr uint32_t kFewEntries = 256;   // entries left that the list select compares with one another instead of taking further digits
-constexpr uint32_t kBandStart = 1u << 17;    // swing after a step without a prediction (an eighth of the band's half width then)
-constexpr uint32_t kBandFloor = 1u << 15;    // least half width, in key units, of the predicted band (about 0.27 % in value)
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel
 
 enum Comp : int { kIdentity = 0, kSign = 1, kTopk = 2, kBlockSign = 3, kRandk = 4 };
-
-// How a row's top-k threshold search starts its step.  A row's mode changes only where one block speaks
-// for the row (the list select, the general search); in between, every kernel re-derives what the row
-// needs from the mode and the row's counters.
-enum SelMode : uint32_t {
-    kWarm = 0,      // a band [lo, hi) predicted from the previous step is filtered
-    kCold = 1,      // no prediction: the band is the first-radix-digit bin holding rank k
-    kSlow = 4       // needs the general (multi pass) search over the row
-};
-
-// One per worker row, plus one (index N) for the server's vector v.
-struct alignas(128) RowDesc {
-    // first 128-byte line: what the kernels read, written once a step by whoever finishes the row's search
-    double l1;             // scaled sign: sum |v_j| (fp64)
-    float scale;           // scaled sign: fp32(l1 / d)
-    uint32_t tau;          // top-k: key of the k-th kept entry
-    uint32_t rank;         // top-k: how many entries with key == tau are kept
-    uint32_t ties;         // top-k: how many entries have key == tau
-    uint32_t cutoff;       // top-k: largest kept index among entries with key == tau
-    uint32_t nonfinite;    // a NaN/Inf reached the L1 sum or a key (last step)
-    uint32_t lo, hi;       // candidate band: keys in [lo, hi) are listed, keys >= hi are surely kept
-    uint32_t mode;         // SelMode
-    uint32_t n_list;       // candidates that were listed when the search finished (random-k marks the kept ones)
-    uint32_t dense;        // the row's candidate bitmap is not valid: test every column
-    uint32_t form;         // top-k worker: form of that bitmap, 1 a bit per 4 columns, 2 per 64-byte line, 0 not valid or none yet
-    uint32_t prev_tau;     // tau of the step before (valid when have_prev)
-    uint32_t have_prev;
-    uint32_t misses;       // steps in which the predicted band was not usable (since the context was created)
-    uint32_t centre;       // where the last change of tau, continued, leads
-    uint32_t swing;        // decaying maximum of the distances between tau and that
-    uint32_t swing_still;  // and of those between tau and prev_tau
-    uint32_t far;          // a slowly decaying maximum of the smaller of the two distances
-    uint32_t was_cold;     // the last band came from the first-digit histogram, not from a prediction
-    uint32_t general;      // the last step took the general search because no list could hold the row's candidates
-    // second line: what the blocks of the passes add to with atomics (kept off the line every block reads when
-    // it starts).  Counters of the pass over the predicted band, one 64-bit word that a block of the filter adds
-    // to with a single atomic.  Low half: candidates appended (may exceed the capacity: overflow); high half:
-    // keys at or above the band.
-    alignas(128) uint32_t n_cand;
-    uint32_t n_sure;
-    // the same for the pass over the first-digit band, which runs when there is no prediction or the predicted
-    // band failed (its own set, so that every kernel can still tell from the first set that the row needed it)
-    alignas(8) uint32_t n_cand2;
-    uint32_t n_sure2;
-    uint32_t n_short;      // entries of the first list digit's bin collected into the row's short list
-    uint32_t nonfinite_acc;   // this step's Inf / NaN sightings (moved to `nonfinite` when the search finishes)
-};
-static_assert(sizeof(RowDesc) == 256, "two lines per row");
-
-__host__ __device__ __forceinline__ uint32_t sure_count(const RowDesc& r) { return r.n_sure; }
-__host__ __device__ __forceinline__ uint32_t sure_count2(const RowDesc& r) { return r.n_sure2; }
-// The second line back to zero (the update kernel does it for every row, once nobody looks at the counters any more).
-__host__ __device__ __forceinline__ void clear_counts(RowDesc& r) {
-    r.n_cand = 0;
-    r.n_cand2 = 0;
-    r.n_short = 0;
-    r.n_sure = r.n_sure2 = 0;
-    r.nonfinite_acc = 0;
-}
-
-// After a filter pass: the band is usable when its list did not overflow and rank k falls inside it.
-__device__ __forceinline__ bool band_ok(const RowDesc& r, uint32_t cap, uint32_t k) {
-    const uint32_t n_sure = sure_count(r);
-    return r.n_cand <= cap && n_sure < k && (uint64_t)k <= (uint64_t)n_sure + r.n_cand &&
-           r.hi - r.lo <= (1u << (2 * kListBits));       // the list select's two digits must span the band
-}
-// Rows that need the first-digit histogram: no prediction, or the predicted band failed.  Stable from the
-// end of the pass over the predicted band until the row's search is finished.
-__device__ __forceinline__ bool wants_cold(const RowDesc& r, uint32_t cap, uint32_t k) {
-    return r.mode == kCold || (r.mode == kWarm && !band_ok(r, cap, k));
-}
 
 // Radix digits of the 31-bit magnitude key, most significant first.
 __host__ __device__ constexpr int digit_shift(int pass) { return pass == 0 ? 19 : (pass == 1 ? 9 : 0); }

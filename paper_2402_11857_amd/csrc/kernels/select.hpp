@@ -512,76 +512,6 @@ __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src,
     }
 }
 
-// Band for the next step.  Two predictions of tau compete: the last one, and the last one extrapolated by its last change.
-// Each has a `swing` of its own, a maximum of its misses that decays by an eighth per step -- by a half while the last
-// miss was under 1/64 of it, so that very quiet rows narrow quickly -- and the one with the smaller swing is the band's
-// centre: the trend while thresholds drift, the last value where they go up and down from step to step, which a trend would
-// follow the wrong way (and with three times the variance of the noise).  The band's half width is six times that swing, for a trend never
-// less than twice the last change of tau, between kBandFloor and 2^25 key units.  After a step without a usable prediction
-// the band starts 2^20 keys wide on either side.  `far` remembers, four times as long, the largest miss of the better of
-// the two, and the half width is never less than twice that: thresholds that stand still for ten steps and then jump
-// (gradients of bf16 mantissas, by 2^16 keys) stay inside.  It is cut off at kBandStart, so that the large misses of a row's
-// first steps do not stay with it.
-// A band that misses costs two more passes over the row; one that is wider than needed only lengthens the
-// candidate list.  Against the trend alone, eight times its swing, over 64 steps with a new batch every step or two in turn: lists
-// a half to a fifth as long; 146 misses instead of 299 on 8 x 1M columns whose scale varies by 30 % between steps, 3 instead of 13 on 5 x 3M of bf16
-// mantissas.  us per step: 5 x 3M, 1 %, 85.8 -> 81.7; 4 x 5.5M, 1.1 %, 132 -> 117; 2 x 4.2M, 5 %, 103 -> 90.
-constexpr int kBandSwings = 6;
-__device__ __forceinline__ int64_t distance(int64_t a, int64_t b) { return a < b ? b - a : a - b; }
-__device__ __forceinline__ int64_t next_swing(int64_t last, int64_t miss) {
-    int64_t swing = 64 * miss < last ? last / 2 : last - last / 8;
-    if (swing < miss) swing = miss;
-    return swing > (int64_t)1 << 22 ? (int64_t)1 << 22 : swing;
-}
-__device__ __forceinline__ void predict_band(RowDesc& r, uint32_t fix_lo, uint32_t fix_hi) {
-    if (fix_hi) {                                   // random-k: the band does not depend on the data
-        r.lo = fix_lo;
-        r.hi = fix_hi;
-        r.prev_tau = r.tau;
-        r.have_prev = 1;
-        r.was_cold = 0;
-        return;
-    }
-    const int64_t tau = (int64_t)r.tau;
-    int64_t delta = r.have_prev ? tau - (int64_t)r.prev_tau : 0;
-    // a change of more than 2^22 keys (a factor of 1.4 in value) that the last prediction missed is a jump, not a
-    // trend: extrapolating it would put the next band as far off again
-    if (r.was_cold && (delta > ((int64_t)1 << 22) || delta < -((int64_t)1 << 22))) delta = 0;
-    int64_t swing = kBandStart, swing_still = kBandStart, far = 0;
-    int64_t margin = (int64_t)8 * kBandStart;
-    bool still = false;
-    if (r.have_prev) {
-        const int64_t miss = distance(tau, (int64_t)r.centre), miss_still = distance(tau, (int64_t)r.prev_tau);
-        const int64_t least = miss < miss_still ? miss : miss_still;
-        far = (int64_t)r.far - (int64_t)r.far / 32;
-        if (far < least) far = least < (int64_t)kBandStart ? least : (int64_t)kBandStart;
-        if (!r.was_cold) {
-            swing = next_swing((int64_t)r.swing, miss);
-            swing_still = next_swing((int64_t)r.swing_still, miss_still);
-            still = swing_still < swing;
-            margin = kBandSwings * (still ? swing_still : swing);
-        }
-    }
-    int64_t trend = tau + delta;
-    if (trend < 0) trend = 0;
-    if (trend > 0x7fffffffll) trend = 0x7fffffffll;
-    if (!still && margin < 2 * distance(delta, 0)) margin = 2 * distance(delta, 0);
-    if (margin < 2 * far) margin = 2 * far;
-    if (margin < (int64_t)kBandFloor) margin = kBandFloor;
-    if (margin > (int64_t)1 << 25) margin = (int64_t)1 << 25;   // two list digits cover a band of 2^26 keys
-    const int64_t centre = still ? tau : trend;
-    const int64_t lo = centre - margin, hi = centre + margin;
-    r.lo = lo < 0 ? 0u : (uint32_t)lo;
-    r.hi = hi > 0x80000000ll ? 0x80000000u : (uint32_t)hi;
-    r.centre = (uint32_t)trend;
-    r.swing = (uint32_t)swing;
-    r.swing_still = (uint32_t)swing_still;
-    r.far = (uint32_t)far;
-    r.prev_tau = r.tau;
-    r.have_prev = 1;
-    r.was_cold = 0;
-}
-
 // One pass of the block over the n listed entries, two entries per 128-bit load and eight loads in flight
 // per thread (a row's list starts 16-byte aligned): fn(entry, valid) is called in wave-uniform control
 // flow (valid false beyond n), so it may use wave_count.
@@ -776,22 +706,7 @@ __device__ __forceinline__ void put_result(RowDesc* __restrict__ desc, const Row
     if (threadIdx.x < kFirstLineWords)
         reinterpret_cast<uint32_t*>(desc)[threadIdx.x] = reinterpret_cast<const uint32_t*>(&now)[threadIdx.x];
 }
-// The end of a search over a list of n_all candidates whose result is in s (thread 0).
-__device__ __forceinline__ void finish_listed(RowDesc& r, const ListLds& s, uint32_t n_all, uint32_t form, bool cold, uint32_t missed,
-                                              uint32_t fix_lo, uint32_t fix_hi) {
-    r.n_list = n_all;
-    r.tau = s.tau;
-    r.rank = s.rank;
-    r.ties = s.nties;
-    r.cutoff = s.cut;
-    r.dense = r.general = 0;
-    r.form = form;
-    r.nonfinite = r.nonfinite_acc;
-    r.was_cold = cold ? 1u : 0u;
-    r.misses += missed;
-    predict_band(r, fix_lo, fix_hi);
-    r.mode = kWarm;
-}
+__device__ __forceinline__ ListFound found_in(const ListLds& s) { return ListFound{s.tau, s.rank, s.nties, s.cut}; }
 
 // grid = rows, kSelectBlock threads: finishes the list select of a row.  Which band the row's list was filtered
 // against -- the predicted one, or the first-digit bin picked (again, here) from the row's histogram --
@@ -854,7 +769,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         n = ph.count;
     }
     select_listed(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
-    if (tid == 0) finish_listed(now, s, n_all, form, cold, missed, 0u, 0u);
+    if (tid == 0) finish_listed(now, found_in(s), n_all, form, cold, missed, 0u, 0u);
     put_result(desc + row, now);
 }
 
@@ -898,39 +813,6 @@ __device__ __forceinline__ void slow_keys_at(const float* __restrict__ g, uint32
         key[2] = key_of(a.z);
         key[3] = key_of(a.w);
     }
-}
-
-// What a general search found.
-struct SlowFound {
-    uint32_t tau, rank, ties, cut, bad;
-    uint32_t first;                            // entries that share tau's first digit
-};
-// A candidate bitmap is worth having while most of the row is not in it (a constant row is read faster without one: 40M
-// columns packed in 63 us against 90).
-__device__ __forceinline__ bool bitmap_pays(const SlowFound& f, uint32_t k, uint32_t d) { return (uint64_t)(k - f.rank + f.ties) * 8 <= d; }
-// And what it leaves in the row's descriptor (thread 0).  degenerate: no candidate list could hold the row, so there is
-// no use in a prediction; form: of the row's candidate bitmap, 0 none.
-__device__ __forceinline__ void finish_general(RowDesc& r, const SlowFound& f, bool degenerate, uint32_t form, uint32_t fix_lo,
-                                               uint32_t fix_hi) {
-    r.tau = f.tau;
-    r.rank = f.rank;
-    r.ties = f.ties;
-    r.cutoff = f.cut;
-    r.dense = form ? 0u : 1u;
-    r.form = form;
-    r.general = degenerate ? 1u : 0u;
-    r.nonfinite = r.nonfinite_acc;
-    r.n_list = degenerate ? 0u : f.first;
-    if (degenerate && !fix_hi) {
-        r.have_prev = 0;
-        r.was_cold = 0;
-        r.mode = kCold;
-        return;
-    }
-    if (degenerate) r.have_prev = 0;           // the band of a random-k draw is known without a prediction
-    r.was_cold = 1;
-    predict_band(r, fix_lo, fix_hi);
-    r.mode = kWarm;
 }
 
 // One block on its own, histograms in LDS.
@@ -1058,8 +940,10 @@ __device__ __forceinline__ SlowEnd slow_multi(SlowLds& s, const float* __restric
     if (tid == 0) {
         s.bad = 0;
         s.dirty = ld_shared(&sync[2]);
+        s.ok = ld_shared(&sync[1]) == 0;
     }
     __syncthreads();
+    if (!s.ok) return kGaveUp;                                  // somebody's wait has run out before this block started
     // whatever an earlier, abandoned search left in the global histograms goes first
     if (s.dirty) {                                              // uniform for the block
         for (uint32_t q = b * 1024 + tid; q < kSlowHistWords; q += B * 1024) st_shared(&ghist[q], 0u);
@@ -1387,9 +1271,9 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     uint32_t* const words = reinterpret_cast<uint32_t*>(row_bits);
     uint2* const row_list = list + (size_t)row * cap;
     uint32_t* const sync = sh.sync + (size_t)blockIdx.y * kSyncWords;
-    const bool cold = now.mode != kWarm || !band_ok(now, cap, k);       // uniform for the row
-    // a row on its predicted band: its list
-    uint32_t lo = now.lo, width = now.hi - lo, n = now.n_cand, rank = k - sure_count(now);
+    const RowWork work = row_work(now, cap, k);                 // the same in every block of the row, however late it starts
+    const bool cold = work.cold;
+    uint32_t lo = work.lo, width = work.width, n = work.n, rank = work.rank;
     if (cold) {
         const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
         uint64_t* const groups = gbits ? gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4) : nullptr;
@@ -1505,7 +1389,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     }
     __syncthreads();
     select_listed(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
-    if (tid == 0) finish_listed(now, s.list, n, form, cold, 0u, fix_lo, fix_hi);
+    if (tid == 0) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
     put_result(desc + row, now);
     if (RK) mark_listed(row_list, n, s.list.tau, s.list.cut, words);
 }

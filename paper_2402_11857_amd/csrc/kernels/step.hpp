@@ -601,11 +601,11 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     }
 }
 
-// What the last kernel of a step with a threshold search leaves behind it: the rows' counters and the meeting points of
-// the blocks that share rows are zero, and the next compressed iteration makes the next draw.  None of its other blocks
-// looks at any of these.  (The grid has at least one thread a row.)
+// What the last kernel of a step with a threshold search leaves behind it: the rows are in the next step's mode, on its band
+// and with counters of zero, the meeting points of the blocks that share rows are zero, and the next compressed iteration
+// makes the next draw.  None of its other blocks looks at any of these.  (The grid has at least one thread a row.)
 struct StepTail {
-    uint32_t* counters;         // second line of the first row's descriptor
+    RowDesc* desc;              // [rows]; a pointer of its own, so that the kernel's loads of what it does not change stay scalar
     uint32_t* sync;             // [nsync]
     uint64_t* draw;             // random-k on a side, else null
     uint32_t rows, nsync;
@@ -613,14 +613,10 @@ struct StepTail {
 __device__ __forceinline__ void end_searches(const StepTail& t) {
     const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
     if (blockIdx.x * kBlock >= max(t.rows, t.nsync)) return;    // uniform for the block
-    if (q < t.rows) {
-        uint2* const c = reinterpret_cast<uint2*>(t.counters + (size_t)q * (sizeof(RowDesc) / 4));
-        c[0] = c[1] = c[2] = make_uint2(0u, 0u);
-    }
+    if (q < t.rows) next_step(t.desc[q]);
     if (q < t.nsync && (q & (kSyncWords - 1)) < 2) t.sync[q] = 0;      // (the third word is the searches' own)
     if (q == 0 && t.draw) *t.draw += 1;
 }
-static_assert(offsetof(RowDesc, n_cand) == 128 && offsetof(RowDesc, nonfinite_acc) == 148, "the six counters of the second line");
 
 // ---------------------------------------------------------------------------------------------
 // Server compression + error update + broadcast + local immediate compensation (Algorithm 1):

@@ -471,8 +471,7 @@ void launch_update(Launcher& L, const float* grads, float* x, float* e) {
     const uint32_t npanels = (c->ncol_tiles + panel - 1) / panel;
     const uint64_t blocks = (uint64_t)npanels * panel * (uint64_t)c->N;
     const bool draws = c->worker_comp == kRandk || c->server_comp == kRandk;
-    const StepTail tail{reinterpret_cast<uint32_t*>(c->desc) + offsetof(RowDesc, n_cand) / 4, c->slow_sync, draws ? &c->rk_state->draw : nullptr,
-                        (uint32_t)c->N + 1, c->slow_slots * kSyncWords};
+    const StepTail tail{c->desc, c->slow_sync, draws ? &c->rk_state->draw : nullptr, (uint32_t)c->N + 1, c->slow_slots * kSyncWords};
     L.begin(S_UPDATE);
     auto launch = [&](auto kernel) {
         kernel<<<(uint32_t)blocks, kBlock, 0, c->stream>>>(grads, x, c->vbuf, e, c->N, panel, c->ncol_tiles, (uint32_t)c->d,

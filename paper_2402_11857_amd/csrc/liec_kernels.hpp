@@ -8,7 +8,8 @@
 // result does not depend on compiler contraction.  Streams that are read or written once are
 // accessed with non-temporal hints.
 //
-// kernels/common.hpp     constants, row descriptor, random-k generator, accessors, reductions
+// kernels/rows.hpp       row descriptor of the threshold search and its changes from step to step (host and device)
+// kernels/common.hpp     constants, random-k generator, accessors, reductions
 // kernels/sign.hpp       scaled sign and blockwise scaled sign: L1 norms and sign bits
 // kernels/select.hpp     threshold search of top-k and random-k
 // kernels/step.hpp       aggregation (server compensation) and update (recompression, error, models)
