@@ -1147,7 +1147,7 @@ __global__ __launch_bounds__(1024) void k_slow_select(const float* __restrict__ 
     put_result(desc + row, s.now);
 }
 
-// Random-k: completes the kept bitmap of a row once (tau, cut-off) are known.  k_filter has set the
+// Random-k: completes the kept bitmap of a row once (tau, cut-off) are known.  The first pass has set the
 // bits of the columns whose key is above the band; here the listed candidates that are kept get
 // theirs (atomic OR on the 32-bit word holding the lane's half-word).
 __device__ __forceinline__ void mark_listed(const uint2* __restrict__ in, uint32_t n, uint32_t tau, uint32_t cut,
@@ -1167,8 +1167,9 @@ __device__ __forceinline__ void mark_listed(const uint2* __restrict__ in, uint32
         }
     }
 }
-// A row that went through the general search has no valid list: its priorities are
-// computed again and whole half-words written.
+// A row whose predicted band did not hold rank k: the first pass's bits are those of the wrong band.  Its priorities are
+// computed again and whole half-words written, by block 0 (3 ms for 25.6M columns, two draws of 10^6 for k = 1 and far
+// less often for larger k).
 __device__ __forceinline__ void mark_row(uint64_t stream, uint32_t d, uint32_t nwt, uint32_t tau, uint32_t cut,
                                          uint16_t* __restrict__ row_bits) {
     const uint32_t k0 = (uint32_t)stream, k1 = (uint32_t)(stream >> 32), lane = threadIdx.x & 63;
@@ -1200,12 +1201,14 @@ struct CollectLds {                            // the second pass of a row witho
     uint2 stage[kStage], wstage[kSelectBlock / 64][kWaveStage];
     uint32_t wsure[kSelectBlock / 64 + 1], staged[2];
 };
-// Lists the entries of keys [lo, lo + 2^19) of this block's share of the row, for block 0, and leaves their group bitmap
-// or, random-k, the bits of the keys above the band.
+// Lists the entries of keys [lo, lo + 2^19) of this block's share of the row, for block 0, and leaves their group bitmap.
+// (The kept bitmap of a random-k row is block 0's alone: a block that is still here when block 0's wait runs out, and
+// block 0 searches and marks the row by itself, would put the bits of the keys above the band in place of finished ones.
+// The group bitmap of a row that ends so is not used.)
 template <bool VEC, bool RK>
 __device__ __forceinline__ void collect_bin(CollectLds& s, const float* __restrict__ g, uint32_t d, uint32_t nwt, uint32_t lo,
                                             uint2* out, uint32_t cap, unsigned long long* counts, uint64_t* __restrict__ groups,
-                                            bool coarse, uint16_t* row_bits, uint64_t stream) {
+                                            bool coarse, uint64_t stream) {
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, B = gridDim.x;
     const uint32_t tpb = (nwt + B - 1) / B, t0 = min(blockIdx.x * tpb, nwt), t1 = min(t0 + tpb, nwt);
     FilterBand fb;
@@ -1224,21 +1227,18 @@ __device__ __forceinline__ void collect_bin(CollectLds& s, const float* __restri
         for (int u = 0; u < 4; ++u)
             slow_keys_at<VEC, RK>(g, d, (uint32_t)stream, (uint32_t)(stream >> 32), t * kWaveTile + u * kChunk + lane * 4, key[u]);
         uint64_t line_word = 0, fine = 0;
-        uint32_t sure16 = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = t * kWaveTile + u * kChunk + lane * 4;
             uint64_t bc[4];
             uint32_t hi4;
-            const uint64_t flags = filter_chunk<false, RK>(key[u], j, d, fb.lo, fb.hi, bc, n_hi, kmax, hi4);
-            sure16 |= hi4 << (4 * u);
+            const uint64_t flags = filter_chunk<false, false>(key[u], j, d, fb.lo, fb.hi, bc, n_hi, kmax, hi4);
             line_word |= any_of_four_lanes(flags) << u;
             fine = lane == (uint32_t)u ? flags : fine;
             stage_candidates<true>(fb, key[u], j, bc, s.stage, s.wstage[wave], wcnt, s.staged, lane);
         }
-        if (RK) {
-            st_shared(&row_bits[(size_t)t * 64 + lane], (uint16_t)sure16);      // block 0 adds the kept ones with atomics
-        } else if (coarse) {
+        if (RK) continue;
+        if (coarse) {
             if (lane == 0) groups[t] = line_word;
         } else if (lane < 4) {
             groups[(size_t)t * 4 + lane] = fine;
@@ -1268,7 +1268,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     __syncthreads();
     const uint32_t form = RK ? 0u : coarse ? 2u : 1u;
     uint16_t* const row_bits = RK ? kbits + (size_t)row * nwt * 64 : nullptr;
-    uint32_t* const words = reinterpret_cast<uint32_t*>(row_bits);
+    const uint64_t stream = RK ? rk_stream(rk.state->seed, rk.state->draw, row) : 0ull;
     uint2* const row_list = list + (size_t)row * cap;
     uint32_t* const sync = sh.sync + (size_t)blockIdx.y * kSyncWords;
     const RowWork work = row_work(now, cap, k);                 // the same in every block of the row, however late it starts
@@ -1277,7 +1277,6 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     if (cold) {
         const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
         uint64_t* const groups = gbits ? gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4) : nullptr;
-        const uint64_t stream = RK ? rk_stream(rk.state->seed, rk.state->draw, row) : 0ull;
         SlowFound f{0, 0, 0, 0, 0, 0};
         SlowEnd end = kGaveUp;
         if (gridDim.x > 1) {
@@ -1289,7 +1288,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                                       now.mode == kSlow ? 0u : cap, meetings, f);
             if (end == kListed) {                               // every block of the row
                 collect_bin<VEC, RK>(s.collect, g, d, nwt, f.tau << 19, row_list, cap,
-                                     reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, row_bits, stream);
+                                     reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, stream);
                 if (blockIdx.x != 0) {
                     slow_arrive(sync);
                     return;
@@ -1391,7 +1390,10 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     select_listed(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
     if (tid == 0) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
     put_result(desc + row, now);
-    if (RK) mark_listed(row_list, n, s.list.tau, s.list.cut, words);
+    if (RK) {
+        if (cold) mark_row(stream, d, nwt, s.list.tau, s.list.cut, row_bits);
+        else mark_listed(row_list, n, s.list.tau, s.list.cut, reinterpret_cast<uint32_t*>(row_bits));
+    }
 }
 
 }  // namespace liec

@@ -110,3 +110,64 @@ def test_a_shared_last_meeting_can_lose_the_result():
 def test_a_budget_of_zero_sends_every_row_to_block_0_alone():
     for blocks, writes in _explore(3, 3, 0, owner=1, protocol="block0_last_meeting"):
         assert blocks[0] == FAIL and writes == 1
+
+
+def _explore_listed(B, budget, collect_writes):
+    """A random-k row without a usable band: after the first-digit meeting every block lists its share of the digit's bin, and
+    block 0, after a last meeting, selects among the entries listed and marks the row's kept bitmap share by share.  When one of
+    its waits runs out it searches alone and marks the row the same way.  collect_writes: while they list, the blocks
+    also store the bits of the keys above the band into their own share of the bitmap (one step).  Returns the bitmaps
+    that can be left when every block has ended: per share 0 nothing, 1 above the band only, 2 finished."""
+    # a block: ("meet", phase, polls), phase as above; ("list",); ("last", phase, polls) of block 0; ("mark", share); "end"
+    finals, seen = set(), set()
+    stack = [((("meet", 0, 0),) * B, 0, 0, (0,) * B)]
+    while stack:
+        state = stack.pop()
+        if state in seen:
+            continue
+        seen.add(state)
+        blocks, arrivals, flag, bits = state
+        if all(b == "end" for b in blocks):
+            finals.add(bits)
+            continue
+        for b, me in enumerate(blocks):
+            if me == "end":
+                continue
+            nb, na, nf, nbits = list(blocks), arrivals, flag, list(bits)
+            gave_up = ("mark", 0) if b == 0 else "end"
+            if me[0] in ("meet", "last"):
+                where, phase, polls = me
+                target = B if where == "meet" else 2 * B
+                if phase == 0:
+                    na += 1
+                    nb[b] = (where, 1, 0) if where == "meet" or b == 0 else "end"     # at the last one only block 0 waits
+                elif phase == 1:
+                    if polls >= budget or flag:
+                        nf = 1
+                        nb[b] = gave_up
+                    else:
+                        nb[b] = (where, 2, polls)
+                elif arrivals >= target:
+                    nb[b] = ("list",) if where == "meet" else ("mark", 0)
+                else:
+                    nb[b] = (where, 1, polls + 1)
+            elif me[0] == "list":
+                if collect_writes:
+                    nbits[b] = 1
+                nb[b] = ("last", 0, 0)
+            else:
+                nbits[me[1]] = 2
+                nb[b] = ("mark", me[1] + 1) if me[1] + 1 < B else "end"
+            stack.append((tuple(nb), na, nf, tuple(nbits)))
+    return finals
+
+
+@pytest.mark.parametrize("B,budget", itertools.product([2, 3], [0, 1, 2]))
+def test_a_kept_bitmap_that_only_block_0_writes_is_finished_in_the_end(B, budget):
+    assert _explore_listed(B, budget, collect_writes=False) == {(2,) * B}
+
+
+def test_a_kept_bitmap_that_the_listing_blocks_write_too_can_lose_kept_columns():
+    """Block 0's wait runs out while another block still lists: that block's store follows block 0's."""
+    lost = [bits for bits in _explore_listed(2, 1, collect_writes=True) if 1 in bits]
+    assert (2, 1) in lost
