@@ -41,10 +41,14 @@ liec_status liec_force_search_mode(liec_ctx *ctx, int32_t mode);
 liec_status liec_get_search_state(liec_ctx *ctx, int32_t row, uint32_t *out);
 
 /*
- * Testing aid for the general search (mode 4 above, also what constant or
- * mostly-zero rows fall to): several thread blocks share a row and wait for one
- * another between its phases; `polls` bounds each wait (default 65536, about 0.2 s).
- * A wait that runs out is not an error: one block then repeats the search on its
+ * Testing aid for the searches in which several thread blocks share a row and wait
+ * for one another between their phases: the general search (mode 4 above, also what
+ * constant or mostly-zero rows fall to) and, on short rows and for random-k, any
+ * search without a usable prediction and any over a long candidate list.  `polls`
+ * bounds each wait (default: one poll per 1024 columns of a row, at least 64 and at
+ * most 65536, about what one block takes for the search: 0.7 ms at 10^6 columns, 42 ms
+ * at most; a wait over a list of n candidates ends after 64 + n / 1024 at the latest).
+ * A wait that runs out is not an error: one block then does the search on its
  * own, with the same result.  0 makes every wait run out at once, which is how the
  * tests reach that path.  LIEC_EINVAL for a negative value.
  */

@@ -96,6 +96,16 @@ LIEC_HD bool wants_cold(const RowDesc& r, uint32_t cap, uint32_t k) {
     return r.mode == kCold || (r.mode == kWarm && !band_ok(r, cap, k));
 }
 
+// Bounds, in polls, of the waits of blocks that share a row for one another.  Blocks of two launches on two streams can each
+// be resident in part and wait for the rest, so a wait lasts no longer than block 0 needs to do the work alone: 0.58 us
+// per wave tile of 1024 columns for a search of the row, about 15 us for a list and a third of a microsecond per 1024 entries
+// of a long one; a poll takes 0.25 us, from the 65th on 0.65.  (A meeting takes 3 us.)
+LIEC_HD uint32_t search_wait(uint32_t nwt) { return nwt < 64u ? 64u : nwt < 65536u ? nwt : 65536u; }
+LIEC_HD uint32_t list_wait(uint32_t bound, uint32_t n) {
+    const uint32_t polls = 64u + n / 1024u;
+    return polls < bound ? polls : bound;
+}
+
 // What a row needs of the kernel that finishes searches (k_select).  Every block of the row derives it for itself, whenever it
 // starts: block 0 may have finished the row by then.
 struct RowWork {

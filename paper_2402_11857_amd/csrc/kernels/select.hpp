@@ -1114,7 +1114,7 @@ struct SharedRows {
     uint32_t* cnt;                             // [rows * kSlowMaxBlocks] ties per block
     uint32_t* list_hist;                       // [rows * B * 256] first list digit per block
     uint32_t* sync;                            // [rows * kSyncWords]; arrivals and give-up flag zero when a step starts (see the update)
-    uint32_t spin_limit;                       // bound, in polls, of the waits
+    uint32_t spin_limit;                       // bound, in polls, of the waits (those for a share of a list are shorter)
 };
 
 // The top-k rows in kSlow mode (long rows; k_select does it for short ones).
@@ -1338,7 +1338,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         }
         __syncthreads();
         if (tid < 256) st_shared(&hists[blockIdx.x * 256 + tid], h[tid]);
-        const bool ok = slow_meet(met, sync, nb, sh.spin_limit);
+        const bool ok = slow_meet(met, sync, nb, list_wait(sh.spin_limit, n));
         if (!ok && blockIdx.x != 0) return;
         if (ok) {
             uint32_t sum = 0;
@@ -1377,7 +1377,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                     slow_arrive(sync);
                     return;
                 }
-                if (slow_meet(met, sync, 2 * nb, sh.spin_limit)) {
+                if (slow_meet(met, sync, 2 * nb, list_wait(sh.spin_limit, n))) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                     first = false;
                     in = out;

@@ -158,7 +158,7 @@ struct liec_ctx {
     uint32_t short_cap = kShortCap;
     // general (degenerate-row) search: B thread blocks share a row when B * rows fit the chip
     uint32_t slow_bw = 1, slow_bs = 1;         // blocks per worker row / for the server's vector
-    uint32_t slow_spin = 1u << 16;             // bound, in polls, of the waits between those blocks
+    uint32_t slow_spin = 0;                    // bound, in polls, of the waits between those blocks
     uint32_t* slow_hist = nullptr;             // [rows that share * kSlowHistWords] digit histograms
     uint32_t* slow_cnt = nullptr;              // [rows that share * kSlowMaxBlocks] ties per block
     uint32_t* slow_sync = nullptr;             // [rows that share * kSyncWords] arrivals, give-up flag, histograms not zero
@@ -631,6 +631,7 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     const uint32_t un = (uint32_t)N;
     c->nwt = (uint32_t)((d + kWaveTile - 1) / kWaveTile);
     c->ncol_tiles = (uint32_t)((d + kColTile - 1) / kColTile);
+    c->slow_spin = search_wait(c->nwt);
     const uint32_t blk_iters = (c->nwt + 3) / 4;               // block iterations that cover one row
     auto clampu = [](uint32_t v, uint32_t lo, uint32_t hi) { return v < lo ? lo : (v > hi ? hi : v); };
     // Grid sizes come from sweeps on the VGG-16- and ResNet-shaped workloads.  Every block gets the same

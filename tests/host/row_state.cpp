@@ -56,6 +56,16 @@ int main() {
             r = now;
         }
     }
+    // a wait that runs out has cost no more than block 0 takes to do the work alone (us, as measured; see the bounds)
+    for (uint32_t nwt = 17; nwt < (1u << 21); nwt += 1 + nwt / 7) {
+        const uint32_t polls = search_wait(nwt);
+        const double waited = 64 * 0.25 + (polls - 64) * 0.65, alone = 15 + 0.58 * nwt;
+        if (waited > 1.2 * alone || (nwt < 65536 && waited < 0.25 * alone)) {
+            if (failed++ < 5) std::printf("%u tiles: a wait of %.0f us against a search of %.0f\n", nwt, waited, alone);
+        }
+        const uint32_t n = nwt * 64, short_wait = list_wait(polls, n);     // the longest list of the row
+        if (short_wait > polls || short_wait > 64 + n / 1024) ++failed;
+    }
     if (!warm || !cold || !moved) ++failed;
     std::printf("%s: %d rows on a list, %d without, %d bands moved\n", failed ? "FAILED" : "row state ok", warm, cold, moved);
     return failed != 0;
