@@ -71,9 +71,10 @@ typedef struct {
                                  among entries whose key equals server_tau_key     */
     int32_t nonfinite;        /* 1 if a NaN/Inf reached an L1 sum or a top-k key   */
     int32_t slow_rows;        /* top-k / random-k: rows (workers + server) whose last
-                                 threshold search fell to the general single-block
-                                 search -- constant or near-constant rows; results are
-                                 exact either way, such rows only take much longer   */
+                                 threshold search was the general one -- constant or
+                                 near-constant rows, or thread blocks that waited for
+                                 one another in vain; results are exact either way, such
+                                 rows only take longer                               */
     int64_t band_misses;      /* top-k: row-steps, since the context was created, whose
                                  threshold fell outside the band predicted from the
                                  previous steps, so that the row needed two more passes

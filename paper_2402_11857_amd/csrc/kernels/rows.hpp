@@ -37,7 +37,7 @@ struct alignas(128) RowDesc {
     uint32_t nonfinite;    // a NaN/Inf reached the L1 sum or a key (last step)
     uint32_t lo, hi;       // candidate band: keys in [lo, hi) are listed, keys >= hi are surely kept
     uint32_t mode;         // SelMode
-    uint32_t n_list;       // candidates that were listed when the search finished (random-k marks the kept ones)
+    uint32_t n_list;       // candidates listed in the last step (0 after a general search), for whoever asks
     uint32_t dense;        // the row's candidate bitmap is not valid: test every column
     uint32_t form;         // top-k worker: form of that bitmap, 1 a bit per 4 columns, 2 per 64-byte line, 0 not valid or none yet
     uint32_t prev_tau;     // tau of the step before (valid when have_prev)
@@ -49,7 +49,7 @@ struct alignas(128) RowDesc {
     uint32_t far;          // a slowly decaying maximum of the smaller of the two distances
     uint32_t was_cold;     // the last band came from the first-digit histogram, not from a prediction
     uint32_t next_lo, next_hi, next_mode;      // band and mode of the next step, which the update kernel puts into force
-    uint32_t general;      // the last step took the general search because no list could hold the row's candidates
+    uint32_t general;      // the last step took the general search: no list could hold the row's candidates, a caller asked for it, or a wait ran out
     // second line: what the blocks of the passes add to with atomics (kept off the line every block reads when
     // it starts).  Counters of the pass over the predicted band, one 64-bit word that a block of the filter adds
     // to with a single atomic.  Low half: candidates appended (may exceed the capacity: overflow); high half:
@@ -226,9 +226,9 @@ LIEC_HD void finish_general(RowDesc& r, const SlowFound& f, bool degenerate, uin
     r.cutoff = f.cut;
     r.dense = form ? 0u : 1u;
     r.form = form;
-    r.general = degenerate ? 1u : 0u;
+    r.general = 1;
     r.nonfinite = r.nonfinite_acc;
-    r.n_list = degenerate ? 0u : f.first;
+    r.n_list = 0;
     if (degenerate && !fix_hi) {
         r.have_prev = 0;
         r.was_cold = 0;

@@ -47,6 +47,10 @@ int main() {
                 if (failed++ < 5) std::printf("chain %d step %d: a block that starts after the row is finished sees other work\n", chain, step);
             }
             const RowDesc done = now;
+            const bool listed = !work.cold || how == 0;                     // what is reported of the search
+            if (done.general != (listed ? 0u : 1u) || done.n_list != (listed ? work.n : 0u)) {
+                if (failed++ < 5) std::printf("chain %d step %d: general %u, %u listed\n", chain, step, done.general, done.n_list);
+            }
             next_step(now);
             if (now.lo != done.next_lo || now.hi != done.next_hi || now.mode != done.next_mode || now.tau != tau || now.n_cand || now.n_sure ||
                 now.nonfinite_acc || now.hi - now.lo > (1u << (2 * kListBits))) {

@@ -50,3 +50,26 @@ def test_search_modes_and_waits_in_any_order(wc, sc, N, d, wk, sk, uniform):
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}: mode {mode}, wait {wait}"
             if mode == 4:
                 assert ctx.info().slow_rows == (N if wk else 0) + (1 if sk else 0), f"step {t}"
+
+
+def test_a_search_that_one_block_repeated_is_reported():
+    """Rows without a prediction are listed by the blocks that share them; when their waits run out block 0 searches the whole
+    row, which counts as a general search."""
+    say("case report of searches whose waits ran out")
+    from paper_2402_11857_amd import LiecContext
+
+    N, d, k = 3, 70_001, 700
+    g = torch.randn((N, d), dtype=torch.float32, device=DEV)
+    x, e = torch.zeros_like(g), torch.zeros(d, dtype=torch.float32, device=DEV)
+    with LiecContext(N, d, "topk", "topk", k, k, 0.05) as ctx:
+        for wait in (WAIT, 0, WAIT):
+            ctx.force_search_mode(1)
+            ctx.set_search_wait(wait)
+            ctx.step(g, x, e)
+            assert ctx.info().slow_rows == (0 if wait else N + 1), wait
+            for row in range(N + 1):
+                st = ctx.search_state(row)
+                assert (st["general_search"], st["listed"] > 0) == ((0, True) if wait else (1, False)), (wait, row, st)
+            ctx.set_search_wait(WAIT)
+            ctx.step(g, x, e)                                   # on the band that either search predicts
+            assert ctx.info().slow_rows == 0
