@@ -514,10 +514,17 @@ __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src,
 
 // One pass of the block over the n listed entries, two entries per 128-bit load and eight loads in flight
 // per thread (a row's list starts 16-byte aligned): fn(entry, valid) is called in wave-uniform control
-// flow (valid false beyond n), so it may use wave_count.
+// flow (valid false beyond n), so it may use wave_count.  fresh: blocks of this launch wrote the entries (put_entry<true>);
+// they are then loaded past the caches, one at a time (an acquire fence instead, which drops an L2's lines, took 8 us).
 constexpr int kSelectBlock = 1024;
+__device__ __forceinline__ uint4 two_entries(const uint4* __restrict__ at, bool fresh) {
+    if (!fresh) return *at;                                     // uniform
+    const unsigned long long* const e = reinterpret_cast<const unsigned long long*>(at);
+    const unsigned long long a = ld_shared(e), b = ld_shared(e + 1);
+    return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+}
 template <typename F>
-__device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, uint32_t n, F fn) {
+__device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, uint32_t n, bool fresh, F fn) {
     const uint32_t tid = threadIdx.x;
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     const uint32_t npairs = (n + 1) / 2;                    // the slot after an odd n is inside the row's capacity
@@ -526,7 +533,7 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t e = base + q * kSelectBlock + tid;
-            a[q] = e < npairs ? in2[e] : make_uint4(0u, 0u, 0u, 0u);
+            a[q] = e < npairs ? two_entries(&in2[e], fresh) : make_uint4(0u, 0u, 0u, 0u);
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -540,13 +547,13 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 // for_each_listed for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once
 // by hold_listed, walked by every pass of the select instead of going back to memory).
 constexpr uint32_t kHeldMax = 16u * kSelectBlock;
-__device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, uint4 (&a)[8]) {
+__device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, bool fresh, uint4 (&a)[8]) {
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     const uint32_t npairs = (n + 1) / 2;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const uint32_t e = q * kSelectBlock + threadIdx.x;
-        a[q] = e < npairs ? in2[e] : make_uint4(0u, 0u, 0u, 0u);
+        a[q] = e < npairs ? two_entries(&in2[e], fresh) : make_uint4(0u, 0u, 0u, 0u);
     }
 }
 template <typename F>
@@ -578,17 +585,17 @@ static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the 
 // in: n entries with keys in [lo, lo + width), `rank`: how many from the top the searched one is.  first: the first digit
 // is not known yet (it has first_shift(width, .) bits below it); otherwise ph and shift say what is.  Every thread of the
 // block calls it; the result is in s (all threads see it).
-__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
-                                              uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
+__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, bool fresh, uint32_t lo,
+                                              uint32_t width, uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     uint32_t* const h = s.h;
     // a list of up to kHeldMax entries is read once and kept in registers for all the passes below
     const bool held = n <= kHeldMax;                            // uniform for the block
     uint4 own[8];
-    if (held) hold_listed(in, n, own);
+    if (held) hold_listed(in, n, fresh, own);
     auto walk = [&](auto fn) {
         if (held) for_each_held(own, n, fn);
-        else for_each_listed(in, n, fn);
+        else for_each_listed(in, n, fresh, fn);
     };
     if (first) {
         // first digit of every listed key, in LDS
@@ -768,7 +775,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
         n = ph.count;
     }
-    select_listed(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
+    select_listed(s, in, n, false, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
     if (tid == 0) finish_listed(now, found_in(s), n_all, form, cold, missed, 0u, 0u);
     put_result(desc + row, now);
 }
@@ -886,11 +893,14 @@ __device__ __forceinline__ SlowFound slow_single(SlowLds& s, const float* __rest
 // for its own stores.  With a device-wide fence (an L2 written back and its stale lines dropped) in every one
 // of the blocks' 16 waves a meeting took 0.1 ms: a general search of 8 x 262144 columns, 5 meetings, 580 us; with one fence a
 // block 55.
-__device__ __forceinline__ void slow_arrive(uint32_t* __restrict__ sync) {
+__device__ __forceinline__ void slow_written() {                // what the block has stored past the L2 is there for all to load
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
     __syncthreads();
+}
+__device__ __forceinline__ void slow_arrive(uint32_t* __restrict__ sync) {
+    slow_written();
     if (threadIdx.x == 0) atomicAdd(&sync[0], 1u);
 }
 __device__ __forceinline__ bool slow_meet(uint32_t& ok_lds, uint32_t* __restrict__ sync, uint32_t target, uint32_t spin_limit) {
@@ -913,7 +923,7 @@ __device__ __forceinline__ bool slow_meet(uint32_t& ok_lds, uint32_t* __restrict
     return ok_lds != 0;
 }
 
-// The B blocks of a row together.  Only block 0's return value matters: kGaveUp when one of its waits ran out (the
+// The B blocks of a row together (one block on its own has nothing to hand over, to meet for or to give up).  Only block 0's return value matters: kGaveUp when one of its waits ran out (the
 // caller then repeats the search on block 0 alone), kFound when `found` is the result.  A block other than 0 whose
 // wait runs out just leaves (block 0 then fails its next wait, because the give-up flag is set or the
 // arrivals never add up).  groups: the row's candidate bitmap (top-k, in the form that k_filter writes), for which the
@@ -933,14 +943,15 @@ __device__ __forceinline__ SlowEnd slow_multi(SlowLds& s, const float* __restric
                               uint32_t spin_limit, uint64_t* __restrict__ groups, bool coarse, uint32_t list_cap, uint32_t& meetings,
                               SlowFound& found) {
     const uint32_t B = gridDim.x, b = blockIdx.x;
+    const bool shared = B > 1;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t tpb = (nwt + B - 1) / B;                     // wave tiles per block: a contiguous range of the row
     const uint32_t t0 = min(b * tpb, nwt), t1 = min(t0 + tpb, nwt);
     meetings = 0;
     if (tid == 0) {
         s.bad = 0;
-        s.dirty = ld_shared(&sync[2]);
-        s.ok = ld_shared(&sync[1]) == 0;
+        s.dirty = shared ? ld_shared(&sync[2]) : 0u;
+        s.ok = shared ? ld_shared(&sync[1]) == 0 : 1u;
     }
     __syncthreads();
     if (!s.ok) return kGaveUp;                                  // somebody's wait has run out before this block started
@@ -972,13 +983,15 @@ __device__ __forceinline__ SlowEnd slow_multi(SlowLds& s, const float* __restric
             }
         }
         __syncthreads();
-        for (int q = tid; q < nbins; q += 1024) {
-            const uint32_t c = s.h[q];
-            if (c) atomicAdd(&ghist[off + q], c);
+        if (shared) {
+            for (int q = tid; q < nbins; q += 1024) {
+                const uint32_t c = s.h[q];
+                if (c) atomicAdd(&ghist[off + q], c);
+            }
+            if (!slow_meet(s.ok, sync, B * ++meetings, spin_limit)) return kGaveUp;
+            for (int q = tid; q < nbins; q += 1024) s.h[q] = ld_shared(&ghist[off + q]);
+            __syncthreads();
         }
-        if (!slow_meet(s.ok, sync, B * ++meetings, spin_limit)) return kGaveUp;
-        for (int q = tid; q < nbins; q += 1024) s.h[q] = ld_shared(&ghist[off + q]);
-        __syncthreads();
         if (pass == 0 && !RK) {                       // keys >= 0x7f800000 (Inf/NaN) sit in the bins from 0xff0 up
             if (tid < 16 && s.h[0xff0 + tid] != 0) s.bad = 1;
         }
@@ -1022,31 +1035,34 @@ __device__ __forceinline__ SlowEnd slow_multi(SlowLds& s, const float* __restric
             }
         }
     }
-    const uint32_t total = block_sum_u32(mine, s.wtot);         // valid on thread 0
-    if (tid == 0) st_shared(&gcnt[b], total);
-    // Last meeting.  From here on block 0 alone speaks for the row: the other blocks publish their count,
-    // arrive and leave without waiting, so no block can pass this meeting while the one that would have
-    // written the result gives up.  Block 0 either sees every count and walks the range that holds the
-    // rank-th tie itself (1/B of the row), or its wait runs out and the caller repeats the search alone.
-    ++meetings;
-    if (b != 0) {
-        slow_arrive(sync);
-        return kFound;
-    }
-    if (!slow_meet(s.ok, sync, B * meetings, spin_limit)) return kGaveUp;
-    clear_slow_hist(ghist, sync);
-    if (tid < (uint32_t)kSlowMaxBlocks) s.part[tid] = tid < B ? ld_shared(&gcnt[tid]) : 0u;
-    __syncthreads();
-    uint32_t before = 0, owner = B;
-    for (uint32_t q = 0; q < B; ++q) {                          // uniform for the block
-        const uint32_t here = s.part[q];
-        if (before < rank && rank <= before + here) {
-            owner = q;
-            break;
+    uint32_t before = 0, owner = 0;
+    if (shared) {
+        const uint32_t total = block_sum_u32(mine, s.wtot);     // valid on thread 0
+        if (tid == 0) st_shared(&gcnt[b], total);
+        // Last meeting.  From here on block 0 alone speaks for the row: the other blocks publish their count,
+        // arrive and leave without waiting, so no block can pass this meeting while the one that would have
+        // written the result gives up.  Block 0 either sees every count and walks the range that holds the
+        // rank-th tie itself (1/B of the row), or its wait runs out and the caller repeats the search alone.
+        ++meetings;
+        if (b != 0) {
+            slow_arrive(sync);
+            return kFound;
         }
-        before += here;
+        if (!slow_meet(s.ok, sync, B * meetings, spin_limit)) return kGaveUp;
+        clear_slow_hist(ghist, sync);
+        if (tid < (uint32_t)kSlowMaxBlocks) s.part[tid] = tid < B ? ld_shared(&gcnt[tid]) : 0u;
+        __syncthreads();
+        owner = B;
+        for (uint32_t q = 0; q < B; ++q) {                      // uniform for the block
+            const uint32_t here = s.part[q];
+            if (before < rank && rank <= before + here) {
+                owner = q;
+                break;
+            }
+            before += here;
+        }
+        if (owner == B) return kGaveUp;                         // counts that do not add up to the histogram: search alone
     }
-    if (owner == B) return kGaveUp;                             // counts that do not add up to the histogram: search alone
     const uint32_t need = rank - before;
     const uint32_t w0 = min(owner * tpb, nwt), w1 = min(w0 + tpb, nwt);   // the owner's range of wave tiles
     if (tid == 0) s.cut = 0xffffffffu;
@@ -1278,31 +1294,25 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
         uint64_t* const groups = gbits ? gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4) : nullptr;
         SlowFound f{0, 0, 0, 0, 0, 0};
-        SlowEnd end = kGaveUp;
-        if (gridDim.x > 1) {
-            uint32_t* const hist = sh.hist + (size_t)blockIdx.y * kSlowHistWords;
-            uint32_t meetings;
-            // (a caller can send a row through the whole of the general search)
-            end = slow_multi<VEC, RK>(s.slow, g, d, nwt, k, (uint32_t)stream, (uint32_t)(stream >> 32), hist,
-                                      sh.cnt + (size_t)blockIdx.y * kSlowMaxBlocks, sync, sh.spin_limit, groups, coarse,
-                                      now.mode == kSlow ? 0u : cap, meetings, f);
-            if (end == kListed) {                               // every block of the row
-                collect_bin<VEC, RK>(s.collect, g, d, nwt, f.tau << 19, row_list, cap,
-                                     reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, stream);
-                if (blockIdx.x != 0) {
-                    slow_arrive(sync);
-                    return;
-                }
-                if (slow_meet(met, sync, gridDim.x * (meetings + 1), sh.spin_limit)) {
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // the list is read with plain loads
-                    clear_slow_hist(hist, sync);
-                } else {
-                    end = kGaveUp;
-                }
+        uint32_t* const hist = sh.hist + (size_t)blockIdx.y * kSlowHistWords;
+        uint32_t meetings;
+        // (a caller can send a row through the whole of the general search)
+        SlowEnd end = slow_multi<VEC, RK>(s.slow, g, d, nwt, k, (uint32_t)stream, (uint32_t)(stream >> 32), hist,
+                                          sh.cnt + (size_t)blockIdx.y * kSlowMaxBlocks, sync, sh.spin_limit, groups, coarse,
+                                          now.mode == kSlow ? 0u : cap, meetings, f);
+        if (end == kListed) {                                   // every block of the row
+            collect_bin<VEC, RK>(s.collect, g, d, nwt, f.tau << 19, row_list, cap,
+                                 reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, stream);
+            if (blockIdx.x != 0) {
+                slow_arrive(sync);
+                return;
             }
-            if (blockIdx.x != 0) return;
-            if (end == kGaveUp && tid == 0) sync[2] = 1;
+            if (gridDim.x == 1) slow_written();
+            else if (slow_meet(met, sync, gridDim.x * (meetings + 1), sh.spin_limit)) clear_slow_hist(hist, sync);
+            else end = kGaveUp;
         }
+        if (blockIdx.x != 0) return;
+        if (end == kGaveUp && tid == 0) sync[2] = 1;            // (a block on its own never gives up)
         if (end == kGaveUp) f = slow_single<VEC, RK>(s.slow, g, d, k, (uint32_t)stream, (uint32_t)(stream >> 32));
         if (tid == 0) {
             now.misses += now.mode == kWarm ? 1u : 0u;          // there was a prediction and it failed
@@ -1324,7 +1334,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     uint32_t n_in = n;
     const uint32_t nb = !cold && n > (uint32_t)kDirectList ? list_blocks_for(n, gridDim.x) : 1u;
     if (blockIdx.x >= nb) return;
-    bool first = true;
+    bool first = true, fresh = cold;
     Pick ph{0, 0, 0};
     const int shift = first_shift(width, kFirstBits);
     if (nb > 1) {
@@ -1378,8 +1388,8 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                     return;
                 }
                 if (slow_meet(met, sync, 2 * nb, list_wait(sh.spin_limit, n))) {
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                     first = false;
+                    fresh = true;
                     in = out;
                     n_in = ph.count;
                 }
@@ -1387,7 +1397,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         }
     }
     __syncthreads();
-    select_listed(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
+    select_listed(s.list, in, n_in, fresh, lo, width, rank, first, ph, shift, d);
     if (tid == 0) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
     put_result(desc + row, now);
     if (RK) {

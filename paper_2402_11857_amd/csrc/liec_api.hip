@@ -735,12 +735,13 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         c->slow_bs = clampu(std::min((uint32_t)cus, useful), 1u, (uint32_t)kSlowMaxBlocks);
         const size_t slots = (c->slow_bw > 1 ? (size_t)N : 0) + (c->slow_bs > 1 ? 1 : 0);
         // The search behind the first pass in one launch instead of four: us per step in one launch against four,
-        // in the steady state and (in brackets) without predictions, top-k on both sides, 1 %: 32 x 16384 38 against 46
-        // (59, 65), 8 x 1M 54 against 63 (96, 106), 5 x 3M 87 against 97 (144, 157), 32 x 1M 133 against 144 (204, 202),
-        // 8 x 4.2M 142 against 154 (219, 228).  Beyond, the launches are under 3 % of a step and the passes of a row without a prediction
-        // have too few blocks: 2 x 16.8M 199 against 204 (362, 312).  Random-k rows always know their band: 8 x 1M 44
-        // against 72, 32 x 4.2M 406 against 452, 32 x 25.6M, 0.1 %, 1810 against 1850 (with the server's draw in the workers'
-        // launches).
+        // in the steady state and (in brackets) without predictions, top-k on both sides, 1 %: 32 x 16384 42 against 51
+        // (59, 67), 8 x 1M 58 against 68 (88, 104), 5 x 3M 91 against 102 (143, 155), 32 x 1M 137 against 150 (176, 203),
+        // 8 x 4.2M 151 against 168 (212, 226), 2 x 8.4M 140 against 145 (213, 207); with few blocks a row, or one, 64 x 65536
+        // 72 against 81 (96, 101), 140 x 200000 180 against 192 (223, 238), 1000 x 16384 628 against 643 (637, 685).  On longer
+        // rows the passes without a prediction have too few blocks: 2 x 16.8M 212 against 214 (383, 288).  Random-k rows always
+        // know their band: 8 x 1M 44 against 72, 32 x 4.2M 406 against 452, 32 x 25.6M, 0.1 %, 1810 against 1850 (with the
+        // server's draw in the workers' launches).
         c->w_one = worker_comp == LIEC_COMP_RANDK || (c->nwt <= 8192u && (uint64_t)c->nwt * un <= 32768u);
         c->s_one = server_comp == LIEC_COMP_RANDK || c->nwt <= 4096u;
         c->slow_slots = (uint32_t)slots;

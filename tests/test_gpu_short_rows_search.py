@@ -73,3 +73,29 @@ def test_a_search_that_one_block_repeated_is_reported():
             ctx.set_search_wait(WAIT)
             ctx.step(g, x, e)                                   # on the band that either search predicts
             assert ctx.info().slow_rows == 0
+
+
+@pytest.mark.parametrize("N,d", [(1, 16_384), (129, 5), (129, 1024), (140, 17_001), (300, 3000)])
+def test_rows_that_one_block_searches_are_listed_like_any_other(N, d):
+    """Short rows and many rows: one block a row.  Without a prediction it makes the first digit's list and the candidate
+    bitmap (ties and zeros among the values: the bin of one key, the bin of zeros)."""
+    say(f"case rows of one block N={N} d={d}")
+    import oracle
+    from paper_2402_11857_amd import LiecContext
+
+    rng = np.random.default_rng(d)
+    k = max(1, d // 50)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, "topk", "topk", k, k, 0.05) as ctx:
+        for t, mode in enumerate([None, 1, 0, 4, 1]):
+            g = rng.standard_normal((N, d), dtype=np.float32)
+            if t == 4:
+                g = np.where(rng.random((N, d)) < 0.3, np.round(g * 4) / 4, 0).astype(np.float32)
+            if mode is not None:
+                ctx.force_search_mode(mode)
+            ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+            torch.cuda.synchronize()
+            oracle.step(g, x, e, "topk", "topk", 0.05, k, k)
+            assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
+            assert ctx.info().slow_rows == (N + 1 if mode == 4 else 0), f"step {t}"
