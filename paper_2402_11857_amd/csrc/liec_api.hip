@@ -93,6 +93,7 @@ hipError_t static_scratch(double** out) {
 // 42.4 against 46.6, 8 x 1M 63.6 against 67.2, 8 x 4.2M 164 against 168; even at 8 x 8M and 8 x 11.7M, where every
 // tile's block adds to the row's one counter word.
 constexpr uint32_t kAggFilterTiles = 4096;
+constexpr uint64_t kFoldSums = 512;                             // most partial sums that the aggregation finishes itself
 constexpr uint32_t kAggChunkBlocks = 65536;                     // most blocks of the aggregation by chunk
 static_assert(kAggFilterTiles <= kAggChunkBlocks, "a block that filters v has one tile");
 
@@ -643,12 +644,16 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // the scaled-sign pass streams best as one 4096-column iteration per block
     c->row_blocks = balanced(1u << 20);
     // Scaled sign on both sides, rows of middling length: blocks of 16 waves leave a quarter of the partial sums, few enough
-    // for the kernels that use the scales to finish them (both sides: two launches less).  us per step with and without:
-    // 8 x 524288 columns 23.0 against 26.0, 4 x 1M 25.6 against 28.2, 2 x 2.1M 30.1 against 31.1, 16 x 262144 23.8 against 26.5,
-    // 16 x 524288 36.6 against 37.3, 8 x 1M 36.9 against 38.6; beyond, the sums are too many again.
-    if (worker_comp == LIEC_COMP_SIGN && server_comp == LIEC_COMP_SIGN && N <= kFoldRows && c->nwt * un > 2048u && c->nwt * un <= 8192u) {
+    // (512) for the aggregation to finish the workers' itself.  us per step with and without: 8 x 524288 columns 23.0 against
+    // 26.0, 16 x 262144 23.8 against 26.5, 6 x 512000 19.5 against 21.9, 4 x 1M 24.7 against 26.8, 8 x 1M 36.1 against 37.5, 2 x 2.1M
+    // 29.6 against 30.0.  On longer rows every one of the aggregation's many blocks adds up a long row's sums, 128 in a round of
+    // loads: 2 x 2.6M 36.5 against 33.6, 1 x 2.6M 30.7 against 28.1, 1 x 8.2M 62.5 against 52.6.  With more than 512 sums in all the wide
+    // blocks alone cost: 5 x 1.68M (515) 41.9 against 40.8.
+    const uint32_t wide_blocks = (c->nwt + 15) / 16;
+    if (worker_comp == LIEC_COMP_SIGN && server_comp == LIEC_COMP_SIGN && N <= kFoldRows && c->nwt * un > 2048u && wide_blocks <= 129u &&
+        wide_blocks * un <= kFoldSums) {
         c->row_threads = 1024;
-        c->row_blocks = (c->nwt + 15) / 16;
+        c->row_blocks = wide_blocks;
     }
     // the filter pays one atomic on the row's counters per block: about 1024 long-lived blocks per row
     // (more when there are too few rows to fill the chip)
@@ -673,7 +678,7 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
     // (1024 partials) the aggregation took 3 us longer and the step 26.4 against 25.7.  A wave forms its workers' scales
     // one after another, 0.5 us each however short the rows: sign / identity, 16 x 16384 13.3 against 13.4, 24 x 16384
     // 16.1 against 14.8, 64 x 16384 30.2 against 21.6.
-    c->fold_workers = worker_comp == LIEC_COMP_SIGN && N <= kFoldRows && (uint64_t)N * c->row_blocks <= 512u;
+    c->fold_workers = worker_comp == LIEC_COMP_SIGN && N <= kFoldRows && (uint64_t)N * c->row_blocks <= kFoldSums;
     auto balanced_filter = [&](uint32_t max_blocks) {
         const uint32_t iters = (c->nwt + 4 * c->filter_run - 1) / (4 * c->filter_run);
         const uint32_t per = (iters + max_blocks - 1) / max_blocks;
