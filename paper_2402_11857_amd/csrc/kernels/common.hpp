@@ -118,16 +118,17 @@ __device__ __forceinline__ float4 ld4(const float* __restrict__ row, uint32_t j,
     return r;
 }
 
-// The 16 columns of this lane of a whole wave tile (all of them below d), as streaming loads.  No branch stands around the
+// The 16 columns of this lane of a whole wave tile (all of them below d), as streaming loads unless NT is false.  No branch stands around the
 // accesses: with the one that ld4 needs at the end of a row off a 16-byte boundary, the compiler does not keep a wave's four
 // loads together.  7 x 7.3M + 1 columns: first pass of scaled sign 40.5 -> 35.9 us (as aligned rows), blockwise 42.9 -> 36.9;
 // the update and the averaging kernels, one load of a kind at a time, gain nothing by it.
-template <bool VEC>
+template <bool VEC, bool NT = true>
 __device__ __forceinline__ void ld_tile(const float* __restrict__ row, uint32_t t, uint32_t lane, float4 (&a)[4]) {
     typedef typename Vec4<VEC>::type vec;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const vec w = __builtin_nontemporal_load(reinterpret_cast<const vec*>(row + (size_t)t * kWaveTile + u * kChunk + lane * 4));
+        const vec* const p = reinterpret_cast<const vec*>(row + (size_t)t * kWaveTile + u * kChunk + lane * 4);
+        const vec w = NT ? __builtin_nontemporal_load(p) : *p;
         a[u] = make_float4(w.x, w.y, w.z, w.w);
     }
 }

@@ -62,15 +62,19 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
     __shared__ float folded[FOLD ? kFoldRows : 1];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     // FOLD: what the first tile needs is requested ahead of the sums, or its latency comes on top of theirs (here and in the
-    // update, with sums in the vector unit: 8 x 262144 columns 17.5 -> 15.3 us a step, 16 x 65536 17.2 -> 14.6)
+    // update, with sums in the vector unit: 8 x 262144 columns 17.4 -> 14.8 us a step, 16 x 65536 16.7 -> 14.0).  Not
+    // the tile that holds the row's end: among its guards the compiler waits for one of the loads before it asks for
+    // the sums (so for all tiles, 1 x 65536 11.2 us instead of 10.7, slower than without the requests).
     uint32_t m0[8];
     float4 e0[4];
+    bool e_ahead = false;
     if (FOLD) {
         const uint32_t t = min(blockIdx.x * 4 + wave, nwt - 1);
 #pragma unroll
-        for (int r = 0; r < 8; ++r) m0[r] = bits[((size_t)min(r, N - 1) * nwt + t) * 64 + lane];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) e0[u] = ld4<VEC>(e_in, t * kWaveTile + lane * 4 + u * kChunk, d);
+        for (int r = 0; r < 8; ++r)
+            if (r < N) m0[r] = bits[((size_t)r * nwt + t) * 64 + lane];         // uniform
+        e_ahead = (t + 1) * (uint32_t)kWaveTile <= d;           // wave-uniform
+        if (e_ahead) ld_tile<VEC, false>(e_in, t, lane, e0);
         // a wave's share of the workers: wave, wave + 4, ..
         double s[kFoldRows / 4];
         wave_l1(w_partial + (size_t)wave * w_parts, (size_t)4 * w_parts, (N - (int)wave + 3) / 4, w_parts, lane, s);
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = j0 + u * kChunk;
-            const float4 e = FOLD && tb == blockIdx.x * 4 ? e0[u] : ld4<VEC>(e_in, j, d);
+            const float4 e = FOLD && e_ahead && tb == blockIdx.x * 4 ? e0[u] : ld4<VEC>(e_in, j, d);
             float4 v;
             v.x = __fmaf_rn(acc[u].x, inv_n, e.x);
             v.y = __fmaf_rn(acc[u].y, inv_n, e.y);
