@@ -154,7 +154,7 @@ struct liec_ctx {
     uint64_t* vodd = nullptr;                  // [nwt * 4] groups of 4 columns in which v is not finite (identity workers, random-k server)
     uint64_t* sgbits = nullptr;                // [nwt * 4] group bitmap of the server's candidates in v (top-k server), fine form
     uint2* list = nullptr;                     // [(N + 1) * cap] candidates (key, index)
-    uint32_t* ghist = nullptr;                 // [(N + 1) * kHistBins] first digit of a row (12 bits) or of its list (8 bits)
+    uint32_t* ghist = nullptr;                 // [(N + 1) * kHistBins] first digit of a row (12 bits) or of its list (8 bits); long rows only
     uint2* shortl = nullptr;                   // [(N + 1) * short_cap] listed entries of the first list digit's bin
     uint32_t short_cap = kShortCap;
     // general (degenerate-row) search: B thread blocks share a row when B * rows fit the chip
@@ -725,10 +725,6 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         e = dev_alloc(c, &c->vodd, (size_t)c->nwt * 4);
     if (e == hipSuccess && server_comp == LIEC_COMP_TOPK) e = dev_alloc(c, &c->sgbits, (size_t)c->nwt * 4);
     if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->list, rows * c->cap);
-    if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->ghist, rows * kHistBins);
-    // (a row that one block searches on its own has no use for it; up to 129 rows: 16 MiB)
-    c->short_cap = N <= 128 ? kShortCapOne : (uint32_t)kShortCap;
-    if (e == hipSuccess && any_topk) e = dev_alloc(c, &c->shortl, rows * c->short_cap);
     if (e == hipSuccess && any_topk) {
         // blocks that share a row meet inside the kernel, so all of them must be resident at once:
         // at most one per compute unit
@@ -749,12 +745,21 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         // server's draw in the workers' launches).
         c->w_one = worker_comp == LIEC_COMP_RANDK || (c->nwt <= 8192u && (uint64_t)c->nwt * un <= 32768u);
         c->s_one = server_comp == LIEC_COMP_RANDK || c->nwt <= 4096u;
+        const bool one = (selects_k((int)worker_comp) && c->w_one) || (selects_k((int)server_comp) && c->s_one);
+        const bool several = (selects_k((int)worker_comp) && !c->w_one) || (selects_k((int)server_comp) && !c->s_one);
+        // the histograms that the several launches hand to one another
+        if (several) e = dev_alloc(c, &c->ghist, rows * kHistBins);
+        if (several && e == hipSuccess) e = hipMemsetAsync(c->ghist, 0, rows * kHistBins * sizeof(uint32_t), c->stream);
+        // (a row that one block searches on its own has no use for the longer one; up to 129 rows: 16 MiB)
+        c->short_cap = one && N <= 128 ? kShortCapOne : (uint32_t)kShortCap;
+        if (e == hipSuccess) e = dev_alloc(c, &c->shortl, rows * c->short_cap);
         c->slow_slots = (uint32_t)slots;
         if (slots) {
-            e = dev_alloc(c, &c->slow_hist, slots * kSlowHistWords);
+            if (e == hipSuccess) e = dev_alloc(c, &c->slow_hist, slots * kSlowHistWords);
             if (e == hipSuccess) e = dev_alloc(c, &c->slow_cnt, slots * kSlowMaxBlocks);
             if (e == hipSuccess) e = dev_alloc(c, &c->slow_sync, slots * kSyncWords);
-            if (e == hipSuccess) e = dev_alloc(c, &c->list_hist, ((size_t)un * c->slow_bw + c->slow_bs) * 256);
+            const size_t sharing = (c->slow_bw > 1 ? (size_t)un * c->slow_bw : 0) + (c->slow_bs > 1 ? c->slow_bs : 0);
+            if (e == hipSuccess && one) e = dev_alloc(c, &c->list_hist, sharing * 256);
             if (e == hipSuccess) e = hipMemsetAsync(c->slow_sync, 0, slots * kSyncWords * sizeof(uint32_t), c->stream);
             if (e == hipSuccess) e = hipMemsetAsync(c->slow_hist, 0, slots * kSlowHistWords * sizeof(uint32_t), c->stream);
         }
@@ -772,7 +777,6 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         }
         e = hipMemcpy(c->desc, init.data(), rows * sizeof(RowDesc), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess && any_topk) e = hipMemsetAsync(c->ghist, 0, rows * kHistBins * sizeof(uint32_t), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
