@@ -24,13 +24,13 @@ ALSO = ["c3_resnet18_sign", "c3_resnet18_blocksign", "c4_resnet50_topk", "c4_res
         "c1_tiny_sign", "c2_topk_mid"]
 # small configurations whose tensors fit the caches and whose step is a chain of short dependent kernels
 CACHE_RESIDENT = {"c1_tiny_sign": "1 MiB of gradients: cache-resident, bound by the latencies of 3 dependent kernels",
-                  "c2_topk_mid": "32 MiB of gradients: cache-resident, bound by the latencies of 11 dependent kernels"}
+                  "c2_topk_mid": "32 MiB of gradients: cache-resident, bound by the latencies of 5 dependent kernels"}
 N_GRAD_BUFFERS = 4          # distinct gradient batches rotated through the timed steps
 REPEATS = 5                 # timed regions per workload; the median one is reported
 # kernels that make up a steady-state step (the rest of a profile summary -- cold and general search,
 # averaging iteration, wire forms, copy probe -- is not part of it)
 STEADY_STATE_KERNELS = ("k_update", "k_filter", "k_aggregate", "k_l1_bits", "k_l1_final", "k_l1_items", "k_list_",
-                        "k_rk_zero", "k_rk_filter_inverse", "k_rk_mark", "k_rk_advance")
+                        "k_select", "k_rk_zero", "k_rk_filter_inverse")
 
 
 def profile_traffic(workload: str):

@@ -515,7 +515,8 @@ __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src,
 // One pass of the block over the n listed entries, two entries per 128-bit load and eight loads in flight
 // per thread (a row's list starts 16-byte aligned): fn(entry, valid) is called in wave-uniform control
 // flow (valid false beyond n), so it may use wave_count.  fresh: blocks of this launch wrote the entries (put_entry<true>);
-// they are then loaded past the caches, one at a time (an acquire fence instead, which drops an L2's lines, took 8 us).
+// they are then loaded past the caches, one at a time (an acquire fence instead drops an L2's lines, once for every wave of the
+// block: a step without predictions of 64 x 65536 columns 104 us against 78).
 constexpr int kSelectBlock = 1024;
 __device__ __forceinline__ uint4 two_entries(const uint4* __restrict__ at, bool fresh) {
     if (!fresh) return *at;                                     // uniform
@@ -1205,12 +1206,12 @@ __device__ __forceinline__ void mark_row(uint64_t stream, uint32_t d, uint32_t n
 
 // ---------------------------------------------------------------------------------------------
 // Everything that follows the pass over the predicted band, in one launch, for rows on which what a launch costs (2 us)
-// counts: five launches of a steady-state step become one.  grid = (B, rows), kSelectBlock threads.
+// counts: four launches of a steady-state top-k step become one.  grid = (B, rows), kSelectBlock threads.
 // Block 0 finishes a row whose list holds rank k and is short; up to B blocks share a longer list's first digit (each
 // leaves a histogram of its share, all add them up, and the entries of the digit's bin go to the row's short list); all B
 // share the search of a row without a usable list: the first digit of the whole row, then a list of the entries of
 // the bin that holds rank k, or, when those are too many, the rest of the general search.  Which of the three it is every
-// block decides by itself from the mode and the counters of the
+// block decides by itself from the mode, the band and the counters of the
 // first pass, which this kernel leaves as they are: block 0 may have finished the row before another block starts.
 // ---------------------------------------------------------------------------------------------
 struct CollectLds {                            // the second pass of a row without a usable prediction

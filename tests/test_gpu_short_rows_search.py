@@ -13,7 +13,7 @@ from _gpu import DEV, GPU_MARKS, say  # noqa: E402
 
 pytestmark = GPU_MARKS
 
-WAIT = 1 << 16                                                  # the default bound
+WAIT = 1 << 16                                                  # longer than any wait by default
 # (mode of the search, bound of its waits): after a wait that ran out the next search finds its histograms not zero
 STEPS = [(None, WAIT), (0, WAIT), (1, 0), (1, WAIT), (4, 3), (0, WAIT), (4, WAIT), (1, 2), (0, 0), (0, WAIT), (4, 0), (1, WAIT)]
 
