@@ -514,18 +514,19 @@ __global__ __launch_bounds__(kBlock) void k_hist0(const float* __restrict__ src,
 
 // One pass of the block over the n listed entries, two entries per 128-bit load and eight loads in flight
 // per thread (a row's list starts 16-byte aligned): fn(entry, valid) is called in wave-uniform control
-// flow (valid false beyond n), so it may use wave_count.  fresh: blocks of this launch wrote the entries (put_entry<true>);
-// they are then loaded past the caches, one at a time (an acquire fence instead drops an L2's lines, once for every wave of the
-// block: a step without predictions of 64 x 65536 columns 104 us against 78).
+// flow (valid false beyond n), so it may use wave_count.  SHARED: blocks of this launch may have written the entries
+// (put_entry<true>); they are then loaded past the caches, one at a time (an acquire fence instead drops an L2's lines, once for
+// every wave of the block: a step without predictions of 64 x 65536 columns 104 us against 78).
 constexpr int kSelectBlock = 1024;
-__device__ __forceinline__ uint4 two_entries(const uint4* __restrict__ at, bool fresh) {
-    if (!fresh) return *at;                                     // uniform
+template <bool SHARED>
+__device__ __forceinline__ uint4 two_entries(const uint4* __restrict__ at) {
+    if (!SHARED) return *at;
     const unsigned long long* const e = reinterpret_cast<const unsigned long long*>(at);
     const unsigned long long a = ld_shared(e), b = ld_shared(e + 1);
     return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
 }
-template <typename F>
-__device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, uint32_t n, bool fresh, F fn) {
+template <bool SHARED, typename F>
+__device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, uint32_t n, F fn) {
     const uint32_t tid = threadIdx.x;
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     const uint32_t npairs = (n + 1) / 2;                    // the slot after an odd n is inside the row's capacity
@@ -534,7 +535,7 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t e = base + q * kSelectBlock + tid;
-            a[q] = e < npairs ? two_entries(&in2[e], fresh) : make_uint4(0u, 0u, 0u, 0u);
+            a[q] = e < npairs ? two_entries<SHARED>(&in2[e]) : make_uint4(0u, 0u, 0u, 0u);
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -548,13 +549,14 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 // for_each_listed for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once
 // by hold_listed, walked by every pass of the select instead of going back to memory).
 constexpr uint32_t kHeldMax = 16u * kSelectBlock;
-__device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, bool fresh, uint4 (&a)[8]) {
+template <bool SHARED>
+__device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, uint4 (&a)[8]) {
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     const uint32_t npairs = (n + 1) / 2;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const uint32_t e = q * kSelectBlock + threadIdx.x;
-        a[q] = e < npairs ? two_entries(&in2[e], fresh) : make_uint4(0u, 0u, 0u, 0u);
+        a[q] = e < npairs ? two_entries<SHARED>(&in2[e]) : make_uint4(0u, 0u, 0u, 0u);
     }
 }
 template <typename F>
@@ -586,17 +588,18 @@ static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the 
 // in: n entries with keys in [lo, lo + width), `rank`: how many from the top the searched one is.  first: the first digit
 // is not known yet (it has first_shift(width, .) bits below it); otherwise ph and shift say what is.  Every thread of the
 // block calls it; the result is in s (all threads see it).
-__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, bool fresh, uint32_t lo,
-                                              uint32_t width, uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
+template <bool SHARED>
+__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
+                                              uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     uint32_t* const h = s.h;
     // a list of up to kHeldMax entries is read once and kept in registers for all the passes below
     const bool held = n <= kHeldMax;                            // uniform for the block
     uint4 own[8];
-    if (held) hold_listed(in, n, fresh, own);
+    if (held) hold_listed<SHARED>(in, n, own);
     auto walk = [&](auto fn) {
         if (held) for_each_held(own, n, fn);
-        else for_each_listed(in, n, fresh, fn);
+        else for_each_listed<SHARED>(in, n, fn);
     };
     if (first) {
         // first digit of every listed key, in LDS
@@ -776,7 +779,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
         n = ph.count;
     }
-    select_listed(s, in, n, false, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
+    select_listed<false>(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
     if (tid == 0) finish_listed(now, found_in(s), n_all, form, cold, missed, 0u, 0u);
     put_result(desc + row, now);
 }
@@ -1335,7 +1338,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     uint32_t n_in = n;
     const uint32_t nb = !cold && n > (uint32_t)kDirectList ? list_blocks_for(n, gridDim.x) : 1u;
     if (blockIdx.x >= nb) return;
-    bool first = true, fresh = cold;
+    bool first = true;
     Pick ph{0, 0, 0};
     const int shift = first_shift(width, kFirstBits);
     if (nb > 1) {
@@ -1390,7 +1393,6 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
                 }
                 if (slow_meet(met, sync, 2 * nb, list_wait(sh.spin_limit, n))) {
                     first = false;
-                    fresh = true;
                     in = out;
                     n_in = ph.count;
                 }
@@ -1398,7 +1400,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         }
     }
     __syncthreads();
-    select_listed(s.list, in, n_in, fresh, lo, width, rank, first, ph, shift, d);
+    select_listed<true>(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
     if (tid == 0) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
     put_result(desc + row, now);
     if (RK) {
