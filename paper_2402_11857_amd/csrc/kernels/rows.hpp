@@ -128,9 +128,11 @@ LIEC_HD RowWork row_work(const RowDesc& r, uint32_t cap, uint32_t k) {
 // (gradients of bf16 mantissas, by 2^16 keys) stay inside.  It is cut off at kBandStart, so that the large misses of a row's
 // first steps do not stay with it.
 // A band that misses costs two more passes over the row; one that is wider than needed only lengthens the
-// candidate list.  Against the trend alone, eight times its swing, over 64 steps with a new batch every step or two in turn: lists
-// a half to a fifth as long; 146 misses instead of 299 on 8 x 1M columns whose scale varies by 30 % between steps, 3 instead of 13 on 5 x 3M of bf16
-// mantissas.  us per step: 5 x 3M, 1 %, 85.8 -> 81.7; 4 x 5.5M, 1.1 %, 132 -> 117; 2 x 4.2M, 5 %, 103 -> 90.
+// candidate list.  Against the trend alone, eight times its swing, us per step of two batches in turn: 8 x 1M columns, 1 %, 53.8 -> 52.6,
+// 5 x 3M of bf16 mantissas 105 -> 98.5.  Means over 56 steps whose gradient scale changes, steps without a usable prediction among
+// them (row-steps that missed in brackets): a random walk of 5 % a step 83 -> 79 (63, 1) and 130 -> 120 (42, 2), 30 % of noise
+// 81 -> 79 (148, 73) and 134 -> 125 (101, 46), 30 % up and down in turn 94 -> 89 (289, 257) and 183 -> 151 (200, 161), growth by 10 % a
+// step 83 -> 80 and 121 -> 119.
 constexpr int kBandSwings = 6;
 LIEC_HD int64_t distance(int64_t a, int64_t b) { return a < b ? b - a : a - b; }
 LIEC_HD int64_t next_swing(int64_t last, int64_t miss) {
