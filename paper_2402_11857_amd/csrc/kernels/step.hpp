@@ -691,8 +691,8 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
     // One stream at a time per wave: waiting for the gradients before asking for the model measured
     // 2-4 % faster than having both 128-bit loads in flight.
     // The sign bits of v have arrived by then, and their half-words are in a register: with the shift next to the load, under
-    // the branch for i != 0, the compiler waits for them before it asks for the gradients (us per step: top-k / sign 16 x 138M
-    // 6490 -> 6290, blockwise 7 x 7.3M 172.5 -> 167.5, scaled sign 16 x 11.7M even).
+    // the branch for i != 0, the compiler waits for them before it asks for the gradients (blockwise 7 x 7.3M + 1 columns 172.2 -> 167.9 us a
+    // step; scaled sign 16 x 11.7M and top-k / sign 16 x 138M even).
     if (!FOLD) asm volatile("s_waitcnt vmcnt(0)" : "+v"(sbits)::"memory");
 #endif
     const float4 xv = FOLD ? x0 : ld4<VEC, true>(xi, j, d);
