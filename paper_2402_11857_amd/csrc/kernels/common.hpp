@@ -147,6 +147,16 @@ __device__ __forceinline__ void st4(float* __restrict__ row, uint32_t j, uint32_
     }
 }
 
+// A value that no block of the running kernel writes: with an address that is the same for the whole wave it comes through the scalar
+// cache into scalar registers, also in loops that store elsewhere.
+template <typename T>
+__device__ __forceinline__ T ld_const(const T* p) {
+    return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+__device__ __forceinline__ float lane_value(float v, uint32_t lane) {     // lane: the same for the whole wave
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), (int)lane));
+}
+
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {   // set bits of mask below this lane
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }

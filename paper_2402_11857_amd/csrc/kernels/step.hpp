@@ -67,14 +67,12 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
     // the sums (so for all tiles, 1 x 65536 11.2 us instead of 10.7, slower than without the requests).
     uint32_t m0[8];
     float4 e0[4];
-    bool e_ahead = false;
     if (FOLD) {
         const uint32_t t = min(blockIdx.x * 4 + wave, nwt - 1);
 #pragma unroll
         for (int r = 0; r < 8; ++r)
             if (r < N) m0[r] = bits[((size_t)r * nwt + t) * 64 + lane];         // uniform
-        e_ahead = (t + 1) * (uint32_t)kWaveTile <= d;           // wave-uniform
-        if (e_ahead) ld_tile<VEC, false>(e_in, t, lane, e0);
+        if ((t + 1) * (uint32_t)kWaveTile <= d) ld_tile<VEC, false>(e_in, t, lane, e0);
         // a wave's share of the workers: wave, wave + 4, ..
         double s[kFoldRows / 4];
         wave_l1(w_partial + (size_t)wave * w_parts, (size_t)4 * w_parts, (N - (int)wave + 3) / 4, w_parts, lane, s);
@@ -95,57 +93,55 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
         const uint32_t t = tb + wave;
         if (!ITEMS && t >= nwt) break;
         const uint32_t j0 = t * kWaveTile + lane * 4;
-        const uint2 entry = ITEMS ? items.tile[tb / 4] : make_uint2(0u, 0u);
+        const bool ahead = FOLD && tb == blockIdx.x * 4;        // requested ahead of the sums
+        const uint64_t ent = ITEMS ? ld_const(reinterpret_cast<const uint64_t*>(items.tile) + tb / 4) : 0ull;
+        const bool whole = (t + 1) * (uint32_t)kWaveTile <= d;  // wave-uniform
+        // Blockwise: e is requested ahead of the bits, and the rows' scales come with one load, a lane each, instead of one
+        // scalar load after the other (3 x 99.4M columns 1130 -> 1080 us a step, 4 x 5.8M 90.4 -> 89.6, 7 x 7.3M 167.2 -> 165.7).  Scaled
+        // sign, whose waves are more and shorter, only loses by the registers that takes (16 x 11.7M 514 -> 517).
+        if (WC == kBlockSign && whole) ld_tile<VEC, false>(e_in, t, lane, e0);
         float4 acc[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (ITEMS && t >= nwt) {                                // a wave without a tile still takes part in the block's sums
-        } else if (WC == kSign) {
+        } else {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
-            auto scale_of = [&](int i) { return FOLD ? folded[i] : desc[i].scale; };
-            int i = 0;
-            if (FOLD && tb == blockIdx.x * 4) {                 // the ones requested ahead
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-                    if (r < N) add_signed(acc, m0[r], scale_of(r));     // uniform
-                i = 8;
-            }
-            for (; i + 8 <= N; i += 8) {                       // 8 rows of bits in flight
-                uint32_t m[8];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) m[r] = bw[(size_t)(i + r) * brow];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) add_signed(acc, m[r], scale_of(i + r));
-            }
-            if (i < N) {                                        // and the rest of them
-                uint32_t m[7];
-#pragma unroll
-                for (int r = 0; r < 7; ++r) m[r] = bw[(size_t)min(i + r, N - 1) * brow];
-#pragma unroll
-                for (int r = 0; r < 7; ++r)
-                    if (i + r < N) add_signed(acc, m[r], scale_of(i + r));      // uniform
-            }
-        } else if (WC == kBlockSign) {
-            const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
-            const size_t brow = (size_t)nwt * 64;
-            const uint32_t tb = bt.tile_blk[t], first = tb & 0x7fffffffu;
-            if (!(tb >> 31)) {                                  // the whole wave tile lies in one block
+            const uint32_t tblk = WC == kBlockSign ? ld_const(bt.tile_blk + t) : 0u, first = tblk & 0x7fffffffu;
+            if (WC == kSign) {
+                auto scale_of = [&](int i) { return FOLD ? folded[i] : desc[i].scale; };
                 int i = 0;
-                for (; i + 8 <= N; i += 8) {
+                if (ahead) {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r)
+                        if (r < N) add_signed(acc, m0[r], scale_of(r));     // uniform
+                    i = 8;
+                }
+                for (; i + 8 <= N; i += 8) {                    // 8 rows of bits in flight
                     uint32_t m[8];
 #pragma unroll
                     for (int r = 0; r < 8; ++r) m[r] = bw[(size_t)(i + r) * brow];
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) add_signed(acc, m[r], bt.scales[(size_t)(i + r) * bt.B + first]);
+                    for (int r = 0; r < 8; ++r) add_signed(acc, m[r], scale_of(i + r));
                 }
-                if (i < N) {
+                if (i < N) {                                    // and the rest of them
                     uint32_t m[7];
 #pragma unroll
                     for (int r = 0; r < 7; ++r) m[r] = bw[(size_t)min(i + r, N - 1) * brow];
 #pragma unroll
                     for (int r = 0; r < 7; ++r)
-                        if (i + r < N) add_signed(acc, m[r], bt.scales[(size_t)(i + r) * bt.B + first]);
+                        if (i + r < N) add_signed(acc, m[r], scale_of(i + r));      // uniform
+                }
+            } else if (!(tblk >> 31)) {                         // the whole wave tile lies in one block
+                float sc = 0.f;                                 // lane i: scale of the i-th of 64 rows
+                for (int i = 0; i < N; i += 8) {
+                    if ((i & 63) == 0 && i + (int)lane < N) sc = bt.scales[(size_t)(i + lane) * bt.B + first];
+                    uint32_t m[8];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) m[r] = bw[(size_t)min(i + r, N - 1) * brow];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r)
+                        if (i + r < N) add_signed(acc, m[r], lane_value(sc, (uint32_t)(i + r) & 63));     // uniform
                 }
             } else {
                 uint32_t bidx[16];
@@ -171,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = j0 + u * kChunk;
-            const float4 e = FOLD && e_ahead && tb == blockIdx.x * 4 ? e0[u] : ld4<VEC>(e_in, j, d);
+            const float4 e = (WC == kBlockSign || ahead) && whole ? e0[u] : ld4<VEC>(e_in, j, d);
             float4 v;
             v.x = __fmaf_rn(acc[u].x, inv_n, e.x);
             v.y = __fmaf_rn(acc[u].y, inv_n, e.y);
@@ -189,7 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
         }
         // a scaled-sign server's message is these bits and one scale: the update kernel reads them instead of v
         if (vbits && (!ITEMS || t < nwt)) vbits[(size_t)t * 64 + lane] = (uint16_t)vm;
-        if (ITEMS) l1_of_tile(items, entry, j0, acc, lds_w, item_partial);
+        if (ITEMS) l1_of_tile(items, make_uint2((uint32_t)ent, (uint32_t)(ent >> 32)), j0, acc, lds_w, item_partial);
     }
     if (SRV_L1) {
         const double s = block_sum_f64(l1, lds_w);
