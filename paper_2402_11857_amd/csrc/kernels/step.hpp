@@ -451,10 +451,14 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     FilterBand fb{};
     bool filter = false;                                        // uniform: the server's row has a predicted band
     uint32_t n_hi = 0, kmax = 0, wcnt = 0;
-    if (SRV_FILTER) {
-        filter = filter_band(desc, (uint32_t)N, false, nullptr, sf.list, sf.cap, sf.k, nullptr, nullptr, fb);
+    if (SRV_FILTER) {                                           // (what filter_band does for a first pass, without a branch or a wait here)
+        filter = ld_const(&desc[N].mode) == kWarm;
+        fb.lo = ld_const(&desc[N].lo);
+        fb.hi = ld_const(&desc[N].hi);
+        fb.out = sf.list + (size_t)N * sf.cap;
+        fb.cap = sf.cap;
+        fb.counts = reinterpret_cast<unsigned long long*>(&desc[N].n_cand);
         if (threadIdx.x < 2) staged[threadIdx.x] = 0;
-        __syncthreads();
     }
     const uint32_t u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // my chunk of the tile
     double l1 = 0.0;
@@ -498,21 +502,29 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
             const size_t grow = coarse ? (size_t)nwt : (size_t)nwt * 4;
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             for (int i0 = 0; i0 < N; i0 += kRows) {
-                uint32_t pick[kRows], tau[kRows], cut[kRows];
+                // requested together and without a branch among them: under one for each row the compiler waits for a row's words
+                // before it asks for the next row's
+                uint32_t pick[kRows], tau[kRows], cut[kRows], dense[kRows];
+                uint64_t w[kRows];
 #pragma unroll
                 for (int r = 0; r < kRows; ++r) {
-                    const int i = i0 + r;
-                    pick[r] = tau[r] = cut[r] = 0;
-                    if (i < N) {                                // uniform
-                        if (WC == kRandk) {
-                            pick[r] = ((uint32_t)bw[(size_t)i * nwt * 64] >> (4 * u)) & 0xfu;
-                        } else {
-                            tau[r] = desc[i].tau;
-                            cut[r] = desc[i].cutoff;
-                            const uint64_t w = gw[(size_t)i * grow];
-                            pick[r] = desc[i].dense ? 1u
-                                                    : (uint32_t)(w >> (coarse ? 4 * (lane >> 2) + u : lane)) & 1u;
-                        }
+                    const int i = min(i0 + r, N - 1);
+                    if (WC == kRandk) {
+                        pick[r] = bw[(size_t)i * nwt * 64];
+                    } else {
+                        tau[r] = ld_const(&desc[i].tau);
+                        cut[r] = ld_const(&desc[i].cutoff);
+                        dense[r] = ld_const(&desc[i].dense);
+                        w[r] = ld_const(gw + (size_t)i * grow);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    if (WC == kRandk) {
+                        pick[r] = i0 + r < N ? (pick[r] >> (4 * u)) & 0xfu : 0u;
+                    } else {
+                        if (dense[r]) w[r] = ~0ull;             // uniform
+                        pick[r] = i0 + r < N ? (uint32_t)(w[r] >> (coarse ? 4 * (lane >> 2) + u : lane)) & 1u : 0u;
                     }
                 }
                 float4 gq[kRows];
@@ -568,6 +580,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
             const uint64_t odd = __ballot(any_nonfinite(v.x, v.y, v.z, v.w));
             if (lane == 0) vodd[(size_t)t * 4 + u] = odd;
         }
+        if (SRV_FILTER) __syncthreads();                        // the stage's counters are set (a block that filters has one tile)
         if (SRV_FILTER && filter) {
             const uint32_t keys[4] = {key_of(v.x), key_of(v.y), key_of(v.z), key_of(v.w)};
             uint64_t bc[4];
