@@ -469,30 +469,35 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
         if (WC == kBlockSign) {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
-            const uint32_t tb = bt.tile_blk[t], first = tb & 0x7fffffffu;
+            const uint32_t tb = ld_const(bt.tile_blk + t), first = tb & 0x7fffffffu;
             uint32_t blk[4] = {first, first, first, first};
             if (tb >> 31) {               // the tile spans a block boundary
 #pragma unroll
                 for (int q = 0; q < 4; ++q) blk[q] = block_of(bt, first, j + q < d ? j + q : d - 1);
             }
+            // lane i: scale of the i-th of 64 rows (a tile in one block), one load instead of a scalar one after the other (us per step:
+            // 8 x 1M 41.9 -> 40.1, 20 x 104143 33.9 -> 29.0, blockwise / sign 64 x 500000 125 -> 109)
+            float sc = 0.f;
             for (int i0 = 0; i0 < N; i0 += kRows) {
+                if (!(tb >> 31) && (i0 & 63) == 0 && i0 + (int)lane < N) sc = bt.scales[(size_t)(i0 + lane) * bt.B + first];
                 uint32_t m[kRows];
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) m[r] = i0 + r < N ? (uint32_t)bw[(size_t)(i0 + r) * brow] >> (4 * u) : 0u;
+                for (int r = 0; r < kRows; ++r) m[r] = bw[(size_t)min(i0 + r, N - 1) * brow];
 #pragma unroll
                 for (int r = 0; r < kRows; ++r) {
                     if (i0 + r < N) {                           // uniform
                         float s[4];
                         if (!(tb >> 31)) {
-                            s[0] = s[1] = s[2] = s[3] = bt.scales[(size_t)(i0 + r) * bt.B + first];
+                            s[0] = s[1] = s[2] = s[3] = lane_value(sc, (uint32_t)(i0 + r) & 63);
                         } else {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) s[q] = bt.scales[(size_t)(i0 + r) * bt.B + blk[q]];
                         }
-                        acc.x = __fadd_rn(acc.x, signed_scale(m[r], 0, s[0]));
-                        acc.y = __fadd_rn(acc.y, signed_scale(m[r], 1, s[1]));
-                        acc.z = __fadd_rn(acc.z, signed_scale(m[r], 2, s[2]));
-                        acc.w = __fadd_rn(acc.w, signed_scale(m[r], 3, s[3]));
+                        const uint32_t b = m[r] >> (4 * u);
+                        acc.x = __fadd_rn(acc.x, signed_scale(b, 0, s[0]));
+                        acc.y = __fadd_rn(acc.y, signed_scale(b, 1, s[1]));
+                        acc.z = __fadd_rn(acc.z, signed_scale(b, 2, s[2]));
+                        acc.w = __fadd_rn(acc.w, signed_scale(b, 3, s[3]));
                     }
                 }
             }

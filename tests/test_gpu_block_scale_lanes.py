@@ -1,4 +1,4 @@
-"""Blockwise workers on rows the aggregation takes by tile: a wave loads the scales of 64 rows at a time, a lane each."""
+"""Blockwise workers: a wave of the aggregation, by tile or by chunk, loads the scales of 64 rows at a time, a lane each."""
 import os
 import sys
 
@@ -13,20 +13,20 @@ from _gpu import DEV, GPU_MARKS, say  # noqa: E402
 pytestmark = GPU_MARKS
 
 
+@pytest.mark.parametrize("d", [2048 * 1024 + 3, 20_003])
 @pytest.mark.parametrize("N,sc", [(63, "blocksign"), (65, "sign"), (73, "blocksign"), (3, "identity")])
-def test_scales_of_more_rows_than_lanes(N, sc):
-    """d is just above the 2048 tiles of 1024 columns from which the kernel by tile runs; a boundary inside a tile and one between tiles."""
+def test_scales_of_more_rows_than_lanes(N, sc, d):
+    """The kernel by tile runs from 2048 tiles of 1024 columns on; a boundary inside a tile and one between tiles."""
     import oracle
     from paper_2402_11857_amd import LiecContext
 
-    d = 2048 * 1024 + 3
     say(f"case block scales by lane N={N} d={d} server {sc}")
     gen = torch.Generator(device=DEV)
     gen.manual_seed(N)
     g = torch.empty((N, d), device=DEV).normal_(generator=gen).mul_(torch.arange(1, N + 1, device=DEV)[:, None])   # every row a scale of its own
     x = torch.zeros((N, d), device=DEV)
     e = torch.empty(d, device=DEV).normal_(generator=gen)
-    off = [0, 5 * 1024, 700_001, d]
+    off = [0, 5 * 1024, d // 3, d]
     xo, eo = np.zeros((N, d), dtype=np.float32), e.cpu().numpy()
     with LiecContext(N, d, "blocksign", sc, 0, 0, 0.1) as ctx:
         ctx.set_blocks(off)
