@@ -27,9 +27,9 @@ constexpr int kWaveStage = 256;         // and of each of its waves once the blo
 constexpr int kDirectList = 16384;      // candidate lists up to this length are selected by one block on its own
 constexpr int kShortCap = 4096;         // entries of the first list digit's bin that are handed to the list select on their own
 constexpr uint32_t kShortCapOne = 16384;     // the same where one launch does the search: as many as one block holds in registers
-constexpr int kHeldBits = 10;           // radix digit of the list select over a list it holds in registers
+constexpr int kHeldBits = 8;            // radix digit of the list select over a list it holds in LDS
 constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key
-constexpr uint32_t kFewEntries = 256;   // entries left that the list select compares with one another instead of taking further digits
+constexpr uint32_t kFewEntries = 128;   // entries left that the list select compares with one another instead of taking further digits
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel
 
 enum Comp : int { kIdentity = 0, kSign = 1, kTopk = 2, kBlockSign = 3, kRandk = 4 };

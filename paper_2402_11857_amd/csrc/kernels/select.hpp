@@ -75,7 +75,7 @@ __device__ __forceinline__ uint64_t filter_chunk(const uint32_t (&keys)[4], uint
 // List select: the keys of a band are taken relative to its lower end and need b <= 26 bits.  The first
 // digit is their top kFirstBits bits when many blocks build its histogram in global memory (256 bins: the
 // blocks' LDS histograms then merge with few global atomics, which are slow across the chip's dies); one block
-// that builds it in LDS, and the digits after it, take kHeldBits (a list held in registers: another pass is
+// that builds it in LDS, and the digits after it, take kHeldBits (a list held in LDS: another pass is
 // cheap) or kListBits bits each.
 constexpr int kFirstBits = 8;
 __device__ __forceinline__ int band_bits(uint32_t width) {            // width: 1 .. 2^26
@@ -546,107 +546,169 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
     }
 }
 
-// for_each_listed for a list of at most 16 * kSelectBlock entries that the block holds in registers (loaded once
-// by hold_listed, walked by every pass of the select instead of going back to memory).
-constexpr uint32_t kHeldMax = 16u * kSelectBlock;
-template <bool SHARED>
-__device__ __forceinline__ void hold_listed(const uint2* __restrict__ in, uint32_t n, uint4 (&a)[8]) {
-    const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
-    const uint32_t npairs = (n + 1) / 2;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint32_t e = q * kSelectBlock + threadIdx.x;
-        a[q] = e < npairs ? two_entries<SHARED>(&in2[e]) : make_uint4(0u, 0u, 0u, 0u);
-    }
-}
-template <typename F>
-__device__ __forceinline__ void for_each_held(const uint4 (&a)[8], uint32_t n, F fn) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        if (2u * q * kSelectBlock >= n) break;                  // uniform for the block: nothing held from here on
-        const uint32_t e = 2 * (q * kSelectBlock + threadIdx.x);
-        fn(make_uint2(a[q].x, a[q].y), e < n);
-        fn(make_uint2(a[q].z, a[q].w), e + 1 < n);
-    }
-}
-
 // What is left of a row's search once its candidates are listed: radix digits over the listed keys narrow them down to
 // the at most kFewEntries that share the digits found so far, and those are compared with one another, which gives tau
 // and the cut-off at once.  When more entries than that share the whole key (quantised gradients: thousands of equal
 // magnitudes), the cut-off is the `rank`-th smallest index among them, found by radix digits of those indices
 // until at most kFewEntries are left, which are compared as before.
-// One block of kSelectBlock threads, a chain of latencies: digits of 10 bits over a list held in registers, because
-// a smaller histogram is cleared and walked faster, and the comparison in place of the second digit, the tie list
-// and its quadratic ranking: 8 x 1M columns, k = 1 %, 11.0 -> 7.3 us; 5 x 3M
-// columns of bf16 gradients, thousands of ties, 32.6 -> 10.7 us.
+// One block of kSelectBlock threads, bound by latency: barriers, round trips to LDS, the code itself, which every launch
+// fetches anew, and on thousands of entries the instructions of one compute unit.  A list of up to kHeldMax entries is copied into LDS
+// once, so that every pass over it is a short loop (held in registers, each pass was that loop unrolled sixteen times); its
+// digits take kHeldBits bits, with kHeldCopies copies of every bin for lanes that name the same one (gradients of few mantissa bits
+// put thousands of entries on one key: with one copy of 1024 bins the first digit of 9000 entries took 5 us, now 1.5), picked by
+// one wave.  Among n <= kFewEntries there are no digits at all (128: comparing costs the square).  us per step, before and after: 5 x 3M
+// columns of bf16 mantissas 99.1 -> 90.5, 8 x 4.2M of them 150 -> 144, 8 x 262144 31.3 -> 30.5, 8 x 1M and 64 x 524288 even.  A digit of the
+// indices counted in the hope that the first digit's bin holds one key alone saves the workers' rows 2 us and costs the
+// server's, whose bins hold several, as much.
+constexpr uint32_t kHeldMax = 16u * kSelectBlock;
+constexpr int kHeldCopies = 16;
 struct ListLds {
-    __align__(16) uint32_t h[kListBins];       // digit histograms, then the last few entries
+    union {
+        __align__(16) uint2 held[kHeldMax];    // the list
+        uint32_t wide[kListBins];              // digit histogram over a longer one
+    };
+    union {
+        __align__(16) uint32_t h[(1 << kHeldBits) * kHeldCopies];      // digit histogram of the held list
+        uint2 few[kFewEntries];                // the last few entries
+    };
+    __align__(16) uint32_t sums[1 << kHeldBits];
     uint32_t part[256], res[3];
     uint32_t tau, cut, rank, nties;            // the result
 };
-static_assert(2 * kFewEntries <= kListBins && kFewEntries <= kSelectBlock, "the last entries reuse the histogram, one per thread");
-// in: n entries with keys in [lo, lo + width), `rank`: how many from the top the searched one is.  first: the first digit
-// is not known yet (it has first_shift(width, .) bits below it); otherwise ph and shift say what is.  Every thread of the
-// block calls it; the result is in s (all threads see it).
+static_assert(sizeof(ListLds) + 2 * sizeof(RowDesc) <= 160 * 1024, "LDS of a compute unit");
+static_assert(kHeldBits == 8 && kHeldCopies == 16 && kSelectBlock == 1024, "a thread clears and adds up four copies of a bin, a wave picks among the bins");
+static_assert(4 * kFewEntries <= kSelectBlock, "four threads compare one of the last entries");
+
+// The list of n <= kHeldMax entries into LDS.  shared (uniform): blocks of this launch wrote it.
 template <bool SHARED>
-__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
-                                              uint32_t rank, bool first, Pick ph, int shift, uint32_t d) {
-    const uint32_t tid = threadIdx.x, lane = tid & 63;
-    uint32_t* const h = s.h;
-    // a list of up to kHeldMax entries is read once and kept in registers for all the passes below
-    const bool held = n <= kHeldMax;                            // uniform for the block
-    uint4 own[8];
-    if (held) hold_listed<SHARED>(in, n, own);
-    auto walk = [&](auto fn) {
-        if (held) for_each_held(own, n, fn);
-        else for_each_listed<SHARED>(in, n, fn);
+__device__ __forceinline__ void hold_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, bool shared) {
+    const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
+    uint4* const out = reinterpret_cast<uint4*>(s.held);
+    const uint32_t npairs = (n + 1) / 2, tid = threadIdx.x;    // the slot after an odd n is inside the row's capacity
+    constexpr int kLoads = 8;                                  // all of kHeldMax, requested together, without a branch among them
+    static_assert(2 * kLoads * kSelectBlock == kHeldMax, "one round");
+    auto hold = [&](auto loads, auto fresh) {
+        constexpr int L = decltype(loads)::value;
+        uint4 a[L];
+#pragma unroll
+        for (int q = 0; q < L; ++q) a[q] = two_entries<decltype(fresh)::value>(&in2[min(q * kSelectBlock + tid, npairs - 1)]);
+#pragma unroll
+        for (int q = 0; q < L; ++q)
+            if (q * kSelectBlock + tid < npairs) out[q * kSelectBlock + tid] = a[q];
     };
-    if (first) {
-        // first digit of every listed key, in LDS
-        shift = first_shift(width, held ? kHeldBits : kListBits);
-        const uint32_t nbins = max(256u, 1u << (band_bits(width) - shift));
-        for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
+    using One = std::integral_constant<int, 1>;
+    using All = std::integral_constant<int, kLoads>;
+    if (SHARED && shared) hold(All{}, std::true_type{});
+    else if (npairs <= kSelectBlock) hold(One{}, std::false_type{});
+    else hold(All{}, std::false_type{});
+    __syncthreads();
+}
+// fn(entry, valid) for every listed entry, in wave-uniform control flow.
+template <bool HELD, bool SHARED, typename F>
+__device__ __forceinline__ void walk_list(const ListLds& s, const uint2* __restrict__ in, uint32_t n, F fn) {
+    if (HELD) {
+#pragma unroll 1
+        for (uint32_t base = 0; base < n; base += kSelectBlock) fn(s.held[base + threadIdx.x], base + threadIdx.x < n);
+    } else {
+        for_each_listed<SHARED>(in, n, fn);
+    }
+}
+// The bin of a digit of at most `bits` bits that holds the entry of rank `rank` (1-based, largest first), of the entries for which
+// digit(entry, valid, bin) is true and leaves their bin.
+template <bool HELD, bool SHARED, typename D>
+__device__ __forceinline__ Pick pick_digit(ListLds& s, const uint2* __restrict__ in, uint32_t n, int bits, uint32_t rank, D digit) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    if (!HELD) {
+        const uint32_t nbins = max(256u, 1u << bits);
+        for (uint32_t b = tid; b < nbins; b += kSelectBlock) s.wide[b] = 0;
         __syncthreads();
-        walk([&](uint2 kv, bool valid) { wave_count(h, valid, (kv.x - lo) >> shift, lane); });
+        walk_list<false, SHARED>(s, in, n, [&](uint2 kv, bool valid) {
+            uint32_t bin = 0;
+            valid = digit(kv, valid, bin);
+            wave_count(s.wide, valid, bin, lane);
+        });
         __syncthreads();
-        ph = block_pick(h, (int)nbins, rank, s.part, s.res);
+        return block_pick(s.wide, (int)nbins, rank, s.part, s.res);
+    }
+    reinterpret_cast<uint4*>(s.h)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    walk_list<true, SHARED>(s, in, n, [&](uint2 kv, bool valid) {
+        uint32_t bin = 0;
+        valid = digit(kv, valid, bin);
+        if (valid) atomicAdd(&s.h[bin * kHeldCopies + (lane & (kHeldCopies - 1))], 1u);
+    });
+    __syncthreads();
+    const uint4 c = reinterpret_cast<const uint4*>(s.h)[tid];
+    uint32_t sum = c.x + c.y + c.z + c.w;                       // four threads a bin
+    sum += dpp_or_zero<0xb1, 0xf>(sum);                         // lanes 1 0 3 2 of every four
+    sum += dpp_or_zero<0x4e, 0xf>(sum);                         // lanes 2 3 0 1
+    if ((tid & 3) == 0) s.sums[tid >> 2] = sum;
+    __syncthreads();
+    if (tid < 64) {                                             // lane l: bins 4l .. 4l + 3
+        const uint4 b = reinterpret_cast<const uint4*>(s.sums)[lane];
+        const uint32_t own = b.x + b.y + b.z + b.w, upto = wave_scan(own), above = last_lane(upto) - upto;
+        const bool mine = above < rank && rank <= above + own;
+        uint32_t bin = 4 * lane + 3, ahead = above, count = b.w;
+        if (rank > ahead + count) {
+            ahead += count;
+            count = b.z;
+            --bin;
+            if (rank > ahead + count) {
+                ahead += count;
+                count = b.y;
+                --bin;
+                if (rank > ahead + count) {
+                    ahead += count;
+                    count = b.x;
+                    --bin;
+                }
+            }
+        }
+        if (mine || (lane == 0 && __ballot(mine) == 0)) {
+            s.res[0] = mine ? bin : 0u;
+            s.res[1] = mine ? rank - ahead : 1u;
+            s.res[2] = mine ? count : 0u;
+        }
+    }
+    __syncthreads();
+    return Pick{s.res[0], s.res[1], s.res[2]};                  // (two more barriers before anyone writes them again)
+}
+
+// The search itself, see select_listed.
+template <bool HELD, bool SHARED>
+__device__ __forceinline__ void narrow_list(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
+                                            uint32_t rank, bool first, Pick ph, int shift, uint32_t d, bool shared) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const int key_bits = HELD ? kHeldBits : kListBits, index_bits = HELD ? kHeldBits : kIndexBits;
+    if (HELD) hold_listed<SHARED>(s, in, n, shared);
+    if (first && n <= kFewEntries) {                            // all of them are compared
+        shift = band_bits(width);
+        ph = Pick{0u, rank, n};
+    } else if (first) {
+        shift = first_shift(width, key_bits);
+        ph = pick_digit<HELD, SHARED>(s, in, n, band_bits(width) - shift, rank, [&](uint2 kv, bool valid, uint32_t& bin) {
+            bin = (kv.x - lo) >> shift;
+            return valid;
+        });
     }
     // The following digits, over the entries that carry the digits found so far, until few are left or the key is known.
-    const int digit_bits_max = held ? kHeldBits : kListBits;
     uint32_t prefix = ph.bin, want = ph.rank_in, left = ph.count;
 #pragma unroll 1
     while (shift > 0 && left > kFewEntries) {
-        if (held) {                                             // gradients of few mantissa bits: one key may be all there is
-            walk([&](uint2 kv, bool valid) {
-                if (valid && ((kv.x - lo) >> shift) == prefix) s.tau = kv.x;     // any of them
-            });
-            __syncthreads();
-            const uint32_t one = s.tau;
-            bool other = false;
-            walk([&](uint2 kv, bool valid) { other |= valid && ((kv.x - lo) >> shift) == prefix && kv.x != one; });
-            if (!__syncthreads_or(other)) {
-                prefix = one - lo;
-                shift = 0;
-                break;
-            }
-        }
-        const int bits = shift < digit_bits_max ? shift : digit_bits_max, below = shift - bits;
-        const uint32_t nbins = max(256u, 1u << bits), mask = (1u << bits) - 1u;
-        for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
-        __syncthreads();
-        walk([&](uint2 kv, bool valid) {
+        const int bits = shift < key_bits ? shift : key_bits, below = shift - bits;
+        const uint32_t mask = (1u << bits) - 1u;
+        const Pick p = pick_digit<HELD, SHARED>(s, in, n, bits, want, [&](uint2 kv, bool valid, uint32_t& bin) {
             const uint32_t rel = kv.x - lo;
-            wave_count(h, valid && (rel >> shift) == prefix, (rel >> below) & mask, lane);
+            bin = (rel >> below) & mask;
+            return valid && (rel >> shift) == prefix;
         });
-        __syncthreads();
-        const Pick p = block_pick(h, (int)nbins, want, s.part, s.res);
         prefix = (prefix << bits) | p.bin;
         want = p.rank_in;
         left = p.count;
         shift = below;
     }
-    // Many entries of one key (quantised gradients): the want-th of them in index order.  Digits of 11 bits over the
-    // indices, counted down from the largest, which turns "want-th smallest" into the "want-th largest" block_pick
+    // Many entries of one key (quantised gradients): the want-th of them in index order.  Digits of the
+    // indices, counted down from the largest, which turns "want-th smallest" into the "want-th largest" that the pick
     // finds; again until few are left.
     const uint32_t ties = left, want_key = want;                // entries of the key, when it is known here
     const uint32_t top = d - 1;
@@ -654,16 +716,13 @@ __device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restric
     uint32_t ifound = 0;
 #pragma unroll 1
     while (left > kFewEntries) {                                // indices are distinct: ends before ishift would go below 0
-        const int bits = ishift < kIndexBits ? ishift : kIndexBits, below = ishift - bits;
-        const uint32_t nbins = max(256u, 1u << bits), mask = (1u << bits) - 1u;
-        for (uint32_t b = tid; b < nbins; b += kSelectBlock) h[b] = 0;
-        __syncthreads();
-        walk([&](uint2 kv, bool valid) {
+        const int bits = ishift < index_bits ? ishift : index_bits, below = ishift - bits;
+        const uint32_t mask = (1u << bits) - 1u;
+        const Pick p = pick_digit<HELD, SHARED>(s, in, n, bits, want, [&](uint2 kv, bool valid, uint32_t& bin) {
             const uint32_t inv = top - kv.y;
-            wave_count(h, valid && kv.x == lo + prefix && (inv >> ishift) == ifound, (inv >> below) & mask, lane);
+            bin = (inv >> below) & mask;
+            return valid && kv.x == lo + prefix && (inv >> ishift) == ifound;
         });
-        __syncthreads();
-        const Pick p = block_pick(h, (int)nbins, want, s.part, s.res);
         ifound = (ifound << bits) | p.bin;
         want = p.rank_in;
         left = p.count;
@@ -671,27 +730,35 @@ __device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restric
     }
     // The entries that are left, compared with one another: the one with want - 1 others ahead of it (larger key, or
     // the same key and a lower index) is the row's k-th.
-    uint2* few = reinterpret_cast<uint2*>(h);
     if (tid == 0) s.nties = 0;
     __syncthreads();
-    walk([&](uint2 kv, bool valid) {
-        if (valid && ((kv.x - lo) >> shift) == prefix && ((top - kv.y) >> ishift) == ifound) {
-            const uint32_t pos = atomicAdd(&s.nties, 1u);
-            if (pos < kFewEntries) few[pos] = kv;
-        }
+    walk_list<HELD, SHARED>(s, in, n, [&](uint2 kv, bool valid) {
+        const bool hit = valid && ((kv.x - lo) >> shift) == prefix && ((top - kv.y) >> ishift) == ifound;
+        const uint64_t m = __ballot(hit);
+        if (m == 0) return;                                     // uniform
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s.nties, (uint32_t)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);
+        if (hit && at < kFewEntries) s.few[at] = kv;
     });
     __syncthreads();
-    if (tid < left) {
-        const uint2 mine = few[tid];
+    if ((tid >> 2) < left) {                                    // four threads an entry, each a quarter of the others
+        const uint2 mine = s.few[tid >> 2];
         uint32_t larger = 0, equal = 0, earlier = 0;
-#pragma unroll 8
-        for (uint32_t r = 0; r < left; ++r) {
-            const uint2 o = few[r];
+#pragma unroll 4
+        for (uint32_t r = tid & 3; r < left; r += 4) {
+            const uint2 o = s.few[r];
             larger += o.x > mine.x ? 1u : 0u;
             equal += o.x == mine.x ? 1u : 0u;
             earlier += o.x == mine.x && o.y < mine.y ? 1u : 0u;
         }
-        if (larger + earlier + 1 == want) {                     // indices are distinct: one thread
+        larger += dpp_or_zero<0xb1, 0xf>(larger);
+        equal += dpp_or_zero<0xb1, 0xf>(equal);
+        earlier += dpp_or_zero<0xb1, 0xf>(earlier);
+        larger += dpp_or_zero<0x4e, 0xf>(larger);
+        equal += dpp_or_zero<0x4e, 0xf>(equal);
+        earlier += dpp_or_zero<0x4e, 0xf>(earlier);
+        if ((tid & 3) == 0 && larger + earlier + 1 == want) {   // indices are distinct: one thread
             const bool by_index = ties != left;                 // the entries went through the index digits
             s.tau = mine.x;
             s.cut = mine.y;
@@ -700,6 +767,16 @@ __device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restric
         }
     }
     __syncthreads();
+}
+// in: n entries with keys in [lo, lo + width), `rank`: how many from the top the searched one is.  first: the first digit
+// is not known yet; otherwise ph and shift say what is.  Every thread of the block calls it; the result is in s (all threads
+// see it).
+// shared (uniform): blocks of this launch wrote the list; SHARED: they may have.
+template <bool SHARED>
+__device__ __forceinline__ void select_listed(ListLds& s, const uint2* __restrict__ in, uint32_t n, uint32_t lo, uint32_t width,
+                                              uint32_t rank, bool first, Pick ph, int shift, uint32_t d, bool shared) {
+    if (n <= kHeldMax) narrow_list<true, SHARED>(s, in, n, lo, width, rank, first, ph, shift, d, shared);       // uniform for the block
+    else narrow_list<false, SHARED>(s, in, n, lo, width, rank, first, ph, shift, d, shared);
 }
 
 // The row's descriptor in LDS, in one round trip instead of one per dependent field.  64 threads or more; the caller
@@ -779,7 +856,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_list_select(uint32_t row0, Row
         in = shortl + (size_t)row * kShortCap;                  // the bin's entries, collected by the second filter pass
         n = ph.count;
     }
-    select_listed<false>(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d);
+    select_listed<false>(s, in, n, lo, hi - lo, k - n_sure, direct, ph, first_shift(hi - lo, kFirstBits), d, false);
     if (tid == 0) finish_listed(now, found_in(s), n_all, form, cold, missed, 0u, 0u);
     put_result(desc + row, now);
 }
@@ -1268,11 +1345,11 @@ __device__ __forceinline__ void collect_bin(CollectLds& s, const float* __restri
 }
 
 template <bool VEC, bool RK>
-__global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict__ src, size_t row_stride, uint32_t d, uint32_t nwt,
-                                                          uint32_t row0, RowDesc* __restrict__ desc, uint2* __restrict__ list,
-                                                          uint32_t cap, uint2* __restrict__ shortl, uint32_t short_cap, uint32_t k, RkDraw rk,
-                                                          uint64_t* __restrict__ gbits, uint16_t* __restrict__ kbits, bool coarse,
-                                                          SharedRows sh) {
+__global__ __launch_bounds__(kSelectBlock) void k_select(RowDesc* __restrict__ desc, uint2* __restrict__ list, uint32_t d, uint32_t row0,
+                                                          uint32_t cap, uint32_t k, uint32_t nwt, uint32_t short_cap,
+                                                          uint2* __restrict__ shortl, bool coarse, const float* __restrict__ src,
+                                                          size_t row_stride, RkDraw rk, uint64_t* __restrict__ gbits,
+                                                          uint16_t* __restrict__ kbits, SharedRows sh) {
     __shared__ union {
         ListLds list;
         SlowLds slow;
@@ -1284,17 +1361,28 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
     const bool srv = RK && row == rk.srv_row;
     if (srv) k = rk.srv_k;
     const uint32_t fix_lo = srv ? rk.srv_lo : rk.fix_lo, fix_hi = srv ? rk.srv_hi : rk.fix_hi;
-    fetch_desc(now, desc + row);
-    __syncthreads();
+    // What the row needs follows from words of its descriptor that stay as they are, in scalar registers; the whole of it, a word a
+    // thread until it has arrived, is for thread 0 at the end.
+    RowDesc seen;
+    seen.mode = ld_const(&desc[row].mode);
+    seen.lo = ld_const(&desc[row].lo);
+    seen.hi = ld_const(&desc[row].hi);
+    seen.n_cand = ld_const(&desc[row].n_cand);
+    seen.n_sure = ld_const(&desc[row].n_sure);
+    const uint32_t desc_word = tid < 64 ? reinterpret_cast<const uint32_t*>(desc + row)[tid] : 0u;
     const uint32_t form = RK ? 0u : coarse ? 2u : 1u;
     uint16_t* const row_bits = RK ? kbits + (size_t)row * nwt * 64 : nullptr;
     const uint64_t stream = RK ? rk_stream(rk.state->seed, rk.state->draw, row) : 0ull;
     uint2* const row_list = list + (size_t)row * cap;
     uint32_t* const sync = sh.sync + (size_t)blockIdx.y * kSyncWords;
-    const RowWork work = row_work(now, cap, k);                 // the same in every block of the row, however late it starts
+    const RowWork work = row_work(seen, cap, k);                // the same in every block of the row, however late it starts
     const bool cold = work.cold;
     uint32_t lo = work.lo, width = work.width, n = work.n, rank = work.rank;
+    auto keep_desc = [&] {
+        if (tid < 64) reinterpret_cast<uint32_t*>(&now)[tid] = desc_word;
+    };
     if (cold) {
+        keep_desc();
         const float* __restrict__ g = src + (size_t)blockIdx.y * row_stride;
         uint64_t* const groups = gbits ? gbits + (size_t)blockIdx.y * nwt * (coarse ? 1 : 4) : nullptr;
         SlowFound f{0, 0, 0, 0, 0, 0};
@@ -1303,7 +1391,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         // (a caller can send a row through the whole of the general search)
         SlowEnd end = slow_multi<VEC, RK>(s.slow, g, d, nwt, k, (uint32_t)stream, (uint32_t)(stream >> 32), hist,
                                           sh.cnt + (size_t)blockIdx.y * kSlowMaxBlocks, sync, sh.spin_limit, groups, coarse,
-                                          now.mode == kSlow ? 0u : cap, meetings, f);
+                                          seen.mode == kSlow ? 0u : cap, meetings, f);
         if (end == kListed) {                                   // every block of the row
             collect_bin<VEC, RK>(s.collect, g, d, nwt, f.tau << 19, row_list, cap,
                                  reinterpret_cast<unsigned long long*>(&desc[row].n_cand2), groups, coarse, stream);
@@ -1400,8 +1488,13 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(const float* __restrict
         }
     }
     __syncthreads();
-    select_listed<true>(s.list, in, n_in, lo, width, rank, first, ph, shift, d);
-    if (tid == 0) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
+    if (!cold) keep_desc();
+    select_listed<true>(s.list, in, n_in, lo, width, rank, first, ph, shift, d, cold || in != row_list);
+    if (tid == 0) {
+        RowDesc r = now;                                        // in registers: its fields one after the other are a round trip to LDS each
+        finish_listed(r, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
+        now = r;
+    }
     put_result(desc + row, now);
     if (RK) {
         if (cold) mark_row(stream, d, nwt, s.list.tau, s.list.cut, row_bits);

@@ -328,7 +328,7 @@ void launch_one(Launcher& L, const float* src, size_t row_stride, uint32_t rows,
     liec_ctx* c = L.c;
     L.begin(slot0 + 3);
     k_select<VEC, RK><<<dim3(row0 ? c->slow_bs : c->slow_bw, rows), kSelectBlock, 0, c->stream>>>(
-        src, row_stride, (uint32_t)c->d, c->nwt, row0, c->desc, c->list, c->cap, c->shortl, c->short_cap, k, rk, gbits, c->bits, coarse,
+        c->desc, c->list, (uint32_t)c->d, row0, c->cap, k, c->nwt, c->short_cap, c->shortl, coarse, src, row_stride, rk, gbits, c->bits,
         shared_rows(c, row0 != 0));
     L.end();
 }

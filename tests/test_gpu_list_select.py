@@ -24,7 +24,7 @@ def _row(rng, d, above, ties, spread):
     return v * rng.choice(np.array([-1.0, 1.0], np.float32), d)
 
 
-# counts around the 256 entries that are compared directly, beyond one index digit's bin, and all of a narrow band
+# counts around the 256 bins of a digit, beyond one index digit's bin, and all of a narrow band
 @pytest.mark.parametrize("d", [200_000, 199_997])
 @pytest.mark.parametrize("ties,where", [(1, "only"), (2, "last"), (255, "middle"), (256, "first"), (257, "middle"), (257, "last"),
                                         (300, "first"), (4095, "middle"), (4097, "last"), (9000, "middle")])
@@ -50,7 +50,7 @@ def test_ties_at_the_threshold(d, ties, where, spread):
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
 
 
-# lists either side of the 16384 entries one block holds in registers: uniform keys, so that the first band is crowded
+# lists either side of the 16384 entries one block holds: uniform keys, so that the first band is crowded
 @pytest.mark.parametrize("k", [1000, 20_000, 60_000])
 def test_list_lengths(k):
     say(f"case list select lengths k={k}")
