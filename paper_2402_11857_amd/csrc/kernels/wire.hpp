@@ -11,7 +11,7 @@ namespace liec {
 // form (a thread turns the 16 bytes of 8 lanes into four 32-bit words, one per chunk; one thread per output byte
 // took 4.7 us for 1.5 MB, this 2.9); k_unpack_sign expands wire bits and scale(s) into the dense
 // message p_j = -s or +s (one 128-bit streaming store per 4 columns: 8 messages of 11.7M columns packed and unpacked
-// took 125 us with plain stores, 98 with streaming ones).
+// took 125 us with plain stores, 98 with streaming ones, 94 with larger blocks).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_pack_sign(const uint16_t* __restrict__ row_bits, uint32_t nwt, uint32_t nbytes,
                                                        uint8_t* __restrict__ out) {
@@ -35,11 +35,11 @@ __global__ __launch_bounds__(kBlock) void k_pack_sign(const uint16_t* __restrict
 }
 
 template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_unpack_sign(const uint8_t* __restrict__ bytes, uint32_t d,
+__global__ __launch_bounds__(1024) void k_unpack_sign(const uint8_t* __restrict__ bytes, uint32_t d,
                                                          const float* __restrict__ scales, float scale0,
                                                          BlockTable bt, float* __restrict__ p) {
     const uint32_t nq = (d + 3) / 4;                            // groups of 4 columns = half a wire byte
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nq; q += gridDim.x * kBlock) {
+    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += gridDim.x * blockDim.x) {
         const uint32_t j0 = q * 4;
         const uint32_t m = (uint32_t)bytes[q >> 1] >> (4 * (q & 1u));
         float v[4];
