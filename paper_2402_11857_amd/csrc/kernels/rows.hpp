@@ -17,7 +17,8 @@ constexpr uint32_t kBandFloor = 1u << 15;    // least half width, in key units, 
 
 // How a row's top-k threshold search starts its step.  Every kernel re-derives what the row needs from the mode, the band
 // and the row's counters, so nothing that any of them looks at changes before the update kernel: whoever finishes the
-// row's search (one block speaks for the row) leaves the next step's mode and band beside the present ones.  The one
+// row's search (one block speaks for the row) leaves the next step's mode and band beside the present ones, or only what the update
+// kernel predicts them from (due).  The one
 // exception is the list select on long rows, one block a row, which sends a row to the general search by its mode.
 enum SelMode : uint32_t {
     kWarm = 0,      // a band [lo, hi) predicted from the previous step is filtered
@@ -49,6 +50,7 @@ struct alignas(128) RowDesc {
     uint32_t far;          // a slowly decaying maximum of the smaller of the two distances
     uint32_t was_cold;     // the last band came from the first-digit histogram, not from a prediction
     uint32_t next_lo, next_hi, next_mode;      // band and mode of the next step, which the update kernel puts into force
+    uint32_t due;          // the band of the next step is still to be predicted (by the update kernel)
     uint32_t general;      // the last step took the general search: no list could hold the row's candidates, a caller asked for it, or a wait ran out
     // second line: what the blocks of the passes add to with atomics (kept off the line every block reads when
     // it starts).  Counters of the pass over the predicted band, one 64-bit word that a block of the filter adds
@@ -74,14 +76,6 @@ LIEC_HD void clear_counts(RowDesc& r) {
     r.n_short = 0;
     r.n_sure = r.n_sure2 = 0;
     r.nonfinite_acc = 0;
-}
-
-// The update kernel, for every row, once nobody looks at the mode, the band or the counters of this step any more.
-LIEC_HD void next_step(RowDesc& r) {
-    r.lo = r.next_lo;
-    r.hi = r.next_hi;
-    r.mode = r.next_mode;
-    clear_counts(r);
 }
 
 // After a filter pass: the band is usable when its list did not overflow and rank k falls inside it.
@@ -189,13 +183,27 @@ LIEC_HD void predict_band(RowDesc& r, uint32_t fix_lo, uint32_t fix_hi) {
     r.was_cold = 0;
 }
 
+// The update kernel, for every row, once nobody looks at the mode, the band or the counters of this step any more.
+LIEC_HD void next_step(RowDesc& r) {
+    if (r.due) {
+        predict_band(r, 0u, 0u);
+        r.next_mode = kWarm;
+        r.due = 0;
+    }
+    r.lo = r.next_lo;
+    r.hi = r.next_hi;
+    r.mode = r.next_mode;
+    clear_counts(r);
+}
+
 // What a search over a list found.
 struct ListFound {
     uint32_t tau, rank, ties, cut;
 };
-// And what it leaves in the row's descriptor (thread 0): n_all candidates were listed.
-LIEC_HD void finish_listed(RowDesc& r, const ListFound& f, uint32_t n_all, uint32_t form, bool cold, uint32_t missed,
-                           uint32_t fix_lo, uint32_t fix_hi) {
+// And what it leaves in the row's descriptor (thread 0): n_all candidates were listed.  The band of the next step comes with it,
+// or (due) from the update kernel, where nothing waits for it: 0.6 us of one thread's integer arithmetic at the end of k_select (us per
+// step, top-k both sides: 4 x 65536 columns 25.3 -> 24.3, 8 x 262144 30.5 -> 29.4, 8 x 1M 50.6 -> 49.8).
+LIEC_HD void record_listed(RowDesc& r, const ListFound& f, uint32_t n_all, uint32_t form, bool cold, uint32_t missed) {
     r.n_list = n_all;
     r.tau = f.tau;
     r.rank = f.rank;
@@ -206,6 +214,12 @@ LIEC_HD void finish_listed(RowDesc& r, const ListFound& f, uint32_t n_all, uint3
     r.nonfinite = r.nonfinite_acc;
     r.was_cold = cold ? 1u : 0u;
     r.misses += missed;
+    r.due = 1;
+}
+LIEC_HD void finish_listed(RowDesc& r, const ListFound& f, uint32_t n_all, uint32_t form, bool cold, uint32_t missed,
+                           uint32_t fix_lo, uint32_t fix_hi) {
+    record_listed(r, f, n_all, form, cold, missed);
+    r.due = 0;
     predict_band(r, fix_lo, fix_hi);
     r.next_mode = kWarm;
 }

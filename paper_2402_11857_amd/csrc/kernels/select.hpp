@@ -1509,9 +1509,8 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(RowDesc* __restrict__ d
     if (!cold) keep_desc();
     select_listed<true>(s.list, in, n_in, lo, width, rank, first, ph, shift, d, cold || in != row_list);
     if (tid == 0) {
-        RowDesc r = now;                                        // in registers: its fields one after the other are a round trip to LDS each
-        finish_listed(r, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
-        now = r;
+        if (RK) finish_listed(now, found_in(s.list), n, form, cold, 0u, fix_lo, fix_hi);
+        else record_listed(now, found_in(s.list), n, form, cold, 0u);
     }
     put_result(desc + row, now);
     if (RK) {

@@ -631,7 +631,29 @@ struct StepTail {
 __device__ __forceinline__ void end_searches(const StepTail& t) {
     const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
     if (blockIdx.x * kBlock >= max(t.rows, t.nsync)) return;    // uniform for the block
-    if (q < t.rows) next_step(t.desc[q]);
+    if (q < t.rows) {
+        RowDesc r = t.desc[q];                                  // in registers while the next band is predicted
+        const bool due = r.due != 0;
+        next_step(r);
+        RowDesc& to = t.desc[q];                                // (what the other blocks read stays unwritten)
+        to.lo = r.lo;
+        to.hi = r.hi;
+        to.mode = r.mode;
+        if (due) {
+            to.prev_tau = r.prev_tau;
+            to.have_prev = r.have_prev;
+            to.centre = r.centre;
+            to.swing = r.swing;
+            to.swing_still = r.swing_still;
+            to.far = r.far;
+            to.was_cold = r.was_cold;
+            to.next_lo = r.next_lo;
+            to.next_hi = r.next_hi;
+            to.next_mode = r.next_mode;
+            to.due = 0;
+        }
+        clear_counts(to);
+    }
     if (q < t.nsync && (q & (kSyncWords - 1)) < 2) t.sync[q] = 0;      // (the third word is the searches' own)
     if (q == 0 && t.draw) *t.draw += 1;
 }
