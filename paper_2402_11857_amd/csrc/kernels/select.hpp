@@ -560,7 +560,10 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 // columns of bf16 mantissas 99.1 -> 90.5, 8 x 4.2M of them 150 -> 144, 8 x 262144 31.3 -> 30.5, 8 x 1M and 64 x 524288 even.  A digit of the
 // indices counted in the hope that the first digit's bin holds one key alone saves the workers' rows 2 us and costs the
 // server's, whose bins hold several, as much.
-constexpr uint32_t kHeldMax = 16u * kSelectBlock;
+// (12 entries a thread leave 45 KB of LDS to other kernels on the compute unit: with 16, 1 KB left, two contexts of 8 x 1M columns on streams of
+// their own took 101 us a round of steps, with 12 68, with registers 75.)
+constexpr uint32_t kHeldMax = 12u * kSelectBlock;
+static_assert(kHeldMax == (uint32_t)kDirectList && kHeldMax == kShortCapOne, "what one block selects from it holds");
 constexpr int kHeldCopies = 16;
 struct ListLds {
     union {
@@ -585,7 +588,7 @@ __device__ __forceinline__ void hold_listed(ListLds& s, const uint2* __restrict_
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     uint4* const out = reinterpret_cast<uint4*>(s.held);
     const uint32_t npairs = (n + 1) / 2, tid = threadIdx.x;    // the slot after an odd n is inside the row's capacity
-    constexpr int kLoads = 8;                                  // all of kHeldMax, requested together, without a branch among them
+    constexpr int kLoads = 6;                                  // all of kHeldMax, requested together, without a branch among them
     static_assert(2 * kLoads * kSelectBlock == kHeldMax, "one round");
     auto hold = [&](auto loads, auto fresh) {
         constexpr int L = decltype(loads)::value;

@@ -13,9 +13,9 @@ from _gpu import DEV, GPU_MARKS, say  # noqa: E402
 pytestmark = GPU_MARKS
 
 
-# up to 128 entries are compared without a digit, 1024 threads walk the list, 2048 entries are one load each, 16384 the most that are held
+# up to 128 entries are compared without a digit, 1024 threads walk the list, 2048 entries are one load each, 12288 the most that are held
 @pytest.mark.parametrize("levels", [0, 3])
-@pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 1023, 1025, 2048, 2049, 8193, 16383, 16384, 16385])
+@pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 1023, 1025, 2048, 2049, 8193, 12287, 12288, 12289, 16385])
 def test_list_of_n_entries(n, levels):
     """n values in [1, 1.0625), which share their first digit, the others below 1/4; with levels, of so many magnitudes only."""
     say(f"case held list n={n} levels={levels}")
