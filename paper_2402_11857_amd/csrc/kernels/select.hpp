@@ -667,7 +667,8 @@ __device__ __forceinline__ Pick pick_digit(ListLds& s, const uint2* __restrict__
                 }
             }
         }
-        if (mine || (lane == 0 && __ballot(mine) == 0)) {
+        const bool none = __ballot(mine) == 0;                  // (a vote of all lanes: one lane writes)
+        if (mine || (lane == 0 && none)) {
             s.res[0] = mine ? bin : 0u;
             s.res[1] = mine ? rank - ahead : 1u;
             s.res[2] = mine ? count : 0u;
