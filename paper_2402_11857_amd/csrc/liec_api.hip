@@ -743,12 +743,15 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         // rows the passes without a prediction have too few blocks: 2 x 16.8M 212 against 214 (383, 288).  Random-k rows always
         // know their band: 8 x 1M 44 against 72, 32 x 4.2M 406 against 452, 32 x 25.6M, 0.1 %, 1810 against 1850 (with the
         // server's draw in the workers' launches).
-        // Beyond that many tiles in all, while a row has at most 4096 of them and the blocks that share the rows fill three
-        // quarters of the chip: 16 x 4.2M 238 against 227 (356, 333), 64 x 1M 237, 227 (339, 292), 31 x 4.1M 411, 396 (586, 553), 64 x 4M
-        // 779, 753 (1105, 1034), 2000 x 100000 1471, 1440 (1735, 1634); with half of it idle 130 x 2.5M 1038, 999 (1417, 1519), on
-        // longer rows 20 x 6M 372, 363 (481, 499), 8 x 8.4M 261, 255 (373, 383).
+        // Beyond that many tiles in all, rows of at most 128 tiles while there are so many that a row's blocks come in turns: 520 x 65536
+        // 323 against 311 (395, 367), 1024 x 130000 781, 758 (985, 914), 2000 x 100000 1419, 1389 (1726, 1649).  Otherwise a row that
+        // misses its band decides: the few blocks it has search it while the rest of the chip waits, where a launch for it
+        // spreads it over the chip.  One row of all missing, four launches against one: 16 x 4.2M 297, 343, 64 x 1M 256, 310, 64 x 4.2M
+        // 941, 1159, 300 x 150000 284, 304, 300 x 1M 1059, 1252, but 520 x 65536 335, 330, 1024 x 130000 806, 792; thresholds that drift by 5 % a
+        // step 31 x 4.1M 604, 639, 64 x 1M 313, 345, 200 x 4.2M 3440, 4150, but 1024 x 130000 915, 910, 2000 x 100000 1643, 1622.  (Rows
+        // that stay on their bands lose 3-5 %: 16 x 4.2M 268 against 258, 64 x 1M 238, 227, 64 x 4.2M 875, 849.)
         c->w_one = worker_comp == LIEC_COMP_RANDK || (c->nwt <= 8192u && (uint64_t)c->nwt * un <= 32768u) ||
-                   (c->nwt <= 4096u && 4u * c->slow_bw * un >= 3u * (uint32_t)cus);
+                   (c->nwt <= 128u && un >= 2u * (uint32_t)cus);
         c->s_one = server_comp == LIEC_COMP_RANDK || c->nwt <= 4096u;
         const bool one = (selects_k((int)worker_comp) && c->w_one) || (selects_k((int)server_comp) && c->s_one);
         const bool several = (selects_k((int)worker_comp) && !c->w_one) || (selects_k((int)server_comp) && !c->s_one);
