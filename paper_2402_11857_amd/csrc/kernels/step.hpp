@@ -710,9 +710,19 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
     // a candidate sits, unless the row's bitmap is not valid), the kept bits (random-k).
     uint32_t sbits = 0;
     bool need_v = true;
-    if (SC == kSign || SC == kBlockSign) sbits = vbits[(size_t)tile * 64 + lane];     // every row's block: no branch here
+    // The sign bits of v, for most pairs with a blockwise side: every row's block asks for them, no branch stands around the load, and their
+    // half-words stay in a register until the gradients are there.  With the shift next to the load, under the branch for i != 0, the compiler
+    // waits for them before it asks for the gradients.  Update kernel, us, so against under the branch, aligned rows and others: blockwise on both
+    // sides 24 x 9M 409, 424 (432, 445), 64 x 1M 122, 127 (127, 130); sign / blockwise 24 x 9M 415, 424 (433, 446); top-k / blockwise 421, 463 (449,
+    // 485); random-k / blockwise 412, 457 (439, 478); blockwise / sign 415, 419 (433, 442); top-k / sign 414, 414 (428, 434).  Under the branch is
+    // better where the scaled sign or no operator is the workers': sign on both sides 24 x 9M 417, 407 (433, 433), 64 x 1M 122, 120; identity / sign
+    // 2 x 25M 90.5, 87.5; identity / blockwise 2 x 25M 96.6, 93.0, 24 x 9M 330, 330 (344, 332); and random-k / sign 24 x 9M 414, 407.
+    constexpr bool kSignsFirst = WC == kBlockSign ? SC == kSign || SC == kBlockSign
+                                                  : (SC == kBlockSign && WC != kIdentity) || (SC == kSign && WC == kTopk);
+    if (kSignsFirst) sbits = vbits[(size_t)tile * 64 + lane];
     if (i != 0) {
         if (SC == kSign || SC == kBlockSign) {
+            if (!kSignsFirst) sbits = ((uint32_t)vbits[(size_t)tile * 64 + lane] >> (4 * chunk)) & 0xfu;
             need_v = false;
         } else if (SC == kTopk) {
             need_v = sd->dense || ((sgbits[(size_t)tile * 4 + chunk] >> lane) & 1u);
@@ -726,15 +736,13 @@ __global__ __launch_bounds__(kBlock) void k_update(const float* __restrict__ gra
 #if defined(__HIP_DEVICE_COMPILE__)
     // One stream at a time per wave: waiting for the gradients before asking for the model measured
     // 2-4 % faster than having both 128-bit loads in flight.
-    // The sign bits of v have arrived by then, and their half-words are in a register: with the shift next to the load, under
-    // the branch for i != 0, the compiler waits for them before it asks for the gradients (blockwise 7 x 7.3M + 1 columns 172.2 -> 167.9 us a
-    // step; scaled sign 16 x 11.7M and top-k / sign 16 x 138M even).
-    if (!FOLD) asm volatile("s_waitcnt vmcnt(0)" : "+v"(sbits)::"memory");
+    if (!FOLD && kSignsFirst) asm volatile("s_waitcnt vmcnt(0)" : "+v"(sbits)::"memory");
+    else if (!FOLD) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
     const float4 xv = FOLD ? x0 : ld4<VEC, true>(xi, j, d);
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (need_v) v = ld4<VEC>(v_in, j, d);
-    sbits = (sbits >> (4 * chunk)) & 0xfu;
+    if (kSignsFirst) sbits = (sbits >> (4 * chunk)) & 0xfu;
     const uint32_t stau = sd->tau, scut = sd->cutoff;
     float sw[4], ss[4];                                    // worker / server scale of each of the 4 columns
     if (WC == kBlockSign || SC == kBlockSign) {
