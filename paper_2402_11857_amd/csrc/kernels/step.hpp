@@ -49,9 +49,15 @@ __device__ __forceinline__ float message_of(float g, uint32_t j, float scale, ui
 // ITEMS (blockwise server): the block's round is one 4096-column tile, and it leaves the partial L1 sums of that
 // tile's items as k_l1_items would after reading v back (7 x 7.3M columns: 19 -> 23 us, and 11 us less for the
 // pass over v).
+// AHEAD (blockwise workers, rows whose e and v are more than the last-level cache keeps): e is requested ahead of the bits, and the rows'
+// scales come with one load, a lane each.  What short rows wait for is not e, and there the registers and the extra load only cost: the
+// tile's block and the rows' scales then come by vector loads that all lanes make (one scalar load after the other: 16 x 7M 26 -> 35 us).  us
+// per step with and without, blockwise on both sides: 1 x 5M columns 42.8, 41.1, 2 x 9M + 1 85.8, 81.8, 1 x 25M 131.4, 128.2, 6 x 9M 174.6, 171.1,
+// 32 x 9M 789, 783, 8 x 25M + 1 even, 5 x 30M + 1 470, 483, 3 x 40M + 1 450, 462, 3 x 75M + 1 826, 860, 3 x 99.4M 1068, 1088; blockwise / sign
+// 1 x 5M 42.2, 39.8, 8 x 25M + 1 589, 583, 5 x 30M + 1 465, 474, 1 x 70M + 1 388, 399.
 // ---------------------------------------------------------------------------------------------
 constexpr int kFoldRows = 16;                                   // workers whose scales a block forms at most, 4 to a wave
-template <int WC, bool SRV_L1, bool VEC, bool FOLD, bool ITEMS>
+template <int WC, bool SRV_L1, bool VEC, bool FOLD, bool ITEMS, bool AHEAD = false>
 __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict__ bits, int N, uint32_t d, uint32_t nwt, float inv_n,
                                                        RowDesc* __restrict__ desc, const float* __restrict__ e_in,
                                                        float* __restrict__ v_out, double* __restrict__ srv_partial,
@@ -94,12 +100,10 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
         if (!ITEMS && t >= nwt) break;
         const uint32_t j0 = t * kWaveTile + lane * 4;
         const bool ahead = FOLD && tb == blockIdx.x * 4;        // requested ahead of the sums
-        const uint64_t ent = ITEMS ? ld_const(reinterpret_cast<const uint64_t*>(items.tile) + tb / 4) : 0ull;
+        const uint64_t* const entry_at = reinterpret_cast<const uint64_t*>(items.tile) + tb / 4;
+        const uint64_t ent = !ITEMS ? 0ull : WC == kSign || AHEAD ? ld_const(entry_at) : *entry_at;
         const bool whole = (t + 1) * (uint32_t)kWaveTile <= d;  // wave-uniform
-        // Blockwise: e is requested ahead of the bits, and the rows' scales come with one load, a lane each, instead of one
-        // scalar load after the other (3 x 99.4M columns 1130 -> 1080 us a step, 4 x 5.8M 90.4 -> 89.6, 7 x 7.3M 167.2 -> 165.7).  Scaled
-        // sign, whose waves are more and shorter, only loses by the registers that takes (16 x 11.7M 514 -> 517).
-        if (WC == kBlockSign && whole) ld_tile<VEC, false>(e_in, t, lane, e0);
+        if (AHEAD && whole) ld_tile<VEC, false>(e_in, t, lane, e0);
         float4 acc[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -107,9 +111,11 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
         } else {
             const uint16_t* __restrict__ bw = bits + (size_t)t * 64 + lane;
             const size_t brow = (size_t)nwt * 64;
-            const uint32_t tblk = WC == kBlockSign ? ld_const(bt.tile_blk + t) : 0u, first = tblk & 0x7fffffffu;
-            if (WC == kSign) {
-                auto scale_of = [&](int i) { return FOLD ? folded[i] : desc[i].scale; };
+            const uint32_t tblk = WC != kBlockSign ? 0u : AHEAD ? ld_const(bt.tile_blk + t) : bt.tile_blk[t], first = tblk & 0x7fffffffu;
+            if (WC == kSign || (!AHEAD && !(tblk >> 31))) {     // (blockwise: the whole wave tile lies in one block)
+                auto scale_of = [&](int i) {
+                    return WC == kBlockSign ? bt.scales[(size_t)i * bt.B + first] : FOLD ? folded[i] : desc[i].scale;
+                };
                 int i = 0;
                 if (ahead) {
 #pragma unroll
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
                     for (int r = 0; r < 7; ++r)
                         if (i + r < N) add_signed(acc, m[r], scale_of(i + r));      // uniform
                 }
-            } else if (!(tblk >> 31)) {                         // the whole wave tile lies in one block
+            } else if (AHEAD && !(tblk >> 31)) {
                 float sc = 0.f;                                 // lane i: scale of the i-th of 64 rows
                 for (int i = 0; i < N; i += 8) {
                     if ((i & 63) == 0 && i + (int)lane < N) sc = bt.scales[(size_t)(i + lane) * bt.B + first];
@@ -167,7 +173,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(const uint16_t* __restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t j = j0 + u * kChunk;
-            const float4 e = (WC == kBlockSign || ahead) && whole ? e0[u] : ld4<VEC>(e_in, j, d);
+            const float4 e = (AHEAD || ahead) && whole ? e0[u] : ld4<VEC>(e_in, j, d);
             float4 v;
             v.x = __fmaf_rn(acc[u].x, inv_n, e.x);
             v.y = __fmaf_rn(acc[u].y, inv_n, e.y);

@@ -94,6 +94,7 @@ hipError_t static_scratch(double** out) {
 // tile's block adds to the row's one counter word.
 constexpr uint32_t kAggFilterTiles = 4096;
 constexpr uint64_t kFoldSums = 512;                             // most partial sums that the aggregation finishes itself
+constexpr uint32_t kAheadTiles = 28672;                         // blockwise workers: rows that the aggregation requests e ahead on, see there
 constexpr uint32_t kAggChunkBlocks = 65536;                     // most blocks of the aggregation by chunk
 static_assert(kAggFilterTiles <= kAggChunkBlocks, "a block that filters v has one tile");
 
@@ -456,6 +457,14 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
             else launch_sparse(k_aggregate_sparse<WC, false, VEC>);
         }
     } else if constexpr (WC != kIdentity) {
+        if constexpr (WC == kBlockSign) {
+            if (!done && c->nwt >= kAheadTiles) {
+                if (srv_l1) launch(k_aggregate<WC, true, VEC, false, false, true>);
+                else if (items) launch(k_aggregate<WC, false, VEC, false, true, true>);
+                else launch(k_aggregate<WC, false, VEC, false, false, true>);
+                done = true;
+            }
+        }
         if (!done) {
             if (srv_l1) launch(k_aggregate<WC, true, VEC, false, false>);
             else if (items) launch(k_aggregate<WC, false, VEC, false, true>);
