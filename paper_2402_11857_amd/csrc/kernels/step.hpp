@@ -437,9 +437,13 @@ struct ServerFilter {          // the first filter pass of the server's row, rid
 // ---------------------------------------------------------------------------------------------
 // SRV_FILTER (top-k server): the values of v are filtered against the server's predicted band while they are in
 // registers, as k_filter's first pass would after reading them back.
+// ROWS: rows requested together.  Words are requested for that many rows whether they are there or not, so up to kFewRows top-k rows take a
+// kernel of that many (us per step with 4 and with 8, top-k / sign: 1 x 2.5M columns 34.3, 36.5, 1 x 8M 82.9, 88.8, 2 x 4M + 1 64.9, 67.6,
+// 4 x 3M 71.3, 74.5, 4 x 65536 even).
 // Identity workers under a random-k server: vodd receives, per chunk, a bit for every 4 columns in which v is not finite,
 // for the update.
-template <int WC, bool SRV_L1, bool VEC, bool SRV_FILTER>
+constexpr int kFewRows = 4;
+template <int WC, bool SRV_L1, bool VEC, bool SRV_FILTER, int ROWS = 8>
 __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restrict__ grads, const uint16_t* __restrict__ bits,
                                                              const uint64_t* __restrict__ gbits, int N, uint32_t d,
                                                              uint32_t nwt, float inv_n, RowDesc* __restrict__ desc,
@@ -453,7 +457,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate_chunk(const float* __restr
     static_assert(!SRV_FILTER || kStage >= kWaveTile, "a tile's candidates fit the block's stage");
     __shared__ uint2 stage[SRV_FILTER ? kStage : 1];
     __shared__ uint32_t wsure[5], staged[2];
-    constexpr int kRows = 8;                                    // rows requested together
+    constexpr int kRows = ROWS;
     FilterBand fb{};
     bool filter = false;                                        // uniform: the server's row has a predicted band
     uint32_t n_hi = 0, kmax = 0, wcnt = 0;

@@ -435,7 +435,15 @@ void launch_aggregate(Launcher& L, const float* grads, const float* e, bool srv_
     const bool items = c->agg_sums_items();
     bool done = false;
     if constexpr (WC != kSign) {                                // (scaled sign has the form by tile only)
-        if (WC == kIdentity || c->agg_chunk) {                  // (the identity the form by chunk only)
+        if constexpr (WC == kTopk) {
+            if (c->agg_chunk && c->N <= kFewRows) {
+                if (srv_l1) launch_chunk(k_aggregate_chunk<WC, true, VEC, false, kFewRows>);
+                else if (c->agg_filters()) launch_chunk(k_aggregate_chunk<WC, false, VEC, true, kFewRows>);
+                else launch_chunk(k_aggregate_chunk<WC, false, VEC, false, kFewRows>);
+                done = true;
+            }
+        }
+        if (!done && (WC == kIdentity || c->agg_chunk)) {       // (the identity the form by chunk only)
             if (srv_l1) launch_chunk(k_aggregate_chunk<WC, true, VEC, false>);
             else if (c->agg_filters()) launch_chunk(k_aggregate_chunk<WC, false, VEC, true>);
             else launch_chunk(k_aggregate_chunk<WC, false, VEC, false>);

@@ -113,6 +113,28 @@ def test_aggregate_by_tile(N, d, k, same):
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
 
 
+# a chunk per wave: up to 4 rows take a kernel that asks for 4 rows' words; both forms of the candidate bitmap, rows that have none
+@pytest.mark.parametrize("sc", ["sign", "topk", "identity"])
+@pytest.mark.parametrize("N,d,k", [(1, 1021, 30), (2, 5000, 40), (3, 5003, 1500), (4, 1028, 60), (5, 1025, 1000)])
+def test_aggregate_few_rows_by_chunk(N, d, k, sc):
+    say(f"case aggregate few rows N={N} d={d} k={k} server {sc}")
+    from paper_2402_11857_amd import LiecContext
+
+    rng = np.random.default_rng(N * 7 + d + k)
+    x, e = np.zeros((N, d), np.float32), np.zeros(d, np.float32)
+    xd, ed = torch.from_numpy(x).to(DEV), torch.from_numpy(e).to(DEV)
+    with LiecContext(N, d, "topk", sc, k, k, 0.05) as ctx:
+        for t in range(4):
+            g = rng.standard_normal((N, d), dtype=np.float32)
+            ctx.set_group_bitmap(t % 2)
+            if t == 3:
+                ctx.force_search_mode(4)                        # no valid bitmap: every column is a candidate
+            ctx.step(torch.from_numpy(g).to(DEV), xd, ed)
+            torch.cuda.synchronize()
+            H.oracle_step_rows(g, x, e, "topk", sc, 0.05, k, k)
+            assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
+
+
 @pytest.mark.parametrize("N,d,k", [(64, 256 * 1024, 300), (64, 256 * 1024 + 3, 200_000), (70, 240 * 1024, 20_000)])
 def test_aggregate_by_tile_randk(N, d, k):
     say(f"case aggregate by tile randk N={N} d={d} k={k}")
