@@ -24,11 +24,11 @@ constexpr int kHistBins = 4096;         // first radix digit of a whole row (12 
 constexpr int kListBins = 1 << kListBits;
 constexpr int kStage = 1024;            // LDS staging slots of a block of the candidate filter
 constexpr int kWaveStage = 256;         // and of each of its waves once the block's are used up (a chunk lists at most 256)
-constexpr int kDirectList = 12288;      // candidate lists up to this length are selected by one block on its own
+constexpr int kDirectList = 16384;      // candidate lists up to this length are selected by one block on its own
 constexpr int kShortCap = 4096;         // entries of the first list digit's bin that are handed to the list select on their own
-constexpr uint32_t kShortCapOne = 12288;     // the same where one launch does the search: as many as one block holds in LDS
+constexpr uint32_t kShortCapOne = 16384;     // the same where one launch does the search: as many as one block holds in LDS
 constexpr int kHeldBits = 8;            // radix digit of the list select over a list it holds in LDS
-constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key
+constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key, of a longer list
 constexpr uint32_t kFewEntries = 128;   // entries left that the list select compares with one another instead of taking further digits
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel
 

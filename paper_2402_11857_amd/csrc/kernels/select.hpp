@@ -554,32 +554,40 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 // One block of kSelectBlock threads, bound by latency: barriers, round trips to LDS, the code itself, which every launch
 // fetches anew, and on thousands of entries the instructions of one compute unit.  A list of up to kHeldMax entries is copied into LDS
 // once, so that every pass over it is a short loop (held in registers, each pass was that loop unrolled sixteen times); its
-// digits take kHeldBits bits, with kHeldCopies copies of every bin for lanes that name the same one (gradients of few mantissa bits
+// digits take kHeldBits bits, with 16 copies of every bin for lanes that name the same one (gradients of few mantissa bits
 // put thousands of entries on one key: with one copy of 1024 bins the first digit of 9000 entries took 5 us, now 1.5), picked by
 // one wave.  Among n <= kFewEntries there are no digits at all (128: comparing costs the square).  us per step, before and after: 5 x 3M
 // columns of bf16 mantissas 99.1 -> 90.5, 8 x 4.2M of them 150 -> 144, 8 x 262144 31.3 -> 30.5, 8 x 1M and 64 x 524288 even.  A digit of the
 // indices counted in the hope that the first digit's bin holds one key alone saves the workers' rows 2 us and costs the
 // server's, whose bins hold several, as much.
-// (12 entries a thread leave 45 KB of LDS to other kernels on the compute unit: with 16, 1 KB left, two contexts of 8 x 1M columns on streams of
-// their own took 101 us a round of steps, with 12 68, with registers 75.)
-constexpr uint32_t kHeldMax = 12u * kSelectBlock;
+// A list of more than kHeldShort entries (12 a thread) takes the place of half the copies: 20 KB of LDS are left on the compute unit, enough for a
+// block of k_filter (17 KB), so that contexts on streams of their own overlap (two of 8 x 1M columns, us a round of steps: 95, with the list in
+// registers 104; with 16 copies beside 16 entries a thread, 13.6 KB left, half as long again).  Lists of 12600 to 16000 entries that one block
+// does not hold cost more, us per step of one row of 1M columns: 30.5 against 28.8 now, without a prediction and with thousands of equal
+// keys 56.5 against 48.8.
+constexpr uint32_t kHeldMax = 16u * kSelectBlock, kHeldShort = 12u * kSelectBlock;
 static_assert(kHeldMax == (uint32_t)kDirectList && kHeldMax == kShortCapOne, "what one block selects from it holds");
-constexpr int kHeldCopies = 16;
+constexpr uint32_t kHeldShifts = 4;            // log2 of the copies of a bin, one less over a list longer than kHeldShort
+constexpr int kHeldBins = 1 << kHeldBits;
 struct ListLds {
     union {
-        __align__(16) uint2 held[kHeldMax];    // the list
-        uint32_t wide[kListBins];              // digit histogram over a longer one
+        struct {
+            __align__(16) uint2 held[kHeldMax];                            // the list
+            __align__(16) uint32_t h_long[kHeldBins << (kHeldShifts - 1)];  // digit histogram of the held list,
+        };
+        struct {
+            uint2 held_short[kHeldShort];
+            __align__(16) uint32_t h_short[kHeldBins << kHeldShifts];       // where it begins while the list is short
+        };
+        uint32_t wide[kListBins];              // digit histogram over a list that is not held
     };
-    union {
-        __align__(16) uint32_t h[(1 << kHeldBits) * kHeldCopies];      // digit histogram of the held list
-        uint2 few[kFewEntries];                // the last few entries
-    };
-    __align__(16) uint32_t sums[1 << kHeldBits];
+    __align__(16) uint32_t sums[kHeldBins];
+    __align__(16) uint2 few[kFewEntries];      // the last few entries
     uint32_t part[256], res[3];
     uint32_t tau, cut, rank, nties;            // the result
 };
-static_assert(sizeof(ListLds) + 2 * sizeof(RowDesc) <= 160 * 1024, "LDS of a compute unit");
-static_assert(kHeldBits == 8 && kHeldCopies == 16 && kSelectBlock == 1024, "a thread clears and adds up four copies of a bin, a wave picks among the bins");
+static_assert(sizeof(ListLds) + 2 * sizeof(RowDesc) + 17 * 1024 <= 160 * 1024, "LDS of a compute unit, a block of the filter beside it");
+static_assert(kHeldBits == 8 && kHeldShifts == 4 && kSelectBlock == 1024, "a thread clears and adds up four copies of a bin, a wave picks among the bins");
 static_assert(4 * kFewEntries <= kSelectBlock, "four threads compare one of the last entries");
 
 // The list of n <= kHeldMax entries into LDS.  shared (uniform): blocks of this launch wrote it.
@@ -588,8 +596,7 @@ __device__ __forceinline__ void hold_listed(ListLds& s, const uint2* __restrict_
     const uint4* __restrict__ in2 = reinterpret_cast<const uint4*>(in);
     uint4* const out = reinterpret_cast<uint4*>(s.held);
     const uint32_t npairs = (n + 1) / 2, tid = threadIdx.x;    // the slot after an odd n is inside the row's capacity
-    constexpr int kLoads = 6;                                  // all of kHeldMax, requested together, without a branch among them
-    static_assert(2 * kLoads * kSelectBlock == kHeldMax, "one round");
+    // requested together, without a branch among them, in one round
     auto hold = [&](auto loads, auto fresh) {
         constexpr int L = decltype(loads)::value;
         uint4 a[L];
@@ -600,9 +607,11 @@ __device__ __forceinline__ void hold_listed(ListLds& s, const uint2* __restrict_
             if (q * kSelectBlock + tid < npairs) out[q * kSelectBlock + tid] = a[q];
     };
     using One = std::integral_constant<int, 1>;
-    using All = std::integral_constant<int, kLoads>;
+    using Short = std::integral_constant<int, kHeldShort / (2 * kSelectBlock)>;
+    using All = std::integral_constant<int, kHeldMax / (2 * kSelectBlock)>;
     if (SHARED && shared) hold(All{}, std::true_type{});
     else if (npairs <= kSelectBlock) hold(One{}, std::false_type{});
+    else if (n <= kHeldShort) hold(Short{}, std::false_type{});
     else hold(All{}, std::false_type{});
     __syncthreads();
 }
@@ -633,19 +642,26 @@ __device__ __forceinline__ Pick pick_digit(ListLds& s, const uint2* __restrict__
         __syncthreads();
         return block_pick(s.wide, (int)nbins, rank, s.part, s.res);
     }
-    reinterpret_cast<uint4*>(s.h)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    const bool is_short = n <= kHeldShort;                      // uniform
+    const uint32_t shift = is_short ? kHeldShifts : kHeldShifts - 1, own_copy = lane & ((1u << shift) - 1u);
+    uint32_t* const h = is_short ? s.h_short : s.h_long;
+    const bool mine4 = tid < (uint32_t)kHeldBins << (shift - 2);       // whole waves
+    if (mine4) reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     walk_list<true, SHARED>(s, in, n, [&](uint2 kv, bool valid) {
         uint32_t bin = 0;
         valid = digit(kv, valid, bin);
-        if (valid) atomicAdd(&s.h[bin * kHeldCopies + (lane & (kHeldCopies - 1))], 1u);
+        if (valid) atomicAdd(&h[(bin << shift) + own_copy], 1u);
     });
     __syncthreads();
-    const uint4 c = reinterpret_cast<const uint4*>(s.h)[tid];
-    uint32_t sum = c.x + c.y + c.z + c.w;                       // four threads a bin
-    sum += dpp_or_zero<0xb1, 0xf>(sum);                         // lanes 1 0 3 2 of every four
-    sum += dpp_or_zero<0x4e, 0xf>(sum);                         // lanes 2 3 0 1
-    if ((tid & 3) == 0) s.sums[tid >> 2] = sum;
+    if (mine4) {
+        const uint4 c = reinterpret_cast<const uint4*>(h)[tid];
+        uint32_t sum = c.x + c.y + c.z + c.w;                   // four threads a bin, or two
+        sum += dpp_or_zero<0xb1, 0xf>(sum);                     // lanes 1 0 3 2 of every four
+        const uint32_t other = dpp_or_zero<0x4e, 0xf>(sum);     // lanes 2 3 0 1
+        if (is_short) sum += other;
+        if ((tid & ((1u << (shift - 2)) - 1u)) == 0) s.sums[tid >> (shift - 2)] = sum;
+    }
     __syncthreads();
     if (tid < 64) {                                             // lane l: bins 4l .. 4l + 3
         const uint4 b = reinterpret_cast<const uint4*>(s.sums)[lane];
@@ -1452,7 +1468,7 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(RowDesc* __restrict__ d
     Pick ph{0, 0, 0};
     const int shift = first_shift(width, kFirstBits);
     if (nb > 1) {
-        uint32_t* const h = s.list.h;
+        uint32_t* const h = s.list.h_long;
         uint32_t* const hists = sh.list_hist + (size_t)blockIdx.y * gridDim.x * 256;
         if (tid < 256) h[tid] = 0;
         __syncthreads();

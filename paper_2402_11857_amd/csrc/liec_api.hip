@@ -775,7 +775,7 @@ liec_status liec_create_ex(liec_ctx** out, int32_t N, int64_t d, liec_comp worke
         // the histograms that the several launches hand to one another
         if (several) e = dev_alloc(c, &c->ghist, rows * kHistBins);
         if (several && e == hipSuccess) e = hipMemsetAsync(c->ghist, 0, rows * kHistBins * sizeof(uint32_t), c->stream);
-        // (a row that one block searches on its own has no use for the longer one; up to 129 rows: 12 MiB)
+        // (a row that one block searches on its own has no use for the longer one; up to 129 rows: 16 MiB)
         c->short_cap = one && N <= 128 ? kShortCapOne : (uint32_t)kShortCap;
         if (e == hipSuccess) e = dev_alloc(c, &c->shortl, rows * c->short_cap);
         c->slow_slots = (uint32_t)slots;

@@ -163,7 +163,7 @@ def test_random_chains_on_degenerate_gradients(case):
 @pytest.mark.parametrize("wc,sc", [("topk", "topk"), ("topk", "sign")])
 def test_quantised_gradients_with_thousands_of_ties_at_the_threshold(wc, sc):
     """Gradients that carry 5 mantissa bits (as after a low-precision backward pass): about 10^4 entries of a
-    row share the threshold magnitude, far more than the 256 entries the list select compares with one another: the
+    row share the threshold magnitude, far more than the 128 entries the list select compares with one another: the
     cut-off is found through digits of their indices.  The result must still be the oracle's,
     and the rows must not fall to the general single-block search (slow_rows stays 0)."""
     import oracle

@@ -50,7 +50,7 @@ def test_ties_at_the_threshold(d, ties, where, spread):
             assert H.bit_equal(xd.cpu().numpy(), x) and H.bit_equal(ed.cpu().numpy(), e), f"step {t}"
 
 
-# lists either side of the 12288 entries one block holds: uniform keys, so that the first band is crowded
+# lists either side of the 16384 entries one block holds: uniform keys, so that the first band is crowded
 @pytest.mark.parametrize("k", [1000, 20_000, 60_000])
 def test_list_lengths(k):
     say(f"case list select lengths k={k}")
