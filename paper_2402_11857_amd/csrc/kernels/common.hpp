@@ -29,7 +29,8 @@ constexpr int kShortCap = 4096;         // entries of the first list digit's bin
 constexpr uint32_t kShortCapOne = 16384;     // the same where one launch does the search: as many as one block holds in LDS
 constexpr int kHeldBits = 8;            // radix digit of the list select over a list it holds in LDS
 constexpr int kIndexBits = 11;          // its radix digit over the indices of entries that share one key, of a longer list
-constexpr uint32_t kFewEntries = 128;   // entries left that the list select compares with one another instead of taking further digits
+constexpr uint32_t kFewHeld = 128;      // entries left that the list select compares with one another instead of taking further digits,
+constexpr uint32_t kFewEntries = 256;   // and of a list it does not hold
 constexpr uint32_t kUpdatePanel = 4096; // column tiles per panel of the update kernel
 
 enum Comp : int { kIdentity = 0, kSign = 1, kTopk = 2, kBlockSign = 3, kRandk = 4 };

@@ -547,16 +547,16 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 }
 
 // What is left of a row's search once its candidates are listed: radix digits over the listed keys narrow them down to
-// the at most kFewEntries that share the digits found so far, and those are compared with one another, which gives tau
+// the at most kFewHeld (kFewEntries) that share the digits found so far, and those are compared with one another, which gives tau
 // and the cut-off at once.  When more entries than that share the whole key (quantised gradients: thousands of equal
 // magnitudes), the cut-off is the `rank`-th smallest index among them, found by radix digits of those indices
-// until at most kFewEntries are left, which are compared as before.
+// until at most so many are left, which are compared as before.
 // One block of kSelectBlock threads, bound by latency: barriers, round trips to LDS, the code itself, which every launch
 // fetches anew, and on thousands of entries the instructions of one compute unit.  A list of up to kHeldMax entries is copied into LDS
 // once, so that every pass over it is a short loop (held in registers, each pass was that loop unrolled sixteen times); its
 // digits take kHeldBits bits, with 16 copies of every bin for lanes that name the same one (gradients of few mantissa bits
 // put thousands of entries on one key: with one copy of 1024 bins the first digit of 9000 entries took 5 us, now 1.5), picked by
-// one wave.  Among n <= kFewEntries there are no digits at all (128: comparing costs the square).  us per step, before and after: 5 x 3M
+// one wave.  Among n <= kFewHeld there are no digits at all (128: comparing costs the square).  us per step, before and after: 5 x 3M
 // columns of bf16 mantissas 99.1 -> 90.5, 8 x 4.2M of them 150 -> 144, 8 x 262144 31.3 -> 30.5, 8 x 1M and 64 x 524288 even.  A digit of the
 // indices counted in the hope that the first digit's bin holds one key alone saves the workers' rows 2 us and costs the
 // server's, whose bins hold several, as much.
@@ -565,6 +565,10 @@ __device__ __forceinline__ void for_each_listed(const uint2* __restrict__ in, ui
 // registers 104; with 16 copies beside 16 entries a thread, 13.6 KB left, half as long again).  Lists of 12600 to 16000 entries that one block
 // does not hold cost more, us per step of one row of 1M columns: 30.5 against 28.8 now, without a prediction and with thousands of equal
 // keys 56.5 against 48.8.
+// A list that is not held is read again for every digit: it stops at kFewEntries, and waves none of whose entries
+// carry the digits found so far are done with them at once.  us per step with 128 and without that, with 256, with both: blockwise / top-k
+// 2 x 20M, 1 %, whose server lists 250 000 to 430 000 entries, 560, 558, 461; top-k on both sides, 5 %, of bf16 mantissas 617, 617, 549;
+// sign / top-k 2 x 20M 389, 380, 355, 3 x 5M 184, 180, 174.
 constexpr uint32_t kHeldMax = 16u * kSelectBlock, kHeldShort = 12u * kSelectBlock;
 static_assert(kHeldMax == (uint32_t)kDirectList && kHeldMax == kShortCapOne, "what one block selects from it holds");
 constexpr uint32_t kHeldShifts = 4;            // log2 of the copies of a bin, one less over a list longer than kHeldShort
@@ -637,7 +641,7 @@ __device__ __forceinline__ Pick pick_digit(ListLds& s, const uint2* __restrict__
         walk_list<false, SHARED>(s, in, n, [&](uint2 kv, bool valid) {
             uint32_t bin = 0;
             valid = digit(kv, valid, bin);
-            wave_count(s.wide, valid, bin, lane);
+            if (__ballot(valid)) wave_count(s.wide, valid, bin, lane);     // uniform: after the first digit most waves have none
         });
         __syncthreads();
         return block_pick(s.wide, (int)nbins, rank, s.part, s.res);
@@ -700,8 +704,9 @@ __device__ __forceinline__ void narrow_list(ListLds& s, const uint2* __restrict_
                                             uint32_t rank, bool first, Pick ph, int shift, uint32_t d, bool shared) {
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const int key_bits = HELD ? kHeldBits : kListBits, index_bits = HELD ? kHeldBits : kIndexBits;
+    constexpr uint32_t kFew = HELD ? kFewHeld : kFewEntries;
     if (HELD) hold_listed<SHARED>(s, in, n, shared);
-    if (first && n <= kFewEntries) {                            // all of them are compared
+    if (first && n <= kFew) {                                   // all of them are compared
         shift = band_bits(width);
         ph = Pick{0u, rank, n};
     } else if (first) {
@@ -714,7 +719,7 @@ __device__ __forceinline__ void narrow_list(ListLds& s, const uint2* __restrict_
     // The following digits, over the entries that carry the digits found so far, until few are left or the key is known.
     uint32_t prefix = ph.bin, want = ph.rank_in, left = ph.count;
 #pragma unroll 1
-    while (shift > 0 && left > kFewEntries) {
+    while (shift > 0 && left > kFew) {
         const int bits = shift < key_bits ? shift : key_bits, below = shift - bits;
         const uint32_t mask = (1u << bits) - 1u;
         const Pick p = pick_digit<HELD, SHARED>(s, in, n, bits, want, [&](uint2 kv, bool valid, uint32_t& bin) {
@@ -735,7 +740,7 @@ __device__ __forceinline__ void narrow_list(ListLds& s, const uint2* __restrict_
     int ishift = band_bits(d);                                  // index bits below the digits found so far
     uint32_t ifound = 0;
 #pragma unroll 1
-    while (left > kFewEntries) {                                // indices are distinct: ends before ishift would go below 0
+    while (left > kFew) {                                       // indices are distinct: ends before ishift would go below 0
         const int bits = ishift < index_bits ? ishift : index_bits, below = ishift - bits;
         const uint32_t mask = (1u << bits) - 1u;
         const Pick p = pick_digit<HELD, SHARED>(s, in, n, bits, want, [&](uint2 kv, bool valid, uint32_t& bin) {
@@ -759,7 +764,7 @@ __device__ __forceinline__ void narrow_list(ListLds& s, const uint2* __restrict_
         uint32_t at = 0;
         if (lane == 0) at = atomicAdd(&s.nties, (uint32_t)__popcll(m));
         at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);
-        if (hit && at < kFewEntries) s.few[at] = kv;
+        if (hit && at < kFew) s.few[at] = kv;
     });
     __syncthreads();
     if ((tid >> 2) < left) {                                    // four threads an entry, each a quarter of the others

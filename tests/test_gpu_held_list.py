@@ -56,8 +56,15 @@ def test_list_of_n_entries(n, levels):
     assert "worker_hist0" not in _check(2, 300_007, n, levels)  # one launch
 
 
+# one key that more entries share than are held
+def test_list_of_one_key_beyond_what_is_held():
+    say("case list of one key, 22000 entries")
+    assert "worker_hist0" not in _check(2, 300_007, 22_000, 1)
+
+
 # the same where several launches search: rows of more than 8192 tiles
-@pytest.mark.parametrize("n,levels", [(128, 0), (129, 0), (2049, 3), (12288, 0), (12289, 3), (16384, 3), (16385, 0)])
+@pytest.mark.parametrize("n,levels", [(128, 0), (129, 0), (2049, 3), (12288, 0), (12289, 3), (16384, 3), (16385, 0),
+                                      (40_000, 0), (40_000, 1), (300_000, 0), (300_001, 3), (300_000, 1500)])
 def test_list_of_n_entries_on_a_long_row(n, levels):
     say(f"case held list, long row, n={n} levels={levels}")
     assert "worker_hist0" in _check(1, 8192 * 1024 + 5, n, levels)
