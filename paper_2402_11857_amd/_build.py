@@ -24,9 +24,10 @@ def hipcc() -> str:
 
 def build_library(verbose: bool = False, defines=(), out: str = LIB_PATH) -> str:
     """Always recompiles.  -ffp-contract=off keeps every fp32 expression a single IEEE operation;
-    packed fp32 instructions are disabled for the device pass.  A kernel's first 16 argument words are in scalar registers
-    when a wave starts instead of being loaded by every wave (short kernels gain most: 8 scaled-sign messages of 11.7M + 1 columns
-    101.7 -> 98.9 us, averaging 27 x 109160 13.6 -> 13.0, top-k 8 x 1M 53.2 -> 52.2; long ones are even).  `defines` (NAME=value strings) and `out`
+    packed fp32 instructions are disabled for the device pass.  A kernel's leading arguments, up to 14 words of them and none from
+    the first struct passed by value on, are in scalar registers when a wave starts instead of being loaded by every wave (short
+    kernels gain most: 8 scaled-sign messages of 11.7M + 1 columns 101.7 -> 98.9 us, averaging 27 x 109160 13.6 -> 13.0, top-k
+    8 x 1M 53.2 -> 52.2; long ones are even).  `defines` (NAME=value strings) and `out`
     let a tuning run build a variant of the library beside the product's."""
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
